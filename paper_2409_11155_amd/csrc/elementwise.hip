@@ -2,6 +2,8 @@
 // embedding + KV-cache write, SwiGLU.  Each kernel moves every byte once with 16-byte accesses and
 // does its arithmetic in fp32.  (Layer structure: paper Section 2.2; KV-cache write before the next
 // chunk's attention: Section 3.1.)
+#include <algorithm>
+
 #include "iso_internal.h"
 
 namespace {
@@ -276,6 +278,31 @@ __global__ __launch_bounds__(256) void quant_rows_kernel(T *part, signed char *_
     }
 }
 
+// Device memory -> pinned host memory by a kernel: what a communication point uses for payloads that are too short for
+// the copy engine (see comm_copy in iso_api.hip) and inside a graph capture.  Bound by the link (55.9 of the copy
+// engine's 56.9 GB/s at 32 workgroups of 256; 16 reach 54.9, and more only queue).
+constexpr int COPY_T = 256, COPY_U = 2, COPY_WG = 32;
+__global__ __launch_bounds__(COPY_T) void copy_out_kernel(const u32x4_t *__restrict__ src, u32x4_t *__restrict__ dst,
+                                                          size_t n16, int tail) {
+    constexpr size_t STEP = (size_t)COPY_T * COPY_U;
+    for (size_t base = (size_t)blockIdx.x * STEP; base < n16; base += (size_t)gridDim.x * STEP) {
+        u32x4_t v[COPY_U];
+#pragma unroll
+        for (int i = 0; i < COPY_U; ++i) {
+            const size_t at = base + (size_t)i * COPY_T + threadIdx.x;
+            if (at < n16) v[i] = __builtin_nontemporal_load(src + at);
+        }
+#pragma unroll
+        for (int i = 0; i < COPY_U; ++i) {
+            const size_t at = base + (size_t)i * COPY_T + threadIdx.x;
+            if (at < n16) __builtin_nontemporal_store(v[i], dst + at);
+        }
+    }
+    if (blockIdx.x == 0 && (int)threadIdx.x < tail)
+        reinterpret_cast<unsigned char *>(dst + n16)[threadIdx.x] =
+            reinterpret_cast<const unsigned char *>(src + n16)[threadIdx.x];
+}
+
 template <typename T> __device__ __forceinline__ float silu_f(float z);
 template <> __device__ __forceinline__ float silu_f<float>(float z) { return z / (1.0f + expf(-z)); }
 template <> __device__ __forceinline__ float silu_f<bf16_t>(float z) { return z / (1.0f + __expf(-z)); }
@@ -369,5 +396,14 @@ hipError_t iso_launch_quant_rows(int dtype, void *part, void *q8, int T, int H, 
         hipLaunchKernelGGL(quant_rows_kernel<float>, grid, block, 0, s, (float *)part, (signed char *)q8, H);
     else
         hipLaunchKernelGGL(quant_rows_kernel<bf16_t>, grid, block, 0, s, (bf16_t *)part, (signed char *)q8, H);
+    return hipGetLastError();
+}
+
+// dst and src 16-byte aligned, dst pinned.
+hipError_t iso_launch_copy_out(void *dst, const void *src, size_t bytes, hipStream_t s) {
+    const size_t n16 = bytes / 16, step = (size_t)COPY_T * COPY_U;
+    const unsigned wgs = (unsigned)std::min<size_t>(COPY_WG, std::max<size_t>(1, (n16 + step - 1) / step));
+    hipLaunchKernelGGL(copy_out_kernel, dim3(wgs), dim3(COPY_T), 0, s, (const u32x4_t *)src, (u32x4_t *)dst, n16,
+                       (int)(bytes % 16));
     return hipGetLastError();
 }

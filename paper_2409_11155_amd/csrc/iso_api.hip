@@ -254,22 +254,52 @@ int sk_status(const iso_ctx *ctx) {
 }
 
 
+// `rows` rows of `pitch` bytes from device memory to pinned host memory, in stream s.
+//
+// Between two chunks' kernels the copy has to leave the compute units alone.  A plain hipMemcpyAsync does not promise
+// that: some HIP runtimes (the one inside PyTorch among them) run it as a shader with hundreds of workgroups as soon as
+// work is queued up, and the other chunk's kernels then stand still until it ends (2048-token 30B layer: its 8 us norm
+// takes 250 us beside a copy, the pass 2760 us; a copy kernel of a few workgroups still clogs the write path, 1570 us).
+// The two-dimensional copy always goes to a copy engine: 1220 us, and 4 layers of the 16k stack 61 -> 41 ms.
+// Short payloads go by kernel, whose start and end are 10 us cheaper than the engine's.  Measured on the 70B TP=8 layer,
+// engine / kernel: beside another chunk, copies of 0.5 MB 334 / 325 us, 1 MB even, 2 MB 445 / 463, 4 MB 535 / 593;
+// with nothing beside it, 2 MB 340 / 317, 4 MB 406 / 390, 8 MB even, 33 MB 1627 / 1647.
+// A graph capture records the kernel as well.
+hipError_t comm_copy(void *dst, const void *src, size_t pitch, size_t rows, bool overlap, hipStream_t s) {
+    const size_t bytes = pitch * rows, by_kernel = overlap ? 1u << 20 : 6u << 20;
+    if (((uintptr_t)dst | (uintptr_t)src) % 16) return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
+    if (bytes <= by_kernel || capturing(s)) return iso_launch_copy_out(dst, src, bytes, s);
+    if (pitch % 16) return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);   // rows the engine cannot take as one
+    return hipMemcpy2DAsync(dst, pitch, src, pitch, pitch, rows, hipMemcpyDeviceToHost, s);
+}
+
+// Whether a kernel may store through this host pointer (pinned memory at the same address on the device).
+bool kernel_can_write(const void *host) {
+    hipPointerAttribute_t at;
+    if (hipPointerGetAttributes(&at, host) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return at.type == hipMemoryTypeHost && at.devicePointer == host;
+}
+
 // Communication point of one chunk: nothing, the [n, H] partial as it is, or its int8 codes + row scales.
 // `which` = 0 after o_proj, 1 after down; the host sink keeps the two points apart.
-int comm_point(iso_ctx *ctx, int comm, int which, int lo, int n, hipStream_t s) {
+int comm_point(iso_ctx *ctx, int comm, int which, int lo, int n, bool overlap, hipStream_t s) {
+    if (comm == ISO_COMM_NONE) return ISO_OK;
     const iso_cfg &c = ctx->cfg;
     const size_t e = ctx->elt, H = (size_t)c.hidden;
     char *partr = (char *)(which ? ctx->part_m : ctx->part) + (size_t)lo * H * e;
     char *sink = (char *)ctx->host_sink + (size_t)which * c.max_seq * H * e;
-    if (comm == ISO_COMM_D2H) {
-        Timed t_(ctx, ISO_K_COMM, s);
-        HIP_TRY(hipMemcpyAsync(sink + (size_t)lo * H * e, partr, (size_t)n * H * e, hipMemcpyDeviceToHost, s));
-    } else if (comm == ISO_COMM_D2H_INT8) {
-        signed char *q = ctx->q8 + (size_t)lo * (H + 16);
+    const void *src = partr;
+    size_t pitch = H * e;
+    if (comm == ISO_COMM_D2H_INT8) {
+        pitch = H + 16;
+        signed char *q = ctx->q8 + (size_t)lo * pitch;
         LAUNCH_TRY(ISO_K_QUANT, s, iso_launch_quant_rows(c.dtype, partr, q, n, (int)H, s), "quantise");
-        Timed t_(ctx, ISO_K_COMM, s);
-        HIP_TRY(hipMemcpyAsync(sink + (size_t)lo * (H + 16), q, (size_t)n * (H + 16), hipMemcpyDeviceToHost, s));
+        src = q;
     }
+    LAUNCH_TRY(ISO_K_COMM, s, comm_copy(sink + (size_t)lo * pitch, src, pitch, (size_t)n, overlap, s), "copy to the host");
     return ISO_OK;
 }
 
@@ -277,6 +307,7 @@ int comm_point(iso_ctx *ctx, int comm, int which, int lo, int n, hipStream_t s) 
 struct Chunk {
     int lo, n;
     hipStream_t s;
+    bool overlap;      // another chunk's kernels may run beside this one's
 };
 
 // Attention block of one chunk.  `first_norm_delta`: when not NULL the block starts with the residual add
@@ -351,7 +382,7 @@ int attn_block_tail(iso_ctx *ctx, const iso_weights *w, void *kc, void *vc, cons
     ISO_TRY(attention(ctx, qkvr, NQKV, kc, vc, attnr, ck.n, ck.lo, ck.lo + ck.n, ck.s));
     ISO_TRY(gemm(ctx, ISO_K_GEMM_O, attnr, w->w_o, partr, ck.n, H, NQD, ck.s, F8Arg{w->w_o_f8, w->s_o, ck.lo}));
     if (after_compute) HIP_TRY(hipEventRecord(after_compute, ck.s));
-    return comm_point(ctx, comm, 0, ck.lo, ck.n, ck.s);
+    return comm_point(ctx, comm, 0, ck.lo, ck.n, ck.overlap, ck.s);
 }
 
 int mlp_block(iso_ctx *ctx, const iso_weights *w, void *x, const Chunk &ck, int comm) {
@@ -402,7 +433,7 @@ int mlp_block(iso_ctx *ctx, const iso_weights *w, void *x, const Chunk &ck, int 
         LAUNCH_TRY(ISO_K_SWIGLU, ck.s, iso_launch_swiglu(c.dtype, gur, actr, ck.n, F, ck.s), "swiglu");
     }
     ISO_TRY(gemm(ctx, ISO_K_GEMM_DOWN, actr, w->w_down, partr, ck.n, H, F, ck.s, F8Arg{w->w_down_f8, w->s_down, ck.lo}));
-    return comm_point(ctx, comm, 1, ck.lo, ck.n, ck.s);
+    return comm_point(ctx, comm, 1, ck.lo, ck.n, ck.overlap, ck.s);
 }
 
 int final_residual(iso_ctx *ctx, void *x, const Chunk &ck) {
@@ -464,7 +495,7 @@ int run_stack(iso_ctx *ctx, const iso_weights *layers, int n_layers, void *x, vo
     else if (overlap) for (int k = 0; k < nc; ++k) st[k] = ctx->stream[k & 1];
     const int n_streams = per_chunk ? nc : (overlap ? 2 : 1);
     Chunk ch[ISO_MAX_CHUNKS];
-    for (int k = 0; k < nc; ++k) ch[k] = Chunk{edges[k], edges[k + 1] - edges[k], st[k]};
+    for (int k = 0; k < nc; ++k) ch[k] = Chunk{edges[k], edges[k + 1] - edges[k], st[k], overlap};
 
     // Stream-K takes every compute unit for one GEMM.  That pays while the other chunk's stream mostly waits for
     // its bf16 transfers; when two chunks compute side by side most of the time (no transfers, or the halved int8
@@ -956,7 +987,10 @@ int iso_gemm_rowpar(iso_ctx *ctx, const void *a, const void *w, void *c, int M, 
     ISO_TRY(gemm(ctx, ISO_K_GEMM_O, a, w, c, M, N, K, (hipStream_t)stream));
     if (host_sink) {
         Timed t_(ctx, ISO_K_COMM, (hipStream_t)stream);
-        HIP_TRY(hipMemcpyAsync(host_sink, c, (size_t)M * N * ctx->elt, hipMemcpyDeviceToHost, (hipStream_t)stream));
+        if (kernel_can_write(host_sink))
+            HIP_TRY(comm_copy(host_sink, c, (size_t)N * ctx->elt, (size_t)M, false, (hipStream_t)stream));
+        else
+            HIP_TRY(hipMemcpyAsync(host_sink, c, (size_t)M * N * ctx->elt, hipMemcpyDeviceToHost, (hipStream_t)stream));
     }
     return ISO_OK;
 }

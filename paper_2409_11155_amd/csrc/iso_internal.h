@@ -79,6 +79,7 @@ hipError_t iso_launch_rmsnorm(int dtype, const void *x, const void *delta_or_nul
 hipError_t iso_launch_rope_kv(int dtype, void *qkv, void *k_cache, void *v_cache, const float *cos_t,
                               const float *sin_t, int Tc, int q_offset, int nq, int nkv, int d, hipStream_t s);
 hipError_t iso_launch_quant_rows(int dtype, void *part, void *q8, int T, int H, hipStream_t s);
+hipError_t iso_launch_copy_out(void *dst_pinned, const void *src, size_t bytes, hipStream_t s);
 hipError_t iso_launch_swiglu(int dtype, const void *gu, void *a, int T, int F, hipStream_t s);
 hipError_t iso_launch_gemm_simple(int dtype, const void *a, const void *w, void *c, int M, int N, int K,
                                   hipStream_t s);
