@@ -242,11 +242,13 @@ enum {
     ISO_FLAG_NO_FUSE = 8,     /* no fused epilogues: gate/up projection and SwiGLU as two kernels, QKV projection
                                  and rotary embedding + KV-cache write as two kernels                  */
     ISO_FLAG_ATTN_STAGED = 16,/* register-staged MFMA attention instead of the direct-to-LDS one    */
-    ISO_FLAG_NO_STREAMK = 32, /* never pick the stream-K launch of the direct-to-LDS GEMM by itself  */
+    ISO_FLAG_NO_STREAMK = 32, /* one workgroup per output tile: neither the stream-K launch of the direct-to-LDS GEMM nor
+                                 narrow tiles or a split k range are picked                          */
     ISO_FLAG_FP8_GEMM = 64    /* bf16 layers: run the four projections on the FP8 matrix cores (needs the FP8
                                  weights in iso_weights; activations are quantised per token row on the fly) */
     /* bits 8..11: tile variant of the direct-to-LDS GEMM (0 = chosen from the shape; 6 = its stream-K launch, which
-     * this value also forces for the FP8 GEMM) */
+     * this value also forces for the FP8 GEMM; 7 = narrow tiles / split k range, with bits 17..20 = number of shares and
+     * bits 21..23 = tile: 0, 1, 2 = 32, 64, 128 rows x 64 columns, 3 = 128 x 128, 4 = 256 x 256) */
     /* bits 12..13: launch shape of the direct-to-LDS attention (0 = chosen from the size; 1 = key tiles split inside
      * the workgroup; 2 = that, and two row blocks (longest with shortest) per workgroup; 3 = one row block per
      * workgroup, two workgroups per compute unit) */
@@ -255,8 +257,10 @@ enum {
 };
 int iso_set_flags(iso_ctx *ctx, int flags);
 
-/* Which kernel a bf16 projection of these sizes takes when nothing is forced, on a device with num_cu compute units
- * (num_cu == 0: as for a stream the context does not own, i.e. never stream-K).  Host only; for tests and tuning.
+/* Which whole-tile kernel a bf16 projection of these sizes takes when nothing is forced, on a device with num_cu compute
+ * units (num_cu == 0: as for a stream the context does not own, i.e. never stream-K).  Sizes for which narrower tiles, a
+ * split k range or another whole tile are estimated to be at least 4 % faster get those instead; that second choice is not
+ * reported here.  Host only; for tests and tuning.
  * kind: ISO_GEMM_TILE_256 / ISO_GEMM_TILE_128 (one 256x256 / 128x128 tile per workgroup, *grid workgroups),
  * ISO_GEMM_STREAMK (*grid workgroups in teams of *team), ISO_GEMM_STAGED / ISO_GEMM_SIMPLE (the fallbacks for sizes
  * the direct-to-LDS kernel does not take; *grid is 0).  Errors: NULL, non-positive sizes (ISO_ERR_SHAPE). */

@@ -140,6 +140,7 @@ long long iso_gemm_sk_plan(int M, int N, int nk, int num_wg, int *TS_, int *G_, 
 
 
 size_t iso_gemm_sk_ws_bytes(int num_wg) { return SK_HDR + (size_t)num_wg * DtlCfg<256, 256, 4, 2>::SLOT_BYTES; }
+size_t iso_gemm_sk_slot_bytes(void) { return DtlCfg<256, 256, 4, 2>::SLOT_BYTES; }
 int iso_gemm_sk_max_wg(void) { return SK_MAX_WG; }
 
 bool iso_gemm_bf16_dtl_supported(int M, int N, int K) {

@@ -132,7 +132,9 @@ struct RopeArgs {
     int q_offset, nq, nkv;
 };
 
-template <typename OP, int BM, int BN, int WM, int WN, bool SWIGLU, bool PIPE, bool SK, bool ROPE>
+// SHARE = true (tile-per-workgroup launches): sk_team workgroups share the k range of a tile; each leaves its fp32 sums
+// in its share of sk_ws, [sk_team][M][N], for a second kernel to add (gemm_split.hip).
+template <typename OP, int BM, int BN, int WM, int WN, bool SWIGLU, bool PIPE, bool SK, bool ROPE, bool SHARE = false>
 __device__ __forceinline__ void gemm_dtl_body(const typename OP::elem *__restrict__ A,
                                               const typename OP::elem *__restrict__ W, const float *__restrict__ sa,
                                               const float *__restrict__ sw, bf16_t *__restrict__ C, int M, int N, int K,
@@ -529,15 +531,32 @@ __device__ __forceinline__ void gemm_dtl_body(const typename OP::elem *__restric
         // workgroup -> tile: contiguous tile range per XCD (workgroup ids go round-robin over the 8 XCDs),
         // groups of 8 tile rows, tile row fastest inside a group (neighbours share the W tile)
         int pid = blockIdx.x;
-        const int per_xcd = nt / 8;
+        const int per_xcd = (SHARE ? (int)gridDim.x : nt) / 8;
         if (pid < per_xcd * 8) pid = (pid % 8) * per_xcd + pid / 8;
+        const int share = SHARE ? pid / nt : 0;
+        if (SHARE) pid %= nt;
         constexpr int GROUP = 8;
         const int width = GROUP * tiles_n;
         const int first_m = (pid / width) * GROUP;
         const int gsize = min(tiles_m - first_m, GROUP);
         set_tile(first_m + (pid % width) % gsize, (pid % width) / gsize);
-        run(0, nk);
-        store_tile();
+        if constexpr (SHARE) {
+            run((int)((long long)nk * share / sk_team), (int)((long long)nk * (share + 1) / sk_team));
+            float *P = reinterpret_cast<float *>(sk_ws) + (size_t)share * M * N;
+            const int gm0 = m0 + wm * Cfg::WTM, gn0 = n0 + wn * Cfg::WTN;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int gm = gm0 + i * 32 + blk_row(r), gn = gn0 + j * 32 + blk_col(r);
+                        if (gm < M && gn < N) P[(size_t)gm * N + gn] = acc[i][j][r];
+                    }
+        } else {
+            run(0, nk);
+            store_tile();
+        }
     } else {
         // Teams of TS workgroups: member r of a team owns tile row gm*TS + r of the team's current column
         // (gm, tile_n), and all members walk the same k range, so the W slices they fetch are shared in L2.

@@ -102,25 +102,29 @@ hipError_t iso_launch_quant_rows_fp8(const void *x, void *q, float *scale, int r
     return hipGetLastError();
 }
 
-// Stream-K when the planner's rule says so (sk may be null: never); else 256x256 tiles when they yield at least 128
-// workgroups, else 128x128 (as the bf16 kernel chooses).
-// variant 6 forces the stream-K launch (tests), anything else leaves the choice to the rule.
+// The whole-tile rule: stream-K when the planner says so (sk may be null: never); else 256x256 tiles when they yield at
+// least 128 workgroups, else 128x128 (as the bf16 kernel chooses).
+int iso_gemm_fp8_whole(int M, int N, int K, const iso_sk_ws *sk) {
+    if (sk_wanted(M, N, K, sk)) return 6;
+    return (long long)((M + 255) / 256) * ((N + 255) / 256) >= 128 ? 1 : 3;
+}
+
+// variant: 1 or 3 as above, 6 = stream-K; anything else leaves the choice to the rule.
 hipError_t iso_launch_gemm_fp8(const void *a8, const float *sa, const void *w8, const float *sw, void *c, int M, int N,
                                int K, int variant, iso_sk_ws *sk, hipStream_t s) {
-    if ((variant & 7) == 6 && !(sk && sk->base)) return hipErrorInvalidValue;
-    if ((variant & 7) == 6 || sk_wanted(M, N, K, sk)) return launch_sk<false>(a8, w8, sa, sw, c, M, N, K, sk, s);
-    const long long tiles_256 = (long long)((M + 255) / 256) * ((N + 255) / 256);
-    if (tiles_256 >= 128) return launch<256, 256, 4, 2, false>(a8, w8, sa, sw, c, M, N, K, s);
+    int v = variant & 7;
+    if (v != 1 && v != 3 && v != 6) v = iso_gemm_fp8_whole(M, N, K, sk);
+    if (v == 6) return sk && sk->base ? launch_sk<false>(a8, w8, sa, sw, c, M, N, K, sk, s) : hipErrorInvalidValue;
+    if (v == 1) return launch<256, 256, 4, 2, false>(a8, w8, sa, sw, c, M, N, K, s);
     return launch<128, 128, 2, 2, false>(a8, w8, sa, sw, c, M, N, K, s);
 }
 
 // act[M, F] = silu(gate) * up with w8 = [gate; up] of shape [2F, K], sw of length 2F
 hipError_t iso_launch_gemm_swiglu_fp8(const void *a8, const float *sa, const void *w8, const float *sw, void *act, int M,
                                       int F, int K, int variant, iso_sk_ws *sk, hipStream_t s) {
-    if ((variant & 7) == 6 && !(sk && sk->base)) return hipErrorInvalidValue;
-    if ((variant & 7) == 6 || sk_wanted(M, 2 * F, K, sk))
-        return launch_sk<true>(a8, w8, sa, sw, act, M, 2 * F, K, sk, s);
-    const long long tiles_256 = (long long)((M + 255) / 256) * ((2 * F + 255) / 256);
-    if (tiles_256 >= 128) return launch<256, 256, 4, 2, true>(a8, w8, sa, sw, act, M, 2 * F, K, s);
+    int v = variant & 7;
+    if (v != 1 && v != 3 && v != 6) v = iso_gemm_fp8_whole(M, 2 * F, K, sk);
+    if (v == 6) return sk && sk->base ? launch_sk<true>(a8, w8, sa, sw, act, M, 2 * F, K, sk, s) : hipErrorInvalidValue;
+    if (v == 1) return launch<256, 256, 4, 2, true>(a8, w8, sa, sw, act, M, 2 * F, K, s);
     return launch<128, 128, 2, 2, true>(a8, w8, sa, sw, act, M, 2 * F, K, s);
 }

@@ -1,0 +1,500 @@
+// Projections that a tile per compute unit cannot fill the chip with: short prompts (bound by the bytes of the weights)
+// and narrow matrices.   c[M,N] = a[M,K] * w[N,K]^T  for bf16 and FP8 operands.  (Projections of the layer: paper
+// Sections 2.2 and 4.1.)
+//
+// Two remedies, chosen together by a cost model (iso_gemm_split_plan below):
+//   * smaller tiles (32 / 64 / 128 rows x 64 columns), gemm_narrow_kernel;
+//   * the k range of a tile dealt to S workgroups, each of which leaves its fp32 partial sums in a workspace [S][M][N];
+//     a second kernel adds them in the order of the shares (the result does not depend on who ran when) and does the
+//     step that follows the projection on the way: nothing, SwiGLU, or rotary embedding + KV-cache write.
+#include <math.h>
+
+#include <algorithm>
+
+#include "gemm_dtl_kernel.h"
+
+namespace {
+
+enum { EPI_BF16 = 0, EPI_SWIGLU = 1, EPI_PARTIAL = 2 };
+
+// Workgroup tile BM x BN, NS LDS stages of one 128-byte k slice each for A and W.  The waves split the K-STEPS of a slice
+// (KW of them) and, where there are more waves than k-steps, the columns: a wave multiplies all BM rows of its k-step, so
+// every byte of the tile is read from LDS once (a spatial split of 128 x 64 over four waves reads it twice), and the KW
+// partial tiles are added through LDS at the end.  With NS - 1 slices requested ahead a compute unit keeps 64 .. 120 KB
+// of loads in flight, which is what streaming weights from HBM at full rate takes (21 KB per microsecond and unit).
+template <typename OP, int BM_, int BN_, int NS_, int OCC_> struct NarrowCfg {
+    static constexpr int BM = BM_, BN = BN_, NS = NS_, OCC = OCC_;
+    static constexpr int KW = 8 / OP::CPS, NW = 4, WN = NW / KW, NT = NW * 64;
+    static constexpr int STAGE = (BM + BN) * ROW_BYTES;
+    static constexpr int A_LOADS = BM / 8 / NW, W_LOADS = BN / 8 / NW, LOADS = A_LOADS + W_LOADS;
+    static constexpr int FM = BM / 32, WCOLS = BN / WN, FN = WCOLS / 32;
+    static constexpr int EP = BN + 8;                                  // fp32 pitch of the staged rows (two-way conflicts at most)
+    static constexpr int EPI_BYTES = KW * 32 * EP * 4;
+    static constexpr int LDS_BYTES = NS * STAGE > EPI_BYTES ? NS * STAGE : EPI_BYTES;
+    static_assert(LDS_BYTES * OCC <= 160 * 1024 && NW % KW == 0 && A_LOADS >= 1 && W_LOADS >= 1 && FN >= 1, "shape");
+    static_assert((NS - 2) * LOADS < 64, "outstanding loads are counted in six bits");
+};
+
+template <typename Cfg, typename OP, int EPI>
+__global__ __launch_bounds__(Cfg::NT, Cfg::OCC) void gemm_narrow_kernel(const typename OP::elem *__restrict__ A,
+                                                                        const typename OP::elem *__restrict__ W,
+                                                                        const float *__restrict__ sa,
+                                                                        const float *__restrict__ sw,
+                                                                        bf16_t *__restrict__ C, float *__restrict__ P, int M,
+                                                                        int N, int K, int tiles_m, int tiles_n, int S) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int BM = Cfg::BM, BN = Cfg::BN, NS = Cfg::NS, NW = Cfg::NW, KW = Cfg::KW, FM = Cfg::FM, FN = Cfg::FN;
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kw = wave % KW, wn = wave / KW;
+
+    // workgroup -> (share, tile column, tile row): each XCD gets a contiguous range, tile rows fastest (neighbours read the
+    // same weights), shares slowest (an XCD reads few k ranges of A)
+    int pid = blockIdx.x;
+    const int per_xcd = gridDim.x / 8;
+    if (pid < per_xcd * 8) pid = (pid % 8) * per_xcd + pid / 8;
+    const int tile_m = pid % tiles_m, tile_n = (pid / tiles_m) % tiles_n, share = pid / (tiles_m * tiles_n);
+    const int nk = K / OP::KE;
+    const int kb = (int)((long long)nk * share / S), n = (int)((long long)nk * (share + 1) / S) - kb;
+    const int m0 = tile_m * BM, n0 = tile_n * BN;
+
+    const int ld_row = lane >> 3, ld_slot = lane & 7;
+    const int a_bytes = (int)((uint32_t)M * (uint32_t)K * (uint32_t)OP::EB);
+    const int w_bytes = (int)((uint32_t)N * (uint32_t)K * (uint32_t)OP::EB);
+    uint32_t a_off[Cfg::A_LOADS], w_off[Cfg::W_LOADS];
+#pragma unroll
+    for (int i = 0; i < Cfg::A_LOADS; ++i) {
+        const int r = (wave + NW * i) * 8 + ld_row;
+        a_off[i] = (uint32_t)min(m0 + r, M - 1) * (uint32_t)K * (uint32_t)OP::EB + (uint32_t)((ld_slot ^ swz(r)) << 4);
+    }
+#pragma unroll
+    for (int i = 0; i < Cfg::W_LOADS; ++i) {
+        const int r = (wave + NW * i) * 8 + ld_row;
+        int grow;
+        if (EPI == EPI_SWIGLU) {        // 32-column blocks alternate gate / up of the same 32 MLP columns
+            const int F = N / 2, f = tile_n * (BN / 2) + (r / 64) * 32 + (r % 32);
+            grow = ((r / 32) & 1) * F + min(f, F - 1);
+        } else {
+            grow = min(n0 + r, N - 1);
+        }
+        w_off[i] = (uint32_t)grow * (uint32_t)K * (uint32_t)OP::EB + (uint32_t)((ld_slot ^ swz(r)) << 4);
+    }
+    // a slice past the share's end is requested through an empty descriptor: nothing is fetched, the count of outstanding
+    // loads stays the same to the end
+    auto issue = [&](int i) {
+        const bool real = i < n;
+        const __amdgpu_buffer_rsrc_t rs_a = __builtin_amdgcn_make_buffer_rsrc((void *)A, 0, real ? a_bytes : 0, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rs_w = __builtin_amdgcn_make_buffer_rsrc((void *)W, 0, real ? w_bytes : 0, 0x00020000);
+        unsigned char *base = lds + (i % NS) * Cfg::STAGE;
+        const int off = (kb + i) * ROW_BYTES;
+#pragma unroll
+        for (int j = 0; j < Cfg::W_LOADS; ++j)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                rs_w, (__attribute__((address_space(3))) void *)(base + BM * ROW_BYTES + (wave + NW * j) * 1024), 16, w_off[j],
+                off, 0, 0);
+#pragma unroll
+        for (int j = 0; j < Cfg::A_LOADS; ++j)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                rs_a, (__attribute__((address_space(3))) void *)(base + (wave + NW * j) * 1024), 16, a_off[j], off, 0, 0);
+    };
+
+    f32x16_t acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    const int frow = lane & 31, fgrp = lane >> 5;
+    const int f_sw = swz(frow), c0 = kw * OP::CPS + fgrp * OP::RPF;
+    for (int i = 0; i < NS - 1; ++i) issue(i);
+    constexpr int PEND = (NS - 2) * Cfg::LOADS;
+    constexpr int WAIT = (PEND & 15) | ((PEND >> 4) << 14) | (7 << 4);      // vmcnt <= PEND, lgkmcnt = 0
+    for (int i = 0; i < n; ++i) {
+        __builtin_amdgcn_s_waitcnt(WAIT);           // my part of slice i has landed, my reads of slice i - 1 are done
+        asm volatile("s_barrier" ::: "memory");     // ... and everybody's
+        issue(i + NS - 1);
+        const unsigned char *ab = lds + (i % NS) * Cfg::STAGE + frow * ROW_BYTES;
+        const unsigned char *wb = ab + (BM + wn * Cfg::WCOLS) * ROW_BYTES;
+        typename OP::frag_t af[FM], wf[FN];
+#pragma unroll
+        for (int j = 0; j < FN; ++j) wf[j] = OP::load(wb + j * 32 * ROW_BYTES, c0, f_sw);
+#pragma unroll
+        for (int j = 0; j < FM; ++j) af[j] = OP::load(ab + j * 32 * ROW_BYTES, c0, f_sw);
+#pragma unroll
+        for (int x = 0; x < FM; ++x)
+#pragma unroll
+            for (int y = 0; y < FN; ++y) acc[x][y] = OP::mfma32(af[x], wf[y], acc[x][y]);
+    }
+    __builtin_amdgcn_s_waitcnt(7 << 4);             // everything, so that the staging below may overwrite the stages
+
+    // epilogue, 32 rows at a time: the KW partial blocks go to LDS, every thread adds the KW values of its outputs in
+    // k-step order
+    float *st = reinterpret_cast<float *>(lds);
+    constexpr int EP = Cfg::EP;
+#pragma unroll
+    for (int x = 0; x < FM; ++x) {
+        __syncthreads();
+#pragma unroll
+        for (int y = 0; y < FN; ++y)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                st[(kw * 32 + 8 * (r / 4) + 4 * fgrp + (r % 4)) * EP + wn * Cfg::WCOLS + y * 32 + frow] = acc[x][y][r];
+        __syncthreads();
+        if (EPI != EPI_SWIGLU) {
+            constexpr int PPR = BN / 8;                               // pieces of eight columns per row
+            for (int p = tid; p < 32 * PPR; p += Cfg::NT) {
+                const int row = p / PPR, cc = (p % PPR) * 8;
+                const int gm = m0 + x * 32 + row, gn = n0 + cc;
+                if (gm >= M || gn >= N) continue;                     // N % 8 == 0
+                float v[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = st[row * EP + cc + e];
+#pragma unroll
+                for (int k = 1; k < KW; ++k)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) v[e] += st[(k * 32 + row) * EP + cc + e];
+                if (EPI == EPI_PARTIAL) {
+                    f32x4_t *o = reinterpret_cast<f32x4_t *>(P + ((size_t)share * M + gm) * N + gn);
+                    o[0] = f32x4_t{v[0], v[1], v[2], v[3]};
+                    o[1] = f32x4_t{v[4], v[5], v[6], v[7]};
+                } else {
+                    bf16x8_t o;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        if constexpr (OP::SCALED) v[e] *= sa[gm] * sw[gn + e];
+                        o[e] = (bf16_t)v[e];
+                    }
+                    *reinterpret_cast<bf16x8_t *>(C + (size_t)gm * N + gn) = o;
+                }
+            }
+        } else {
+            constexpr int PPR = BN / 2 / 4;                           // pieces of four MLP columns per row
+            const int F = N / 2;
+            for (int p = tid; p < 32 * PPR; p += Cfg::NT) {
+                const int row = p / PPR, cc = (p % PPR) * 4;
+                const int gm = m0 + x * 32 + row, gf = tile_n * (BN / 2) + cc;
+                if (gm >= M || gf >= F) continue;                     // F % 8 == 0
+                const int lc = (cc / 32) * 64 + (cc % 32);
+                bf16x4_t o;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    float g = 0.f, u = 0.f;
+#pragma unroll
+                    for (int k = 0; k < KW; ++k) {
+                        g += st[(k * 32 + row) * EP + lc + e];
+                        u += st[(k * 32 + row) * EP + lc + 32 + e];
+                    }
+                    if constexpr (OP::SCALED) {
+                        g *= sa[gm] * sw[gf + e];
+                        u *= sa[gm] * sw[F + gf + e];
+                    }
+                    o[e] = (bf16_t)(g / (1.0f + __expf(-g)) * u);
+                }
+                *reinterpret_cast<bf16x4_t *>(C + (size_t)gm * F + gf) = o;
+            }
+        }
+    }
+#endif
+}
+
+// The shares of a whole-tile kernel (gemm_dtl_kernel.h): 128 x 128 (four waves, two workgroups per unit) or 256 x 256.
+template <typename OP, int BM, int BN, int WM, int WN>
+__global__ __launch_bounds__(WM * WN * 64) void gemm_share_kernel(const typename OP::elem *__restrict__ A,
+                                                                  const typename OP::elem *__restrict__ W,
+                                                                  float *__restrict__ P, int M, int N, int K, int tiles_m,
+                                                                  int tiles_n, int S) {
+    gemm_dtl_body<OP, BM, BN, WM, WN, false, true, false, false, true>(A, W, nullptr, nullptr, nullptr, M, N, K, tiles_m,
+                                                                       tiles_n, reinterpret_cast<unsigned char *>(P), 0u,
+                                                                       nullptr, S, 0, RopeArgs{});
+}
+
+// ---- second kernels: sum of the shares, eight columns per thread --------------------------------------------------
+struct Shares {
+    const float *p;              // [S][M][N]
+    size_t stride;               // M * N
+    int S;
+    const float *sa, *sw;        // FP8 row scales, or null
+};
+__device__ __forceinline__ void sum_shares(const Shares &sh, int row, int col, int N, float (&v)[8]) {
+    const float *p = sh.p + (size_t)row * N + col;
+    f32x4_t lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
+#pragma unroll 4
+    for (int s = 0; s < sh.S; ++s) {
+        lo += *reinterpret_cast<const f32x4_t *>(p + (size_t)s * sh.stride);
+        hi += *reinterpret_cast<const f32x4_t *>(p + (size_t)s * sh.stride + 4);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { v[e] = lo[e]; v[e + 4] = hi[e]; }
+    if (sh.sa) {
+        const float a = sh.sa[row];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] *= a * sh.sw[col + e];
+    }
+}
+
+__global__ __launch_bounds__(256) void share_sum_kernel(Shares sh, bf16_t *__restrict__ C, int M, int N) {
+    const int u = blockIdx.x * 256 + threadIdx.x, per_row = N / 8;
+    const int row = u / per_row, col = (u % per_row) * 8;
+    if (row >= M) return;
+    float v[8];
+    sum_shares(sh, row, col, N, v);
+    bf16x8_t o;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = (bf16_t)v[e];
+    *reinterpret_cast<bf16x8_t *>(C + (size_t)row * N + col) = o;
+}
+
+__global__ __launch_bounds__(256) void share_sum_swiglu_kernel(Shares sh, bf16_t *__restrict__ act, int M, int F) {
+    const int u = blockIdx.x * 256 + threadIdx.x, per_row = F / 8;
+    const int row = u / per_row, col = (u % per_row) * 8;
+    if (row >= M) return;
+    float g[8], up[8];
+    sum_shares(sh, row, col, 2 * F, g);
+    sum_shares(sh, row, F + col, 2 * F, up);
+    bf16x8_t o;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = (bf16_t)(g[e] / (1.0f + __expf(-g[e])) * up[e]);
+    *reinterpret_cast<bf16x8_t *>(act + (size_t)row * F + col) = o;
+}
+
+// Rotary embedding and KV-cache write (same arithmetic and roundings as rope_kv_kernel: the projection output is rounded
+// to bf16, rotated in fp32 and rounded again); the k and v columns of qkv are not written.
+__global__ __launch_bounds__(256) void share_sum_rope_kernel(Shares sh, bf16_t *__restrict__ qkv, RopeArgs rope, int M, int d) {
+    const int half = d / 2, N = (rope.nq + 2 * rope.nkv) * d;
+    const int per_head = half / 8, per_row = (rope.nq + 2 * rope.nkv) * per_head;
+    const int u = blockIdx.x * 256 + threadIdx.x;
+    const int row = u / per_row;
+    if (row >= M) return;
+    const int head = (u % per_row) / per_head, i0 = (u % per_head) * 8, col = head * d + i0;
+    float lo[8], hi[8];
+    sum_shares(sh, row, col, N, lo);
+    sum_shares(sh, row, col + half, N, hi);
+    const size_t pos = (size_t)(rope.q_offset + row);
+    bf16_t *dst = qkv + (size_t)row * N + col;
+    if (head >= rope.nq + rope.nkv) dst = rope.v_cache + (pos * rope.nkv + (head - rope.nq - rope.nkv)) * d + i0;
+    else if (head >= rope.nq) dst = rope.k_cache + (pos * rope.nkv + (head - rope.nq)) * d + i0;
+    bf16x8_t olo, ohi;
+    if (head >= rope.nq + rope.nkv) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { olo[e] = (bf16_t)lo[e]; ohi[e] = (bf16_t)hi[e]; }
+    } else {
+        const float *cp = rope.cos_t + pos * half + i0, *sp = rope.sin_t + pos * half + i0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float l = (float)(bf16_t)lo[e], h = (float)(bf16_t)hi[e];
+            olo[e] = (bf16_t)(l * cp[e] - h * sp[e]);
+            ohi[e] = (bf16_t)(h * cp[e] + l * sp[e]);
+        }
+    }
+    *reinterpret_cast<bf16x8_t *>(dst) = olo;
+    *reinterpret_cast<bf16x8_t *>(dst + half) = ohi;
+}
+
+// ---- launchers ----------------------------------------------------------------------------------------------------
+struct Operands {
+    const void *a, *w;
+    const float *sa, *sw;
+    void *c;
+    float *p;
+    int M, N, K;
+};
+
+template <typename OP, typename Cfg, int EPI> hipError_t launch_narrow(const Operands &o, int S, hipStream_t s) {
+    static iso_dev_mask lds_allowed{0};
+    auto kern = gemm_narrow_kernel<Cfg, OP, EPI>;
+    if (hipError_t e = iso_allow_lds(reinterpret_cast<const void *>(kern), Cfg::LDS_BYTES, &lds_allowed); e != hipSuccess)
+        return e;
+    const int tiles_m = (o.M + Cfg::BM - 1) / Cfg::BM, tiles_n = (o.N + Cfg::BN - 1) / Cfg::BN;
+    typedef const typename OP::elem *ptr;
+    hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n * S), dim3(Cfg::NT), Cfg::LDS_BYTES, s, (ptr)o.a, (ptr)o.w, o.sa, o.sw,
+                       (bf16_t *)o.c, o.p, o.M, o.N, o.K, tiles_m, tiles_n, S);
+    return hipGetLastError();
+}
+
+template <typename OP, int BM, int BN, int WM, int WN> hipError_t launch_share(const Operands &o, int S, hipStream_t s) {
+    using Cfg = DtlCfg<BM, BN, WM, WN>;
+    constexpr int LDS_BYTES = Cfg::W3 ? Cfg::LDS_BYTES_W3 : Cfg::LDS_BYTES;
+    static iso_dev_mask lds_allowed{0};
+    auto kern = gemm_share_kernel<OP, BM, BN, WM, WN>;
+    if (hipError_t e = iso_allow_lds(reinterpret_cast<const void *>(kern), LDS_BYTES, &lds_allowed); e != hipSuccess) return e;
+    const int tiles_m = (o.M + BM - 1) / BM, tiles_n = (o.N + BN - 1) / BN;
+    typedef const typename OP::elem *ptr;
+    hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n * S), dim3(Cfg::NT), LDS_BYTES, s, (ptr)o.a, (ptr)o.w, o.p, o.M, o.N, o.K,
+                       tiles_m, tiles_n, S);
+    return hipGetLastError();
+}
+
+template <typename OP, int EPI> hipError_t launch_cfg(int cfg, const Operands &o, int S, hipStream_t s) {
+    switch (cfg) {
+        case 0: return launch_narrow<OP, NarrowCfg<OP, 32, 64, 6, 2>, EPI>(o, S, s);
+        case 1: return launch_narrow<OP, NarrowCfg<OP, 64, 64, 5, 2>, EPI>(o, S, s);
+        case 2: return launch_narrow<OP, NarrowCfg<OP, 128, 64, 3, 2>, EPI>(o, S, s);
+        default: break;
+    }
+    if constexpr (EPI == EPI_PARTIAL) {
+        if (cfg == 3) return launch_share<OP, 128, 128, 2, 2>(o, S, s);
+        if (cfg == 4) {
+            if constexpr (OP::SCALED) return launch_share<OP, 256, 256, 4, 2>(o, S, s);
+            else return launch_share<Bf16Op<true>, 256, 256, 4, 2>(o, S, s);
+        }
+    }
+    return hipErrorInvalidValue;
+}
+
+unsigned blocks_for(size_t units) { return (unsigned)((units + 255) / 256); }
+
+
+// ---- which kernel ----------------------------------------------------------------------------------------------
+// Microseconds of a launch, as fitted to 22 000 launches measured on MI355X (16 matrix shapes of the 30B / 70B shards and
+// of a heads-of-64 layer, 16 to 16384 rows, every tile with 1 to 15 shares, weights from HBM):
+//     start + rounds * round + slices * slice(load) + [shares > 1] (sum0 + sum_mb * MB of partial sums)
+// with rounds = times the launch fills the chip (`per_cu` workgroups on each unit), load = workgroups per unit in the last
+// round: slice(load) = slice + crowd * min(load, 1), and + pair * (pair0 + (1 - pair0) (load - 1)) when some units hold two.
+// A launch that shares the chip with the other chunk's (`shared`: two chunks computing side by side) leaves its last round's
+// idle units to that one, so there 0.7 of the price is the part of the chip it uses (measured over 60 split layers: 0 and 1
+// instead of 0.7 lose 5 and 2 %) and the switch has to promise 8 %.
+// Never below the time of the weights' bytes from HBM.  Root mean square error 3-8 %; picking the fastest by these numbers
+// gives launches 1.5 % slower than the best measured one on average, 1.38x (bf16) / 1.30x (FP8) faster than the whole-tile
+// rule alone over that grid: 2.4-4x at up to 256 rows, 1.2-1.8x at 512-1024, a few per cent above.
+struct Tile {
+    int bm, bn, per_cu, kind;    // kind: tile of this file (0 .. 4), or -v: variant v of the whole-tile kernel, one share
+    double start, round, slice, crowd, pair, pair0, sum0, sum_mb;
+};
+constexpr Tile TILES_BF16[] = {
+    {32, 64, 2, 0, 3.5, 0.0, 0.175, 0.042, 0.205, 0.61, 2.1, 0.54},
+    {64, 64, 2, 1, 3.9, 0.0, 0.223, 0.043, 0.208, 0.95, 2.1, 0.51},
+    {128, 64, 2, 2, 3.8, 0.9, 0.299, 0.115, 0.312, 0.79, 2.1, 0.41},
+    {128, 128, 2, 3, 6.9, 0.0, 0.458, 0.093, 0.414, 0.64, 1.0, 0.32},
+    {256, 256, 1, 4, 4.1, 4.3, 1.048, 0.423, 0.0, 0.0, 1.3, 0.23},
+    {256, 256, 1, -1, 2.5, 6.2, 0.988, 0.453, 0.0, 0.0, 0.0, 0.0},
+    {128, 128, 2, -3, 2.3, 1.6, 0.444, 0.128, 0.387, 0.67, 0.0, 0.0},
+    {128, 256, 1, -4, 0.8, 2.7, 0.668, 0.265, 0.0, 0.0, 0.0, 0.0},
+};
+constexpr Tile TILES_FP8[] = {
+    {32, 64, 2, 0, 2.4, 1.8, 0.150, 0.049, 0.133, 1.0, 3.0, 0.27},
+    {64, 64, 2, 1, 2.3, 2.0, 0.187, 0.051, 0.191, 1.0, 2.9, 0.32},
+    {128, 64, 2, 2, 3.8, 1.1, 0.278, 0.088, 0.275, 0.94, 2.2, 0.37},
+    {128, 128, 2, 3, 2.9, 2.6, 0.353, 0.284, 0.224, 0.74, 3.2, 0.26},
+    {256, 256, 1, 4, 5.3, 5.0, 0.921, 0.394, 0.0, 0.0, 0.0, 0.23},
+    {256, 256, 1, -1, 1.7, 8.2, 0.838, 0.623, 0.0, 0.0, 0.0, 0.0},
+    {128, 128, 2, -3, 2.4, 1.9, 0.497, 0.131, 0.345, 0.47, 0.0, 0.0},
+};
+// Stream-K by team size 1, 2, 4, 8: start + slice * k-slices of a team + fetch * teams per tile column.
+struct StreamK {
+    double start, slice, fetch;
+};
+constexpr StreamK SK_BF16[] = {{20.4, 2.08, 2.9}, {25.7, 1.56, 2.6}, {24.4, 1.61, 1.3}, {11.7, 1.71, 4.0}};
+constexpr StreamK SK_FP8[] = {{29.1, 2.14, 0.0}, {36.5, 1.39, 0.0}, {30.4, 1.59, 0.0}, {20.5, 1.77, 0.0}};
+double stream_k_us(bool fp8, int M, int N, int nk, int ncu) {
+    int team, grid, grouped;
+    const double slices = (double)iso_gemm_sk_plan(M, N, nk, ncu, &team, &grid, &grouped);
+    const double teams = grid / team, cols = (double)(((M + 255) / 256) / team) * ((N + 255) / 256);
+    const StreamK &k = (fp8 ? SK_FP8 : SK_BF16)[team == 8 ? 3 : team / 2];
+    return k.start + k.slice * slices + k.fetch * teams / cols;
+}
+
+double tile_us(const Tile &t, int M, int N, int nk, int S, int ncu, bool shared) {
+    const double wgs = (double)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * S;
+    const double slots = (double)ncu * t.per_cu, full = std::max(0.0, ceil(wgs / slots) - 1.0);
+    const double load = (wgs - full * slots) / ncu, slices = (nk + S - 1) / S;
+    auto slice = [&](double x) {
+        return t.slice + t.crowd * std::min(x, 1.0) + (x > 1.0 ? t.pair * (t.pair0 + (1.0 - t.pair0) * (x - 1.0)) : 0.0);
+    };
+    double us = t.start + (full + 1.0) * t.round + slices * (full * slice(t.per_cu) + slice(load));
+    if (shared) us = 0.3 * us + 0.7 * (t.start + wgs / slots * (t.round + slices * slice(t.per_cu)));
+    us = std::max(us, t.start + ((double)N * nk / 5.2e6 + (double)M * nk / 1e7) * ROW_BYTES);
+    if (S > 1) us += t.sum0 + t.sum_mb * ((double)S * M * N * 4e-6);
+    return us;
+}
+
+}  // namespace
+
+bool iso_gemm_split_supported(bool fp8, int M, int N, int K) {
+    const int ke = fp8 ? Fp8Op::KE : Bf16Op<false>::KE;
+    return M >= 1 && N >= 8 && (N % 8) == 0 && K >= ke && (K % ke) == 0 && (long long)M * K < (1ll << 31) &&
+           (long long)N * K < (1ll << 31) && (long long)M * (N / 8) < (1ll << 31) - 256;
+}
+
+// `whole` is the whole-tile rule's own choice (variant 1, 3, 4 or 6 = stream-K).  It stays unless something else is
+// estimated at least 4 % faster (8 % beside another chunk).  ws_bytes: room for partial sums (0: one share only).  `rope`: the QKV projection, where
+// only variants 1 and 6 and the tiles of this file (through their second kernel) finish with the rotary step; the others
+// need a kernel more (about 5 us).
+iso_split_plan iso_gemm_split_plan(bool fp8, bool rope, int whole, int M, int N, int K, size_t ws_bytes, int ncu, bool shared) {
+    const int nk = K / (fp8 ? Fp8Op::KE : Bf16Op<false>::KE);
+    const Tile *tiles = fp8 ? TILES_FP8 : TILES_BF16;
+    const int n_tiles = fp8 ? (int)(sizeof(TILES_FP8) / sizeof(Tile)) : (int)(sizeof(TILES_BF16) / sizeof(Tile));
+    const double extra = rope && fp8 ? 5.0 : 0.0;
+    auto whole_extra = [&](int v) { return rope && !fp8 && v != 1 && v != 6 ? 5.0 : extra; };
+    double best = 1e30;
+    if (whole == 6) best = stream_k_us(fp8, M, N, nk, ncu) + extra;
+    for (int i = 0; i < n_tiles; ++i)
+        if (tiles[i].kind == -whole) best = tile_us(tiles[i], M, N, nk, 1, ncu, shared) + whole_extra(whole);
+    best *= shared ? 0.92 : 0.96;
+    iso_split_plan plan{-1, 1, whole};
+    constexpr int SHARES[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 15};
+    for (int i = 0; i < n_tiles; ++i) {
+        const Tile &t = tiles[i];
+        for (int S : SHARES) {
+            if (t.kind < 0 ? S > 1 : ((t.kind >= 3 && S == 1) || S * 2 > nk)) continue;
+            if ((S > 1 || (rope && t.kind >= 0)) && (size_t)S * M * N * 4 > ws_bytes) break;
+            double us = tile_us(t, M, N, nk, S, ncu, shared);
+            if (t.kind < 0) us += whole_extra(-t.kind);
+            else if (rope && S == 1) us += t.sum0 + t.sum_mb * ((double)M * N * 4e-6);
+            if (us < best) {
+                best = us;
+                plan = t.kind < 0 ? iso_split_plan{-1, 1, -t.kind} : iso_split_plan{t.kind, S, 0};
+            }
+        }
+    }
+    return plan;
+}
+
+hipError_t iso_launch_gemm_split(const iso_split_plan &plan, const void *a, const void *w, const float *sa, const float *sw,
+                                 void *c, int M, int N, int K, iso_sk_ws *ws, hipStream_t s) {
+    const bool fp8 = sa != nullptr;
+    float *p = plan.shares > 1 && ws && ws->base ? (float *)((char *)ws->base + SK_HDR) : nullptr;
+    if (plan.shares > 1 && !p) return hipErrorInvalidValue;
+    const Operands o{a, w, sa, sw, c, p, M, N, K};
+    if (plan.shares == 1)
+        return fp8 ? launch_cfg<Fp8Op, EPI_BF16>(plan.tile, o, 1, s) : launch_cfg<Bf16Op<false>, EPI_BF16>(plan.tile, o, 1, s);
+    hipError_t e = fp8 ? launch_cfg<Fp8Op, EPI_PARTIAL>(plan.tile, o, plan.shares, s)
+                       : launch_cfg<Bf16Op<false>, EPI_PARTIAL>(plan.tile, o, plan.shares, s);
+    if (e != hipSuccess) return e;
+    const Shares sh{p, (size_t)M * N, plan.shares, sa, sw};
+    hipLaunchKernelGGL(share_sum_kernel, dim3(blocks_for((size_t)M * (N / 8))), dim3(256), 0, s, sh, (bf16_t *)c, M, N);
+    return hipGetLastError();
+}
+
+hipError_t iso_launch_gemm_split_swiglu(const iso_split_plan &plan, const void *a, const void *w, const float *sa,
+                                        const float *sw, void *act, int M, int F, int K, iso_sk_ws *ws, hipStream_t s) {
+    const bool fp8 = sa != nullptr;
+    float *p = plan.shares > 1 && ws && ws->base ? (float *)((char *)ws->base + SK_HDR) : nullptr;
+    if (plan.shares > 1 && !p) return hipErrorInvalidValue;
+    const Operands o{a, w, sa, sw, act, p, M, 2 * F, K};
+    if (plan.shares == 1)
+        return fp8 ? launch_cfg<Fp8Op, EPI_SWIGLU>(plan.tile, o, 1, s) : launch_cfg<Bf16Op<false>, EPI_SWIGLU>(plan.tile, o, 1, s);
+    hipError_t e = fp8 ? launch_cfg<Fp8Op, EPI_PARTIAL>(plan.tile, o, plan.shares, s)
+                       : launch_cfg<Bf16Op<false>, EPI_PARTIAL>(plan.tile, o, plan.shares, s);
+    if (e != hipSuccess) return e;
+    const Shares sh{p, (size_t)M * 2 * F, plan.shares, sa, sw};
+    hipLaunchKernelGGL(share_sum_swiglu_kernel, dim3(blocks_for((size_t)M * (F / 8))), dim3(256), 0, s, sh, (bf16_t *)act, M, F);
+    return hipGetLastError();
+}
+
+hipError_t iso_launch_gemm_split_rope(const iso_split_plan &plan, const void *a, const void *w, const float *sa, const float *sw,
+                                      void *qkv, int M, int N, int K, iso_sk_ws *ws, const float *cos_t, const float *sin_t,
+                                      void *k_cache, void *v_cache, int q_offset, int nq, int nkv, int d, hipStream_t s) {
+    if (!ws || !ws->base) return hipErrorInvalidValue;
+    float *p = (float *)((char *)ws->base + SK_HDR);
+    const Operands o{a, w, sa, sw, nullptr, p, M, N, K};
+    hipError_t e = sa ? launch_cfg<Fp8Op, EPI_PARTIAL>(plan.tile, o, plan.shares, s)
+                      : launch_cfg<Bf16Op<false>, EPI_PARTIAL>(plan.tile, o, plan.shares, s);
+    if (e != hipSuccess) return e;
+    const Shares sh{p, (size_t)M * N, plan.shares, sa, sw};
+    const RopeArgs rope{cos_t, sin_t, (bf16_t *)k_cache, (bf16_t *)v_cache, q_offset, nq, nkv};
+    hipLaunchKernelGGL(share_sum_rope_kernel, dim3(blocks_for((size_t)M * (N / 16))), dim3(256), 0, s, sh, (bf16_t *)qkv, rope,
+                       M, d);
+    return hipGetLastError();
+}

@@ -124,6 +124,34 @@ iso_sk_ws *sk_for(iso_ctx *ctx, hipStream_t s) {
     return nullptr;
 }
 
+// Workspace of a split product on stream s (null: a foreign stream, only unsplit plans there).  Unlike stream-K it has no
+// launch numbers, so it may be recorded into a graph; launches that share it are ordered by their stream.
+iso_sk_ws *split_ws_for(iso_ctx *ctx, hipStream_t s) {
+    for (int k = 0; k < ISO_MAX_CHUNKS; ++k)
+        if (ctx->sk[k].base && s == (k < 2 ? ctx->stream[k] : ctx->xstream[k])) return &ctx->sk[k];
+    return nullptr;
+}
+
+// What one projection launch of the layer becomes (`rope`: the QKV projection, see iso_gemm_split_plan).
+iso_split_plan plan_gemm(iso_ctx *ctx, bool fp8, bool rope, int M, int N, int K, hipStream_t s) {
+    const int forced = (ctx->flags >> 8) & 15;
+    const iso_split_plan whole{-1, 1, forced == 7 ? 0 : forced};
+    if (ctx->cfg.dtype != ISO_BF16 || !iso_gemm_split_supported(fp8, M, N, K)) return whole;
+    if (ctx->flags & (ISO_FLAG_SIMPLE_GEMM | ISO_FLAG_GEMM_STAGED)) return whole;
+    const iso_sk_ws *ws = split_ws_for(ctx, s);
+    const size_t bytes = ws ? (size_t)ws->num_wg * iso_gemm_sk_slot_bytes() : 0;
+    if (forced == 7) {       // tests, measurement: bits 17..20 shares, 21..23 tile
+        iso_split_plan p{std::min(4, (ctx->flags >> 21) & 7), std::max(1, (ctx->flags >> 17) & 15), 0};
+        p.shares = std::min(p.shares, K / (fp8 ? 128 : 64));
+        if (p.tile > 2 && p.shares < 2) return whole;          // one share of a whole tile: the whole-tile kernels
+        if ((p.shares > 1 || rope) && (size_t)p.shares * M * N * 4 > bytes) return whole;
+        return p;
+    }
+    if (forced || (ctx->flags & ISO_FLAG_NO_STREAMK)) return whole;
+    const int rule = fp8 ? iso_gemm_fp8_whole(M, N, K, sk_for(ctx, s)) : iso_gemm_bf16_dtl_resolve(M, N, K, 0, sk_for(ctx, s));
+    return iso_gemm_split_plan(fp8, rope, rule, M, N, K, bytes, iso_num_cu(), ctx->sk_hold != 0);
+}
+
 // Key-split attention workspace for a launch on stream s: one per stream of the context's own, none for others.
 constexpr int ATTN_SLOTS = 512, ATTN_BLOCKS = 512;
 
@@ -186,6 +214,15 @@ bool use_fp8(const iso_ctx *ctx, const F8Arg &f8, int M, int N, int K) {
            iso_gemm_fp8_supported(M, N, K);
 }
 
+int gemm_fp8(iso_ctx *ctx, const void *a8, const float *sa, const void *w8, const float *sw, void *c, int M, int N, int K,
+             bool rope, hipStream_t s) {
+    const iso_split_plan sp = plan_gemm(ctx, true, rope, M, N, K, s);
+    const hipError_t e = sp.tile >= 0 ? iso_launch_gemm_split(sp, a8, w8, sa, sw, c, M, N, K, split_ws_for(ctx, s), s)
+                                      : iso_launch_gemm_fp8(a8, sa, w8, sw, c, M, N, K, sp.whole, sk_for(ctx, s), s);
+    if (e != hipSuccess) return fail(ISO_ERR_HIP, "fp8 gemm launch (M=%d N=%d K=%d): %s", M, N, K, hipGetErrorString(e));
+    return ISO_OK;
+}
+
 int gemm(iso_ctx *ctx, int kind, const void *a, const void *w, void *c, int M, int N, int K, hipStream_t s,
          const F8Arg &f8 = F8Arg()) {
     const size_t e_ = ctx->elt;
@@ -196,10 +233,8 @@ int gemm(iso_ctx *ctx, int kind, const void *a, const void *w, void *c, int M, i
             LAUNCH_TRY(ISO_K_QUANT, s, iso_launch_quant_rows_fp8(a, a8, sa, M, K, s), "fp8 row quantiser");
         Timed t_(ctx, kind, s);
         return for_segments(ctx, M, [&](int lo, int n) {
-            hipError_t e = iso_launch_gemm_fp8(a8 + (size_t)lo * K, sa + lo, f8.w8, f8.sw, (char *)c + (size_t)lo * N * e_,
-                                               n, N, K, (ctx->flags >> 8) & 15, sk_for(ctx, s), s);
-            if (e != hipSuccess) return fail(ISO_ERR_HIP, "fp8 gemm launch (M=%d N=%d K=%d): %s", n, N, K, hipGetErrorString(e));
-            return (int)ISO_OK;
+            return gemm_fp8(ctx, a8 + (size_t)lo * K, sa + lo, f8.w8, f8.sw, (char *)c + (size_t)lo * N * e_, n, N, K,
+                            kind == ISO_K_GEMM_QKV, s);
         });
     }
     Timed t_(ctx, kind, s);
@@ -208,8 +243,11 @@ int gemm(iso_ctx *ctx, int kind, const void *a, const void *w, void *c, int M, i
         void *cr = (char *)c + (size_t)lo * N * e_;
         hipError_t e;
         const bool mfma = ctx->cfg.dtype == ISO_BF16 && !(ctx->flags & ISO_FLAG_SIMPLE_GEMM);
-        if (mfma && !(ctx->flags & ISO_FLAG_GEMM_STAGED) && iso_gemm_bf16_dtl_supported(n, N, K))
-            e = iso_launch_gemm_bf16_dtl(ar, w, cr, n, N, K, (ctx->flags >> 8) & 15, sk_for(ctx, s), s);
+        const iso_split_plan sp = plan_gemm(ctx, false, kind == ISO_K_GEMM_QKV, n, N, K, s);
+        if (sp.tile >= 0)
+            e = iso_launch_gemm_split(sp, ar, w, nullptr, nullptr, cr, n, N, K, split_ws_for(ctx, s), s);
+        else if (mfma && !(ctx->flags & ISO_FLAG_GEMM_STAGED) && iso_gemm_bf16_dtl_supported(n, N, K))
+            e = iso_launch_gemm_bf16_dtl(ar, w, cr, n, N, K, sp.whole, sk_for(ctx, s), s);
         else if (mfma && iso_gemm_bf16_mfma_supported(n, N, K))
             e = iso_launch_gemm_bf16_mfma(ar, w, cr, n, N, K, s);
         else
@@ -339,9 +377,22 @@ int attn_block_head(iso_ctx *ctx, const iso_weights *w, void *x, void *kc, void 
     } else {
         LAUNCH_TRY(ISO_K_RMSNORM, ck.s, iso_launch_rmsnorm(c.dtype, xr, nullptr, nullptr, nullptr, w->g_attn, yr, ck.n, H, c.rms_eps, ck.s), "rmsnorm");
     }
+    // A split product's second kernel does the rotary embedding and the KV-cache write on the way.
+    const bool fp8_qkv = use_fp8(ctx, f8, ck.n, NQKV, H);
+    const iso_split_plan sp = plan_gemm(ctx, fp8_qkv, true, ck.n, NQKV, H, ck.s);
+    if (sp.tile >= 0 && ctx->gemm_segments <= 1 && !(ctx->flags & ISO_FLAG_NO_FUSE) && split_ws_for(ctx, ck.s)) {
+        if (fp8_qkv && !f8.prequant)
+            LAUNCH_TRY(ISO_K_QUANT, ck.s, iso_launch_quant_rows_fp8(yr, a8, sa, ck.n, H, ck.s), "fp8 row quantiser");
+        LAUNCH_TRY(ISO_K_GEMM_QKV, ck.s,
+                   iso_launch_gemm_split_rope(sp, fp8_qkv ? (const void *)a8 : yr, fp8_qkv ? f8.w8 : w->w_qkv,
+                                              fp8_qkv ? sa : nullptr, fp8_qkv ? f8.sw : nullptr, qkvr, ck.n, NQKV, H,
+                                              split_ws_for(ctx, ck.s), ctx->rope_cos, ctx->rope_sin, kc, vc, ck.lo, c.n_q_heads,
+                                              c.n_kv_heads, c.head_dim, ck.s), "split qkv+rope");
+        return ISO_OK;
+    }
     // bf16 layers with head_dim 128: rotary embedding and KV-cache write ride in the projection's epilogue whenever
     // the launch rule picks a kernel whose waves own whole heads (the 256-wide tile or its stream-K launch)
-    const bool dtl = c.dtype == ISO_BF16 && c.head_dim == 128 && !use_fp8(ctx, f8, ck.n, NQKV, H) &&
+    const bool dtl = c.dtype == ISO_BF16 && c.head_dim == 128 && !fp8_qkv &&
                      !(ctx->flags & (ISO_FLAG_SIMPLE_GEMM | ISO_FLAG_GEMM_STAGED | ISO_FLAG_NO_FUSE)) &&
                      iso_gemm_bf16_dtl_supported(ck.n, NQKV, H);
     if (dtl) {
@@ -349,14 +400,16 @@ int attn_block_head(iso_ctx *ctx, const iso_weights *w, void *x, void *kc, void 
         const int per = ((ck.n + segs - 1) / segs + 255) / 256 * 256;
         bool all_fusable = true;                    // every segment must resolve to a head-owning variant
         for (int lo = 0; lo < ck.n; lo += per) {
-            const int v = iso_gemm_bf16_dtl_resolve(std::min(per, ck.n - lo), NQKV, H, (ctx->flags >> 8) & 15, sk_for(ctx, ck.s));
+            const int n = std::min(per, ck.n - lo);
+            const iso_split_plan p = plan_gemm(ctx, false, true, n, NQKV, H, ck.s);
+            const int v = p.tile >= 0 ? 0 : iso_gemm_bf16_dtl_resolve(n, NQKV, H, p.whole, sk_for(ctx, ck.s));
             all_fusable = all_fusable && (v == 1 || v == 6);
         }
         if (all_fusable) {
             Timed t_(ctx, ISO_K_GEMM_QKV, ck.s);
             return for_segments(ctx, ck.n, [&](int lo, int n) {
                 iso_sk_ws *sk = sk_for(ctx, ck.s);
-                const int v = iso_gemm_bf16_dtl_resolve(n, NQKV, H, (ctx->flags >> 8) & 15, sk);
+                const int v = iso_gemm_bf16_dtl_resolve(n, NQKV, H, plan_gemm(ctx, false, true, n, NQKV, H, ck.s).whole, sk);
                 hipError_t e_ = iso_launch_gemm_qkv_rope_bf16(yr + (size_t)lo * H * e, w->w_qkv, qkvr + (size_t)lo * NQKV * e, n,
                                                               NQKV, H, v, sk, ctx->rope_cos, ctx->rope_sin, kc, vc, ck.lo + lo,
                                                               c.n_q_heads, c.n_kv_heads, ck.s);
@@ -415,16 +468,24 @@ int mlp_block(iso_ctx *ctx, const iso_weights *w, void *x, const Chunk &ck, int 
             LAUNCH_TRY(ISO_K_QUANT, ck.s, iso_launch_quant_rows_fp8(yr, a8, sa, ck.n, H, ck.s), "fp8 row quantiser");
         Timed t_(ctx, ISO_K_GEMM_GATE_UP, ck.s);
         ISO_TRY(for_segments(ctx, ck.n, [&](int lo, int n) {
-            hipError_t e_ = iso_launch_gemm_swiglu_fp8(a8 + (size_t)lo * H, sa + lo, f8gu.w8, f8gu.sw, actr + (size_t)lo * F * e,
-                                                       n, F, H, (ctx->flags >> 8) & 15, sk_for(ctx, ck.s), ck.s);
+            const iso_split_plan sp = plan_gemm(ctx, true, false, n, 2 * F, H, ck.s);
+            hipError_t e_ = sp.tile >= 0 ? iso_launch_gemm_split_swiglu(sp, a8 + (size_t)lo * H, f8gu.w8, sa + lo, f8gu.sw,
+                                                                       actr + (size_t)lo * F * e, n, F, H,
+                                                                       split_ws_for(ctx, ck.s), ck.s)
+                                        : iso_launch_gemm_swiglu_fp8(a8 + (size_t)lo * H, sa + lo, f8gu.w8, f8gu.sw, actr + (size_t)lo * F * e,
+                                                       n, F, H, sp.whole, sk_for(ctx, ck.s), ck.s);
             if (e_ != hipSuccess) return fail(ISO_ERR_HIP, "fp8 gate/up+swiglu launch: %s", hipGetErrorString(e_));
             return (int)ISO_OK;
         }));
     } else if (fused) {   // gate/up projection with the activation in its epilogue: the [Tc, 2F] tensor never exists
         Timed t_(ctx, ISO_K_GEMM_GATE_UP, ck.s);
         ISO_TRY(for_segments(ctx, ck.n, [&](int lo, int n) {
-            hipError_t e_ = iso_launch_gemm_swiglu_bf16(yr + (size_t)lo * H * e, w->w_gate_up, actr + (size_t)lo * F * e, n, F, H,
-                                                        (ctx->flags >> 8) & 15, sk_for(ctx, ck.s), ck.s);
+            const iso_split_plan sp = plan_gemm(ctx, false, false, n, 2 * F, H, ck.s);
+            hipError_t e_ = sp.tile >= 0 ? iso_launch_gemm_split_swiglu(sp, yr + (size_t)lo * H * e, w->w_gate_up, nullptr,
+                                                                       nullptr, actr + (size_t)lo * F * e, n, F, H,
+                                                                       split_ws_for(ctx, ck.s), ck.s)
+                                        : iso_launch_gemm_swiglu_bf16(yr + (size_t)lo * H * e, w->w_gate_up, actr + (size_t)lo * F * e, n, F, H,
+                                                        sp.whole, sk_for(ctx, ck.s), ck.s);
             if (e_ != hipSuccess) return fail(ISO_ERR_HIP, "gate/up+swiglu launch: %s", hipGetErrorString(e_));
             return (int)ISO_OK;
         }));
@@ -474,6 +535,8 @@ int chunk_streams(iso_ctx *ctx, int nc, hipStream_t *out) {
             HIP_TRY(hipStreamCreateWithFlags(&ctx->xstream[k], hipStreamNonBlocking));
             if (ctx->cfg.dtype == ISO_BF16 && !ctx->aws[k].part) {   // same launch choices as on the caller's streams
                 HIP_TRY(attn_ws_create(&ctx->aws[k]));
+                ctx->sk[k].num_wg = ctx->sk[0].num_wg;
+                HIP_TRY(hipMalloc(&ctx->sk[k].base, iso_gemm_sk_ws_bytes(ctx->sk[k].num_wg)));
                 HIP_TRY(hipDeviceSynchronize());
             }
         }
@@ -767,7 +830,7 @@ int iso_destroy(iso_ctx *ctx) {
         if (ctx->xstream[k]) (void)hipStreamDestroy(ctx->xstream[k]);
     }
     if (ctx->sk[0].err) (void)hipHostFree(ctx->sk[0].err);
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < ISO_MAX_CHUNKS; ++i)
         if (ctx->sk[i].base) (void)hipFree(ctx->sk[i].base);
     for (int i = 0; i < ISO_MAX_CHUNKS; ++i) {
         if (ctx->aws[i].part) (void)hipFree(ctx->aws[i].part);
@@ -825,10 +888,7 @@ int iso_gemm_fp8(iso_ctx *ctx, const void *a8, const float *sa, const void *w8, 
     if (!iso_gemm_fp8_supported(M, N, K)) return fail(ISO_ERR_SHAPE, "M=%d N=%d K=%d: need M >= 1, N %% 8 == 0, K %% 128 == 0", M, N, K);
     ISO_TRY(sk_status(ctx));
     Timed t_(ctx, ISO_K_GEMM_O, (hipStream_t)stream);
-    hipError_t e = iso_launch_gemm_fp8(a8, sa, w8, sw, c, M, N, K, (ctx->flags >> 8) & 15, sk_for(ctx, (hipStream_t)stream),
-                                       (hipStream_t)stream);
-    if (e != hipSuccess) return fail(ISO_ERR_HIP, "fp8 gemm launch: %s", hipGetErrorString(e));
-    return ISO_OK;
+    return gemm_fp8(ctx, a8, sa, w8, sw, c, M, N, K, false, (hipStream_t)stream);
 }
 
 int iso_set_gemm_segments(iso_ctx *ctx, int n) {

@@ -61,7 +61,9 @@ struct iso_ctx {
     float *rope_sin;   // [max_seq, d/2]
     int gemm_segments; // launches per projection GEMM along M (0 or 1: one launch)
     int sk_hold;       // set while a pass enqueues work for which stream-K is not to be picked
-    iso_sk_ws sk[2];   // stream-K GEMM workspaces, one per caller stream (bf16 contexts only; base == null otherwise)
+    // GEMM workspaces (bf16 contexts only; base == null otherwise): [0], [1] for the caller's streams, used by the stream-K
+    // launch and by split products; [k] for xstream[k], split products only
+    iso_sk_ws sk[ISO_MAX_CHUNKS];
     iso_attn_ws aws[ISO_MAX_CHUNKS];   // key-split attention workspaces: [0], [1] for the caller's streams, [k] for xstream[k]
     void *host_sink;   // pinned, 2 * max_seq * hidden elements
     // optional per-launch timing (iso_timing_*): event pairs recorded around every launch, in its stream
@@ -98,6 +100,7 @@ hipError_t iso_launch_gemm_swiglu_bf16(const void *a, const void *w, void *act, 
                                        iso_sk_ws *sk_or_null, hipStream_t s);
 void iso_gemm_bf16_dtl_plan(int M, int N, int K, int num_wg, int *kind, int *team, int *grid);
 size_t iso_gemm_sk_ws_bytes(int num_wg);   // device bytes a stream-K workspace for num_wg workgroups needs
+size_t iso_gemm_sk_slot_bytes(void);       // of which behind the flag words, per workgroup
 int iso_gemm_sk_max_wg(void);
 bool iso_gemm_swiglu_bf16_supported(int M, int F, int K);
 bool iso_gemm_fp8_supported(int M, int N, int K);
@@ -109,6 +112,22 @@ hipError_t iso_launch_gemm_fp8(const void *a8, const float *sa, const void *w8, 
                                int K, int variant, iso_sk_ws *sk_or_null, hipStream_t s);
 hipError_t iso_launch_gemm_swiglu_fp8(const void *a8, const float *sa, const void *w8, const float *sw, void *act, int M,
                                       int F, int K, int variant, iso_sk_ws *sk_or_null, hipStream_t s);
+// What a projection is launched as.  tile >= 0: a tile shape of gemm_split.hip with the k range in `shares` parts (more than
+// one share, and the rotary form always, needs a workspace); tile < 0: variant `whole` of the whole-tile kernels.
+struct iso_split_plan {
+    int tile, shares, whole;
+};
+iso_split_plan iso_gemm_split_plan(bool fp8, bool rope, int whole, int M, int N, int K, size_t ws_bytes, int ncu, bool shared);
+int iso_gemm_fp8_whole(int M, int N, int K, const iso_sk_ws *sk_or_null);   // the FP8 rule's variant (1, 3 or 6)
+bool iso_gemm_split_supported(bool fp8, int M, int N, int K);
+// sa / sw null: bf16 operands, else FP8 operands and their row scales
+hipError_t iso_launch_gemm_split(const iso_split_plan &plan, const void *a, const void *w, const float *sa, const float *sw,
+                                 void *c, int M, int N, int K, iso_sk_ws *ws_or_null, hipStream_t s);
+hipError_t iso_launch_gemm_split_swiglu(const iso_split_plan &plan, const void *a, const void *w, const float *sa,
+                                        const float *sw, void *act, int M, int F, int K, iso_sk_ws *ws_or_null, hipStream_t s);
+hipError_t iso_launch_gemm_split_rope(const iso_split_plan &plan, const void *a, const void *w, const float *sa, const float *sw,
+                                      void *qkv, int M, int N, int K, iso_sk_ws *ws, const float *cos_t, const float *sin_t,
+                                      void *k_cache, void *v_cache, int q_offset, int nq, int nkv, int d, hipStream_t s);
 // stream-K with the workspace in a static device array (no allocation at call time)
 hipError_t iso_gemm_static_setup(void);     // once per device, with that device current
 size_t iso_gemm_static_scratch_bytes(void);
