@@ -19,12 +19,20 @@
 
 namespace {
 
-constexpr int D = 128;
 constexpr int BM = 128;            // query rows per workgroup (4 waves x 32)
 constexpr int BN = 64;             // keys per tile
-constexpr int ROW_B = D * 2;       // bytes per K/V row in LDS
-constexpr int TILE_B = BN * ROW_B; // 16 KB
-constexpr int STAGE_B = 2 * TILE_B;
+template <int D> struct Head {     // D = head_dim: 128 or 64
+    static constexpr int ROW_B = D * 2;                // bytes per K/V row in LDS
+    static constexpr int TILE_B = BN * ROW_B;          // 16 or 8 KB
+    static constexpr int STAGE_B = 2 * TILE_B;
+    static constexpr int CHUNKS = ROW_B / 16;          // 16-byte chunks per row
+    static constexpr int ROWS_PER_LOAD = 1024 / ROW_B; // rows of one wave-load
+    static constexpr int LOADS = TILE_B / 1024 / 4;    // wave-loads per wave and tile
+    // Chunk swizzles (applied on the global side).  A wave's K read takes one chunk of 32 rows, its V read four
+    // neighbouring chunks of eight rows; a row of 256 bytes spans all 64 banks, a row of 128 bytes half of them.
+    static __device__ __forceinline__ int k_swz(int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); }
+    static __device__ __forceinline__ int v_swz(int row) { return D == 128 ? ((row & 3) << 2) : (((row >> 1) & 1) << 2); }
+};
 // Key split across workgroups (launches that leave most compute units idle): one partial state of a row block =
 // 16 float4 of unnormalised output + (running maximum, partial sum) for each of the 256 lanes that hold it.
 constexpr int PART_O_BYTES = 16 * 256 * 16;
@@ -75,7 +83,11 @@ __device__ __forceinline__ float half_swap_max(float v) {
 // cache-bypassing stores and then raises the row block's arrival counter; the workgroup that arrives last fetches all
 // ksplit states and folds them in share order -- the result does not depend on who arrived last -- normalises, writes
 // the rows and puts the counter back to zero for the next launch.  Nobody waits for anybody.
-template <int NSTAGE, int KVS, bool SKEW>
+//
+// D = 64: the products of a head are half as long against the same number of exponentials, so the matrix pipe has room, and
+// the probabilities go into the second product as two bf16 terms each (value + remainder, 16 mantissa bits): this head size
+// then keeps the accuracy of the fp32 kernel it took before.
+template <int D, int NSTAGE, int KVS, bool SKEW>
 __global__ __launch_bounds__(256 * KVS, KVS == 1 ? 2 : 1) void attn_bf16_dtl_kernel(const bf16_t *__restrict__ Q,
                                                             const bf16_t *__restrict__ Kc,
                                                             const bf16_t *__restrict__ Vc,
@@ -83,6 +95,9 @@ __global__ __launch_bounds__(256 * KVS, KVS == 1 ? 2 : 1) void attn_bf16_dtl_ker
                                                             int kv_len, int nq, int nkv, int q_stride, int pair,
                                                             int ksplit, unsigned char *part_ws, unsigned *part_cnt) {
 #if defined(__HIP_DEVICE_COMPILE__)
+    using Hd = Head<D>;
+    constexpr int ROW_B = Hd::ROW_B, TILE_B = Hd::TILE_B, STAGE_B = Hd::STAGE_B, LOADS = Hd::LOADS;
+    constexpr int NP = D == 64 ? 2 : 1;        // bf16 terms per probability
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     __shared__ int last_arriver;
 
@@ -119,31 +134,31 @@ __global__ __launch_bounds__(256 * KVS, KVS == 1 ? 2 : 1) void attn_bf16_dtl_ker
         for (int ks = 0; ks < D / 16; ++ks) qf[ks] = *reinterpret_cast<const bf16x8_t *>(qp + ks * 16);
     }
 
-    // ---- direct-to-LDS loads: wave-load = 4 rows x 256 B; lane = (row l/16, slot l%16)
+    // ---- direct-to-LDS loads: wave-load = 4 rows x 256 B (8 x 128); lane = (row l / CHUNKS, slot l % CHUNKS)
     const uint32_t row_stride = (uint32_t)nkv * D * 2u;                         // bytes between cache rows
     const uint32_t n_rec = (uint32_t)(kv_len - 1) * row_stride + (uint32_t)ROW_B;  // this head's slice, rows < kv_len
     const __amdgpu_buffer_rsrc_t rs_k =
         __builtin_amdgcn_make_buffer_rsrc((void *)(Kc + (size_t)g * D), 0, (int)n_rec, 0x00020000);
     const __amdgpu_buffer_rsrc_t rs_v =
         __builtin_amdgcn_make_buffer_rsrc((void *)(Vc + (size_t)g * D), 0, (int)n_rec, 0x00020000);
-    uint32_t k_off[4], v_off[4];
+    uint32_t k_off[LOADS], v_off[LOADS];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int r = (wave + 4 * i) * 4 + (lane >> 4);
-        const int slot = lane & 15;
-        k_off[i] = (uint32_t)r * row_stride + (uint32_t)((slot ^ (r & 15)) << 4);
-        v_off[i] = (uint32_t)r * row_stride + (uint32_t)((slot ^ ((r & 3) << 2)) << 4);
+    for (int i = 0; i < LOADS; ++i) {
+        const int r = (wave + 4 * i) * Hd::ROWS_PER_LOAD + lane / Hd::CHUNKS;
+        const int slot = lane % Hd::CHUNKS;
+        k_off[i] = (uint32_t)r * row_stride + (uint32_t)((slot ^ Hd::k_swz(r)) << 4);
+        v_off[i] = (uint32_t)r * row_stride + (uint32_t)((slot ^ Hd::v_swz(r)) << 4);
     }
     auto issue = [&](int stage, int j0) {
         unsigned char *base = lds_g + stage * STAGE_B;
         const uint32_t tile_off = (uint32_t)j0 * row_stride;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < LOADS; ++i)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
                 rs_k, (__attribute__((address_space(3))) void *)(base + (wave + 4 * i) * 1024), 16, k_off[i] + tile_off, 0,
                 0, 0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < LOADS; ++i)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
                 rs_v, (__attribute__((address_space(3))) void *)(base + TILE_B + (wave + 4 * i) * 1024), 16,
                 v_off[i] + tile_off, 0, 0, 0);
@@ -153,7 +168,7 @@ __global__ __launch_bounds__(256 * KVS, KVS == 1 ? 2 : 1) void attn_bf16_dtl_ker
         unsigned char *base = lds_g + stage * STAGE_B + which * TILE_B;
         const uint32_t tile_off = (uint32_t)j0 * row_stride;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < LOADS; ++i)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
                 which ? rs_v : rs_k, (__attribute__((address_space(3))) void *)(base + (wave + 4 * i) * 1024), 16,
                 (which ? v_off[i] : k_off[i]) + tile_off, 0, 0, 0);
@@ -162,11 +177,11 @@ __global__ __launch_bounds__(256 * KVS, KVS == 1 ? 2 : 1) void attn_bf16_dtl_ker
     // ---- LDS read addressing
     // K (A operand of S^T): lane = key row lcol of the 32-key block, 16-byte chunk 2*ks + lgrp, swizzled by row & 15
     const int k_row_off = lcol * ROW_B;
-    const int k_sw = lcol & 15;
+    const int k_sw = Hd::k_swz(lcol);
     // V (A operand of O^T, transposing read): 16-lane group = 4 keys x 16 dims
     const int s16 = lane & 15, half16 = (lane >> 4) & 1;
     const int v_row_base = 4 * lgrp + (s16 >> 2);                 // + 32 sub + 16 t + 8 h
-    const int v_sw = ((s16 >> 2) & 3) << 2;
+    const int v_sw = Hd::v_swz(v_row_base);                       // the rows a lane reads differ by multiples of eight
     const int v_chunk_base = 2 * half16 + ((s16 & 3) >> 1);       // + 4 dt
     const int v_byte = (s16 & 1) << 3;
 
@@ -206,7 +221,7 @@ __global__ __launch_bounds__(256 * KVS, KVS == 1 ? 2 : 1) void attn_bf16_dtl_ker
         __syncthreads();
     };
 
-    // --- S^T = K Q^T of tile jt (K stage jt % 2) for two 32-key blocks.  The 16 K fragments are fetched four at a
+    // --- S^T = K Q^T of tile jt (K stage jt % 2) for two 32-key blocks.  The 16 (8) K fragments are fetched four at a
     //     time, one group ahead of the MFMAs that use them (left to itself the compiler issues every LDS read right
     //     before its MFMA and the matrix pipe waits out the LDS latency sixteen times per tile).  WEAVE: once the last
     //     K fragment reads are out (LDS writes keep their order against LDS reads), requests(0) and requests(1) -- four
@@ -220,8 +235,9 @@ __global__ __launch_bounds__(256 * KVS, KVS == 1 ? 2 : 1) void attn_bf16_dtl_ker
 #pragma unroll
             for (int r = 0; r < 16; ++r) sc_t[sub][r] = 0.f;
         bf16x8_t kf[2][4];
-        auto read_k = [&](int buf, int grp) {          // group = (sub, half of the head dim): 4 k-steps
-            const int sub = grp >> 1, ks0 = (grp & 1) * 4;
+        constexpr int GPS = D / 64, NGRP = 2 * GPS;    // groups of four k-steps per 32-key block, and in all
+        auto read_k = [&](int buf, int grp) {
+            const int sub = grp / GPS, ks0 = (grp % GPS) * 4;
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 kf[buf][i] = *reinterpret_cast<const bf16x8_t *>(kb + sub * 32 * ROW_B + k_row_off +
@@ -229,15 +245,16 @@ __global__ __launch_bounds__(256 * KVS, KVS == 1 ? 2 : 1) void attn_bf16_dtl_ker
         };
         read_k(0, 0);
 #pragma unroll
-        for (int grp = 0; grp < 4; ++grp) {
-            if (grp + 1 < 4) read_k((grp + 1) & 1, grp + 1);
+        for (int grp = 0; grp < NGRP; ++grp) {
+            if (grp + 1 < NGRP) read_k((grp + 1) & 1, grp + 1);
             __builtin_amdgcn_sched_barrier(0);
-            const int sub = grp >> 1, ks0 = (grp & 1) * 4;
+            const int sub = grp / GPS, ks0 = (grp % GPS) * 4;
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 sc_t[sub] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[grp & 1][i], qf[ks0 + i], sc_t[sub], 0, 0, 0);
-            if (WEAVE && grp >= 2) {
-                requests(grp - 2);
+            if (WEAVE && grp >= NGRP - GPS) {      // D = 64: both requests (two loads each) behind the last group
+                requests(grp - (NGRP - GPS));
+                if (GPS == 1) requests(1);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -251,7 +268,7 @@ __global__ __launch_bounds__(256 * KVS, KVS == 1 ? 2 : 1) void attn_bf16_dtl_ker
     // --- mask (only tiles that touch the diagonal or the end of the cache), running maximum and sum, probabilities.
     //     The scores stay unscaled: the softmax scale is positive, so the running maximum can be kept in raw units and
     //     the scale folded into the exponent's multiply-add.
-    auto softmax = [&](int j0, auto tail_c, f32x16_t (&sc_t)[2], bf16x8_t (&pb)[2][2]) {
+    auto softmax = [&](int j0, auto tail_c, f32x16_t (&sc_t)[2], bf16x8_t (&pb)[NP][2][2]) {
         constexpr bool TAIL = decltype(tail_c)::value;
         if (TAIL && ((j0 + BN - 1 > q_offset + m0 + wave * 32) || (j0 + BN > kv_len))) {
 #pragma unroll
@@ -277,7 +294,9 @@ __global__ __launch_bounds__(256 * KVS, KVS == 1 ? 2 : 1) void attn_bf16_dtl_ker
             for (int r = 0; r < 16; ++r) {
                 const float p = __builtin_amdgcn_exp2f(fmaf(sc_t[sub][r], sc, neg_m));
                 psum += p;
-                pb[sub][r / 8][r % 8] = (bf16_t)p;
+                const bf16_t hi = (bf16_t)p;
+                pb[0][sub][r / 8][r % 8] = hi;
+                if constexpr (NP == 2) pb[1][sub][r / 8][r % 8] = (bf16_t)(p - (float)hi);
             }
         // rescale the running sums only when some row of this wave saw a new maximum (wave-uniform branch):
         // deep into a long cache the maxima have settled and the 64 multiplies per tile are skipped
@@ -296,7 +315,7 @@ __global__ __launch_bounds__(256 * KVS, KVS == 1 ? 2 : 1) void attn_bf16_dtl_ker
     // --- O^T += V^T P^T with V tile vt (V stage vt % 2).  k-slots 8*lgrp .. +8 of MFMA step (sub, t) hold keys
     //     32 sub + 16 t + 4 lgrp + {0..3} and 32 sub + 16 t + 8 + 4 lgrp + {0..3}: two transposing reads.
     //     The V fragments of one 32-dim block (4 MFMAs) are fetched while the previous block is multiplied.
-    auto pv = [&](int vt, bf16x8_t (&pb)[2][2]) {
+    auto pv = [&](int vt, bf16x8_t (&pb)[NP][2][2]) {
         bf16x8_t vf[2][4];
         const uint32_t vb_addr = lds_addr + (uint32_t)((vt % NSTAGE) * STAGE_B + TILE_B + v_row_base * ROW_B + v_byte);
         auto read_v = [&](int buf, int dt) {
@@ -320,7 +339,9 @@ __global__ __launch_bounds__(256 * KVS, KVS == 1 ? 2 : 1) void attn_bf16_dtl_ker
             }
 #pragma unroll
             for (int st = 0; st < 4; ++st)
-                o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[dt & 1][st], pb[st >> 1][st & 1], o[dt], 0, 0, 0);
+#pragma unroll
+                for (int np = 0; np < NP; ++np)
+                    o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[dt & 1][st], pb[np][st >> 1][st & 1], o[dt], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
@@ -339,7 +360,7 @@ __global__ __launch_bounds__(256 * KVS, KVS == 1 ? 2 : 1) void attn_bf16_dtl_ker
                 if (j0 > wave_q_max) return;            // every key of this tile is above this wave's diagonal
             }
             f32x16_t sc_t[2];
-            bf16x8_t pb[2][2];
+            bf16x8_t pb[NP][2][2];
             qk_scores(jt, sc_t, std::integral_constant<bool, !TAIL>{},
                       [&](int which) { issue_half((jt + 1) % NSTAGE, j0 + BN, which); });
             softmax(j0, tail_c, sc_t, pb);
@@ -356,7 +377,7 @@ __global__ __launch_bounds__(256 * KVS, KVS == 1 ? 2 : 1) void attn_bf16_dtl_ker
         // the same order as the plain loop, so the results are bit-identical.
         // K tile jt+1 and V tile jt are requested in iteration jt: V stage jt % 2 was last read (tile jt-2) in
         // iteration jt-1, K stage (jt+1) % 2 (tile jt-1) likewise.
-        bf16x8_t pb[2][2];
+        bf16x8_t pb[NP][2][2];
         bool have_p = false;                            // wave-uniform
         auto tile = [&](int jt, auto tail_c) {
             constexpr bool TAIL = decltype(tail_c)::value;
@@ -390,8 +411,8 @@ __global__ __launch_bounds__(256 * KVS, KVS == 1 ? 2 : 1) void attn_bf16_dtl_ker
         // merge the two groups: group 1 parks (m, l, o) of its rows in LDS, group 0 folds them into its own.
         // A lane of group 0 and the lane with the same wave and lane number in group 1 hold the same rows and dims.
         __syncthreads();                    // every wave is done with the K/V stages
-        float *xo = reinterpret_cast<float *>(lds);                       // [64 values][256 threads]
-        float *xm = xo + 64 * 256;                                        // [2][256]
+        float *xo = reinterpret_cast<float *>(lds);                       // [D / 2 values][256 threads]
+        float *xm = xo + D / 2 * 256;                                     // [2][256]
         const int t4 = tid & 255;
         if (kgrp == 1) {
 #pragma unroll
@@ -456,9 +477,9 @@ __global__ __launch_bounds__(256 * KVS, KVS == 1 ? 2 : 1) void attn_bf16_dtl_ker
                 for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
             for (int sp = 0; sp < ksplit; ++sp) {
                 const uint32_t slot = (uint32_t)sp * PART_BYTES;
-                f32x4_t po[16];
+                f32x4_t po[D / 8];
 #pragma unroll
-                for (int v = 0; v < 16; ++v)
+                for (int v = 0; v < D / 8; ++v)
                     po[v] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(
                                                             rs_part, slot + (uint32_t)((v * 256 + t4) * 16), 0, PART_COHERENT));
                 const float m_b = __uint_as_float(
@@ -499,22 +520,24 @@ __global__ __launch_bounds__(256 * KVS, KVS == 1 ? 2 : 1) void attn_bf16_dtl_ker
 
 bool iso_attn_bf16_dtl_supported(int d, int kv_len, int nkv) {
     // the K/V slice of one head must be addressable with 32-bit byte offsets
-    return d == D && (long long)kv_len * nkv * D * 2 < (1ll << 31);
+    return (d == 128 || d == 64) && (long long)kv_len * nkv * d * 2 < (1ll << 31);
 }
 
 // shape: 0 = chosen from the size; forced by tests and measurement: 1 = key split inside the workgroup, 2 = key split
 // and two row blocks per workgroup, 3 = one row block, two workgroups per compute unit.
 // ksplit_req: 0 = key split across workgroups chosen from the size, 1 = never, 2..4 = that many shares (forced by tests;
 // ignored when the workspace is missing or too small).
-hipError_t iso_launch_attn_bf16_dtl(const void *q, const void *k, const void *v, void *out, int Tc, int q_offset,
-                                    int kv_len, int nq, int nkv, int d, int q_stride, int shape, int ksplit_req,
-                                    const iso_attn_ws *ws, hipStream_t s) {
-    if (d != D) return hipErrorInvalidValue;
+namespace {
+template <int D>
+hipError_t launch_attn(const void *q, const void *k, const void *v, void *out, int Tc, int q_offset, int kv_len,
+                       int nq, int nkv, int q_stride, int shape, int ksplit_req, const iso_attn_ws *ws, hipStream_t s) {
+    // two stages per key group; the merge of the two groups needs D / 2 + 2 floats per thread pair
+    constexpr int LDS1 = 2 * Head<D>::STAGE_B, LDS2 = 2 * LDS1 > (D / 2 + 2) * 1024 ? 2 * LDS1 : (D / 2 + 2) * 1024;
     static iso_dev_mask lds_allowed[2];
-    if (hipError_t e = iso_allow_lds(reinterpret_cast<const void *>(attn_bf16_dtl_kernel<2, 1, false>), 2 * STAGE_B, &lds_allowed[0]);
+    if (hipError_t e = iso_allow_lds(reinterpret_cast<const void *>(attn_bf16_dtl_kernel<D, 2, 1, false>), LDS1, &lds_allowed[0]);
         e != hipSuccess)
         return e;
-    if (hipError_t e = iso_allow_lds(reinterpret_cast<const void *>(attn_bf16_dtl_kernel<2, 2, true>), 2 * 2 * STAGE_B, &lds_allowed[1]);
+    if (hipError_t e = iso_allow_lds(reinterpret_cast<const void *>(attn_bf16_dtl_kernel<D, 2, 2, true>), LDS2, &lds_allowed[1]);
         e != hipSuccess)
         return e;
     const int n_blocks = (Tc + BM - 1) / BM;
@@ -546,15 +569,25 @@ hipError_t iso_launch_attn_bf16_dtl(const void *q, const void *k, const void *v,
         if (wgs * ksplit > ws->max_slots) ksplit = 1;
     }
     if (mode == 0 || mode == 1)
-        hipLaunchKernelGGL((attn_bf16_dtl_kernel<2, 2, true>), dim3(mode == 0 ? n_blocks : (n_blocks + 1) / 2, nq, ksplit),
-                           dim3(512), 2 * 2 * STAGE_B, s, (const bf16_t *)q, (const bf16_t *)k, (const bf16_t *)v,
+        hipLaunchKernelGGL((attn_bf16_dtl_kernel<D, 2, 2, true>), dim3(mode == 0 ? n_blocks : (n_blocks + 1) / 2, nq, ksplit),
+                           dim3(512), LDS2, s, (const bf16_t *)q, (const bf16_t *)k, (const bf16_t *)v,
                            (bf16_t *)out, Tc, q_offset, kv_len, nq, nkv, q_stride, mode, ksplit,
                            ws ? ws->part : nullptr, ws ? ws->cnt : nullptr);
     else
-        hipLaunchKernelGGL((attn_bf16_dtl_kernel<2, 1, false>), dim3(n_blocks, nq, ksplit), dim3(256), 2 * STAGE_B, s,
+        hipLaunchKernelGGL((attn_bf16_dtl_kernel<D, 2, 1, false>), dim3(n_blocks, nq, ksplit), dim3(256), LDS1, s,
                            (const bf16_t *)q, (const bf16_t *)k, (const bf16_t *)v, (bf16_t *)out, Tc, q_offset, kv_len, nq,
                            nkv, q_stride, 0, ksplit, ws ? ws->part : nullptr, ws ? ws->cnt : nullptr);
     return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t iso_launch_attn_bf16_dtl(const void *q, const void *k, const void *v, void *out, int Tc, int q_offset,
+                                    int kv_len, int nq, int nkv, int d, int q_stride, int shape, int ksplit_req,
+                                    const iso_attn_ws *ws, hipStream_t s) {
+    if (d == 128) return launch_attn<128>(q, k, v, out, Tc, q_offset, kv_len, nq, nkv, q_stride, shape, ksplit_req, ws, s);
+    if (d == 64) return launch_attn<64>(q, k, v, out, Tc, q_offset, kv_len, nq, nkv, q_stride, shape, ksplit_req, ws, s);
+    return hipErrorInvalidValue;
 }
 
 size_t iso_attn_part_bytes(void) { return PART_BYTES; }
