@@ -49,8 +49,7 @@ typedef enum { ISO_F32 = 0, ISO_BF16 = 1 } iso_dtype;
 
 /* What stands at the two communication points of a layer (after o_proj, after down). */
 typedef enum {
-    ISO_COMM_NONE = 0, /* nothing: compute only.  With no transfer to hide the library may compute neighbouring chunks */
-                       /* together; the result does not depend on the cut (beyond the order of fp32 sums)            */
+    ISO_COMM_NONE = 0, /* nothing: compute only                                                      */
     ISO_COMM_D2H = 1,  /* copy the [Tc, hidden] partial to pinned host memory in the chunk's stream;  */
                        /* the consumer kernel is behind the copy in stream order                      */
     ISO_COMM_D2H_INT8 = 2 /* Section 3.2 (communication dominates): quantise the partial to int8 first.   */
@@ -59,6 +58,10 @@ typedef enum {
                        /* pitch hidden + 16 bytes); the layer continues with code*scale, the value a receiver */
                        /* of the quantised payload would add to its residual stream.                          */
 } iso_comm;
+
+/* A cut serves to hide transfers behind another chunk's work.  Where they are too short for that (or there are none) the
+ * library computes neighbouring chunks together, unless kernel-choice flags are set; results do not depend on the cut beyond
+ * the order of fp32 sums. */
 
 /* How the two chunks are issued (Section 1, Figure 1 (a) versus (d)). */
 typedef enum {

@@ -549,19 +549,28 @@ int chunk_streams(iso_ctx *ctx, int nc, hipStream_t *out) {
 int run_stack(iso_ctx *ctx, const iso_weights *layers, int n_layers, void *x, void *k_caches, void *v_caches,
               const int *edges_in, int nc, int comm, int sched) {
     const iso_cfg &c = ctx->cfg;
-    // Chunks exist to hide transfers.  With none to hide, rows that a smaller cut would only spread over more and smaller
-    // products stay together: one chunk up to 2048 tokens or without a second stream, else two (they fill each other's last
-    // rounds of the chip).  The rows of a layer do not depend on the cut, only the order of some sums does.  Measured, cut in
-    // two against whole: 1024 tokens 403 / 356 us (30B TP=4), 362 / 291 (70B TP=8); 2048 642 / 587 and 527 / 459; 3000
-    // 773 / 848 and 689 / 721; 6 against 2 chunks of 8192 tokens 5271 / 4417 us (30B TP=4, two layers).
+    // Chunks exist to hide transfers.  Where there is little or nothing to hide, rows that a cut would only spread over more
+    // and smaller products stay together: the rows of a layer do not depend on the cut, only the order of some sums does.
+    // (With kernel-choice flags set, for tests and measurement, the cut is taken as it is.)
+    //   * Transfers of at most 4 MB: measured, cut in half / whole: 70B TP=8, bf16 payload, 128 tokens (2 MB) 226 / 197 us,
+    //     256 (4 MB) 313 / 307, 400 (6.6 MB) 398 / 433; int8 payload, 256 (2 MB) 339 / 236, 512 (4 MB) 408 / 360, 768 (6 MB)
+    //     482 / 513; hidden 2048, bf16, 512 (2 MB) 218 / 193, 1024 (4 MB) even, 1536 (6 MB) 424 / 488; int8, 1024 (2 MB)
+    //     319 / 251, 1536 (3 MB) 355 / 372 -- hence the limit on tokens beside the one on bytes.
+    //   * No transfers: one chunk up to 2048 tokens or without a second stream, else two (they fill each other's last rounds
+    //     of the chip): 1024 tokens 403 / 356 us (30B TP=4), 362 / 291 (70B TP=8); 2048 642 / 587 and 527 / 459; 3000
+    //     773 / 848 and 689 / 721; 6 against 2 chunks of 8192 tokens 5271 / 4417 us (30B TP=4, two layers).
     int edges[ISO_MAX_CHUNKS + 1];
     std::copy(edges_in, edges_in + nc + 1, edges);
-    if (comm == ISO_COMM_NONE && nc > 1) {
-        const int T = edges[nc];
-        if (T <= 2048 || sched == ISO_SCHED_SERIAL || ctx->stream[1] == ctx->stream[0]) {
+    const int T = edges[nc];
+    const size_t row_bytes = comm == ISO_COMM_D2H_INT8 ? (size_t)c.hidden + 16 : (size_t)c.hidden * ctx->elt;
+    const bool whole = comm == ISO_COMM_NONE
+                           ? T <= 2048 || sched == ISO_SCHED_SERIAL || ctx->stream[1] == ctx->stream[0]
+                           : T <= 1280 && T * row_bytes <= 4u << 20;
+    if (nc > 1 && !(ctx->flags & ~ISO_FLAG_FP8_GEMM)) {
+        if (whole) {
             edges[1] = T;
             nc = 1;
-        } else if (nc > 2) {
+        } else if (comm == ISO_COMM_NONE && nc > 2) {
             int k = 1;       // the cut nearest to 0.55 T: the later half of a causal prompt is the dearer one
             for (int j = 2; j < nc; ++j)
                 if (fabs(edges[j] - 0.55 * T) < fabs(edges[k] - 0.55 * T)) k = j;
