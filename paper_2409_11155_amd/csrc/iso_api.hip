@@ -250,6 +250,8 @@ int gemm(iso_ctx *ctx, int kind, const void *a, const void *w, void *c, int M, i
             e = iso_launch_gemm_bf16_dtl(ar, w, cr, n, N, K, sp.whole, sk_for(ctx, s), s);
         else if (mfma && iso_gemm_bf16_mfma_supported(n, N, K))
             e = iso_launch_gemm_bf16_mfma(ar, w, cr, n, N, K, s);
+        else if (ctx->cfg.dtype == ISO_F32 && !(ctx->flags & ISO_FLAG_SIMPLE_GEMM) && iso_gemm_f32_supported(ar, w, n, N, K))
+            e = iso_launch_gemm_f32(ar, w, cr, n, N, K, s);
         else
             e = iso_launch_gemm_simple(ctx->cfg.dtype, ar, w, cr, n, N, K, s);
         if (e != hipSuccess)
@@ -269,6 +271,8 @@ int attention(iso_ctx *ctx, const void *q, int q_stride, const void *kc, const v
                                      (ctx->flags >> 12) & 3, (ctx->flags >> 14) & 7, attn_ws_for(ctx, s), s);
     else if (mfma && iso_attn_bf16_mfma_supported(c.head_dim))
         e = iso_launch_attn_bf16_mfma(q, kc, vc, out, Tc, q_offset, kv_len, c.n_q_heads, c.n_kv_heads, c.head_dim, q_stride, s);
+    else if (c.dtype == ISO_F32 && !(ctx->flags & ISO_FLAG_SIMPLE_ATTN))
+        e = iso_launch_attn_f32(q, kc, vc, out, Tc, q_offset, kv_len, c.n_q_heads, c.n_kv_heads, c.head_dim, q_stride, s);
     else
         e = iso_launch_attn_simple(c.dtype, q, kc, vc, out, Tc, q_offset, kv_len, c.n_q_heads, c.n_kv_heads, c.head_dim, q_stride, s);
     if (e != hipSuccess) return fail(ISO_ERR_HIP, "attention launch: %s", hipGetErrorString(e));
@@ -489,6 +493,9 @@ int mlp_block(iso_ctx *ctx, const iso_weights *w, void *x, const Chunk &ck, int 
             if (e_ != hipSuccess) return fail(ISO_ERR_HIP, "gate/up+swiglu launch: %s", hipGetErrorString(e_));
             return (int)ISO_OK;
         }));
+    } else if (c.dtype == ISO_F32 && !(ctx->flags & (ISO_FLAG_SIMPLE_GEMM | ISO_FLAG_NO_FUSE)) && ctx->gemm_segments <= 1 &&
+               iso_gemm_f32_supported(yr, w->w_gate_up, ck.n, 2 * F, H)) {
+        LAUNCH_TRY(ISO_K_GEMM_GATE_UP, ck.s, iso_launch_gemm_swiglu_f32(yr, w->w_gate_up, actr, ck.n, F, H, ck.s), "gate/up+swiglu");
     } else {
         ISO_TRY(gemm(ctx, ISO_K_GEMM_GATE_UP, yr, w->w_gate_up, gur, ck.n, 2 * F, H, ck.s, f8gu));
         LAUNCH_TRY(ISO_K_SWIGLU, ck.s, iso_launch_swiglu(c.dtype, gur, actr, ck.n, F, ck.s), "swiglu");

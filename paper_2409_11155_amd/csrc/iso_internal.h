@@ -85,6 +85,12 @@ hipError_t iso_launch_copy_out(void *dst_pinned, const void *src, size_t bytes, 
 hipError_t iso_launch_swiglu(int dtype, const void *gu, void *a, int T, int F, hipStream_t s);
 hipError_t iso_launch_gemm_simple(int dtype, const void *a, const void *w, void *c, int M, int N, int K,
                                   hipStream_t s);
+// fp32 matrix instructions; *_supported: K % 4 == 0, 16-byte aligned operands
+bool iso_gemm_f32_supported(const void *a, const void *w, int M, int N, int K);
+hipError_t iso_launch_gemm_f32(const void *a, const void *w, void *c, int M, int N, int K, hipStream_t s);
+hipError_t iso_launch_gemm_swiglu_f32(const void *a, const void *w, void *act, int M, int F, int K, hipStream_t s);
+hipError_t iso_launch_attn_f32(const void *q, const void *k, const void *v, void *out, int Tc, int q_offset, int kv_len, int nq,
+                               int nkv, int d, int q_stride, hipStream_t s);
 hipError_t iso_launch_gemm_bf16_mfma(const void *a, const void *w, void *c, int M, int N, int K, hipStream_t s);
 bool iso_gemm_bf16_mfma_supported(int M, int N, int K);
 hipError_t iso_launch_gemm_bf16_dtl(const void *a, const void *w, void *c, int M, int N, int K, int variant,
