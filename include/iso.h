@@ -252,7 +252,8 @@ enum {
                                  weights in iso_weights; activations are quantised per token row on the fly) */
     /* bits 8..11: tile variant of the direct-to-LDS GEMM (0 = chosen from the shape; 6 = its stream-K launch, which
      * this value also forces for the FP8 GEMM; 7 = narrow tiles / split k range, with bits 17..20 = number of shares and
-     * bits 21..23 = tile: 0, 1, 2 = 32, 64, 128 rows x 64 columns, 3 = 128 x 128, 4 = 256 x 256) */
+     * bits 21..23 = tile: 0, 1, 2 = 32, 64, 128 rows x 64 columns, 3 = 128 x 128, 4 = 256 x 256,
+     * 5 = 192 x 256) */
     /* bits 12..13: launch shape of the direct-to-LDS attention (0 = chosen from the size; 1 = key tiles split inside
      * the workgroup; 2 = that, and two row blocks (longest with shortest) per workgroup; 3 = one row block per
      * workgroup, two workgroups per compute unit) */

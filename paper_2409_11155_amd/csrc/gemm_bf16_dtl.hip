@@ -197,8 +197,8 @@ void iso_gemm_bf16_dtl_plan(int M, int N, int K, int num_wg, int *kind, int *tea
 
 // variant: 0 = pick by shape; 1 = 256x256 8 waves (16x16x32 MFMAs: measured 6-8 % ahead of 32x32x16 on the launches
 //          that fill the chip, 2-6 % behind on the smaller tiles and in the stream-K launch, which keep 32x32x16),
-//          2 = 256x128 8 waves, 3 = 128x128 4 waves, 4 = 128x256 8 waves, 5 = 256x256 4 waves, 6 = 256x256 stream-K;
-//          +8 selects the plain (non-interleaved) main loop.
+//          2 = 256x128 8 waves, 3 = 128x128 4 waves, 4 = 128x256 8 waves, 5 = 192x256 8 waves (16x16x32), 6 = 256x256
+//          stream-K; +8 selects the plain (non-interleaved) main loop, where the variant has one (not 5, 6).
 // sk may be null: then the stream-K kernel is not considered (variant 6 is an error).
 hipError_t iso_launch_gemm_bf16_dtl(const void *a, const void *w, void *c, int M, int N, int K, int variant,
                                     iso_sk_ws *sk, hipStream_t s) {
@@ -214,7 +214,7 @@ hipError_t iso_launch_gemm_bf16_dtl(const void *a, const void *w, void *c, int M
                          : launch<256, 256, 4, 2, false, true, true>(a, w, c, M, N, K, s);
         case 2: ISO_DTL(256, 128, 4, 2);
         case 4: ISO_DTL(128, 256, 2, 4);
-        case 5: ISO_DTL(256, 256, 2, 2);
+        case 5: return launch<192, 256, 2, 4, false, true, true>(a, w, c, M, N, K, s);
         case 6: return (sk && sk->base) ? launch_sk<false>(a, w, c, M, N, K, sk, s) : hipErrorInvalidValue;
         default: ISO_DTL(128, 128, 2, 2);
     }
@@ -277,6 +277,7 @@ hipError_t iso_launch_gemm_swiglu_bf16(const void *a, const void *w, void *act, 
         case 1: return launch<256, 256, 4, 2, true, true, true>(a, w, act, M, 2 * F, K, s);
         case 2: return launch<256, 128, 4, 2, true, true>(a, w, act, M, 2 * F, K, s);
         case 4: return launch<128, 256, 2, 4, true, true>(a, w, act, M, 2 * F, K, s);
+        case 5: return launch<192, 256, 2, 4, true, true, true>(a, w, act, M, 2 * F, K, s);
         case 6: return (sk && sk->base) ? launch_sk<true>(a, w, act, M, 2 * F, K, sk, s) : hipErrorInvalidValue;
         default: return launch<128, 128, 2, 2, true, true>(a, w, act, M, 2 * F, K, s);
     }

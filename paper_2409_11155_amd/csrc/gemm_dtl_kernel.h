@@ -649,7 +649,7 @@ __device__ __forceinline__ void gemm_dtl_body(const typename OP::elem *__restric
                 // every load before the next one, and a cache-bypassing load is a trip to memory (8 us per partial
                 // tile that way, measured).
                 constexpr int NV = TM * TN * 4, BATCH = 16;
-                static_assert(NV % BATCH == 0, "partial tile is a whole number of load batches");
+                static_assert(!SK || NV % BATCH == 0, "partial tile is a whole number of load batches");
                 for (int j = qfirst; j < q; ++j) {
                     const uint32_t src_off = (uint32_t)(wg_of(j) * (int)Cfg::SLOT_BYTES) + (uint32_t)tid * 16u;
 #pragma unroll

@@ -199,7 +199,8 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::OCC) void gemm_narrow_kernel(const ty
 #endif
 }
 
-// The shares of a whole-tile kernel (gemm_dtl_kernel.h): 128 x 128 (four waves, two workgroups per unit) or 256 x 256.
+// The shares of a whole-tile kernel (gemm_dtl_kernel.h): 128 x 128 (four waves, two workgroups per unit), 256 x 256 or
+// 192 x 256.
 template <typename OP, int BM, int BN, int WM, int WN>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_share_kernel(const typename OP::elem *__restrict__ A,
                                                                   const typename OP::elem *__restrict__ W,
@@ -339,6 +340,10 @@ template <typename OP, int EPI> hipError_t launch_cfg(int cfg, const Operands &o
             if constexpr (OP::SCALED) return launch_share<OP, 256, 256, 4, 2>(o, S, s);
             else return launch_share<Bf16Op<true>, 256, 256, 4, 2>(o, S, s);
         }
+        if (cfg == 5) {
+            if constexpr (OP::SCALED) return launch_share<OP, 192, 256, 2, 4>(o, S, s);
+            else return launch_share<Bf16Op<true>, 192, 256, 2, 4>(o, S, s);
+        }
     }
     return hipErrorInvalidValue;
 }
@@ -358,8 +363,13 @@ unsigned blocks_for(size_t units) { return (unsigned)((units + 255) / 256); }
 // Never below the time of the weights' bytes from HBM.  Root mean square error 3-8 %; picking the fastest by these numbers
 // gives launches 1.5 % slower than the best measured one on average, 1.38x (bf16) / 1.30x (FP8) faster than the whole-tile
 // rule alone over that grid: 2.4-4x at up to 256 rows, 1.2-1.8x at 512-1024, a few per cent above.
+// The 192 x 256 tile (whole, or its k range in shares) is for row counts that 256-row tiles fit badly or that leave units
+// idle: a round of it costs 0.81 of a 256 x 256 one for 0.75 of the arithmetic.  Whole, against the best of the others:
+// 1500 x 8192 x 3584 76.2 -> 69.3 us, 777 x 11264 x 2048 43.9 -> 38.6, 1900 x 4992 x 6656 128.9 -> 111.8, 3000 x 8192 x 2048
+// 95.9 -> 84.8; behind where 256 rows fill their rounds (2048 x 8192 x 3584 89.2 / 127.8).  In shares: 333 x 7168 x 8192
+// 56.9 -> 53.6, 1500 x 2048 x 5632 47.5 -> 43.9.  (A 256 x 128 tile in shares was the fastest in 5 of 288 shapes, by 2 %.)
 struct Tile {
-    int bm, bn, per_cu, kind;    // kind: tile of this file (0 .. 4), or -v: variant v of the whole-tile kernel, one share
+    int bm, bn, per_cu, kind;    // kind: tile of this file (0 .. 5), or -v: variant v of the whole-tile kernel, one share
     double start, round, slice, crowd, pair, pair0, sum0, sum_mb;
 };
 constexpr Tile TILES_BF16[] = {
@@ -371,6 +381,8 @@ constexpr Tile TILES_BF16[] = {
     {256, 256, 1, -1, 2.5, 6.2, 0.988, 0.453, 0.0, 0.0, 0.0, 0.0},
     {128, 128, 2, -3, 2.3, 1.6, 0.444, 0.128, 0.387, 0.67, 0.0, 0.0},
     {128, 256, 1, -4, 0.8, 2.7, 0.668, 0.265, 0.0, 0.0, 0.0, 0.0},
+    {192, 256, 1, 5, 3.9, 4.1, 0.792, 0.440, 0.0, 0.0, 1.3, 0.20},
+    {192, 256, 1, -5, 2.0, 4.4, 0.805, 0.353, 0.0, 0.0, 0.0, 0.0},
 };
 constexpr Tile TILES_FP8[] = {
     {32, 64, 2, 0, 2.4, 1.8, 0.150, 0.049, 0.133, 1.0, 3.0, 0.27},
@@ -380,6 +392,8 @@ constexpr Tile TILES_FP8[] = {
     {256, 256, 1, 4, 5.3, 5.0, 0.921, 0.394, 0.0, 0.0, 0.0, 0.23},
     {256, 256, 1, -1, 1.7, 8.2, 0.838, 0.623, 0.0, 0.0, 0.0, 0.0},
     {128, 128, 2, -3, 2.4, 1.9, 0.497, 0.131, 0.345, 0.47, 0.0, 0.0},
+    {192, 256, 1, 5, 5.3, 3.3, 0.700, 0.370, 0.0, 0.0, 0.0, 0.24},
+    {192, 256, 1, -5, 2.1, 5.5, 0.646, 0.630, 0.0, 0.0, 0.0, 0.0},
 };
 // Stream-K by team size 1, 2, 4, 8: start + slice * k-slices of a team + fetch * teams per tile column.
 struct StreamK {
@@ -417,7 +431,7 @@ bool iso_gemm_split_supported(bool fp8, int M, int N, int K) {
            (long long)N * K < (1ll << 31) && (long long)M * (N / 8) < (1ll << 31) - 256;
 }
 
-// `whole` is the whole-tile rule's own choice (variant 1, 3, 4 or 6 = stream-K).  It stays unless something else is
+// `whole` is the whole-tile rule's own choice (variant 1, 3, 4, 5 or 6 = stream-K).  It stays unless something else is
 // estimated at least 4 % faster (8 % beside another chunk).  ws_bytes: room for partial sums (0: one share only).  `rope`: the QKV projection, where
 // only variants 1 and 6 and the tiles of this file (through their second kernel) finish with the rotary step; the others
 // need a kernel more (about 5 us).

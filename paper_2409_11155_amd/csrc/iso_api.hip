@@ -141,7 +141,7 @@ iso_split_plan plan_gemm(iso_ctx *ctx, bool fp8, bool rope, int M, int N, int K,
     const iso_sk_ws *ws = split_ws_for(ctx, s);
     const size_t bytes = ws ? (size_t)ws->num_wg * iso_gemm_sk_slot_bytes() : 0;
     if (forced == 7) {       // tests, measurement: bits 17..20 shares, 21..23 tile
-        iso_split_plan p{std::min(4, (ctx->flags >> 21) & 7), std::max(1, (ctx->flags >> 17) & 15), 0};
+        iso_split_plan p{std::min(5, (ctx->flags >> 21) & 7), std::max(1, (ctx->flags >> 17) & 15), 0};
         p.shares = std::min(p.shares, K / (fp8 ? 128 : 64));
         if (p.tile > 2 && p.shares < 2) return whole;          // one share of a whole tile: the whole-tile kernels
         if ((p.shares > 1 || rope) && (size_t)p.shares * M * N * 4 > bytes) return whole;
