@@ -32,7 +32,7 @@ template <typename OP, int BM_, int BN_, int NS_, int OCC_> struct NarrowCfg {
     static constexpr int EPI_BYTES = KW * 32 * EP * 4;
     static constexpr int LDS_BYTES = NS * STAGE > EPI_BYTES ? NS * STAGE : EPI_BYTES;
     static_assert(LDS_BYTES * OCC <= 160 * 1024 && NW % KW == 0 && A_LOADS >= 1 && W_LOADS >= 1 && FN >= 1, "shape");
-    static_assert((NS - 2) * LOADS < 64, "outstanding loads are counted in six bits");
+    static_assert((NS - 1) * LOADS < 64, "outstanding loads are counted in six bits");
 };
 
 template <typename Cfg, typename OP, int EPI>
@@ -82,11 +82,11 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::OCC) void gemm_narrow_kernel(const ty
     }
     // a slice past the share's end is requested through an empty descriptor: nothing is fetched, the count of outstanding
     // loads stays the same to the end
-    auto issue = [&](int i) {
+    auto issue = [&](int i, int stage) {
         const bool real = i < n;
         const __amdgpu_buffer_rsrc_t rs_a = __builtin_amdgcn_make_buffer_rsrc((void *)A, 0, real ? a_bytes : 0, 0x00020000);
         const __amdgpu_buffer_rsrc_t rs_w = __builtin_amdgcn_make_buffer_rsrc((void *)W, 0, real ? w_bytes : 0, 0x00020000);
-        unsigned char *base = lds + (i % NS) * Cfg::STAGE;
+        unsigned char *base = lds + stage * Cfg::STAGE;
         const int off = (kb + i) * ROW_BYTES;
 #pragma unroll
         for (int j = 0; j < Cfg::W_LOADS; ++j)
@@ -108,25 +108,56 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::OCC) void gemm_narrow_kernel(const ty
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
     const int frow = lane & 31, fgrp = lane >> 5;
     const int f_sw = swz(frow), c0 = kw * OP::CPS + fgrp * OP::RPF;
-    for (int i = 0; i < NS - 1; ++i) issue(i);
-    constexpr int PEND = (NS - 2) * Cfg::LOADS;
-    constexpr int WAIT = (PEND & 15) | ((PEND >> 4) << 14) | (7 << 4);      // vmcnt <= PEND, lgkmcnt = 0
-    for (int i = 0; i < n; ++i) {
-        __builtin_amdgcn_s_waitcnt(WAIT);           // my part of slice i has landed, my reads of slice i - 1 are done
-        asm volatile("s_barrier" ::: "memory");     // ... and everybody's
-        issue(i + NS - 1);
-        const unsigned char *ab = lds + (i % NS) * Cfg::STAGE + frow * ROW_BYTES;
+    // The operands of slice i + 1 are read from LDS, and slice i + NS is requested into the stage that slice i has left,
+    // while slice i is multiplied from registers: a wave alone on its SIMD has nobody else to fill its waits with.  (One after
+    // the other, reading, requesting and multiplying took twice the 64 bytes a clock that a unit can take in: 128 x 64 at 40
+    // workgroups 0.35 us a slice of 24 KB, now 0.25.)  400 x 2048 x 2048 10.9 -> 9.2 us, 200 x 1280 x 8192 17.5 -> 15.8; even
+    // where two workgroups share the unit.
+    typename OP::frag_t af[2][FM], wf[2][FN];
+    auto read = [&](int stage, int buf) {
+        const unsigned char *ab = lds + stage * Cfg::STAGE + frow * ROW_BYTES;
         const unsigned char *wb = ab + (BM + wn * Cfg::WCOLS) * ROW_BYTES;
-        typename OP::frag_t af[FM], wf[FN];
 #pragma unroll
-        for (int j = 0; j < FN; ++j) wf[j] = OP::load(wb + j * 32 * ROW_BYTES, c0, f_sw);
+        for (int j = 0; j < FN; ++j) wf[buf][j] = OP::load(wb + j * 32 * ROW_BYTES, c0, f_sw);
 #pragma unroll
-        for (int j = 0; j < FM; ++j) af[j] = OP::load(ab + j * 32 * ROW_BYTES, c0, f_sw);
+        for (int j = 0; j < FM; ++j) af[buf][j] = OP::load(ab + j * 32 * ROW_BYTES, c0, f_sw);
+    };
+    auto wait_for = [](auto pending_c) {            // vmcnt <= pending, lgkmcnt = 0
+        constexpr int P = decltype(pending_c)::value;
+        __builtin_amdgcn_s_waitcnt((P & 15) | ((P >> 4) << 14) | (7 << 4));
+        asm volatile("s_barrier" ::: "memory");
+    };
+    for (int i = 0; i < NS; ++i) issue(i, i);
+    wait_for(std::integral_constant<int, (NS - 1) * Cfg::LOADS>{});
+    read(0, 0);
+    int cur = 0;                                    // stage of slice i
+    auto step = [&](int i, auto buf_c) {
+        constexpr int B = decltype(buf_c)::value;
+        // my part of slice i + 1 has landed and my reads of slice i are done, and everybody's
+        wait_for(std::integral_constant<int, (NS - 2) * Cfg::LOADS>{});
+        const int nx = cur + 1 == NS ? 0 : cur + 1;
+        read(nx, B ^ 1);
+        issue(i + NS, cur);
 #pragma unroll
         for (int x = 0; x < FM; ++x)
 #pragma unroll
-            for (int y = 0; y < FN; ++y) acc[x][y] = OP::mfma32(af[x], wf[y], acc[x][y]);
+            for (int y = 0; y < FN; ++y) acc[x][y] = OP::mfma32(af[B][x], wf[B][y], acc[x][y]);
+        __builtin_amdgcn_sched_group_barrier(0x100, OP::RPF * (FM + FN), 0);       // the LDS reads, then the requests
+        constexpr int PER = (Cfg::LOADS + FM * FN - 1) / (FM * FN);                // between the products
+#pragma unroll
+        for (int k = 0; k < FM * FN; ++k) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x020, PER, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        cur = nx;
+    };
+    int i = 0;
+    for (; i + 1 < n; i += 2) {
+        step(i, std::integral_constant<int, 0>{});
+        step(i + 1, std::integral_constant<int, 1>{});
     }
+    if (i < n) step(i, std::integral_constant<int, 0>{});
     __builtin_amdgcn_s_waitcnt(7 << 4);             // everything, so that the staging below may overwrite the stages
 
     // epilogue, 32 rows at a time: the KW partial blocks go to LDS, every thread adds the KW values of its outputs in
@@ -328,10 +359,14 @@ template <typename OP, int BM, int BN, int WM, int WN> hipError_t launch_share(c
 }
 
 template <typename OP, int EPI> hipError_t launch_cfg(int cfg, const Operands &o, int S, hipStream_t s) {
+    // A 128 x 64 tile that has its compute unit to itself takes six stages: 7 % at up to half the units busy, 2 % above.
+    // (The two smaller tiles lose 4 % with all of the LDS: the launch before them has to leave a unit completely.)
+    const bool alone = (long long)((o.M + 127) / 128) * ((o.N + 63) / 64) * S <= iso_num_cu();
     switch (cfg) {
         case 0: return launch_narrow<OP, NarrowCfg<OP, 32, 64, 6, 2>, EPI>(o, S, s);
         case 1: return launch_narrow<OP, NarrowCfg<OP, 64, 64, 5, 2>, EPI>(o, S, s);
-        case 2: return launch_narrow<OP, NarrowCfg<OP, 128, 64, 3, 2>, EPI>(o, S, s);
+        case 2: return alone ? launch_narrow<OP, NarrowCfg<OP, 128, 64, 6, 1>, EPI>(o, S, s)
+                             : launch_narrow<OP, NarrowCfg<OP, 128, 64, 3, 2>, EPI>(o, S, s);
         default: break;
     }
     if constexpr (EPI == EPI_PARTIAL) {
