@@ -13,15 +13,15 @@
 
 namespace {
 
-constexpr int QB = 16, KB = 64;      // query rows per workgroup, keys per tile
+constexpr int QB = 16;               // query rows per workgroup
 
-template <int D>
-__global__ __launch_bounds__(256) void attn_f32_kernel(const float *__restrict__ Q, const float *__restrict__ Kc,
+template <int D, int KB, int NW>     // KB keys per tile, NW waves
+__global__ __launch_bounds__(NW * 64) void attn_f32_kernel(const float *__restrict__ Q, const float *__restrict__ Kc,
                                                        const float *__restrict__ Vc, float *__restrict__ Out, int Tc,
                                                        int q_offset, int kv_len, int nq, int nkv, int q_stride) {
     constexpr int DS = D / 16;       // 16-dim steps of a score (four instructions each), 16-dim blocks of an output
-    __shared__ float so[4][QB][D + 4];
-    __shared__ float sm[4][QB], sl[4][QB];
+    __shared__ float so[NW][QB][D + 4];
+    __shared__ float sm[NW][QB], sl[NW][QB];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 15, grp = lane >> 4;
     const int i0 = ((int)gridDim.x - 1 - (int)blockIdx.x) * QB;      // longest rows first
@@ -41,10 +41,23 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float *__restrict__
 #pragma unroll
     for (int d = 0; d < DS; ++d) o[d] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     float m = -INFINITY, l = 0.f;
-    for (int j0 = wave * KB; j0 < n_vis; j0 += 4 * KB) {
+    for (int j0 = wave * KB; j0 < n_vis; j0 += NW * KB) {
         f32x4_t sc[KB / 16];
+        // V is requested along with K, so that a tile is one trip to memory (D = 128 has no registers for that).
+        // Rows past the visible keys of every query here have probability zero, but must not bring a NaN: clamp.
+        constexpr bool EARLY_V = D == 64;
+        float vf[EARLY_V ? KB / 16 : 1][4][DS];
+        auto load_v = [&](int b, float (&dst)[4][DS]) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float *vr = vp + (size_t)min(j0 + 16 * b + 4 * grp + r, n_vis - 1) * row;
+#pragma unroll
+                for (int d = 0; d < DS; ++d) dst[r][d] = vr[16 * d];
+            }
+        };
 #pragma unroll
         for (int b = 0; b < KB / 16; ++b) {
+            if (EARLY_V) load_v(b, vf[EARLY_V ? b : 0]);
             const float *kr = kp + (size_t)min(j0 + 16 * b + col, kv_len - 1) * row;
             f32x4_t kf[DS];
 #pragma unroll
@@ -82,15 +95,14 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float *__restrict__
 #pragma unroll
         for (int d = 0; d < DS; ++d) o[d] *= alpha;
 #pragma unroll
-        for (int b = 0; b < KB / 16; ++b)
+        for (int b = 0; b < KB / 16; ++b) {
+            if (!EARLY_V) load_v(b, vf[0]);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                // rows past the visible keys of every query here have probability zero, but must not bring a NaN: clamp
-                const float *vr = vp + (size_t)min(j0 + 16 * b + 4 * grp + r, n_vis - 1) * row;
+            for (int r = 0; r < 4; ++r)
 #pragma unroll
                 for (int d = 0; d < DS; ++d)
-                    o[d] = __builtin_amdgcn_mfma_f32_16x16x4f32(vr[16 * d], sc[b][r], o[d], 0, 0, 0);
-            }
+                    o[d] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[EARLY_V ? b : 0][r][d], sc[b][r], o[d], 0, 0, 0);
+        }
     }
     l += __shfl_xor(l, 16, 64);
     l += __shfl_xor(l, 32, 64);
@@ -101,15 +113,15 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float *__restrict__
 #pragma unroll
     for (int d = 0; d < DS; ++d) *reinterpret_cast<f32x4_t *>(&so[wave][col][16 * d + 4 * grp]) = o[d];
     __syncthreads();
-    for (int e = tid; e < QB * D; e += 256) {
+    for (int e = tid; e < QB * D; e += NW * 64) {
         const int q = e / D, d = e % D;
         if (i0 + q >= Tc) continue;
         float mt = sm[0][q];
 #pragma unroll
-        for (int w = 1; w < 4; ++w) mt = fmaxf(mt, sm[w][q]);
+        for (int w = 1; w < NW; ++w) mt = fmaxf(mt, sm[w][q]);
         float num = 0.f, den = 0.f;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
+        for (int w = 0; w < NW; ++w) {
             const float f = expf(sm[w][q] - mt);                     // a wave without keys has m = -inf and weight zero
             num += so[w][q][d] * f;
             den += sl[w][q] * f;
@@ -122,13 +134,17 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float *__restrict__
 
 hipError_t iso_launch_attn_f32(const void *q, const void *k, const void *v, void *out, int Tc, int q_offset, int kv_len, int nq,
                                int nkv, int d, int q_stride, hipStream_t s) {
-    dim3 grid((Tc + QB - 1) / QB, nq), block(256);
-    if (d == 64)
-        hipLaunchKernelGGL(attn_f32_kernel<64>, grid, block, 0, s, (const float *)q, (const float *)k, (const float *)v,
-                           (float *)out, Tc, q_offset, kv_len, nq, nkv, q_stride);
+    const dim3 grid((Tc + QB - 1) / QB, nq);
+    const float *qf = (const float *)q, *kf = (const float *)k, *vf = (const float *)v;
+    if (d == 64 && kv_len <= 128)
+        hipLaunchKernelGGL((attn_f32_kernel<64, 32, 4>), grid, dim3(256), 0, s, qf, kf, vf, (float *)out, Tc, q_offset, kv_len, nq,
+                           nkv, q_stride);
+    else if (d == 64)
+        hipLaunchKernelGGL((attn_f32_kernel<64, 32, 8>), grid, dim3(512), 0, s, qf, kf, vf, (float *)out, Tc, q_offset, kv_len, nq,
+                           nkv, q_stride);
     else if (d == 128)
-        hipLaunchKernelGGL(attn_f32_kernel<128>, grid, block, 0, s, (const float *)q, (const float *)k, (const float *)v,
-                           (float *)out, Tc, q_offset, kv_len, nq, nkv, q_stride);
+        hipLaunchKernelGGL((attn_f32_kernel<128, 64, 4>), grid, dim3(256), 0, s, qf, kf, vf, (float *)out, Tc, q_offset, kv_len, nq,
+                           nkv, q_stride);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }

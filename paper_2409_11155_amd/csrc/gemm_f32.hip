@@ -31,24 +31,40 @@ template <> struct F32Mfma<32> {
     static __device__ __forceinline__ int row(int r, int grp) { return 8 * (r / 4) + 4 * grp + (r % 4); }
 };
 
-// KW waves share the k range of a tile, WM x WN tiles per workgroup; KW * WM * WN = 4.
-template <int MR, int WM, int WN, int KW, bool SWIGLU>
+// What follows the sums: nothing, SwiGLU, or (the QKV projection) rotary embedding and KV-cache write.  The last two tie two
+// rows of W to one output column index, gate and up or the two halves of a head, and a tile computes both.
+enum { EPI_NONE = 0, EPI_SWIGLU = 1, EPI_ROPE = 2 };
+struct RopeF32 {
+    const float *cos_t, *sin_t;      // [max_seq, d / 2]
+    float *k_cache, *v_cache;
+    int q_offset, nq, nkv, d;
+};
+
+// KW waves share the k range of a tile, WM x WN tiles per workgroup; KW * WM * WN = 4.  UNROLL steps of k are requested at a
+// time: twelve where a wave has more than four of them, so that the down projection (K = 688) is one trip to memory as well
+// (128 x 256 x 688: 5.2 -> 4.1 us).
+template <int MR, int WM, int WN, int KW, int UNROLL, int EPI>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ W,
-                                                       float *__restrict__ C, int M, int N, int K) {
+                                                       float *__restrict__ C, int M, int N, int K, RopeF32 rope) {
     using Op = F32Mfma<MR>;
-    constexpr int NB = SWIGLU ? 2 : 1;              // W row blocks per tile: gate and up
+    constexpr bool SWIGLU = EPI == EPI_SWIGLU, ROPE = EPI == EPI_ROPE;
+    constexpr int NB = EPI == EPI_NONE ? 1 : 2;     // W row blocks per tile
     constexpr int GRP = 64 / MR, STEP = 4 * GRP;    // k per step (four matrix instructions)
-    constexpr int UNROLL = MR == 16 ? 4 : 4;
+    static_assert(!ROPE || KW > 1, "the rotary step works on the tile in LDS");
     __shared__ float part[KW > 1 ? KW * NB * MR * (MR + 1) : 1];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int kw = wave % KW, wm = (wave / KW) % WM, wn = wave / (KW * WM);
     const int lrow = lane % MR, grp = lane / MR;
     const int m0 = (blockIdx.y * WM + wm) * MR, n0 = (blockIdx.x * WN + wn) * MR;
-    const int n_out = SWIGLU ? N / 2 : N;
+    const int n_out = NB == 2 ? N / 2 : N;
     const float *ap = A + (size_t)min(m0 + lrow, M - 1) * K;
     const float *wp[NB];
+    const int half = ROPE ? rope.d / 2 : 1, head = ROPE ? n0 / half : 0;     // half % 16 == 0: a tile lies in one head
 #pragma unroll
-    for (int b = 0; b < NB; ++b) wp[b] = W + (size_t)(b * n_out + min(n0 + lrow, n_out - 1)) * K;
+    for (int b = 0; b < NB; ++b) {
+        const int n = min(n0 + lrow, n_out - 1);
+        wp[b] = W + (size_t)(ROPE ? n + (head + b) * half : b * n_out + n) * K;
+    }
     typename Op::acc_t acc[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b)
@@ -103,20 +119,48 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
                 for (int k = 1; k < KW; ++k) v[b] += part[((k * NB + b) * MR + row) * P + col];
             }
             if constexpr (SWIGLU) v[0] = v[0] / (1.0f + expf(-v[0])) * v[1];
-            C[(size_t)m * n_out + n] = v[0];
+            if constexpr (ROPE) {
+                const int i = n - head * half, pos = rope.q_offset + m;
+                float *lo = C + (size_t)m * N + (size_t)head * rope.d + i;
+                if (head >= rope.nq) {              // k and v heads go to their caches only
+                    const bool is_k = head < rope.nq + rope.nkv;
+                    lo = (is_k ? rope.k_cache : rope.v_cache) +
+                         ((size_t)pos * rope.nkv + head - rope.nq - (is_k ? 0 : rope.nkv)) * rope.d + i;
+                }
+                float a = v[0], b = v[1];
+                if (head < rope.nq + rope.nkv) {
+                    const float c = rope.cos_t[(size_t)pos * half + i], sn = rope.sin_t[(size_t)pos * half + i];
+                    a = v[0] * c - v[1] * sn;
+                    b = v[1] * c + v[0] * sn;
+                }
+                lo[0] = a;
+                lo[half] = b;
+            } else {
+                C[(size_t)m * n_out + n] = v[0];
+            }
         }
     }
 }
 
-template <bool SWIGLU> hipError_t launch_f32(const void *a, const void *w, void *c, int M, int N, int K, hipStream_t s) {
-    const int n_out = SWIGLU ? N / 2 : N;
-    const long long big = (long long)((M + 63) / 64) * ((n_out + 63) / 64);
-    if (big >= 256)
-        hipLaunchKernelGGL((gemm_f32_kernel<32, 2, 2, 1, SWIGLU>), dim3((n_out + 63) / 64, (M + 63) / 64), dim3(256), 0, s,
-                           (const float *)a, (const float *)w, (float *)c, M, N, K);
+// Small tiles until there are 256 of the large ones.
+bool small_tiles(int M, int n_out) { return (long long)((M + 63) / 64) * ((n_out + 63) / 64) < 256; }
+
+template <int EPI>
+hipError_t launch_f32(const void *a, const void *w, void *c, int M, int N, int K, const RopeF32 &rope, hipStream_t s) {
+    const int n_out = EPI == EPI_NONE ? N : N / 2;
+    const float *af = (const float *)a, *wf = (const float *)w;
+    const dim3 grid16((n_out + 15) / 16, (M + 15) / 16);
+    if constexpr (EPI != EPI_ROPE) {
+        if (!small_tiles(M, n_out)) {
+            hipLaunchKernelGGL((gemm_f32_kernel<32, 2, 2, 1, 4, EPI>), dim3((n_out + 63) / 64, (M + 63) / 64), dim3(256), 0, s, af, wf,
+                               (float *)c, M, N, K, rope);
+            return hipGetLastError();
+        }
+    }
+    if (K <= 4 * 4 * 16)
+        hipLaunchKernelGGL((gemm_f32_kernel<16, 1, 1, 4, 4, EPI>), grid16, dim3(256), 0, s, af, wf, (float *)c, M, N, K, rope);
     else
-        hipLaunchKernelGGL((gemm_f32_kernel<16, 1, 1, 4, SWIGLU>), dim3((n_out + 15) / 16, (M + 15) / 16), dim3(256), 0, s,
-                           (const float *)a, (const float *)w, (float *)c, M, N, K);
+        hipLaunchKernelGGL((gemm_f32_kernel<16, 1, 1, 4, 12, EPI>), grid16, dim3(256), 0, s, af, wf, (float *)c, M, N, K, rope);
     return hipGetLastError();
 }
 
@@ -127,9 +171,22 @@ bool iso_gemm_f32_supported(const void *a, const void *w, int M, int N, int K) {
 }
 
 hipError_t iso_launch_gemm_f32(const void *a, const void *w, void *c, int M, int N, int K, hipStream_t s) {
-    return launch_f32<false>(a, w, c, M, N, K, s);
+    return launch_f32<EPI_NONE>(a, w, c, M, N, K, RopeF32{}, s);
 }
 
 hipError_t iso_launch_gemm_swiglu_f32(const void *a, const void *w, void *act, int M, int F, int K, hipStream_t s) {
-    return launch_f32<true>(a, w, act, M, 2 * F, K, s);
+    return launch_f32<EPI_SWIGLU>(a, w, act, M, 2 * F, K, RopeF32{}, s);
+}
+
+// QKV projection with rotary embedding and KV-cache write in its epilogue (the k and v columns of qkv are not written): one
+// launch less for the small tiles (128 tokens, 12 heads of 64: 4.6 + 2.5 -> 5.0 us and a gap); larger products keep the two
+// kernels.
+bool iso_gemm_rope_f32_supported(const void *a, const void *w, int M, int N, int K) {
+    return iso_gemm_f32_supported(a, w, M, N, K) && small_tiles(M, N);
+}
+
+hipError_t iso_launch_gemm_rope_f32(const void *a, const void *w, void *qkv, int M, int K, const float *cos_t, const float *sin_t,
+                                    void *k_cache, void *v_cache, int q_offset, int nq, int nkv, int d, hipStream_t s) {
+    const RopeF32 rope{cos_t, sin_t, (float *)k_cache, (float *)v_cache, q_offset, nq, nkv, d};
+    return launch_f32<EPI_ROPE>(a, w, qkv, M, (nq + 2 * nkv) * d, K, rope, s);
 }

@@ -394,6 +394,13 @@ int attn_block_head(iso_ctx *ctx, const iso_weights *w, void *x, void *kc, void 
                                               c.n_kv_heads, c.head_dim, ck.s), "split qkv+rope");
         return ISO_OK;
     }
+    if (c.dtype == ISO_F32 && !(ctx->flags & (ISO_FLAG_SIMPLE_GEMM | ISO_FLAG_NO_FUSE)) && ctx->gemm_segments <= 1 &&
+        iso_gemm_rope_f32_supported(yr, w->w_qkv, ck.n, NQKV, H)) {
+        LAUNCH_TRY(ISO_K_GEMM_QKV, ck.s,
+                   iso_launch_gemm_rope_f32(yr, w->w_qkv, qkvr, ck.n, H, ctx->rope_cos, ctx->rope_sin, kc, vc, ck.lo, c.n_q_heads,
+                                            c.n_kv_heads, c.head_dim, ck.s), "qkv+rope");
+        return ISO_OK;
+    }
     // bf16 layers with head_dim 128: rotary embedding and KV-cache write ride in the projection's epilogue whenever
     // the launch rule picks a kernel whose waves own whole heads (the 256-wide tile or its stream-K launch)
     const bool dtl = c.dtype == ISO_BF16 && c.head_dim == 128 && !fp8_qkv &&

@@ -89,6 +89,9 @@ hipError_t iso_launch_gemm_simple(int dtype, const void *a, const void *w, void 
 bool iso_gemm_f32_supported(const void *a, const void *w, int M, int N, int K);
 hipError_t iso_launch_gemm_f32(const void *a, const void *w, void *c, int M, int N, int K, hipStream_t s);
 hipError_t iso_launch_gemm_swiglu_f32(const void *a, const void *w, void *act, int M, int F, int K, hipStream_t s);
+bool iso_gemm_rope_f32_supported(const void *a, const void *w, int M, int N, int K);
+hipError_t iso_launch_gemm_rope_f32(const void *a, const void *w, void *qkv, int M, int K, const float *cos_t, const float *sin_t,
+                                    void *k_cache, void *v_cache, int q_offset, int nq, int nkv, int d, hipStream_t s);
 hipError_t iso_launch_attn_f32(const void *q, const void *k, const void *v, void *out, int Tc, int q_offset, int kv_len, int nq,
                                int nkv, int d, int q_stride, hipStream_t s);
 hipError_t iso_launch_gemm_bf16_mfma(const void *a, const void *w, void *c, int M, int N, int K, hipStream_t s);

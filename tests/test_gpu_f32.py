@@ -43,3 +43,26 @@ def test_layer_f32_fused_swiglu(hidden, nq, nkv, d, ffn, T, split):
         assert orc.max_rel_err(f64(out), ref["x_out"]) <= TOL_LAYER["f32"]
         assert orc.max_rel_err(f64(kc)[:T], ref["k_cache"]) <= TOL_LAYER["f32"]
         assert np.isnan(f64(kc)[T:]).all()
+
+
+@pytest.mark.parametrize("hidden,nq,nkv,d,ffn,T,split", [
+    (64, 4, 2, 64, 200, 17, 5), (264, 2, 1, 128, 520, 150, 61), (260, 4, 4, 64, 688, 129, 128), (256, 4, 1, 64, 688, 300, 31)])
+def test_rotary_step_and_cache_write_in_the_qkv_epilogue_f32(hidden, nq, nkv, d, ffn, T, split):
+    """Against the separate rotary kernel: V rows are the same bits (same sums, nothing follows them), rotated K rows differ by
+    the contraction of a multiply and an add (2^-23 of each product); key counts at the edge of the two attention shapes."""
+    if hidden % 8:
+        hidden += 4
+    w = iso_inputs.make_layer(hidden, nq, nkv, d, ffn, seed=43, dtype="f32")
+    x = iso_inputs.make_hidden(T, hidden, seed=43, dtype="f32")
+    ref = orc.layer_unsplit(h64(x, "f32"), oracle_weights(w, "f32"), shape_of(hidden, nq, nkv, d, ffn))
+    with make_ctx(hidden, nq, nkv, d, ffn, "f32", T + 3) as ctx:
+        got = []
+        for flags in (0, iso.ISO_FLAG_NO_FUSE):
+            ctx.set_flags(flags)
+            out, kc, vc = run_layer(ctx, iso.upload_weights(w, "f32"), x, "f32", T, split, nkv, d, T + 3, iso.ISO_COMM_D2H,
+                                    poison=True)
+            assert orc.max_rel_err(f64(out), ref["x_out"]) <= TOL_LAYER["f32"]
+            assert np.isnan(f64(kc)[T:]).all() and np.isnan(f64(vc)[T:]).all()
+            got.append((f64(kc)[:T], vc.numpy()[:T]))
+        np.testing.assert_allclose(got[0][0], got[1][0], rtol=0, atol=2.0 ** -22 * np.abs(got[1][0]).max())
+        np.testing.assert_array_equal(got[0][1], got[1][1])
