@@ -469,8 +469,9 @@ bool iso_gemm_split_supported(bool fp8, int M, int N, int K) {
 // `whole` is the whole-tile rule's own choice (variant 1, 3, 4, 5 or 6 = stream-K).  It stays unless something else is
 // estimated at least 4 % faster (8 % beside another chunk).  ws_bytes: room for partial sums (0: one share only).  `rope`: the QKV projection, where
 // only variants 1 and 6 and the tiles of this file (through their second kernel) finish with the rotary step; the others
-// need a kernel more (about 5 us).
-iso_split_plan iso_gemm_split_plan(bool fp8, bool rope, int whole, int M, int N, int K, size_t ws_bytes, int ncu, bool shared) {
+// need a kernel more (about 5 us).  *us_or_null: the estimate for the plan returned.
+iso_split_plan iso_gemm_split_plan(bool fp8, bool rope, int whole, int M, int N, int K, size_t ws_bytes, int ncu, bool shared,
+                                   double *us_or_null) {
     const int nk = K / (fp8 ? Fp8Op::KE : Bf16Op<false>::KE);
     const Tile *tiles = fp8 ? TILES_FP8 : TILES_BF16;
     const int n_tiles = fp8 ? (int)(sizeof(TILES_FP8) / sizeof(Tile)) : (int)(sizeof(TILES_BF16) / sizeof(Tile));
@@ -480,6 +481,7 @@ iso_split_plan iso_gemm_split_plan(bool fp8, bool rope, int whole, int M, int N,
     if (whole == 6) best = stream_k_us(fp8, M, N, nk, ncu) + extra;
     for (int i = 0; i < n_tiles; ++i)
         if (tiles[i].kind == -whole) best = tile_us(tiles[i], M, N, nk, 1, ncu, shared) + whole_extra(whole);
+    double estimate = best;
     best *= shared ? 0.92 : 0.96;
     iso_split_plan plan{-1, 1, whole};
     constexpr int SHARES[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 15};
@@ -492,11 +494,12 @@ iso_split_plan iso_gemm_split_plan(bool fp8, bool rope, int whole, int M, int N,
             if (t.kind < 0) us += whole_extra(-t.kind);
             else if (rope && S == 1) us += t.sum0 + t.sum_mb * ((double)M * N * 4e-6);
             if (us < best) {
-                best = us;
+                best = estimate = us;
                 plan = t.kind < 0 ? iso_split_plan{-1, 1, -t.kind} : iso_split_plan{t.kind, S, 0};
             }
         }
     }
+    if (us_or_null) *us_or_null = estimate;
     return plan;
 }
 

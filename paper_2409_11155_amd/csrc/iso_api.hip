@@ -559,6 +559,25 @@ int chunk_streams(iso_ctx *ctx, int nc, hipStream_t *out) {
     return ISO_OK;
 }
 
+// Estimated microseconds of the bf16 projections of one layer over `rows` rows, `shared`: beside another chunk's.  Negative
+// where one of them has no estimate.
+double projections_us(const iso_ctx *ctx, int rows, bool shared) {
+    const iso_cfg &c = ctx->cfg;
+    const iso_sk_ws *ws = &ctx->sk[0];
+    const int H = c.hidden, D = c.n_q_heads * c.head_dim, F = c.ffn;
+    const int nk[4][2] = {{n_qkv(c), H}, {H, D}, {2 * F, H}, {H, F}};
+    double sum = 0.0;
+    for (int i = 0; i < 4; ++i) {
+        const int N = nk[i][0], K = nk[i][1];
+        if (!ws->base || !iso_gemm_split_supported(false, rows, N, K)) return -1.0;
+        double us = 0.0;
+        (void)iso_gemm_split_plan(false, i == 0, iso_gemm_bf16_dtl_resolve(rows, N, K, 0, shared ? nullptr : ws), rows, N, K,
+                                  (size_t)ws->num_wg * iso_gemm_sk_slot_bytes(), iso_num_cu(), shared, &us);
+        sum += us;
+    }
+    return sum;
+}
+
 // edges[0..nc]: chunk c is rows [edges[c], edges[c+1]).
 int run_stack(iso_ctx *ctx, const iso_weights *layers, int n_layers, void *x, void *k_caches, void *v_caches,
               const int *edges_in, int nc, int comm, int sched) {
@@ -570,27 +589,36 @@ int run_stack(iso_ctx *ctx, const iso_weights *layers, int n_layers, void *x, vo
     //     256 (4 MB) 313 / 307, 400 (6.6 MB) 398 / 433; int8 payload, 256 (2 MB) 339 / 236, 512 (4 MB) 408 / 360, 768 (6 MB)
     //     482 / 513; hidden 2048, bf16, 512 (2 MB) 218 / 193, 1024 (4 MB) even, 1536 (6 MB) 424 / 488; int8, 1024 (2 MB)
     //     319 / 251, 1536 (3 MB) 355 / 372 -- hence the limit on tokens beside the one on bytes.
-    //   * No transfers: one chunk up to 2048 tokens or without a second stream, else two (they fill each other's last rounds
-    //     of the chip): 1024 tokens 403 / 356 us (30B TP=4), 362 / 291 (70B TP=8); 2048 642 / 587 and 527 / 459; 3000
-    //     773 / 848 and 689 / 721; 6 against 2 chunks of 8192 tokens 5271 / 4417 us (30B TP=4, two layers).
+    //   * No transfers: one chunk up to 2816 tokens or without a second stream, else two (they fill each other's last rounds
+    //     of the chip).  Whole / cut in half, 20 lengths of each shard: up to 2800 tokens 0.85-1.03 (bf16 mean 0.95, FP8 0.92;
+    //     70B TP=8 2304 582 -> 566 us, 30B TP=4 702 -> 649), above that 0.88-1.12 by how the row counts fall on the tiles;
+    //     6 against 2 chunks of 8192 tokens 5271 / 4417 us (30B TP=4, two layers).  So longer bf16 prompts stay whole where the
+    //     projections' estimates promise 4.5 %: 70B TP=4 8192 cut at 60 % 3190 -> 3012 us, 70B TP=8 4500 1080 -> 989; of the
+    //     cuts that this takes back the mean measured 0.95 of the cut's time, the worst 1.05.  (FP8 estimates leave out the
+    //     quantisers and do not tell: 0.90-1.12 at the same estimate.)
     int edges[ISO_MAX_CHUNKS + 1];
     std::copy(edges_in, edges_in + nc + 1, edges);
     const int T = edges[nc];
-    const size_t row_bytes = comm == ISO_COMM_D2H_INT8 ? (size_t)c.hidden + 16 : (size_t)c.hidden * ctx->elt;
-    const bool whole = comm == ISO_COMM_NONE
-                           ? T <= 2048 || sched == ISO_SCHED_SERIAL || ctx->stream[1] == ctx->stream[0]
-                           : T <= 1280 && T * row_bytes <= 4u << 20;
     if (nc > 1 && !(ctx->flags & ~ISO_FLAG_FP8_GEMM)) {
-        if (whole) {
-            edges[1] = T;
-            nc = 1;
-        } else if (comm == ISO_COMM_NONE && nc > 2) {
+        const size_t row_bytes = comm == ISO_COMM_D2H_INT8 ? (size_t)c.hidden + 16 : (size_t)c.hidden * ctx->elt;
+        bool whole = comm == ISO_COMM_NONE ? T <= 2816 || sched == ISO_SCHED_SERIAL || ctx->stream[1] == ctx->stream[0]
+                                           : T <= 1280 && T * row_bytes <= 4u << 20;
+        if (!whole && comm == ISO_COMM_NONE) {
             int k = 1;       // the cut nearest to 0.55 T: the later half of a causal prompt is the dearer one
             for (int j = 2; j < nc; ++j)
                 if (fabs(edges[j] - 0.55 * T) < fabs(edges[k] - 0.55 * T)) k = j;
             edges[1] = edges[k];
             edges[2] = T;
             nc = 2;
+            if (c.dtype == ISO_BF16 && !(ctx->flags & ISO_FLAG_FP8_GEMM)) {
+                const double one = projections_us(ctx, T, false), lo = projections_us(ctx, edges[1], true),
+                             hi = projections_us(ctx, T - edges[1], true);
+                whole = one > 0.0 && lo > 0.0 && hi > 0.0 && one < 0.955 * (lo + hi);
+            }
+        }
+        if (whole) {
+            edges[1] = T;
+            nc = 1;
         }
     }
     const size_t cache_bytes = (size_t)c.max_seq * c.n_kv_heads * c.head_dim * ctx->elt;
