@@ -528,6 +528,26 @@ bool iso_attn_bf16_dtl_supported(int d, int kv_len, int nkv) {
 // ksplit_req: 0 = key split across workgroups chosen from the size, 1 = never, 2..4 = that many shares (forced by tests;
 // ignored when the workspace is missing or too small).
 namespace {
+// Shares of a launch whose longest row block has `tiles` key tiles: an iteration of the tile loop takes 1.4 us (the second key
+// group runs one behind), parking, counting and fetching 3.4 us (heads of 64: 2.0), each of
+// up to four shares 0.3; more of them 2.2 (the last arriver's fetches queue up) and 1.2 each.
+// Measured, shares 1 / 4 / 7: 32 rows over 8000 keys 96 / 34 / 27 us, 512 over 20000 (8 heads) 241 / 75 / 57, 512 over 512
+// 19.9 / 16.9 / 18.8, 512 rows alone (eight tiles) 14.3 / 15.2 / 17.5; 32 rows over 30000 keys, 4 / 16 shares: 91 / 43.
+constexpr int MAX_SHARES = 16;
+int key_shares(int tiles, int most, double fixed_us) {
+    int best = 1;
+    double best_us = 1e30;
+    for (int s = 1; s <= most; ++s) {
+        const int share = (tiles + s - 1) / s, half = (share + 1) / 2;
+        const double us = 1.4 * max(half, share - half + 1) + (s > 4 ? fixed_us + 2.2 + 1.2 * (s - 4) : s > 1 ? fixed_us + 0.3 * s : 0.0);
+        if (us < best_us) {
+            best_us = us;
+            best = s;
+        }
+    }
+    return best;
+}
+
 template <int D>
 hipError_t launch_attn(const void *q, const void *k, const void *v, void *out, int Tc, int q_offset, int kv_len,
                        int nq, int nkv, int q_stride, int shape, int ksplit_req, const iso_attn_ws *ws, hipStream_t s) {
@@ -553,18 +573,16 @@ hipError_t launch_attn(const void *q, const void *k, const void *v, void *out, i
     const long long rounds = (paired + ncu - 1) / ncu;
     const bool pair_ok = wgs >= 320 && wgs <= 2048 && (paired <= ncu || paired * 10 >= 9 * rounds * ncu);
     const int mode = shape >= 1 && shape <= 3 ? shape - 1 : (pair_ok ? 1 : wgs < 512 ? 0 : 2);
-    // Launches of at most half as many workgroups as the chip has compute units also split the keys ACROSS
-    // workgroups, into as many shares as fit the chip once (at most 4, and at least two key tiles per share and wave
-    // group on the longest row block): the serial chain of key tiles per workgroup, which is what such a launch takes,
-    // shrinks by that factor.
+    // Launches of at most half as many workgroups as the chip has compute units also split the keys ACROSS workgroups, into
+    // at most as many shares as fit the chip once: the serial chain of key tiles per workgroup, which is what such a launch
+    // takes, shrinks by that factor (key_shares).
     int ksplit = 1;
     if (ws && ws->part && ws->cnt && wgs <= ws->max_blocks) {
         if (ksplit_req >= 2) {
             ksplit = ksplit_req;
         } else if (ksplit_req == 0 && mode == 0 && wgs * 2 <= ncu) {
             const int longest = (min(kv_len, q_offset + Tc) + BN - 1) / BN;      // key tiles of the last row block
-            ksplit = (int)min((long long)4, (long long)ncu / wgs);
-            while (ksplit > 1 && longest < 4 * ksplit) --ksplit;
+            ksplit = key_shares(longest, (int)min((long long)MAX_SHARES, (long long)ncu / wgs), D == 64 ? 2.0 : 3.4);
         }
         if (wgs * ksplit > ws->max_slots) ksplit = 1;
     }
