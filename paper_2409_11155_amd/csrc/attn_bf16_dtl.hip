@@ -6,8 +6,8 @@
 // softmax statistics are per-lane scalars and the probabilities feed the second product O^T = V^T P^T
 // straight from registers).  What differs is how K and V reach the matrix cores:
 //   * K and V tiles (64 keys x 128 dims) go global -> LDS directly (buffer_load ... lds) into two stages;
-//     the loads of tile j+1 are in flight while tile j is multiplied; one barrier per tile.  Rows past
-//     kv_len are out of the buffer's range and read as zero.
+//     the loads of tile j+1 are in flight while tile j is multiplied; one barrier per tile.  Rows that no row of
+//     the row block sees are out of the buffer's range and read as zero.
 //   * Both tiles keep their natural row-major layout; the 16-byte chunks of a row are XOR-swizzled on the
 //     global side (the LDS slot of a lane's 16 bytes is fixed by the lane number) so that the operand reads
 //     are free of bank conflicts.
@@ -136,7 +136,10 @@ __global__ __launch_bounds__(256 * KVS, KVS == 1 ? 2 : 1) void attn_bf16_dtl_ker
 
     // ---- direct-to-LDS loads: wave-load = 4 rows x 256 B (8 x 128); lane = (row l / CHUNKS, slot l % CHUNKS)
     const uint32_t row_stride = (uint32_t)nkv * D * 2u;                         // bytes between cache rows
-    const uint32_t n_rec = (uint32_t)(kv_len - 1) * row_stride + (uint32_t)ROW_B;  // this head's slice, rows < kv_len
+    // this head's slice, up to the last row that a row of the block sees: whatever a caller's cache holds behind it (memory
+    // never written, say) must not meet the zero probabilities of the last tile in the second product
+    const int kv_end = min(kv_len, q_offset + min(m0 + BM, Tc));    // exclusive
+    const uint32_t n_rec = (uint32_t)(kv_end - 1) * row_stride + (uint32_t)ROW_B;
     const __amdgpu_buffer_rsrc_t rs_k =
         __builtin_amdgcn_make_buffer_rsrc((void *)(Kc + (size_t)g * D), 0, (int)n_rec, 0x00020000);
     const __amdgpu_buffer_rsrc_t rs_v =
@@ -194,7 +197,6 @@ __global__ __launch_bounds__(256 * KVS, KVS == 1 ? 2 : 1) void attn_bf16_dtl_ker
     float l_run = 0.f;
     const float sc = 1.4426950408889634f / sqrtf((float)D);
 
-    const int kv_end = min(kv_len, q_offset + min(m0 + BM, Tc));    // exclusive
     const int n_tiles_blk = (kv_end + BN - 1) / BN;                  // key tiles of the row block
     // this workgroup's share [wg_lo, wg_lo + n_tiles_all) of them (all, unless the keys are split across workgroups)
     const int share = (n_tiles_blk + ksplit - 1) / ksplit;
@@ -349,7 +351,7 @@ __global__ __launch_bounds__(256 * KVS, KVS == 1 ? 2 : 1) void attn_bf16_dtl_ker
     if (!(SKEW && KVS > 1) || kgrp == 0) {
         // One tile per iteration: scores, softmax, second product.  In the branch-free body the eight requests for
         // tile jt+1 ride behind the MFMAs of the first product (no test for the end of the range: a tile past this
-        // group's share is never used, its stage is free, and rows past the cache read as zero).
+        // group's share is never used, its stage is free, and rows past the last visible one read as zero).
         auto tile = [&](int jt, auto tail_c) {
             constexpr bool TAIL = decltype(tail_c)::value;
             const int j0 = (t_lo + jt) * BN;

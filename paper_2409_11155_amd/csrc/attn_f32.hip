@@ -58,7 +58,7 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(const float *__restri
 #pragma unroll
         for (int b = 0; b < KB / 16; ++b) {
             if (EARLY_V) load_v(b, vf[EARLY_V ? b : 0]);
-            const float *kr = kp + (size_t)min(j0 + 16 * b + col, kv_len - 1) * row;
+            const float *kr = kp + (size_t)min(j0 + 16 * b + col, n_vis - 1) * row;
             f32x4_t kf[DS];
 #pragma unroll
             for (int s = 0; s < DS; ++s) kf[s] = *reinterpret_cast<const f32x4_t *>(kr + 16 * s);
