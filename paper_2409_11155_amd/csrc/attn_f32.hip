@@ -9,7 +9,7 @@
 // fetched four dims at a time (16 bytes per lane); V one dim per lane, 64 contiguous bytes per 16 lanes.
 // Bound by the trips to memory of a few waves.  Measured on 128 tokens, 4 heads of 64: 9 us against 33 us of the kernel that
 // gives every query row a wave and every lane a whole key row.
-#include "iso_internal.h"
+#include "attn_row.h"
 
 namespace {
 
@@ -113,20 +113,33 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(const float *__restri
 #pragma unroll
     for (int d = 0; d < DS; ++d) *reinterpret_cast<f32x4_t *>(&so[wave][col][16 * d + 4 * grp]) = o[d];
     __syncthreads();
-    for (int e = tid; e < QB * D; e += NW * 64) {
-        const int q = e / D, d = e % D;
-        if (i0 + q >= Tc) continue;
+    for (int q = wave; q < QB && i0 + q < Tc; q += NW) {             // a wave per row
         float mt = sm[0][q];
 #pragma unroll
         for (int w = 1; w < NW; ++w) mt = fmaxf(mt, sm[w][q]);
-        float num = 0.f, den = 0.f;
+        float num[D / 64] = {}, den = 0.f, probe = 0.f;
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
             const float f = expf(sm[w][q] - mt);                     // a wave without keys has m = -inf and weight zero
-            num += so[w][q][d] * f;
+#pragma unroll
+            for (int r = 0; r < D / 64; ++r) num[r] += so[w][q][lane + 64 * r] * f;
             den += sl[w][q] * f;
         }
-        Out[((size_t)(i0 + q) * nq + h) * D + d] = num / den;
+        float *op = Out + ((size_t)(i0 + q) * nq + h) * D;
+#pragma unroll
+        for (int r = 0; r < D / 64; ++r) {
+            num[r] /= den;
+            op[lane + 64 * r] = num[r];
+            probe = fmaf(num[r], 0.f, probe);
+        }
+        // A key that a row does not see has probability zero there, but 0 x infinity and 0 x NaN in the second product are
+        // NaN: a row with a result that is not finite is computed again, from the keys it sees.
+        if (__builtin_amdgcn_ballot_w64(probe != 0.f) != 0) {
+            __builtin_amdgcn_s_waitcnt(0);                           // the stores above come first
+            const float *qp = Q + (size_t)(i0 + q) * q_stride + (size_t)h * D;
+            attn_row<float, D>([&](int e) { return qp[e] * scale; }, Kc + (size_t)g * D, Vc + (size_t)g * D, row,
+                               min(kv_len, q_offset + i0 + q + 1), op, lane);
+        }
     }
 }
 

@@ -2,15 +2,10 @@
 // 64-key slices, fp32 throughout.  This is the fp32 path of the small workload and the fallback for
 // shapes the MFMA kernel does not take.  (Chunk over the cache written by the earlier chunk: paper
 // Section 3.1; chunked prefill, Section 2.1.)
-#include "iso_internal.h"
+#include "attn_row.h"
 
 namespace {
 
-template <typename T> __device__ __forceinline__ float exp_f(float z);
-template <> __device__ __forceinline__ float exp_f<float>(float z) { return expf(z); }
-template <> __device__ __forceinline__ float exp_f<bf16_t>(float z) { return __expf(z); }
-
-// D = head_dim (64 or 128).  Lane l owns output dims l, l+64 (D = 128) or l (D = 64).
 template <typename T, int D>
 __global__ __launch_bounds__(256) void attn_simple_kernel(const T *__restrict__ q, const T *__restrict__ kc,
                                                           const T *__restrict__ vc, T *__restrict__ out, int Tc,
@@ -29,37 +24,8 @@ __global__ __launch_bounds__(256) void attn_simple_kernel(const T *__restrict__ 
     if (!active) return;
     int n_vis = q_offset + i + 1;
     if (n_vis > kv_len) n_vis = kv_len;
-    constexpr int PER = D / 64;
-    float o[PER] = {};
-    float m = -INFINITY, l = 0.f;
-    for (int j0 = 0; j0 < n_vis; j0 += 64) {
-        const int j = j0 + lane;
-        float sc = -INFINITY;
-        if (j < n_vis) {
-            const T *kr = kc + ((size_t)j * nkv + g) * D;
-            float acc = 0.f;
-#pragma unroll 8
-            for (int e = 0; e < D; ++e) acc = fmaf(qs[wave][e], iso_to_f32(kr[e]), acc);
-            sc = acc;
-        }
-        const float m_new = fmaxf(m, iso_wave_max(sc));
-        const float p = (j < n_vis) ? exp_f<T>(sc - m_new) : 0.f;
-        const float alpha = exp_f<T>(m - m_new);     // m = -inf on the first slice gives 0
-        l = l * alpha + iso_wave_sum(p);
-#pragma unroll
-        for (int r = 0; r < PER; ++r) o[r] *= alpha;
-        const int cnt = min(64, n_vis - j0);
-        for (int jj = 0; jj < cnt; ++jj) {
-            const float pj = __shfl(p, jj, 64);
-            const T *vr = vc + ((size_t)(j0 + jj) * nkv + g) * D;
-#pragma unroll
-            for (int r = 0; r < PER; ++r) o[r] = fmaf(pj, iso_to_f32(vr[lane + 64 * r]), o[r]);
-        }
-        m = m_new;
-    }
-    const float inv = 1.0f / l;
-#pragma unroll
-    for (int r = 0; r < PER; ++r) out[((size_t)i * nq + h) * D + lane + 64 * r] = iso_from_f32<T>(o[r] * inv);
+    const T *k0 = kc + (size_t)g * D, *v0 = vc + (size_t)g * D;
+    attn_row<T, D>([&](int e) { return qs[wave][e]; }, k0, v0, (size_t)nkv * D, n_vis, out + ((size_t)i * nq + h) * D, lane);
 }
 
 }  // namespace

@@ -45,3 +45,41 @@ def test_cache_rows_behind_the_last_visible_one_may_hold_anything(dt, d, flags, 
         ctx.set_flags(flags)
         err = orc.max_rel_err(attend(ctx, q, k, v, dt, nq, d, Tc, q_offset, kv_len), ref)
     assert err <= tol, (err, tol)
+
+
+@pytest.mark.parametrize("dt,d,flags", KERNELS)
+@pytest.mark.parametrize("Tc,q_offset,bad", [(40, 0, 17), (200, 77, 150), (130, 500, 628), (70, 2000, 2001)])
+def test_a_later_tokens_non_finite_value_stays_out_of_the_earlier_rows(dt, d, flags, Tc, q_offset, bad):
+    """Key `bad` holds an infinity, a NaN and a finite value per head in V: rows that see it become inf / NaN in those two
+    dims and stay right in the others, rows before it stay right everywhere."""
+    nq, nkv, kv_len = 4, 2, q_offset + Tc
+    q, k, v = iso_inputs.make_qkv_cache(Tc, kv_len, nq, nkv, d, seed=Tc + q_offset, dtype=dt)
+    ref = orc.attention_chunk(h64(q, dt), h64(k, dt), h64(v, dt), q_offset, kv_len).reshape(Tc, nq, d)
+    tol = bound(dt, h64(v, dt), ref)
+    v[bad, :, 3] = np.inf if dt == "f32" else 0x7F80
+    v[bad, :, d - 1] = np.nan if dt == "f32" else 0xFFFF
+    with make_ctx(256, nq, nkv, d, 64, dt, kv_len) as ctx:
+        ctx.set_flags(flags)
+        got = attend(ctx, q, k, v, dt, nq, d, Tc, q_offset, kv_len).reshape(Tc, nq, d)
+    sees = bad - q_offset
+    assert np.isposinf(got[sees:, :, 3]).all() and np.isnan(got[sees:, :, d - 1]).all()
+    got[sees:, :, 3], got[sees:, :, d - 1] = ref[sees:, :, 3], ref[sees:, :, d - 1]
+    err = orc.max_rel_err(got, ref)
+    assert err <= tol, (err, tol)
+
+
+@pytest.mark.parametrize("dt,d,flags", KERNELS)
+def test_scores_far_below_zero(dt, d, flags):
+    """Every raw score of a row is -1.6e31 * d: softmax over equal scores, so each row is the mean of the V rows it sees."""
+    nq, nkv, Tc, q_offset = 4, 2, 100, 300
+    kv_len = q_offset + Tc
+    q, k, v = iso_inputs.make_qkv_cache(Tc, kv_len, nq, nkv, d, seed=5, dtype=dt)
+    big = lambda shape, x: iso_inputs.store(np.full(shape, x, dtype=np.float32), dt)
+    q, k = big(q.shape, 2.0 ** 52), big(k.shape, -(2.0 ** 52))
+    v64 = h64(v, dt)
+    ref = (np.cumsum(v64, axis=0) / np.arange(1, kv_len + 1)[:, None, None])[q_offset:].repeat(nq // nkv, axis=1)
+    tol = bound(dt, v64, ref)
+    with make_ctx(256, nq, nkv, d, 64, dt, kv_len) as ctx:
+        ctx.set_flags(flags)
+        err = orc.max_rel_err(attend(ctx, q, k, v, dt, nq, d, Tc, q_offset, kv_len), ref.reshape(Tc, nq * d))
+    assert err <= tol, (err, tol)
