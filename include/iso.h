@@ -24,7 +24,11 @@
  *     library's other streams join through its events) once the same call has run eagerly, so that
  *     streams, events and kernel attributes exist.  While a stream is capturing, the stream-K GEMM
  *     launch is not used (its launches are numbered, a replay would repeat a number) and per-launch
- *     timing is off.
+ *     timing is off.  A recorded iso_gemm_rowpar, iso_gemm_fp8, element-wise call or attention with
+ *     heads of 64 holds the caller's buffers only and may be replayed on any stream, beside other
+ *     work of the context.  A recorded layer or stack call holds the context's workspace, recorded
+ *     attention with heads of 128 its scratch memory of that stream: replay those within the life of
+ *     the context, ordered with its other layer calls or its other attention on that stream.
  */
 #ifndef ISO_H_
 #define ISO_H_

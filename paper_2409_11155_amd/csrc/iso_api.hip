@@ -124,21 +124,27 @@ iso_sk_ws *sk_for(iso_ctx *ctx, hipStream_t s) {
     return nullptr;
 }
 
-// Workspace of a split product on stream s (null: a foreign stream, only unsplit plans there).  Unlike stream-K it has no
-// launch numbers, so it may be recorded into a graph; launches that share it are ordered by their stream.
-iso_sk_ws *split_ws_for(iso_ctx *ctx, hipStream_t s) {
+// Workspace of a split product on stream s (null, for a foreign stream: only unsplit plans).  Launches that share one are ordered
+// by their stream.  That does not hold for a product recorded into a HIP graph: a replay may run on any stream, beside eager
+// products on this one.  Recorded calls of the stand-alone products (`layer` false) get none, they hold the caller's buffers only;
+// recorded layers, which hold the context's activations anyway and are replayed in order with its other layers, have workspaces
+// that eager products never touch.  (An extra chunk stream runs nothing but layers.)
+iso_sk_ws *split_ws_for(iso_ctx *ctx, hipStream_t s, bool layer = true) {
     for (int k = 0; k < ISO_MAX_CHUNKS; ++k)
-        if (ctx->sk[k].base && s == (k < 2 ? ctx->stream[k] : ctx->xstream[k])) return &ctx->sk[k];
+        if (ctx->sk[k].base && s == (k < 2 ? ctx->stream[k] : ctx->xstream[k])) {
+            if (!capturing(s)) return &ctx->sk[k];
+            return !layer ? nullptr : k < 2 ? &ctx->sk_rec[k] : &ctx->sk[k];
+        }
     return nullptr;
 }
 
 // What one projection launch of the layer becomes (`rope`: the QKV projection, see iso_gemm_split_plan).
-iso_split_plan plan_gemm(iso_ctx *ctx, bool fp8, bool rope, int M, int N, int K, hipStream_t s) {
+iso_split_plan plan_gemm(iso_ctx *ctx, bool fp8, bool rope, int M, int N, int K, hipStream_t s, bool layer = true) {
     const int forced = (ctx->flags >> 8) & 15;
     const iso_split_plan whole{-1, 1, forced == 7 ? 0 : forced};
     if (ctx->cfg.dtype != ISO_BF16 || !iso_gemm_split_supported(fp8, M, N, K)) return whole;
     if (ctx->flags & (ISO_FLAG_SIMPLE_GEMM | ISO_FLAG_GEMM_STAGED)) return whole;
-    const iso_sk_ws *ws = split_ws_for(ctx, s);
+    const iso_sk_ws *ws = split_ws_for(ctx, s, layer);
     const size_t bytes = ws ? (size_t)ws->num_wg * iso_gemm_sk_slot_bytes() : 0;
     if (forced == 7) {       // tests, measurement: bits 17..20 shares, 21..23 tile
         iso_split_plan p{std::min(5, (ctx->flags >> 21) & 7), std::max(1, (ctx->flags >> 17) & 15), 0};
@@ -152,10 +158,13 @@ iso_split_plan plan_gemm(iso_ctx *ctx, bool fp8, bool rope, int M, int N, int K,
     return iso_gemm_split_plan(fp8, rope, rule, M, N, K, bytes, iso_num_cu(), ctx->sk_hold != 0);
 }
 
-// Key-split attention workspace for a launch on stream s: one per stream of the context's own, none for others.
+// Key-split attention workspace for a launch on stream s: one per stream of the context's own, none for others.  Heads of 64 do
+// without it while a stream is recording, for the reason above; heads of 128 keep it there (half the time of a short chunk), and
+// the header says what that asks of a replay.
 constexpr int ATTN_SLOTS = 512, ATTN_BLOCKS = 512;
 
 const iso_attn_ws *attn_ws_for(const iso_ctx *ctx, hipStream_t s) {
+    if (ctx->cfg.head_dim == 64 && capturing(s)) return nullptr;
     if (s == ctx->stream[0] && ctx->aws[0].part) return &ctx->aws[0];
     if (s == ctx->stream[1] && ctx->aws[1].part) return &ctx->aws[1];
     for (int k = 2; k < ISO_MAX_CHUNKS; ++k)
@@ -215,16 +224,16 @@ bool use_fp8(const iso_ctx *ctx, const F8Arg &f8, int M, int N, int K) {
 }
 
 int gemm_fp8(iso_ctx *ctx, const void *a8, const float *sa, const void *w8, const float *sw, void *c, int M, int N, int K,
-             bool rope, hipStream_t s) {
-    const iso_split_plan sp = plan_gemm(ctx, true, rope, M, N, K, s);
-    const hipError_t e = sp.tile >= 0 ? iso_launch_gemm_split(sp, a8, w8, sa, sw, c, M, N, K, split_ws_for(ctx, s), s)
+             bool rope, hipStream_t s, bool layer = true) {
+    const iso_split_plan sp = plan_gemm(ctx, true, rope, M, N, K, s, layer);
+    const hipError_t e = sp.tile >= 0 ? iso_launch_gemm_split(sp, a8, w8, sa, sw, c, M, N, K, split_ws_for(ctx, s, layer), s)
                                       : iso_launch_gemm_fp8(a8, sa, w8, sw, c, M, N, K, sp.whole, sk_for(ctx, s), s);
     if (e != hipSuccess) return fail(ISO_ERR_HIP, "fp8 gemm launch (M=%d N=%d K=%d): %s", M, N, K, hipGetErrorString(e));
     return ISO_OK;
 }
 
 int gemm(iso_ctx *ctx, int kind, const void *a, const void *w, void *c, int M, int N, int K, hipStream_t s,
-         const F8Arg &f8 = F8Arg()) {
+         const F8Arg &f8 = F8Arg(), bool layer = true) {
     const size_t e_ = ctx->elt;
     if (use_fp8(ctx, f8, M, N, K)) {
         unsigned char *a8 = ctx->a8 + (size_t)f8.row0 * ctx->a8_pitch;
@@ -234,7 +243,7 @@ int gemm(iso_ctx *ctx, int kind, const void *a, const void *w, void *c, int M, i
         Timed t_(ctx, kind, s);
         return for_segments(ctx, M, [&](int lo, int n) {
             return gemm_fp8(ctx, a8 + (size_t)lo * K, sa + lo, f8.w8, f8.sw, (char *)c + (size_t)lo * N * e_, n, N, K,
-                            kind == ISO_K_GEMM_QKV, s);
+                            kind == ISO_K_GEMM_QKV, s, layer);
         });
     }
     Timed t_(ctx, kind, s);
@@ -243,9 +252,9 @@ int gemm(iso_ctx *ctx, int kind, const void *a, const void *w, void *c, int M, i
         void *cr = (char *)c + (size_t)lo * N * e_;
         hipError_t e;
         const bool mfma = ctx->cfg.dtype == ISO_BF16 && !(ctx->flags & ISO_FLAG_SIMPLE_GEMM);
-        const iso_split_plan sp = plan_gemm(ctx, false, kind == ISO_K_GEMM_QKV, n, N, K, s);
+        const iso_split_plan sp = plan_gemm(ctx, false, kind == ISO_K_GEMM_QKV, n, N, K, s, layer);
         if (sp.tile >= 0)
-            e = iso_launch_gemm_split(sp, ar, w, nullptr, nullptr, cr, n, N, K, split_ws_for(ctx, s), s);
+            e = iso_launch_gemm_split(sp, ar, w, nullptr, nullptr, cr, n, N, K, split_ws_for(ctx, s, layer), s);
         else if (mfma && !(ctx->flags & ISO_FLAG_GEMM_STAGED) && iso_gemm_bf16_dtl_supported(n, N, K))
             e = iso_launch_gemm_bf16_dtl(ar, w, cr, n, N, K, sp.whole, sk_for(ctx, s), s);
         else if (mfma && iso_gemm_bf16_mfma_supported(n, N, K))
@@ -836,7 +845,9 @@ int iso_create(iso_ctx **out, const iso_cfg *cfg, void *stream0, void *stream1) 
                 ctx->sk[i].num_wg = cus;
                 ctx->sk[i].epoch = 0;
                 ok = hip_ok(hipMalloc(&ctx->sk[i].base, bytes), "hipMalloc(stream-K workspace)") &&
-                     hip_ok(hipMemset(ctx->sk[i].base, 0, 4096), "hipMemset(stream-K flags)");
+                     hip_ok(hipMemset(ctx->sk[i].base, 0, 4096), "hipMemset(stream-K flags)") &&
+                     hip_ok(hipMalloc(&ctx->sk_rec[i].base, bytes), "hipMalloc(workspace of recorded layers)");
+                ctx->sk_rec[i].num_wg = cus;
             }
             if (!ok) break;
             // key-split attention workspaces: one per stream (both streams may run an attention launch at once)
@@ -904,6 +915,8 @@ int iso_destroy(iso_ctx *ctx) {
     if (ctx->sk[0].err) (void)hipHostFree(ctx->sk[0].err);
     for (int i = 0; i < ISO_MAX_CHUNKS; ++i)
         if (ctx->sk[i].base) (void)hipFree(ctx->sk[i].base);
+    for (int i = 0; i < 2; ++i)
+        if (ctx->sk_rec[i].base) (void)hipFree(ctx->sk_rec[i].base);
     for (int i = 0; i < ISO_MAX_CHUNKS; ++i) {
         if (ctx->aws[i].part) (void)hipFree(ctx->aws[i].part);
         if (ctx->aws[i].cnt) (void)hipFree(ctx->aws[i].cnt);
@@ -960,7 +973,7 @@ int iso_gemm_fp8(iso_ctx *ctx, const void *a8, const float *sa, const void *w8, 
     if (!iso_gemm_fp8_supported(M, N, K)) return fail(ISO_ERR_SHAPE, "M=%d N=%d K=%d: need M >= 1, N %% 8 == 0, K %% 128 == 0", M, N, K);
     ISO_TRY(sk_status(ctx));
     Timed t_(ctx, ISO_K_GEMM_O, (hipStream_t)stream);
-    return gemm_fp8(ctx, a8, sa, w8, sw, c, M, N, K, false, (hipStream_t)stream);
+    return gemm_fp8(ctx, a8, sa, w8, sw, c, M, N, K, false, (hipStream_t)stream, false);
 }
 
 int iso_set_gemm_segments(iso_ctx *ctx, int n) {
@@ -1116,7 +1129,7 @@ int iso_gemm_rowpar(iso_ctx *ctx, const void *a, const void *w, void *c, int M, 
     if (M < 1 || N < 1 || K < 1) return fail(ISO_ERR_SHAPE, "M=%d N=%d K=%d must be positive", M, N, K);
     if (ctx->cfg.dtype == ISO_BF16 && (K % 8)) return fail(ISO_ERR_SHAPE, "K=%d must be a multiple of 8 for bf16", K);
     ISO_TRY(sk_status(ctx));
-    ISO_TRY(gemm(ctx, ISO_K_GEMM_O, a, w, c, M, N, K, (hipStream_t)stream));
+    ISO_TRY(gemm(ctx, ISO_K_GEMM_O, a, w, c, M, N, K, (hipStream_t)stream, F8Arg(), false));
     if (host_sink) {
         Timed t_(ctx, ISO_K_COMM, (hipStream_t)stream);
         if (kernel_can_write(host_sink))

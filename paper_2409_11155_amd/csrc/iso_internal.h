@@ -64,6 +64,7 @@ struct iso_ctx {
     // GEMM workspaces (bf16 contexts only; base == null otherwise): [0], [1] for the caller's streams, used by the stream-K
     // launch and by split products; [k] for xstream[k], split products only
     iso_sk_ws sk[ISO_MAX_CHUNKS];
+    iso_sk_ws sk_rec[2];                // the same for layers recorded into a HIP graph on the caller's streams, split products only
     iso_attn_ws aws[ISO_MAX_CHUNKS];   // key-split attention workspaces: [0], [1] for the caller's streams, [k] for xstream[k]
     void *host_sink;   // pinned, 2 * max_seq * hidden elements
     // optional per-launch timing (iso_timing_*): event pairs recorded around every launch, in its stream

@@ -28,6 +28,7 @@ def hip_runtime():
     rt.hipStreamEndCapture.argtypes = [ctypes.c_void_p, ctypes.POINTER(ctypes.c_void_p)]
     rt.hipGraphInstantiate.argtypes = [ctypes.POINTER(ctypes.c_void_p), ctypes.c_void_p, ctypes.c_void_p, ctypes.c_char_p,
                                        ctypes.c_size_t]
+    rt.hipGraphGetNodes.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.POINTER(ctypes.c_size_t)]
     rt.hipGraphLaunch.argtypes = [ctypes.c_void_p, ctypes.c_void_p]
     rt.hipGraphExecDestroy.argtypes = [ctypes.c_void_p]
     rt.hipGraphDestroy.argtypes = [ctypes.c_void_p]
@@ -50,8 +51,13 @@ class Captured:
         self.exe = ctypes.c_void_p()
         assert rt.hipGraphInstantiate(ctypes.byref(self.exe), graph, None, None, 0) == 0
 
-    def launch(self):
-        assert self.rt.hipGraphLaunch(self.exe, self.stream) == 0
+    def nodes(self):
+        n = ctypes.c_size_t()
+        assert self.rt.hipGraphGetNodes(self.graph, None, ctypes.byref(n)) == 0
+        return n.value
+
+    def launch(self, stream=None):
+        assert self.rt.hipGraphLaunch(self.exe, self.stream if stream is None else stream) == 0
 
     def destroy(self):
         self.rt.hipGraphExecDestroy(self.exe)
@@ -129,4 +135,78 @@ def test_captured_iso_layer_replays_bit_identically_to_the_eager_step():
             g.launch()
             ctx.sync()
             np.testing.assert_array_equal(xd.numpy(), eager)
+        g.destroy()
+
+
+@pytest.mark.parametrize("flags", [0, (7 << 8) | (6 << 17) | (4 << 21), 6 << 8])
+@pytest.mark.parametrize("fp8", [False, True])
+def test_captured_products_hold_no_partial_sums_of_the_context(fp8, flags):
+    """Recorded on stream 0 and replayed on another stream beside eager products on stream 0 (by the launch rule, in six shares
+    of the k range, by stream-K): one kernel, the caller's buffers only, so every replay and every eager product is right."""
+    dt, (M, N, K) = "bf16", (512, 5120, 8192)
+    a, b = (iso_inputs.randn((M, K), seed=s, dtype=dt) for s in (81, 82))
+    w = iso_inputs.randn((N, K), seed=83, dtype=dt, scale=K ** -0.5)
+    linear = orc.linear_fp8 if fp8 else orc.linear
+    ref_a, ref_b = (linear(iso_inputs.to_f64(x, dt), iso_inputs.to_f64(w, dt)) for x in (a, b))
+    rt = hip_runtime()
+    with iso.Context(iso.make_cfg(256, 4, 4, 64, 64, dt, 256)) as ctx:
+        other = iso.Stream()
+
+        def operands(x):
+            if not fp8:
+                return [dev(x, dt), dev(w, dt)]
+            out = []
+            for m in (x, w):
+                q, s = iso.DeviceArray(m.shape, "u8"), iso.DeviceArray((m.shape[0],), "f32")
+                ctx.quantize_rows_fp8(dev(m, dt), m.shape[0], K, q, s, ctx.stream0)
+                out += [q, s]
+            return out
+
+        op_a, op_b = operands(a), operands(b)
+        product = lambda op, c: (ctx.gemm_fp8 if fp8 else ctx.gemm_rowpar)(*op, c, M, N, K, ctx.stream0)
+        c, eager = iso.DeviceArray((M, N), dt, fill_byte=0xFF), iso.DeviceArray((M, N), dt, fill_byte=0xFF)
+        ctx.set_flags(flags)
+        product(op_b, eager)
+        ctx.set_flags(flags if flags >> 8 != 6 else 0)          # a forced stream-K launch cannot be recorded
+        g = Captured(rt, ctx.stream0.handle, lambda: product(op_a, c))
+        ctx.set_flags(flags)
+        ctx.sync()
+        assert g.nodes() == 1
+        for rep in range(3):
+            c.fill(0xFF)
+            eager.fill(0xFF)
+            for _ in range(4):
+                product(op_b, eager)
+                g.launch(other.handle)
+            iso.device_sync()
+            assert orc.max_rel_err(iso_inputs.to_f64(c.numpy(), dt), ref_a) <= 1e-2, rep
+            assert orc.max_rel_err(iso_inputs.to_f64(eager.numpy(), dt), ref_b) <= 1e-2, rep
+        g.destroy()
+
+
+def test_captured_attention_with_heads_of_64_beside_eager_attention():
+    """Few rows over a long cache, where an eager launch deals the keys to many workgroups: the recorded launch does not."""
+    dt, d, nq, nkv, Tc, q_offset = "bf16", 64, 4, 2, 33, 4095
+    kv = q_offset + Tc
+    k, v = (iso_inputs.randn((kv, nkv, d), seed=s, dtype=dt) for s in (91, 92))
+    qs = [iso_inputs.randn((Tc, nq, d), seed=s, dtype=dt) for s in (93, 94)]
+    refs = [orc.attention_chunk(*(iso_inputs.to_f64(t, dt) for t in (q, k, v)), q_offset, kv).reshape(Tc, nq * d) for q in qs]
+    rt = hip_runtime()
+    with iso.Context(iso.make_cfg(256, nq, nkv, d, 64, dt, kv)) as ctx:
+        other = iso.Stream()
+        kd, vd, qd = dev(k, dt), dev(v, dt), [dev(q, dt) for q in qs]
+        outs = [iso.DeviceArray((Tc, nq * d), dt, fill_byte=0xFF) for _ in qs]
+        attend = lambda i: ctx.attn_chunk(qd[i], kd, vd, outs[i], Tc, q_offset, kv, ctx.stream0)
+        attend(1)
+        g = Captured(rt, ctx.stream0.handle, lambda: attend(0))
+        ctx.sync()
+        for rep in range(3):
+            for o in outs:
+                o.fill(0xFF)
+            for _ in range(8):
+                attend(1)
+                g.launch(other.handle)
+            iso.device_sync()
+            for o, ref in zip(outs, refs):
+                assert orc.max_rel_err(iso_inputs.to_f64(o.numpy(), dt), ref) <= 1e-2, rep
         g.destroy()
