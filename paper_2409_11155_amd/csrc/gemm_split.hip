@@ -511,6 +511,7 @@ hipError_t iso_launch_gemm_split(const iso_split_plan &plan, const void *a, cons
     const Operands o{a, w, sa, sw, c, p, M, N, K};
     if (plan.shares == 1)
         return fp8 ? launch_cfg<Fp8Op, EPI_BF16>(plan.tile, o, 1, s) : launch_cfg<Bf16Op<false>, EPI_BF16>(plan.tile, o, 1, s);
+    const std::lock_guard<std::mutex> hold(ws->lock);
     hipError_t e = fp8 ? launch_cfg<Fp8Op, EPI_PARTIAL>(plan.tile, o, plan.shares, s)
                        : launch_cfg<Bf16Op<false>, EPI_PARTIAL>(plan.tile, o, plan.shares, s);
     if (e != hipSuccess) return e;
@@ -527,6 +528,7 @@ hipError_t iso_launch_gemm_split_swiglu(const iso_split_plan &plan, const void *
     const Operands o{a, w, sa, sw, act, p, M, 2 * F, K};
     if (plan.shares == 1)
         return fp8 ? launch_cfg<Fp8Op, EPI_SWIGLU>(plan.tile, o, 1, s) : launch_cfg<Bf16Op<false>, EPI_SWIGLU>(plan.tile, o, 1, s);
+    const std::lock_guard<std::mutex> hold(ws->lock);
     hipError_t e = fp8 ? launch_cfg<Fp8Op, EPI_PARTIAL>(plan.tile, o, plan.shares, s)
                        : launch_cfg<Bf16Op<false>, EPI_PARTIAL>(plan.tile, o, plan.shares, s);
     if (e != hipSuccess) return e;
@@ -541,6 +543,7 @@ hipError_t iso_launch_gemm_split_rope(const iso_split_plan &plan, const void *a,
     if (!ws || !ws->base) return hipErrorInvalidValue;
     float *p = (float *)((char *)ws->base + SK_HDR);
     const Operands o{a, w, sa, sw, nullptr, p, M, N, K};
+    const std::lock_guard<std::mutex> hold(ws->lock);
     hipError_t e = sa ? launch_cfg<Fp8Op, EPI_PARTIAL>(plan.tile, o, plan.shares, s)
                       : launch_cfg<Bf16Op<false>, EPI_PARTIAL>(plan.tile, o, plan.shares, s);
     if (e != hipSuccess) return e;

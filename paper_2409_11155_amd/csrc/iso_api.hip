@@ -786,8 +786,7 @@ int iso_create(iso_ctx **out, const iso_cfg *cfg, void *stream0, void *stream1) 
     ISO_TRY(check_cfg(cfg));
     int dev = -1;
     HIP_TRY(hipGetDevice(&dev));
-    iso_ctx *ctx = new iso_ctx();
-    memset(ctx, 0, sizeof(*ctx));
+    iso_ctx *ctx = new iso_ctx();            // value-initialised: every plain member is zero
     ctx->cfg = *cfg;
     ctx->device = dev;
     ctx->stream[0] = (hipStream_t)stream0;

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include <atomic>
+#include <mutex>
 
 #include "iso.h"
 
@@ -17,12 +18,15 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
 // Workspace of one stream-K GEMM in flight (flag words + one fp32 partial tile per workgroup).  Launches that
-// share a workspace must be ordered (same stream); the context keeps one per stream of its own.
+// share a workspace must be ordered (same stream); the context keeps one per stream of its own.  Host threads may enqueue
+// products on the same stream: `lock` keeps a launch number with its launch, and the kernel that leaves partial sums next to
+// the one that adds them.
 struct iso_sk_ws {
     void *base;        // device; flag words zeroed once at creation, never reset (each launch uses a new epoch)
     unsigned *err;     // pinned host word the kernel sets if a bounded wait ran out
     unsigned epoch;    // launch counter
     int num_wg;        // grid size = compute units of the device
+    std::mutex lock;
 };
 
 // Workspace of the attention launches that split the keys of a row block across workgroups: partial states and one
