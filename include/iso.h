@@ -64,8 +64,8 @@ typedef enum {
 } iso_comm;
 
 /* A cut serves to hide transfers behind another chunk's work.  Where they are too short for that (or there are none) the
- * library computes neighbouring chunks together, unless kernel-choice flags are set; results do not depend on the cut beyond
- * the order of fp32 sums. */
+ * library computes neighbouring chunks together, unless ISO_FLAG_KEEP_CUT or a kernel-choice flag is set; results do not depend
+ * on the cut beyond the order of fp32 sums. */
 
 /* How the two chunks are issued (Section 1, Figure 1 (a) versus (d)). */
 typedef enum {
@@ -123,7 +123,8 @@ int iso_validate_cfg(const iso_cfg *cfg);
 
 /* Fills `out` with the chunk ranges for a prompt of T tokens cut at `split` (Section 3.1; an unequal
  * cut is the remedy of Section 6 for the dearer second half).  split == 0 or split == T means one
- * chunk.  Host only.  Errors: NULL, bad cfg, T < 1, T > max_seq (ISO_ERR_WORKSPACE), split outside
+ * chunk.  This is the cut as it is asked for: it does not know the comm mode and flags by which a call may
+ * compute its chunks together (see above).  Host only.  Errors: NULL, bad cfg, T < 1, T > max_seq (ISO_ERR_WORKSPACE), split outside
  * [0, T] (ISO_ERR_SPLIT). */
 int iso_plan_chunks(const iso_cfg *cfg, int T, int split, iso_plan *out);
 
@@ -252,8 +253,10 @@ enum {
     ISO_FLAG_ATTN_STAGED = 16,/* register-staged MFMA attention instead of the direct-to-LDS one    */
     ISO_FLAG_NO_STREAMK = 32, /* one workgroup per output tile: neither the stream-K launch of the direct-to-LDS GEMM nor
                                  narrow tiles or a split k range are picked                          */
-    ISO_FLAG_FP8_GEMM = 64    /* bf16 layers: run the four projections on the FP8 matrix cores (needs the FP8
+    ISO_FLAG_FP8_GEMM = 64,   /* bf16 layers: run the four projections on the FP8 matrix cores (needs the FP8
                                  weights in iso_weights; activations are quantised per token row on the fly) */
+    ISO_FLAG_KEEP_CUT = 128   /* the chunks of a layer or stack call run as they were asked for, whatever there is to
+                                 hide; the choice of kernels for a chunk is not touched                */
     /* bits 8..11: tile variant of the direct-to-LDS GEMM (0 = chosen from the shape; 6 = its stream-K launch, which
      * this value also forces for the FP8 GEMM; 7 = narrow tiles / split k range, with bits 17..20 = number of shares and
      * bits 21..23 = tile: 0, 1, 2 = 32, 64, 128 rows x 64 columns, 3 = 128 x 128, 4 = 256 x 256,

@@ -30,6 +30,7 @@ ISO_MAX_CHUNKS = 8
 ISO_FLAG_SIMPLE_GEMM, ISO_FLAG_SIMPLE_ATTN, ISO_FLAG_GEMM_STAGED, ISO_FLAG_NO_FUSE, ISO_FLAG_ATTN_STAGED = 1, 2, 4, 8, 16
 ISO_FLAG_NO_STREAMK = 32
 ISO_FLAG_FP8_GEMM = 64
+ISO_FLAG_KEEP_CUT = 128
 
 EXPORTS = [
     "iso_validate_cfg", "iso_plan_chunks", "iso_plan_split", "iso_plan_chunk_count", "iso_stack_prefill_chunks", "iso_create", "iso_destroy", "iso_sync", "iso_last_error",

@@ -593,7 +593,7 @@ int run_stack(iso_ctx *ctx, const iso_weights *layers, int n_layers, void *x, vo
     const iso_cfg &c = ctx->cfg;
     // Chunks exist to hide transfers.  Where there is little or nothing to hide, rows that a cut would only spread over more
     // and smaller products stay together: the rows of a layer do not depend on the cut, only the order of some sums does.
-    // (With kernel-choice flags set, for tests and measurement, the cut is taken as it is.)
+    // (With ISO_FLAG_KEEP_CUT or kernel-choice flags set the cut is taken as it is.)
     //   * Transfers of at most 4 MB: measured, cut in half / whole: 70B TP=8, bf16 payload, 128 tokens (2 MB) 226 / 197 us,
     //     256 (4 MB) 313 / 307, 400 (6.6 MB) 398 / 433; int8 payload, 256 (2 MB) 339 / 236, 512 (4 MB) 408 / 360, 768 (6 MB)
     //     482 / 513; hidden 2048, bf16, 512 (2 MB) 218 / 193, 1024 (4 MB) even, 1536 (6 MB) 424 / 488; int8, 1024 (2 MB)

@@ -28,3 +28,37 @@ def test_whole_or_cut(T, split):
     for a, b in zip(*got):
         assert np.isfinite(a).all()
         assert orc.max_rel_err(a, b) <= 2 * TOL_LAYER["bf16"]
+
+
+@pytest.mark.parametrize("dt,d,comm,fp8", [("f32", 64, iso.ISO_COMM_D2H, 0), ("bf16", 128, iso.ISO_COMM_NONE, 0),
+                                           ("bf16", 64, iso.ISO_COMM_D2H_INT8, 0),
+                                           ("bf16", 128, iso.ISO_COMM_D2H, iso.ISO_FLAG_FP8_GEMM)])
+def test_keep_cut_runs_every_chunk_that_was_asked_for(dt, d, comm, fp8):
+    """By default a short prompt is one chunk; with the flag there are as many launches as chunks, on every schedule, and rows
+    and caches agree.  Bounds beside the one above: FP8, the roundings that another order of sums moves shift codes by a step (see
+    test_gpu_fp8); int8 payload, a neighbouring code at each of the two points, row maximum (at most 6 rms) / 127 apiece."""
+    hidden, nq, nkv, ffn, T, bounds = 512, 4, 2, 768, 300, [70, 130, 131, 280]
+    w = iso_inputs.make_layer(hidden, nq, nkv, d, ffn, seed=49, dtype=dt)
+    x = iso_inputs.make_hidden(T, hidden, seed=49, dtype=dt)
+    with make_ctx(hidden, nq, nkv, d, ffn, dt, T) as ctx:
+        wd = iso.upload_weights(w, dt)
+        if fp8:
+            wd = ctx.add_fp8_weights(wd)
+        got = []
+        for flags, chunks in ((0, 1), (iso.ISO_FLAG_KEEP_CUT, 5)):
+            for sched in (iso.ISO_SCHED_OVERLAP, iso.ISO_SCHED_SERIAL, iso.ISO_SCHED_STREAM_PER_CHUNK):
+                ctx.set_flags(flags | fp8)
+                xd = iso.DeviceArray.from_numpy(x, dt)
+                kc, vc = (iso.DeviceArray((1, T, nkv, d), dt, fill_byte=0xFF) for _ in range(2))
+                ctx.timing_enable(True)
+                ctx.stack_prefill_chunks([wd], xd, kc, vc, T, bounds, comm, sched)
+                ctx.sync()
+                n = ctx.timing_read()
+                ctx.timing_enable(False)
+                assert n["attn"][1] == chunks and n["gemm_down"][1] == chunks
+                assert n["comm"][1] == (0 if comm == iso.ISO_COMM_NONE else 2 * chunks)
+                got.append([f64(a) for a in (xd, kc, vc)])
+    tol = 0.2 if fp8 else 2 * TOL_LAYER[dt] + (2 / 127.0 * 6 if comm == iso.ISO_COMM_D2H_INT8 else 0)
+    for other in got[1:]:
+        for a, b in zip(got[0], other):
+            assert np.isfinite(b).all() and orc.max_rel_err(b, a) <= tol
