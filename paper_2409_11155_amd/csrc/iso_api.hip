@@ -587,6 +587,23 @@ double projections_us(const iso_ctx *ctx, int rows, bool shared) {
     return sum;
 }
 
+// Which of the layer's products over `rows` rows the kernels for large operands take, a bit per product and kernel: their 32-bit
+// offsets end at 2^31 elements of an operand (with 28672 MLP columns at 74898 rows).
+unsigned kernels_for(const iso_ctx *ctx, int rows) {
+    const iso_cfg &c = ctx->cfg;
+    const int H = c.hidden, D = c.n_q_heads * c.head_dim, F = c.ffn;
+    const int nk[4][2] = {{n_qkv(c), H}, {H, D}, {2 * F, H}, {H, F}};
+    unsigned bits = 0;
+    for (int i = 0; i < 4; ++i) {
+        const int N = nk[i][0], K = nk[i][1];
+        const bool bf16 = c.dtype == ISO_BF16;
+        bits |= (unsigned)(bf16 ? iso_gemm_bf16_dtl_supported(rows, N, K) : iso_gemm_f32_supported(nullptr, nullptr, rows, N, K)) << i;
+        bits |= (unsigned)(bf16 && iso_gemm_fp8_supported(rows, N, K)) << (i + 4);
+        bits |= (unsigned)(bf16 && iso_gemm_split_supported(false, rows, N, K)) << (i + 8);
+    }
+    return bits;
+}
+
 // edges[0..nc]: chunk c is rows [edges[c], edges[c+1]).
 int run_stack(iso_ctx *ctx, const iso_weights *layers, int n_layers, void *x, void *k_caches, void *v_caches,
               const int *edges_in, int nc, int comm, int sched) {
@@ -612,14 +629,22 @@ int run_stack(iso_ctx *ctx, const iso_weights *layers, int n_layers, void *x, vo
         const size_t row_bytes = comm == ISO_COMM_D2H_INT8 ? (size_t)c.hidden + 16 : (size_t)c.hidden * ctx->elt;
         bool whole = comm == ISO_COMM_NONE ? T <= 2816 || sched == ISO_SCHED_SERIAL || ctx->stream[1] == ctx->stream[0]
                                            : T <= 1280 && T * row_bytes <= 4u << 20;
+        int least = T;
+        for (int k = 0; k < nc; ++k) least = std::min(least, edges[k + 1] - edges[k]);
+        // rows are put together only while every product keeps the kernels that the smallest chunk gets
+        auto fits = [&](int rows) { return kernels_for(ctx, rows) == kernels_for(ctx, least); };
+        const bool one_fits = fits(T);
+        whole = whole && one_fits;
         if (!whole && comm == ISO_COMM_NONE) {
             int k = 1;       // the cut nearest to 0.55 T: the later half of a causal prompt is the dearer one
             for (int j = 2; j < nc; ++j)
                 if (fabs(edges[j] - 0.55 * T) < fabs(edges[k] - 0.55 * T)) k = j;
-            edges[1] = edges[k];
-            edges[2] = T;
-            nc = 2;
-            if (c.dtype == ISO_BF16 && !(ctx->flags & ISO_FLAG_FP8_GEMM)) {
+            if (fits(std::max(edges[k], T - edges[k]))) {
+                edges[1] = edges[k];
+                edges[2] = T;
+                nc = 2;
+            }
+            if (nc == 2 && one_fits && c.dtype == ISO_BF16 && !(ctx->flags & ISO_FLAG_FP8_GEMM)) {
                 const double one = projections_us(ctx, T, false), lo = projections_us(ctx, edges[1], true),
                              hi = projections_us(ctx, T - edges[1], true);
                 whole = one > 0.0 && lo > 0.0 && hi > 0.0 && one < 0.955 * (lo + hi);

@@ -62,3 +62,33 @@ def test_keep_cut_runs_every_chunk_that_was_asked_for(dt, d, comm, fp8):
     for other in got[1:]:
         for a, b in zip(got[0], other):
             assert np.isfinite(b).all() and orc.max_rel_err(b, a) <= tol
+
+
+@pytest.mark.parametrize("fp8", [0, iso.ISO_FLAG_FP8_GEMM])
+@pytest.mark.parametrize("T,bounds,sched", [(76000, [38000], iso.ISO_SCHED_SERIAL),
+                                            (150000, [30000, 70000, 140000], iso.ISO_SCHED_OVERLAP)])
+def test_chunks_are_not_put_together_beyond_the_limits_of_their_kernels(T, bounds, sched, fp8):
+    """28672 MLP columns: the down projection's operand reaches 2^31 elements at 74899 rows, where its kernel ends.  All of the
+    prompt (76000 rows), or the better of its halves (80000), lies beyond, every chunk below: the cut stays, with the same
+    kernels and therefore the same bits as with the cut pinned."""
+    hidden, nq, nkv, d, ffn, dt = 128, 1, 1, 128, 28672, "bf16"
+    w = iso_inputs.make_layer(hidden, nq, nkv, d, ffn, seed=50, dtype=dt)
+    x = iso_inputs.make_hidden(T, hidden, seed=50, dtype=dt)
+    with make_ctx(hidden, nq, nkv, d, ffn, dt, T) as ctx:
+        wd = iso.upload_weights(w, dt)
+        if fp8:
+            wd = ctx.add_fp8_weights(wd)
+        got = []
+        for flags in (0, iso.ISO_FLAG_KEEP_CUT):
+            ctx.set_flags(flags | fp8)
+            xd = iso.DeviceArray.from_numpy(x, dt)
+            kc, vc = (iso.DeviceArray((1, T, nkv, d), dt, fill_byte=0xFF) for _ in range(2))
+            ctx.timing_enable(True)
+            ctx.stack_prefill_chunks([wd], xd, kc, vc, T, bounds, iso.ISO_COMM_NONE, sched)
+            ctx.sync()
+            n = ctx.timing_read()
+            ctx.timing_enable(False)
+            assert n["gemm_down"][1] == len(bounds) + 1
+            got.append([a.numpy() for a in (xd, kc, vc)] + [n["quant"][1]])
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
