@@ -73,7 +73,8 @@ typedef enum {
                               and chunks of >= 1024 rows chunk 1's attention block starts when chunk 0's has been
                               issued, otherwise chunk 1's attention starts when chunk 0's K/V rows are written */
     ISO_SCHED_SERIAL = 1,  /* every chunk on stream0, one block after the other, copies in line        */
-    ISO_SCHED_STREAM_PER_CHUNK = 2 /* each chunk on a stream of its own (the context makes the extra ones), attention
+    ISO_SCHED_STREAM_PER_CHUNK = 2 /* each chunk on a stream of its own (the context makes the extra ones on first use,
+                                      each with about 100 MB of scratch memory in a bf16 context), attention
                                       blocks chained in chunk order; meant for more than two chunks            */
 } iso_sched;
 

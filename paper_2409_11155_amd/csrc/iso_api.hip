@@ -549,18 +549,23 @@ int check_layer_args(iso_ctx *ctx, const iso_weights *layers, int n_layers, void
     return sk_status(ctx);
 }
 
-// Extra streams for ISO_SCHED_STREAM_PER_CHUNK, created on first use (default priority, like every stream here).
+// Extra streams for ISO_SCHED_STREAM_PER_CHUNK, created on first use (default priority, like every stream here), with the
+// workspaces that give them the launch choices of the caller's streams.  The one for partial sums is optional: without it
+// (64 MiB may be more than is left) products on that stream are not split.
 int chunk_streams(iso_ctx *ctx, int nc, hipStream_t *out) {
     out[0] = ctx->stream[0];
     out[1] = ctx->stream[1];
     for (int k = 2; k < nc; ++k) {
         if (!ctx->xstream[k]) {
             HIP_TRY(hipStreamCreateWithFlags(&ctx->xstream[k], hipStreamNonBlocking));
-            if (ctx->cfg.dtype == ISO_BF16 && !ctx->aws[k].part) {   // same launch choices as on the caller's streams
+            if (ctx->cfg.dtype == ISO_BF16) {
                 HIP_TRY(attn_ws_create(&ctx->aws[k]));
+                HIP_TRY(hipDeviceSynchronize());                     // its counters are cleared on the null stream
                 ctx->sk[k].num_wg = ctx->sk[0].num_wg;
-                HIP_TRY(hipMalloc(&ctx->sk[k].base, iso_gemm_sk_ws_bytes(ctx->sk[k].num_wg)));
-                HIP_TRY(hipDeviceSynchronize());
+                if (hipMalloc(&ctx->sk[k].base, iso_gemm_sk_ws_bytes(ctx->sk[k].num_wg)) != hipSuccess) {
+                    ctx->sk[k].base = nullptr;
+                    (void)hipGetLastError();
+                }
             }
         }
         out[k] = ctx->xstream[k];

@@ -1,0 +1,72 @@
+"""The host side of libiso without a GPU: the library's HIP calls go to tests/fake_hip.cpp, which records them.  Each case runs in a
+process of its own (the stand-in has to be there before the library is loaded)."""
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+WORKSPACE = 4096 + 256 * 256 * 1024          # stream-K / split-product workspace of a stream on 256 compute units
+
+PRELUDE = """
+import ctypes, sys
+fake = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+fake.fake_log.restype = ctypes.c_char_p
+fake.fake_refuse.argtypes = [ctypes.c_size_t]
+import paper_2409_11155_amd as iso
+def log():
+    lines = [l.split(" ", 2) for l in fake.fake_log().decode().splitlines()]
+    fake.fake_clear()
+    return lines
+def array(*shape, dt="bf16"):
+    return iso.DeviceArray(shape, dt)
+def layer(hidden, nq, nkv, d, ffn, dt="bf16"):
+    return {"w_qkv": array((nq + 2 * nkv) * d, hidden, dt=dt), "w_o": array(hidden, nq * d, dt=dt),
+            "w_gate_up": array(2 * ffn, hidden, dt=dt), "w_down": array(hidden, ffn, dt=dt), "g_attn": array(hidden, dt=dt),
+            "g_mlp": array(hidden, dt=dt)}
+"""
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    if not shutil.which("g++"):
+        pytest.skip("no host compiler")
+    path = str(tmp_path_factory.mktemp("fake") / "libfakehip.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-pthread", "-o", path,
+                    os.path.join(ROOT, "tests", "fake_hip.cpp")], check=True)
+    return path
+
+
+def run(fake, code):
+    p = subprocess.run([sys.executable, "-c", PRELUDE + code, fake], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    assert p.returncode == 0, p.stdout + p.stderr
+
+
+def test_a_refused_workspace_of_an_extra_chunk_stream_costs_the_split_products_only(fake):
+    """The 64 MiB for partial sums are optional: without them the chunks of that stream run unsplit launches, the call succeeds,
+    no error is left behind for the next launch to report, and nothing is launched before the attention counters, cleared by a
+    memset on the null stream, are known to be zero."""
+    run(fake, f"""
+T, hidden, nq, nkv, d, ffn = 400, 512, 4, 1, 128, 768
+w = layer(hidden, nq, nkv, d, ffn)
+for refuse in (0, {WORKSPACE}):
+    with iso.Context(iso.make_cfg(hidden, nq, nkv, d, ffn, "bf16", T)) as ctx:
+        ctx.set_flags(iso.ISO_FLAG_KEEP_CUT)
+        x, k, v = array(T, hidden), array(1, T, nkv, d), array(1, T, nkv, d)
+        fake.fake_refuse(refuse)
+        log()
+        for call in range(2):
+            ctx.stack_prefill_chunks([w], x, k, v, T, [100, 200, 300], iso.ISO_COMM_D2H, iso.ISO_SCHED_STREAM_PER_CHUNK)
+            lines = log()
+            kinds = [l[0] for l in lines]
+            assert kinds.count("refused") == (2 if refuse and call == 0 else 0), kinds
+            assert kinds.count("kernel") > 30
+            if call == 0:
+                zeroed = max(i for i, n in enumerate(kinds) if n == "memset")
+                assert "device_sync" in kinds[zeroed:kinds.index("kernel")], kinds
+            split = {{l[1] for l in lines if l[0] == "kernel" and "share_sum" in l[2]}}
+            assert len(split) == (2 if refuse else 4), split         # streams with split products
+        fake.fake_refuse(0)
+""")
