@@ -70,3 +70,26 @@ for refuse in (0, {WORKSPACE}):
             assert len(split) == (2 if refuse else 4), split         # streams with split products
         fake.fake_refuse(0)
 """)
+
+
+def test_the_two_kernels_of_a_split_product_stay_together_under_two_threads(fake):
+    """Launches take 2 ms here, so that two threads on one stream meet between a kernel that leaves partial sums and the one
+    that adds them if nothing keeps them apart."""
+    run(fake, """
+import threading
+with iso.Context(iso.make_cfg(256, 4, 4, 64, 64, "bf16", 256)) as ctx:
+    ctx.set_flags((7 << 8) | (3 << 17))
+    a, w, c = array(64, 1024), array(64, 1024), array(64, 64)
+    log()
+    fake.fake_launch_us(2000)
+    start = threading.Barrier(2)
+    def enqueue():
+        start.wait()
+        for _ in range(10):
+            ctx.gemm_rowpar(a, w, c, 64, 64, 1024, ctx.stream0)
+    threads = [threading.Thread(target=enqueue) for _ in range(2)]
+    [t.start() for t in threads]
+    [t.join() for t in threads]
+    order = ["sum" if "share_sum" in l[2] else "partial" for l in log() if l[0] == "kernel"]
+    assert order == ["partial", "sum"] * 20, order
+""")
