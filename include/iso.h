@@ -338,8 +338,8 @@ int iso_host_alloc(void **ptr, size_t bytes);             /* pinned host memory 
 int iso_host_free(void *ptr);
 int iso_copy_h2d(void *dst_dev, const void *src_host, size_t bytes);
 int iso_copy_d2h(void *dst_host, const void *src_dev, size_t bytes);
-/* Asynchronous device-to-host copy in `stream` (dst_host pinned, e.g. from iso_host_alloc): the same call the
- * communication stand-in makes, exposed so that a caller can keep the copy engine busy beside a kernel. */
+/* Plain asynchronous device-to-host copy in `stream` (dst_host pinned, e.g. from iso_host_alloc), for a caller that wants to keep
+ * a copy running beside a kernel.  (The communication stand-in picks by size between the copy engine and a short kernel.) */
 int iso_copy_d2h_async(void *dst_host, const void *src_dev, size_t bytes, void *stream);
 int iso_copy_d2d(void *dst_dev, const void *src_dev, size_t bytes);
 int iso_stream_create(void **stream);                     /* non-blocking stream, default priority  */

@@ -314,7 +314,9 @@ int sk_status(const iso_ctx *ctx) {
 // The two-dimensional copy always goes to a copy engine: 1220 us, and 4 layers of the 16k stack 61 -> 41 ms.
 // Short payloads go by kernel, whose start and end are 10 us cheaper than the engine's.  Measured on the 70B TP=8 layer,
 // engine / kernel: beside another chunk, copies of 0.5 MB 334 / 325 us, 1 MB even, 2 MB 445 / 463, 4 MB 535 / 593;
-// with nothing beside it, 2 MB 340 / 317, 4 MB 406 / 390, 8 MB even, 33 MB 1627 / 1647.
+// with nothing beside it, 2 MB 340 / 317, 4 MB 406 / 390, 8 MB even, 33 MB 1627 / 1647.  A row-parallel product with its copy,
+// two of them beside one product of 2048 x 7168 x 8192 on the other stream (150 us): copies of 2 MB 156 / 204 us, 4 MB 255 / 263,
+// 6 MB 301 / 328; alone, product and copy 58 / 46, 97 / 90, 136 / 129.
 // A graph capture records the kernel as well.
 hipError_t comm_copy(void *dst, const void *src, size_t pitch, size_t rows, bool overlap, hipStream_t s) {
     const size_t bytes = pitch * rows, by_kernel = overlap ? 1u << 20 : 6u << 20;
@@ -1161,8 +1163,8 @@ int iso_gemm_rowpar(iso_ctx *ctx, const void *a, const void *w, void *c, int M, 
     ISO_TRY(gemm(ctx, ISO_K_GEMM_O, a, w, c, M, N, K, (hipStream_t)stream, F8Arg(), false));
     if (host_sink) {
         Timed t_(ctx, ISO_K_COMM, (hipStream_t)stream);
-        if (kernel_can_write(host_sink))
-            HIP_TRY(comm_copy(host_sink, c, (size_t)N * ctx->elt, (size_t)M, false, (hipStream_t)stream));
+        if (kernel_can_write(host_sink))     // what the caller runs beside it is not known here: as between two chunks
+            HIP_TRY(comm_copy(host_sink, c, (size_t)N * ctx->elt, (size_t)M, true, (hipStream_t)stream));
         else
             HIP_TRY(hipMemcpyAsync(host_sink, c, (size_t)M * N * ctx->elt, hipMemcpyDeviceToHost, (hipStream_t)stream));
     }

@@ -7,6 +7,7 @@
 
 #include <map>
 #include <mutex>
+#include <set>
 #include <string>
 
 struct dim3 { unsigned x, y, z; };
@@ -17,6 +18,7 @@ static std::string g_log;                       // one line per call: what, stre
 static std::map<const void *, std::string> &names() { static std::map<const void *, std::string> m; return m; }
 static size_t g_refuse;                         // hipMalloc of this many bytes fails
 static int g_last, g_launch_us;
+static std::set<const void *> g_pinned;
 static long g_handles = 0x100;
 struct Call { dim3 grid, block; size_t lds; stream_t s; };
 static thread_local Call t_call;
@@ -50,8 +52,8 @@ int hipMalloc(void **p, size_t n) {
     return 0;
 }
 int hipFree(void *p) { free(p); return 0; }
-int hipHostMalloc(void **p, size_t n, unsigned) { *p = aligned_alloc(4096, (n + 4095) / 4096 * 4096); return 0; }
-int hipHostFree(void *p) { free(p); return 0; }
+int hipHostMalloc(void **p, size_t n, unsigned) { *p = aligned_alloc(4096, (n + 4095) / 4096 * 4096); g_pinned.insert(*p); return 0; }
+int hipHostFree(void *p) { g_pinned.erase(p); free(p); return 0; }
 int hipMemset(void *p, int v, size_t n) { memset(p, v, n); note("memset", 0, std::to_string(n)); return 0; }
 int hipMemcpy(void *d, const void *s, size_t n, int) { memcpy(d, s, n); return 0; }
 int hipMemcpyAsync(void *, const void *, size_t n, int, stream_t s) { note("copy", s, std::to_string(n)); return 0; }
@@ -64,7 +66,12 @@ int hipDeviceGetAttribute(int *v, int, int) { *v = 256; return 0; }
 int hipDeviceSynchronize() { note("device_sync", 0, ""); return 0; }
 int hipFuncSetAttribute(const void *, int, int) { return 0; }
 int hipGetSymbolAddress(void **p, const void *) { static char array[64]; *p = array; return 0; }
-int hipPointerGetAttributes(void *, const void *) { return g_last = 1; }
+struct Attributes { int type, device; void *device_pointer, *host_pointer; };
+int hipPointerGetAttributes(Attributes *a, const void *p) {       // knows the start of a pinned allocation
+    if (!g_pinned.count(p)) return g_last = 1;
+    *a = Attributes{1, 0, (void *)p, (void *)p};
+    return 0;
+}
 int hipStreamCreateWithFlags(stream_t *s, unsigned) { *s = (stream_t)g_handles++; return 0; }
 int hipStreamDestroy(stream_t) { return 0; }
 int hipStreamSynchronize(stream_t) { return 0; }

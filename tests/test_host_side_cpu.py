@@ -93,3 +93,17 @@ with iso.Context(iso.make_cfg(256, 4, 4, 64, 64, "bf16", 256)) as ctx:
     order = ["sum" if "share_sum" in l[2] else "partial" for l in log() if l[0] == "kernel"]
     assert order == ["partial", "sum"] * 20, order
 """)
+
+
+def test_the_copy_behind_a_row_parallel_product_leaves_the_compute_units_alone(fake):
+    """The caller may run anything beside it: more than 1 MB goes by the copy engine, as between two chunks of a layer."""
+    run(fake, """
+with iso.Context(iso.make_cfg(256, 4, 4, 64, 64, "bf16", 256)) as ctx:
+    for M, how in ((32, "kernel"), (64, "kernel"), (65, "copy2d"), (128, "copy2d"), (384, "copy2d"), (512, "copy2d")):
+        a, w, c, sink = array(M, 64), array(8192, 64), array(M, 8192), iso.PinnedArray((M, 8192), "bf16")
+        log()
+        ctx.gemm_rowpar(a, w, c, M, 8192, 64, ctx.stream0, sink.ptr)
+        last = log()[-1]
+        assert last[0] == how and ("copy_out" in last[2]) == (how == "kernel"), (M, last)
+        sink.free()
+""")
