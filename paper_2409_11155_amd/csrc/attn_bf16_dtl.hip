@@ -529,8 +529,9 @@ __global__ __launch_bounds__(256 * KVS, KVS == 1 ? 2 : 1) void attn_bf16_dtl_ker
     }
     // A key that a row does not see has probability zero there, but 0 x infinity and 0 x NaN in the second product are NaN,
     // and a row whose scores all lie below the start of the running maximum has the sum zero: rows with a result that is not
-    // finite are computed again, from the keys they see.  (The test runs while the stores above are on their way.)
-    const uint64_t odd = __builtin_amdgcn_ballot_w64(probe != 0.f);
+    // finite are looked at again.  (The test runs while the stores above are on their way.)  Not where the sum is NaN: it comes
+    // from the scores of visible keys alone, so the row is NaN for good (every row of a model that diverged).
+    const uint64_t odd = __builtin_amdgcn_ballot_w64(probe != 0.f && l_tot == l_tot);
     uint32_t again = (uint32_t)odd | (uint32_t)(odd >> 32);      // bit = row of the wave; both halves hold dims of it
     if (again) {
         __builtin_amdgcn_s_waitcnt(0);                           // those stores come first
@@ -540,10 +541,20 @@ __global__ __launch_bounds__(256 * KVS, KVS == 1 ? 2 : 1) void attn_bf16_dtl_ker
         const void *kernarg = (const void *)__builtin_amdgcn_kernarg_segment_ptr();
         asm volatile("" : "+s"(kernarg));
         const AttnArgs &a = *(const AttnArgs *)kernarg;
-        const int head = blockIdx.y, slice = head / (a.nq / a.nkv) * D;
+        const int head = blockIdx.y, slice = head / (a.nq / a.nkv) * D, w0 = m0 + wave * 32;
         const float scale = 1.0f / sqrtf((float)D);
+        if (NP == 1) {
+            // What a row has from keys it sees stands; only rows above a key with such values are computed again, from the
+            // keys they see.  (With two terms per probability even a visible infinity may have become a NaN.)
+            const uint64_t zero = __builtin_amdgcn_ballot_w64(l_tot == 0.f);
+            int above = 0;                                       // rows of the wave above the last such key
+            if (attn_rows_not_finite<bf16_t, D>(a.v + slice, (size_t)a.nkv * D, a.q_offset + w0 + 1,
+                                                min(a.kv_len, a.q_offset + min(m0 + BM, a.Tc)), lane, &above))
+                above = min(32, above - (a.q_offset + w0));
+            again &= (uint32_t)zero | (uint32_t)((1ull << above) - 1);
+        }
         for (; again; again &= again - 1) {
-            const int i = m0 + wave * 32 + __builtin_ctz(again);
+            const int i = w0 + __builtin_ctz(again);
             const bf16_t *qp = a.q + (size_t)i * a.q_stride + (size_t)head * D;
             attn_row<bf16_t, D>([&](int e) { return (float)qp[e] * scale; }, a.k + slice, a.v + slice, (size_t)a.nkv * D,
                                 min(a.kv_len, a.q_offset + i + 1), a.out + ((size_t)i * a.nq + head) * D, lane);

@@ -133,8 +133,11 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(const float *__restri
             probe = fmaf(num[r], 0.f, probe);
         }
         // A key that a row does not see has probability zero there, but 0 x infinity and 0 x NaN in the second product are
-        // NaN: a row with a result that is not finite is computed again, from the keys it sees.
-        if (__builtin_amdgcn_ballot_w64(probe != 0.f) != 0) {
+        // NaN: a row with a result that is not finite, and such a key behind it, is computed again from the keys it sees --
+        // unless the sum of its probabilities, which come from visible keys alone, is NaN as well.
+        int at;
+        if (__builtin_amdgcn_ballot_w64(probe != 0.f && den == den) != 0 &&
+            attn_rows_not_finite<float, D>(Vc + (size_t)g * D, row, q_offset + i0 + q + 1, n_vis, lane, &at)) {
             __builtin_amdgcn_s_waitcnt(0);                           // the stores above come first
             const float *qp = Q + (size_t)(i0 + q) * q_stride + (size_t)h * D;
             attn_row<float, D>([&](int e) { return qp[e] * scale; }, Kc + (size_t)g * D, Vc + (size_t)g * D, row,

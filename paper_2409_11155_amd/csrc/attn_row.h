@@ -45,3 +45,18 @@ __device__ __forceinline__ void attn_row(Q &&q, const T *kc, const T *vc, size_t
 #pragma unroll
     for (int r = 0; r < PER; ++r) out[lane + 64 * r] = iso_from_f32<T>(o[r] * inv);
 }
+
+// Whether one of the rows [lo, hi) of a head's V slice holds an infinity or a NaN; *last = the last such row.
+template <typename T, int D>
+__device__ __forceinline__ bool attn_rows_not_finite(const T *vc, size_t stride, int lo, int hi, int lane, int *last) {
+    bool any = false;
+    for (int j = lo; j < hi; ++j) {
+        float probe = 0.f;
+#pragma unroll
+        for (int r = 0; r < D / 64; ++r) probe = fmaf(iso_to_f32(vc[(size_t)j * stride + lane + 64 * r]), 0.f, probe);
+        if (__builtin_amdgcn_ballot_w64(probe != 0.f) == 0) continue;
+        any = true;
+        *last = j;
+    }
+    return any;
+}
