@@ -196,6 +196,7 @@ def test_layer_with_chunk_0_rows_missing_from_the_cache_is_caught_by_the_poison(
         xd = dev(x, dt)
         kc.fill(NAN_BYTE)
         vc.fill(NAN_BYTE)
+        ctx.set_flags(iso.ISO_FLAG_KEEP_CUT)
         ctx.layer_prefill(wd, xd, kc, vc, T, split, iso.ISO_COMM_D2H, iso.ISO_SCHED_OVERLAP)
         ctx.sync()
         got = h64(xd.numpy(), dt)

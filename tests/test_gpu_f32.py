@@ -58,7 +58,7 @@ def test_rotary_step_and_cache_write_in_the_qkv_epilogue_f32(hidden, nq, nkv, d,
     with make_ctx(hidden, nq, nkv, d, ffn, "f32", T + 3) as ctx:
         got = []
         for flags in (0, iso.ISO_FLAG_NO_FUSE):
-            ctx.set_flags(flags)
+            ctx.set_flags(flags | iso.ISO_FLAG_KEEP_CUT)        # the second chunk rotates from q_offset = split on
             out, kc, vc = run_layer(ctx, iso.upload_weights(w, "f32"), x, "f32", T, split, nkv, d, T + 3, iso.ISO_COMM_D2H,
                                     poison=True)
             assert orc.max_rel_err(f64(out), ref["x_out"]) <= TOL_LAYER["f32"]

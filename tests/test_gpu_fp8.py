@@ -104,7 +104,7 @@ def test_small_bf16_layer_with_fp8_projections(hidden, nq, nkv, ffn, T, splits, 
     exact = orc.layer_unsplit(h64(x, dt), oracle_weights(w, dt), sh)
     with make_ctx(hidden, nq, nkv, d, ffn, dt, 320) as ctx:
         w_dev = ctx.add_fp8_weights(iso.upload_weights(w, dt))
-        ctx.set_flags(iso.ISO_FLAG_FP8_GEMM | sk)
+        ctx.set_flags(iso.ISO_FLAG_FP8_GEMM | iso.ISO_FLAG_KEEP_CUT | sk)
         for split in splits:
             xd = dev(x, dt)
             kc = iso.DeviceArray((320, nkv, d), dt, fill_byte=NAN_BYTE)
@@ -267,7 +267,7 @@ def test_two_layer_stack_with_fp8_projections():
         ref = orc.layer_unsplit(ref, oracle_weights(w, dt), sh, fp8=True)["x_out"]
     with make_ctx(hidden, nq, nkv, d, ffn, dt, 320) as ctx:
         layers_dev = [ctx.add_fp8_weights(iso.upload_weights(w, dt)) for w in layers]
-        ctx.set_flags(iso.ISO_FLAG_FP8_GEMM)
+        ctx.set_flags(iso.ISO_FLAG_FP8_GEMM | iso.ISO_FLAG_KEEP_CUT)
         outs = []
         for split in (0, 130):
             xd = dev(x, dt)

@@ -69,9 +69,10 @@ def dev(a, dt):
 
 
 def test_captured_gemm_of_stream_k_size_replays_correctly():
-    """512 x 5120 x 8192 is a shape the eager launch gives to the stream-K kernel (20 k-slices per team on 256
-    compute units), whose launches are numbered.  Recorded into a graph the product must take a launch that can be
-    replayed: three replays, the output cleared and the same stream-K workspace used by eager launches in between."""
+    """512 x 5120 x 8192 is a shape the whole-tile rule gives to the stream-K kernel (20 k-slices per team on 256
+    compute units), whose launches are numbered; the eager launches here are forced to it.  Recorded into a graph the
+    product must take a launch that can be replayed: three replays, the output cleared and the same stream-K workspace
+    used by eager launches in between."""
     dt, (M, N, K) = "bf16", (512, 5120, 8192)
     assert iso.gemm_launch_plan(M, N, K, 256)[0] == 6
     a = iso_inputs.randn((M, K), seed=5, dtype=dt)
@@ -84,12 +85,15 @@ def test_captured_gemm_of_stream_k_size_replays_correctly():
         ad, wd = dev(a, dt), dev(w, dt)
         other = dev(iso_inputs.randn((M, K), seed=7, dtype=dt), dt)      # a different product for the same workspace
         eager = iso.DeviceArray((M, N), dt, fill_byte=0)
+        ctx.set_flags(6 << 8)
         ctx.gemm_rowpar(ad, wd, eager, M, N, K, ctx.stream0)
         ctx.sync()
+        ctx.set_flags(0)                                               # recording: the rule's choice for a stream that records
         assert orc.max_rel_err(iso_inputs.to_f64(eager.numpy(), dt), ref) <= 1e-2
         out = iso.DeviceArray((M, N), dt, fill_byte=0xFF)
         g = Captured(rt, s0, lambda: ctx.gemm_rowpar(ad, wd, out, M, N, K, ctx.stream0))
         ctx.sync()
+        ctx.set_flags(6 << 8)
         first = None
         for rep in range(3):
             out.fill(0xFF)                                             # NaN pattern: a replay must write every element
@@ -117,6 +121,7 @@ def test_captured_iso_layer_replays_bit_identically_to_the_eager_step():
     rt = hip_runtime()
     cfg = iso.make_cfg(hidden, nq, nkv, d, ffn, dt, 320)
     with iso.Context(cfg) as ctx:
+        ctx.set_flags(iso.ISO_FLAG_KEEP_CUT)                           # 300 tokens would be one chunk otherwise
         w_dev = iso.upload_weights(w, dt)
         xd = dev(x, dt)
         kc = iso.DeviceArray((320, nkv, d), dt, fill_byte=0xFF)
@@ -128,6 +133,7 @@ def test_captured_iso_layer_replays_bit_identically_to_the_eager_step():
         g = Captured(rt, ctx.stream0.handle,
                      lambda: ctx.layer_prefill(w_dev, xd, kc, vc, T, split, iso.ISO_COMM_D2H, iso.ISO_SCHED_OVERLAP))
         ctx.sync()
+        assert g.nodes() >= 2 * 9                                      # two chunks of seven kernels and two copies at least
         for rep in range(3):
             xd.upload(x)
             kc.fill(0xFF)

@@ -38,8 +38,11 @@ def shape_of(hidden, nq, nkv, d, ffn, eps=1e-6, base=10000.0):
 
 
 def make_ctx(hidden, nq, nkv, d, ffn, dtype, max_seq, two_streams=True):
+    """A context that runs the cuts it is asked for (short prompts would be put together otherwise)."""
     cfg = iso.make_cfg(hidden, nq, nkv, d, ffn, dtype, max_seq)
-    return iso.Context(cfg, two_streams=two_streams)
+    ctx = iso.Context(cfg, two_streams=two_streams)
+    ctx.set_flags(iso.ISO_FLAG_KEEP_CUT)
+    return ctx
 
 
 # ------------------------------------------------------------------------------ element-wise steps
@@ -386,7 +389,7 @@ def test_small_bf16_layer_all_rows(flags, hidden, nq, nkv, ffn, T, splits):
     ref = orc.layer_unsplit(h64(x, dt), oracle_weights(w, dt), shape_of(hidden, nq, nkv, d, ffn))
     w_dev = iso.upload_weights(w, dt)
     with make_ctx(hidden, nq, nkv, d, ffn, dt, 320) as ctx:
-        ctx.set_flags(flags)
+        ctx.set_flags(flags | iso.ISO_FLAG_KEEP_CUT)
         for split in splits:
             out, kc, vc = run_layer(ctx, w_dev, x, dt, T, split, nkv, d, 320, iso.ISO_COMM_D2H, poison=True)
             err = orc.max_rel_err(f64(out), ref["x_out"])
@@ -413,7 +416,7 @@ def test_rotary_and_cache_write_in_the_qkv_epilogue_against_the_separate_kernel(
     with make_ctx(hidden, nq, nkv, d, ffn, dt, max_seq) as ctx:
         got = {}
         for name, flags in (("fused", variant), ("separate", variant | iso.ISO_FLAG_NO_FUSE)):
-            ctx.set_flags(flags)
+            ctx.set_flags(flags | iso.ISO_FLAG_KEEP_CUT)
             ctx.timing_enable(True)
             out, kc, vc = run_layer(ctx, w_dev, x, dt, T, split, nkv, d, max_seq, iso.ISO_COMM_D2H, poison=True)
             n_rope = ctx.timing_read()["rope_kv"][1]
@@ -517,7 +520,10 @@ def test_kv_event_orders_the_chunks_and_runs_are_bit_identical():
     with make_ctx(hidden, nq, nkv, d, ffn, dt, T) as ctx:
         first = None
         for _ in range(10):
+            ctx.timing_enable(True)
             out, _, _ = run_layer(ctx, w, x, dt, T, split, nkv, d, T, iso.ISO_COMM_D2H, poison=True)
+            assert ctx.timing_read()["attn"][1] == 2           # two chunks, or there is nothing to order
+            ctx.timing_enable(False)
             bits = out.numpy()
             assert not np.isnan(iso_inputs.bf16_bits_to_f32(bits)).any()
             if first is None:
