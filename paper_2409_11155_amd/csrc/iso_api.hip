@@ -322,8 +322,12 @@ hipError_t comm_copy(void *dst, const void *src, size_t pitch, size_t rows, bool
     const size_t bytes = pitch * rows, by_kernel = overlap ? 1u << 20 : 6u << 20;
     if (((uintptr_t)dst | (uintptr_t)src) % 16) return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
     if (bytes <= by_kernel || capturing(s)) return iso_launch_copy_out(dst, src, bytes, s);
-    if (pitch % 16) return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);   // rows the engine cannot take as one
-    return hipMemcpy2DAsync(dst, pitch, src, pitch, pitch, rows, hipMemcpyDeviceToHost, s);
+    // The engine moves rows of 512 bytes and more at the rate of the link (4 MB: 84 us; of 256 bytes 104, of 64 227, of 16 885),
+    // so narrow rows, which lie one behind the other, go several to a row.
+    size_t per = 1;
+    while (per * pitch < 512 || rows % per || per * pitch % 16)
+        if (++per * pitch > 1u << 15) return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
+    return hipMemcpy2DAsync(dst, per * pitch, src, per * pitch, per * pitch, rows / per, hipMemcpyDeviceToHost, s);
 }
 
 // Whether a kernel may store through this host pointer (pinned memory at the same address on the device).

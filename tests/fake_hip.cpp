@@ -57,7 +57,7 @@ int hipHostFree(void *p) { g_pinned.erase(p); free(p); return 0; }
 int hipMemset(void *p, int v, size_t n) { memset(p, v, n); note("memset", 0, std::to_string(n)); return 0; }
 int hipMemcpy(void *d, const void *s, size_t n, int) { memcpy(d, s, n); return 0; }
 int hipMemcpyAsync(void *, const void *, size_t n, int, stream_t s) { note("copy", s, std::to_string(n)); return 0; }
-int hipMemcpy2DAsync(void *, size_t, const void *, size_t, size_t w, size_t h, int, stream_t s) { note("copy2d", s, std::to_string(w * h)); return 0; }
+int hipMemcpy2DAsync(void *, size_t, const void *, size_t, size_t w, size_t h, int, stream_t s) { note("copy2d", s, std::to_string(w) + "x" + std::to_string(h)); return 0; }
 int hipGetLastError() { const int e = g_last; g_last = 0; return e; }
 const char *hipGetErrorString(int) { return "fake error"; }
 int hipGetDevice(int *d) { *d = 0; return 0; }

@@ -107,3 +107,24 @@ with iso.Context(iso.make_cfg(256, 4, 4, 64, 64, "bf16", 256)) as ctx:
         assert last[0] == how and ("copy_out" in last[2]) == (how == "kernel"), (M, last)
         sink.free()
 """)
+
+
+def test_the_copy_engine_gets_rows_of_at_least_512_bytes(fake):
+    """Narrow results: several rows of the matrix to one of the copy (all bytes, each once); a count of rows that nothing divides
+    goes by the plain copy."""
+    run(fake, """
+with iso.Context(iso.make_cfg(256, 4, 4, 64, 64, "bf16", 256)) as ctx:
+    for M, N, how in ((70000, 8, "copy2d"), (99999, 8, "copy2d"), (30000, 24, "copy2d"), (100003, 8, "copy"), (5000, 128, "copy2d"),
+                      (2050, 264, "copy2d"), (300003, 4, "copy"), (65537, 40, "copy"), (600, 32768, "copy2d")):
+        a, w, c, sink = array(M, 64), array(N, 64), array(M, N), iso.PinnedArray((M, N), "bf16")
+        log()
+        ctx.gemm_rowpar(a, w, c, M, N, 64, ctx.stream0, sink.ptr)
+        last = log()[-1]
+        assert last[0] == how, (M, N, last)
+        if how == "copy2d":
+            width, height = map(int, last[2].split("x"))
+            assert width * height == 2 * M * N and width >= 512 and width % 16 == 0, (M, N, last)
+        else:
+            assert int(last[2]) == 2 * M * N
+        sink.free()
+""")
