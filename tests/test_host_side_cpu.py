@@ -145,3 +145,14 @@ for dt, d, limit in (("f32", 64, 12), ("f32", 128, 32), ("bf16", 64, 12), ("bf16
                     (launch,) = log()
                     assert ("attn_simple" in launch[2]) == (keys <= limit and not flags), (dt, d, keys, Tc, off, kv, flags, launch)
 """)
+
+
+def test_products_of_a_single_k_slice_stay_with_the_whole_tile_rule(fake):
+    run(fake, """
+with iso.Context(iso.make_cfg(256, 4, 4, 64, 64, "bf16", 256)) as ctx:
+    a = array(64, 64)
+    for M, N, K, narrow in ((3, 32, 64, False), (86, 560, 64, False), (195, 168, 64, False), (65, 8, 128, True)):
+        log()
+        ctx.gemm_rowpar(a, a, a, M, N, K, ctx.stream0)
+        assert ("narrow" in log()[0][2]) == narrow, (M, N, K)
+""")
