@@ -484,8 +484,8 @@ iso_split_plan iso_gemm_split_plan(bool fp8, bool rope, int whole, int M, int N,
     double estimate = best;
     best *= shared ? 0.92 : 0.96;
     iso_split_plan plan{-1, 1, whole};
-    if (nk == 1) {       // a single slice is all start and epilogue, below what the fit resolves: the narrow epilogue loses (K = 64,
-        if (us_or_null) *us_or_null = estimate;      // 3 x 32 3.6 / 3.1 us, 86 x 560 4.1 / 3.6, 202 x 136 3.9 / 3.6)
+    if (nk == 1) {       // a single slice is all start and epilogue, below what the fit resolves: it would pick the 128 x 256 tile
+        if (us_or_null) *us_or_null = estimate;      // (K = 64: 3 x 32 3.6 / 3.1 us of the rule, 86 x 560 4.1 / 3.6, 202 x 136 3.9 / 3.6)
         return plan;
     }
     constexpr int SHARES[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 15};

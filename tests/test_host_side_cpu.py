@@ -151,8 +151,9 @@ def test_products_of_a_single_k_slice_stay_with_the_whole_tile_rule(fake):
     run(fake, """
 with iso.Context(iso.make_cfg(256, 4, 4, 64, 64, "bf16", 256)) as ctx:
     a = array(64, 64)
-    for M, N, K, narrow in ((3, 32, 64, False), (86, 560, 64, False), (195, 168, 64, False), (65, 8, 128, True)):
+    for M, N, K, kernel in ((3, 32, 64, "Li128ELi128ELi2"), (86, 560, 64, "Li128ELi128ELi2"), (195, 168, 64, "Li128ELi128ELi2"),
+                            (65, 8, 128, "gemm_narrow_kernel")):
         log()
         ctx.gemm_rowpar(a, a, a, M, N, K, ctx.stream0)
-        assert ("narrow" in log()[0][2]) == narrow, (M, N, K)
+        assert kernel in log()[0][2], (M, N, K)
 """)
