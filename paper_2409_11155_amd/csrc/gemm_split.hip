@@ -444,6 +444,9 @@ double stream_k_us(bool fp8, int M, int N, int nk, int ncu) {
     return k.start + k.slice * slices + k.fetch * teams / cols;
 }
 
+// What the operands' bytes take at least.
+double bytes_us(int M, int N, int nk) { return ((double)N * nk / 5.2e6 + (double)M * nk / 1e7) * ROW_BYTES; }
+
 double tile_us(const Tile &t, int M, int N, int nk, int S, int ncu, bool shared) {
     const double wgs = (double)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * S;
     const double slots = (double)ncu * t.per_cu, full = std::max(0.0, ceil(wgs / slots) - 1.0);
@@ -453,7 +456,7 @@ double tile_us(const Tile &t, int M, int N, int nk, int S, int ncu, bool shared)
     };
     double us = t.start + (full + 1.0) * t.round + slices * (full * slice(t.per_cu) + slice(load));
     if (shared) us = 0.3 * us + 0.7 * (t.start + wgs / slots * (t.round + slices * slice(t.per_cu)));
-    us = std::max(us, t.start + ((double)N * nk / 5.2e6 + (double)M * nk / 1e7) * ROW_BYTES);
+    us = std::max(us, t.start + bytes_us(M, N, nk));
     if (S > 1) us += t.sum0 + t.sum_mb * ((double)S * M * N * 4e-6);
     return us;
 }
@@ -489,11 +492,15 @@ iso_split_plan iso_gemm_split_plan(bool fp8, bool rope, int whole, int M, int N,
         return plan;
     }
     constexpr int SHARES[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 15};
+    const double floor_us = bytes_us(M, N, nk), mb = (double)M * N * 4e-6;
     for (int i = 0; i < n_tiles; ++i) {
         const Tile &t = tiles[i];
         for (int S : SHARES) {
-            if (t.kind < 0 ? S > 1 : ((t.kind >= 3 && S == 1) || S * 2 > nk)) continue;
+            if (t.kind >= 3 && S == 1) continue;
+            if (S > 1 && (t.kind < 0 || S * 2 > nk)) break;
             if ((S > 1 || (rope && t.kind >= 0)) && (size_t)S * M * N * 4 > ws_bytes) break;
+            // this and every larger number of shares costs at least so much (host time: this runs at every launch)
+            if (t.start + floor_us + (S > 1 ? t.sum0 + t.sum_mb * S * mb : 0.0) >= best) break;
             double us = tile_us(t, M, N, nk, S, ncu, shared);
             if (t.kind < 0) us += whole_extra(-t.kind);
             else if (rope && S == 1) us += t.sum0 + t.sum_mb * ((double)M * N * 4e-6);
