@@ -128,12 +128,29 @@ iso_sk_ws *sk_for(iso_ctx *ctx, hipStream_t s) {
 // by their stream.  That does not hold for a product recorded into a HIP graph: a replay may run on any stream, beside eager
 // products on this one.  Recorded calls of the stand-alone products (`layer` false) get none, they hold the caller's buffers only;
 // recorded layers, which hold the context's activations anyway and are replayed in order with its other layers, have workspaces
-// that eager products never touch.  (An extra chunk stream runs nothing but layers.)
+// that eager products never touch, allocated when the first one is recorded (none if that fails).  (An extra chunk stream runs
+// nothing but layers.)
+iso_sk_ws *recorded_ws(iso_ctx *ctx, int k) {
+    iso_sk_ws &ws = ctx->sk_rec[k];
+    const std::lock_guard<std::mutex> hold(ws.lock);
+    if (!ws.num_wg) {
+        ws.num_wg = ctx->sk[k].num_wg;
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;         // an allocation is not part of what is recorded
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (hipMalloc(&ws.base, iso_gemm_sk_ws_bytes(ws.num_wg)) != hipSuccess) {
+            ws.base = nullptr;
+            (void)hipGetLastError();
+        }
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+    return ws.base ? &ws : nullptr;
+}
+
 iso_sk_ws *split_ws_for(iso_ctx *ctx, hipStream_t s, bool layer = true) {
     for (int k = 0; k < ISO_MAX_CHUNKS; ++k)
         if (ctx->sk[k].base && s == (k < 2 ? ctx->stream[k] : ctx->xstream[k])) {
             if (!capturing(s)) return &ctx->sk[k];
-            return !layer ? nullptr : k < 2 ? &ctx->sk_rec[k] : &ctx->sk[k];
+            return !layer ? nullptr : k < 2 ? recorded_ws(ctx, k) : &ctx->sk[k];
         }
     return nullptr;
 }
@@ -887,9 +904,7 @@ int iso_create(iso_ctx **out, const iso_cfg *cfg, void *stream0, void *stream1) 
                 ctx->sk[i].num_wg = cus;
                 ctx->sk[i].epoch = 0;
                 ok = hip_ok(hipMalloc(&ctx->sk[i].base, bytes), "hipMalloc(stream-K workspace)") &&
-                     hip_ok(hipMemset(ctx->sk[i].base, 0, 4096), "hipMemset(stream-K flags)") &&
-                     hip_ok(hipMalloc(&ctx->sk_rec[i].base, bytes), "hipMalloc(workspace of recorded layers)");
-                ctx->sk_rec[i].num_wg = cus;
+                     hip_ok(hipMemset(ctx->sk[i].base, 0, 4096), "hipMemset(stream-K flags)");
             }
             if (!ok) break;
             // key-split attention workspaces: one per stream (both streams may run an attention launch at once)

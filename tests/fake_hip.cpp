@@ -17,7 +17,7 @@ static std::mutex g_lock;
 static std::string g_log;                       // one line per call: what, stream, detail
 static std::map<const void *, std::string> &names() { static std::map<const void *, std::string> m; return m; }
 static size_t g_refuse;                         // hipMalloc of this many bytes fails
-static int g_last, g_launch_us;
+static int g_last, g_launch_us, g_capturing;
 static std::set<const void *> g_pinned;
 static long g_handles = 0x100;
 struct Call { dim3 grid, block; size_t lds; stream_t s; };
@@ -31,6 +31,7 @@ static void note(const std::string &what, stream_t s, const std::string &detail)
 extern "C" {
 void fake_refuse(size_t bytes) { g_refuse = bytes; }
 void fake_launch_us(int us) { g_launch_us = us; }
+void fake_capturing(int on) { g_capturing = on; }
 const char *fake_log() { return g_log.c_str(); }
 void fake_clear() { g_log.clear(); }
 
@@ -75,7 +76,8 @@ int hipPointerGetAttributes(Attributes *a, const void *p) {       // knows the s
 int hipStreamCreateWithFlags(stream_t *s, unsigned) { *s = (stream_t)g_handles++; return 0; }
 int hipStreamDestroy(stream_t) { return 0; }
 int hipStreamSynchronize(stream_t) { return 0; }
-int hipStreamIsCapturing(stream_t, int *c) { *c = 0; return 0; }
+int hipStreamIsCapturing(stream_t, int *c) { *c = g_capturing; return 0; }
+int hipThreadExchangeStreamCaptureMode(int *) { return 0; }
 int hipStreamWaitEvent(stream_t s, void *e, unsigned) { note("wait", s, std::to_string((long)e)); return 0; }
 int hipEventCreate(void **e) { *e = (void *)g_handles++; return 0; }
 int hipEventCreateWithFlags(void **e, unsigned) { *e = (void *)g_handles++; return 0; }

@@ -38,9 +38,9 @@ def hip_runtime():
 class Captured:
     """Records what `enqueue()` puts on `stream` (and on the streams it forks to) into an executable graph."""
 
-    def __init__(self, rt, stream, enqueue):
+    def __init__(self, rt, stream, enqueue, mode=CAPTURE_RELAXED):
         self.rt, self.stream = rt, stream
-        assert rt.hipStreamBeginCapture(stream, CAPTURE_RELAXED) == 0
+        assert rt.hipStreamBeginCapture(stream, mode) == 0
         try:
             enqueue()
         finally:
@@ -109,7 +109,8 @@ def test_captured_gemm_of_stream_k_size_replays_correctly():
         g.destroy()
 
 
-def test_captured_iso_layer_replays_bit_identically_to_the_eager_step():
+@pytest.mark.parametrize("mode", [0, 1, CAPTURE_RELAXED])              # global, per thread, relaxed
+def test_captured_iso_layer_replays_bit_identically_to_the_eager_step(mode):
     """A two-chunk ISO step with both transfers (fork to the second stream, K/V event, two copies per chunk, join)
     recorded from stream0 and replayed three times on fresh inputs and NaN-filled caches."""
     dt, d = "bf16", 128
@@ -131,7 +132,7 @@ def test_captured_iso_layer_replays_bit_identically_to_the_eager_step():
         eager = xd.numpy().copy()
         assert orc.max_rel_err(iso_inputs.to_f64(eager, dt), ref) <= 2e-2
         g = Captured(rt, ctx.stream0.handle,
-                     lambda: ctx.layer_prefill(w_dev, xd, kc, vc, T, split, iso.ISO_COMM_D2H, iso.ISO_SCHED_OVERLAP))
+                     lambda: ctx.layer_prefill(w_dev, xd, kc, vc, T, split, iso.ISO_COMM_D2H, iso.ISO_SCHED_OVERLAP), mode)
         ctx.sync()
         assert g.nodes() >= 2 * 9                                      # two chunks of seven kernels and two copies at least
         for rep in range(3):

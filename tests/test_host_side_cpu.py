@@ -157,3 +157,34 @@ with iso.Context(iso.make_cfg(256, 4, 4, 64, 64, "bf16", 256)) as ctx:
         ctx.gemm_rowpar(a, a, a, M, N, K, ctx.stream0)
         assert kernel in log()[0][2], (M, N, K)
 """)
+
+
+def test_what_is_recorded_into_a_graph_keeps_out_of_the_eager_workspaces(fake):
+    """Recorded products are one kernel.  The first recorded layer allocates a workspace of its own and then runs the launches of
+    the eager one; if that allocation fails its products are not split."""
+    run(fake, f"""
+T, hidden, nq, nkv, d, ffn = 200, 512, 4, 1, 128, 768
+w = layer(hidden, nq, nkv, d, ffn)
+def kernels():
+    return [l[2] for l in log() if l[0] == "kernel"]
+for refuse in (0, {WORKSPACE}):
+    with iso.Context(iso.make_cfg(hidden, nq, nkv, d, ffn, "bf16", T)) as ctx:
+        x, k, v, a = array(T, hidden), array(T, nkv, d), array(T, nkv, d), array(64, 64)
+        prefill = lambda: ctx.layer_prefill(w, x, k, v, T, 0, iso.ISO_COMM_NONE, iso.ISO_SCHED_OVERLAP)
+        product = lambda: ctx.gemm_rowpar(a, a, a, 512, 5120, 8192, ctx.stream0)
+        log(); prefill(); eager = kernels()
+        assert any("share_sum" in n for n in eager)
+        product(); assert len(kernels()) == 2
+        fake.fake_capturing(1)
+        fake.fake_refuse(refuse)
+        product(); assert len(kernels()) == 1
+        for call in range(2):
+            prefill()
+            lines = log()
+            assert [l[2] for l in lines if l[0] == "malloc"] == ([] if refuse or call else ["{WORKSPACE}"])
+            assert sum(l[0] == "refused" for l in lines) == (1 if refuse and not call else 0)
+            recorded = [l[2] for l in lines if l[0] == "kernel"]
+            assert recorded == eager if not refuse else not any("share_sum" in n for n in recorded)
+        fake.fake_capturing(0)
+        fake.fake_refuse(0)
+""")
