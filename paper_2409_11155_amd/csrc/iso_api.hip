@@ -292,11 +292,12 @@ int attention(iso_ctx *ctx, const void *q, int q_stride, const void *kc, const v
     Timed t_(ctx, ISO_K_ATTN, s);
     hipError_t e;
     // Over a handful of keys the one-wave-per-row kernel is done before the others have filled their first tile.  Kernel times
-    // in us, it / the matrix-core kernel of the type, one row: fp32 heads of 64 over 1 key 2.9 / 4.0, over 16 4.5 / 4.1; fp32
-    // heads of 128 1 key 3.8 / 7.8, 32 7.2 / 8.2, 64 10.8 / 8.3; bf16 heads of 64 1 key 3.1 / 5.0, 16 4.7 / 5.0.  (bf16 heads of
-    // 128 stay where they were: 16 keys 5.7 / 6.1, 32 7.6 / 6.1.)  Not where a launch shape is forced.
+    // in us, it / the matrix-core kernel of the type, as many rows as keys: fp32 heads of 64 over 1 key 2.9 / 4.0, over 16 4.7 /
+    // 5.2, 32 6.3 / 5.3; fp32 heads of 128 1 key 3.8 / 7.8, 37 8.6 / 9.7, 64 12.1 / 9.6; bf16 heads of 64 1 key 3.1 / 5.0, 13 5.0 /
+    // 5.5, 16 5.2 / 5.0.  (bf16 heads of 128 stay where they were: 16 keys 6.6 / 6.3, 32 7.7 / 6.5.)  Not where a launch shape is
+    // forced.
     const long long keys = std::min((long long)kv_len, (long long)q_offset + Tc);
-    const bool few = !((ctx->flags >> 12) & 31) && keys <= (c.dtype == ISO_F32 ? (c.head_dim == 128 ? 32 : 12) : c.head_dim == 64 ? 12 : 0);
+    const bool few = !((ctx->flags >> 12) & 31) && keys <= (c.dtype == ISO_F32 ? (c.head_dim == 128 ? 40 : 16) : c.head_dim == 64 ? 14 : 0);
     const bool simple = few || (ctx->flags & ISO_FLAG_SIMPLE_ATTN);
     const bool mfma = c.dtype == ISO_BF16 && !simple;
     if (mfma && !(ctx->flags & ISO_FLAG_ATTN_STAGED) && iso_attn_bf16_dtl_supported(c.head_dim, kv_len, c.n_kv_heads))

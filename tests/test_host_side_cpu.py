@@ -131,12 +131,13 @@ with iso.Context(iso.make_cfg(256, 4, 4, 64, 64, "bf16", 256)) as ctx:
 
 
 def test_attention_over_a_handful_of_keys_takes_the_kernel_with_the_least_to_set_up(fake):
-    """Up to 12 visible keys (fp32 heads of 128: 32); bf16 heads of 128 and forced launch shapes keep the tiles."""
+    """fp32 up to 16 (heads of 64) or 40 visible keys, bf16 heads of 64 up to 14; bf16 heads of 128 and forced launch shapes keep
+    the tiles."""
     run(fake, """
-for dt, d, limit in (("f32", 64, 12), ("f32", 128, 32), ("bf16", 64, 12), ("bf16", 128, 0)):
+for dt, d, limit in (("f32", 64, 16), ("f32", 128, 40), ("bf16", 64, 14), ("bf16", 128, 0)):
     with iso.Context(iso.make_cfg(256, 4, 2, d, 64, dt, 256)) as ctx:
         q = array(64, 256, dt=dt)
-        for keys in (1, 12, 13, 32, 33, 64):
+        for keys in (1, 14, 15, 16, 17, 40, 41, 64):
             for Tc, off, kv in ((keys, 0, keys), (1, keys - 1, 200), (50, 30, keys)):
                 for flags in (0, 1 << 12, 2 << 14):
                     ctx.set_flags(flags)
