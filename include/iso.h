@@ -28,7 +28,8 @@
  *     heads of 64 holds the caller's buffers only and may be replayed on any stream, beside other
  *     work of the context.  A recorded layer or stack call holds the context's workspace, recorded
  *     attention with heads of 128 its scratch memory of that stream: replay those within the life of
- *     the context, ordered with its other layer calls or its other attention on that stream.
+ *     the context, ordered with its other layer calls or its other attention on that stream.  (The
+ *     first recorded layer call of a bf16 context allocates 64 MiB per stream for such replays.)
  */
 #ifndef ISO_H_
 #define ISO_H_
@@ -244,7 +245,7 @@ int iso_rope_kv_write(iso_ctx *ctx, void *qkv, void *k_cache, void *v_cache, int
 int iso_swiglu(iso_ctx *ctx, const void *gu, void *a, int T, void *stream);
 
 /* Kernel selection, for tests and measurement.  Default 0 = the matrix-core kernels wherever the dtype
- * and shapes allow.  The forced alternatives are complete HIP kernels as well (they are the fp32 path). */
+ * and shapes allow.  The forced alternatives are complete HIP kernels as well. */
 enum {
     ISO_FLAG_SIMPLE_GEMM = 1, /* SIMT tile GEMM instead of the MFMA GEMMs                  */
     ISO_FLAG_SIMPLE_ATTN = 2, /* one-wave-per-row attention instead of the MFMA attention  */

@@ -1,4 +1,4 @@
-// Chunk attention over the KV cache on the gfx950 matrix cores, pipelined variant (bf16, head_dim 128).
+// Chunk attention over the KV cache on the gfx950 matrix cores, pipelined variant (bf16, head_dim 128 or 64).
 // Local query row i of the chunk is token q_offset + i and sees keys j <= q_offset + i, j < kv_len
 // (paper Section 3.1: the second chunk reads the cache the first chunk wrote, plus its own causal block).
 //
@@ -6,7 +6,7 @@
 // softmax statistics are per-lane scalars and the probabilities feed the second product O^T = V^T P^T
 // straight from registers).  What differs is how K and V reach the matrix cores:
 //   * K and V tiles (64 keys x 128 dims) go global -> LDS directly (buffer_load ... lds) into two stages;
-//     the loads of tile j+1 are in flight while tile j is multiplied; one barrier per tile.  Rows that no row of
+//     the loads of tile j+1 are in flight while tile j is multiplied; one barrier per tile.  Keys that no row of
 //     the row block sees are out of the buffer's range and read as zero.
 //   * Both tiles keep their natural row-major layout; the 16-byte chunks of a row are XOR-swizzled on the
 //     global side (the LDS slot of a lane's 16 bytes is fixed by the lane number) so that the operand reads
@@ -92,8 +92,10 @@ __device__ __forceinline__ float half_swap_max(float v) {
 // the rows and puts the counter back to zero for the next launch.  Nobody waits for anybody.
 //
 // D = 64: the products of a head are half as long against the same number of exponentials, so the matrix pipe has room, and
-// the probabilities go into the second product as two bf16 terms each (value + remainder, 16 mantissa bits): this head size
-// then keeps the accuracy of the fp32 kernel it took before.
+// the probabilities go into the second product as two bf16 terms each (value + remainder, 16 to 17 mantissa bits).  Against 64
+// bits the result is as far off as that of the fp32 kernel before it, to six digits: 777 rows 1.59532e-3 both, 2048 over 8048 keys
+// 1.65792e-3, 32 rows 1.51869e-3 (the bf16 rounding of the output; nine sizes, the seventh digit is one higher).  A third term
+// gives the seventh digit back and costs 18 % of the launch at 777 rows and 27 % at 2048 over 8048 keys.
 template <int D, int NSTAGE, int KVS, bool SKEW>
 __global__ __launch_bounds__(256 * KVS, KVS == 1 ? 2 : 1) void attn_bf16_dtl_kernel(const bf16_t *__restrict__ Q,
                                                             const bf16_t *__restrict__ Kc,

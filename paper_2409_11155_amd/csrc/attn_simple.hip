@@ -1,6 +1,6 @@
 // Chunk attention over the KV cache, one wavefront per (query row, query head): online softmax over
-// 64-key slices, fp32 throughout.  This is the fp32 path of the small workload and the fallback for
-// shapes the MFMA kernel does not take.  (Chunk over the cache written by the earlier chunk: paper
+// 64-key slices, fp32 throughout.  It takes calls that see a handful of keys, caches too large for the
+// 32-bit offsets of the tiles with heads of 64, and whatever ISO_FLAG_SIMPLE_ATTN forces here.  (Chunk over the cache written by the earlier chunk: paper
 // Section 3.1; chunked prefill, Section 2.1.)
 #include "attn_row.h"
 

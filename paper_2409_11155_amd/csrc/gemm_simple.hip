@@ -1,6 +1,5 @@
 // Portable SIMT tile GEMM  c[M,N] = a[M,K] * w[N,K]^T  with fp32 accumulation, any M, N, K.
-// It is the fp32 path of the small workload and the fallback for bf16 shapes the MFMA kernel does not
-// take.  (Projections of the layer: paper Section 2.2.)
+// It is the fallback for fp32 and bf16 shapes and alignments that the MFMA kernels do not take.  (Projections of the layer: paper Section 2.2.)
 #include "iso_internal.h"
 
 namespace {

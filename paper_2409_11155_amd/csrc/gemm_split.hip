@@ -394,7 +394,8 @@ unsigned blocks_for(size_t units) { return (unsigned)((units + 255) / 256); }
 // round: slice(load) = slice + crowd * min(load, 1), and + pair * (pair0 + (1 - pair0) (load - 1)) when some units hold two.
 // A launch that shares the chip with the other chunk's (`shared`: two chunks computing side by side) leaves its last round's
 // idle units to that one, so there 0.7 of the price is the part of the chip it uses (measured over 60 split layers: 0 and 1
-// instead of 0.7 lose 5 and 2 %) and the switch has to promise 8 %.
+// instead of 0.7 lose 5 and 2 %) and the switch has to promise 8 %.  (A blend, not a model of the other launch: the QKV products
+// of a 4096-token 70B TP=8 prompt cut in half, 2048 x 1280 x 8192 each, are priced at 55 us and take 94 and 127 side by side.)
 // Never below the time of the weights' bytes from HBM.  Root mean square error 3-8 %; picking the fastest by these numbers
 // gives launches 1.5 % slower than the best measured one on average, 1.38x (bf16) / 1.30x (FP8) faster than the whole-tile
 // rule alone over that grid: 2.4-4x at up to 256 rows, 1.2-1.8x at 512-1024, a few per cent above.

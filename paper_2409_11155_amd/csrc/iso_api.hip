@@ -336,7 +336,10 @@ int sk_status(const iso_ctx *ctx) {
 // that: some HIP runtimes (the one inside PyTorch among them) run it as a shader with hundreds of workgroups as soon as
 // work is queued up, and the other chunk's kernels then stand still until it ends (2048-token 30B layer: its 8 us norm
 // takes 250 us beside a copy, the pass 2760 us; a copy kernel of a few workgroups still clogs the write path, 1570 us).
-// The two-dimensional copy always goes to a copy engine: 1220 us, and 4 layers of the 16k stack 61 -> 41 ms.
+// The two-dimensional copy always goes to a copy engine: 1220 us, and 4 layers of the 16k stack 44.7 -> 40.8 ms.  It shares that
+// engine with the driver: for some 60 ms after device memory was freed each such copy waits about 150 us for it (1024 rows of
+// 6672 bytes 129 -> 270 us, of 13312 bytes 248 -> 390), and a pass of the 30B layer that falls into that time takes 1760 us (plain
+// copies 1840), with FP8 products and int8 payload 1280 (1050); outside it, one pass at a time, 1220 (1260) and 745 (740).
 // Short payloads go by kernel, whose start and end are 10 us cheaper than the engine's.  Measured on the 70B TP=8 layer,
 // engine / kernel: beside another chunk, copies of 0.5 MB 334 / 325 us, 1 MB even, 2 MB 445 / 463, 4 MB 535 / 593;
 // with nothing beside it, 2 MB 340 / 317, 4 MB 406 / 390, 8 MB even, 33 MB 1627 / 1647.  A row-parallel product with its copy,
