@@ -172,7 +172,9 @@ const char *iso_last_error(void);         /* message for the calling thread's la
  * split    0 or T: one chunk on stream0.  1..T-1: two chunks [0,split) and [split,T).
  * comm     iso_comm; sched: iso_sched (ignored for one chunk).
  * On entry stream1 is made to wait for the work already in stream0; on return stream0 waits for
- * stream1, so the call behaves like one operation enqueued on stream0.
+ * stream1, so the call behaves like one operation enqueued on stream0.  Chunks that are computed
+ * together (see above) run on stream0 alone: stream1 is not touched then and neither waits for the
+ * other, which costs a short call as much as its kernels.  With ISO_FLAG_KEEP_CUT they always do.
  * Errors: NULL, ISO_ERR_WORKSPACE if T > max_seq, ISO_ERR_SPLIT, ISO_ERR_SHAPE if T < 1. */
 int iso_layer_prefill(iso_ctx *ctx, const iso_weights *w, void *x, void *k_cache, void *v_cache,
                       int T, int split, int comm, int sched);
