@@ -32,7 +32,10 @@ int fail(int code, const char *fmt, ...) {
 #define HIP_TRY(expr)                                                                              \
     do {                                                                                           \
         hipError_t e_ = (expr);                                                                    \
-        if (e_ != hipSuccess) return fail(ISO_ERR_HIP, "%s: %s", #expr, hipGetErrorString(e_));    \
+        if (e_ != hipSuccess) {                                                                    \
+            (void)hipGetLastError();   /* reported here, not once more by the next launch */       \
+            return fail(ISO_ERR_HIP, "%s: %s", #expr, hipGetErrorString(e_));                      \
+        }                                                                                          \
     } while (0)
 
 size_t elt_size(int dtype) { return dtype == ISO_F32 ? 4 : 2; }
@@ -124,12 +127,7 @@ iso_sk_ws *sk_for(iso_ctx *ctx, hipStream_t s) {
     return nullptr;
 }
 
-// Workspace of a split product on stream s (null, for a foreign stream: only unsplit plans).  Launches that share one are ordered
-// by their stream.  That does not hold for a product recorded into a HIP graph: a replay may run on any stream, beside eager
-// products on this one.  Recorded calls of the stand-alone products (`layer` false) get none, they hold the caller's buffers only;
-// recorded layers, which hold the context's activations anyway and are replayed in order with its other layers, have workspaces
-// that eager products never touch, allocated when the first one is recorded (none if that fails).  (An extra chunk stream runs
-// nothing but layers.)
+// Workspace of the layers recorded on the caller's stream k, allocated when the first one is (null if that fails).
 iso_sk_ws *recorded_ws(iso_ctx *ctx, int k) {
     iso_sk_ws &ws = ctx->sk_rec[k];
     const std::lock_guard<std::mutex> hold(ws.lock);
@@ -146,6 +144,11 @@ iso_sk_ws *recorded_ws(iso_ctx *ctx, int k) {
     return ws.base ? &ws : nullptr;
 }
 
+// Workspace of a split product on stream s (null, for a foreign stream: only unsplit plans).  Launches that share one are ordered
+// by their stream.  That does not hold for a product recorded into a HIP graph: a replay may run on any stream, beside eager
+// products on this one.  Recorded calls of the stand-alone products (`layer` false) get none, they hold the caller's buffers only;
+// recorded layers, which hold the context's activations anyway and are replayed in order with its other layers, have workspaces
+// that eager products never touch.  (An extra chunk stream runs nothing but layers.)
 iso_sk_ws *split_ws_for(iso_ctx *ctx, hipStream_t s, bool layer = true) {
     for (int k = 0; k < ISO_MAX_CHUNKS; ++k)
         if (ctx->sk[k].base && s == (k < 2 ? ctx->stream[k] : ctx->xstream[k])) {
@@ -864,6 +867,7 @@ int iso_create(iso_ctx **out, const iso_cfg *cfg, void *stream0, void *stream1) 
     const size_t table = (size_t)cfg->max_seq * half;
     int rc = ISO_OK;
     auto hip_ok = [&](hipError_t e, const char *what) {
+        if (e != hipSuccess) (void)hipGetLastError();
         if (e != hipSuccess && rc == ISO_OK) rc = fail(ISO_ERR_HIP, "%s: %s", what, hipGetErrorString(e));
         return e == hipSuccess;
     };

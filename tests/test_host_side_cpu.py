@@ -189,3 +189,23 @@ for refuse in (0, {WORKSPACE}):
         fake.fake_capturing(0)
         fake.fake_refuse(0)
 """)
+
+
+def test_an_error_that_was_reported_is_not_reported_again_by_the_next_launch(fake):
+    """The runtime keeps the last error until it is asked for, and every launch asks: a call that failed for lack of memory must
+    not make the next one fail (here the retry, whose extra stream then does without the key-split workspace)."""
+    run(fake, f"""
+T, hidden, nq, nkv, d, ffn = 300, 512, 4, 1, 128, 768
+w = layer(hidden, nq, nkv, d, ffn)
+with iso.Context(iso.make_cfg(hidden, nq, nkv, d, ffn, "bf16", T)) as ctx:
+    ctx.set_flags(iso.ISO_FLAG_KEEP_CUT)
+    x, k, v = array(T, hidden), array(1, T, nkv, d), array(1, T, nkv, d)
+    call = lambda: ctx.stack_prefill_chunks([w], x, k, v, T, [100, 200], iso.ISO_COMM_D2H, iso.ISO_SCHED_STREAM_PER_CHUNK)
+    fake.fake_refuse({512 * (16 * 256 * 16 + 256 * 8)})
+    try:
+        call()
+        raise SystemExit("the allocation was not refused")
+    except iso.IsoError as e:
+        assert e.code == iso.ISO_ERR_HIP
+    call()
+""")
