@@ -14,14 +14,14 @@ static __device__ __align__(256) unsigned char scratch[ISO_STATIC_SK_BYTES];
 
 namespace {
 
-constexpr int BK = Bf16Op<false>::KE;  // k elements per slice
+constexpr int BK = Bf16Op::KE;  // k elements per slice
 
-template <int BM, int BN, int WM, int WN, bool SWIGLU, bool PIPE, bool M16 = false>
+template <int BM, int BN, int WM, int WN, bool SWIGLU, bool PIPE>
 hipError_t launch(const void *a, const void *w, void *c, int M, int N, int K, hipStream_t s) {
     using Cfg = DtlCfg<BM, BN, WM, WN>;
     constexpr int LDS_BYTES = (PIPE && Cfg::W3) ? Cfg::LDS_BYTES_W3 : Cfg::LDS_BYTES;
     static iso_dev_mask lds_allowed{0};
-    auto kern = gemm_bf16_dtl_kernel<BM, BN, WM, WN, SWIGLU, PIPE, false, M16>;
+    auto kern = gemm_bf16_dtl_kernel<BM, BN, WM, WN, SWIGLU, PIPE, false>;
     if (hipError_t e = iso_allow_lds(reinterpret_cast<const void *>(kern), LDS_BYTES, &lds_allowed); e != hipSuccess)
         return e;
     const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
@@ -196,10 +196,8 @@ void iso_gemm_bf16_dtl_plan(int M, int N, int K, int num_wg, int *kind, int *tea
     *grid = G;
 }
 
-// variant: 0 = pick by shape; 1 = 256x256 8 waves (16x16x32 MFMAs: measured 6-8 % ahead of 32x32x16 on the launches
-//          that fill the chip, 2-6 % behind on the smaller tiles and in the stream-K launch, which keep 32x32x16),
-//          2 = 256x128 8 waves, 3 = 128x128 4 waves, 4 = 128x256 8 waves, 5 = 192x256 8 waves (16x16x32), 6 = 256x256
-//          stream-K; +8 selects the plain (non-interleaved) main loop, where the variant has one (not 5, 6).
+// variant: 0 = pick by shape; 1 = 256x256, 4 = 128x256, 5 = 192x256 (gemm_pp_kernel.h), 2 = 256x128 8 waves, 3 = 128x128
+//          4 waves, 6 = 256x256 stream-K; +8 selects the plain (non-interleaved) main loop of 1, 2 and 3.
 // sk may be null: then the stream-K kernel is not considered (variant 6 is an error).
 hipError_t iso_launch_gemm_bf16_dtl(const void *a, const void *w, void *c, int M, int N, int K, int variant,
                                     iso_sk_ws *sk, hipStream_t s) {
@@ -209,13 +207,13 @@ hipError_t iso_launch_gemm_bf16_dtl(const void *a, const void *w, void *c, int M
 #define ISO_DTL(BM_, BN_, WM_, WN_)                                                       \
     return plain ? launch<BM_, BN_, WM_, WN_, false, false>(a, w, c, M, N, K, s)          \
                  : launch<BM_, BN_, WM_, WN_, false, true>(a, w, c, M, N, K, s)
+    const iso_pp_args whole{a, w, nullptr, nullptr, c, nullptr, M, N, K, 1, {}};
     switch (v) {
-        case 1:   // the interleaved loop of the full-size tile issues its products as 16x16x32 MFMAs
-            return plain ? launch<256, 256, 4, 2, false, false>(a, w, c, M, N, K, s)
-                         : launch<256, 256, 4, 2, false, true, true>(a, w, c, M, N, K, s);
+        case 1:
+            return plain ? launch<256, 256, 4, 2, false, false>(a, w, c, M, N, K, s) : iso_launch_gemm_pp(256, ISO_PP_PLAIN, whole, s);
         case 2: ISO_DTL(256, 128, 4, 2);
-        case 4: ISO_DTL(128, 256, 2, 4);
-        case 5: return launch<192, 256, 2, 4, false, true, true>(a, w, c, M, N, K, s);
+        case 4: return iso_launch_gemm_pp(128, ISO_PP_PLAIN, whole, s);
+        case 5: return iso_launch_gemm_pp(192, ISO_PP_PLAIN, whole, s);
         case 6: return (sk && sk->base) ? launch_sk<false>(a, w, c, M, N, K, sk, s) : hipErrorInvalidValue;
         default: ISO_DTL(128, 128, 2, 2);
     }
@@ -230,31 +228,17 @@ int iso_gemm_bf16_dtl_resolve(int M, int N, int K, int variant, const iso_sk_ws 
     return ((variant >> 3) & 1) ? v + 8 : v;
 }
 
-// QKV projection with rotary embedding and KV-cache write in its epilogue (head_dim 128).  Only the variants whose
-// waves own 128 output columns take it: `resolved` must be 1 (256x256 tile per workgroup) or 6 (its stream-K launch),
-// as given by iso_gemm_bf16_dtl_resolve; anything else is hipErrorInvalidValue and the caller runs the plain
-// projection followed by the separate rotary kernel.
-hipError_t iso_launch_gemm_qkv_rope_bf16(const void *a, const void *w, void *qkv, int M, int N, int K, int resolved,
-                                         iso_sk_ws *sk, const float *cos_t, const float *sin_t, void *k_cache,
-                                         void *v_cache, int q_offset, int nq, int nkv, hipStream_t s) {
-    if (N != (nq + 2 * nkv) * 128 || (resolved != 1 && resolved != 6)) return hipErrorInvalidValue;
+// QKV projection with rotary embedding and KV-cache write in the epilogue of the stream-K launch, whose waves own 128 output
+// columns (head_dim 128; the whole tiles have theirs in gemm_pp_kernel.h).
+hipError_t iso_launch_gemm_qkv_rope_bf16_sk(const void *a, const void *w, void *qkv, int M, int N, int K, iso_sk_ws *sk,
+                                            const iso_rope_args &rp, hipStream_t s) {
+    if (rp.d != 128 || N != (rp.nq + 2 * rp.nkv) * 128 || !(sk && sk->base)) return hipErrorInvalidValue;
     using Cfg = DtlCfg<256, 256, 4, 2>;
     constexpr int LDS_BYTES = Cfg::W3 ? Cfg::LDS_BYTES_W3 : Cfg::LDS_BYTES;
-    const RopeArgs rope{cos_t, sin_t, (bf16_t *)k_cache, (bf16_t *)v_cache, q_offset, nq, nkv};
+    const RopeArgs rope{rp.cos_t, rp.sin_t, (bf16_t *)rp.k_cache, (bf16_t *)rp.v_cache, rp.q_offset, rp.nq, rp.nkv};
     const int tiles_m = (M + 255) / 256, tiles_n = (N + 255) / 256;
-    if (resolved == 1) {
-        static iso_dev_mask lds_allowed{0};
-        auto kern = gemm_bf16_dtl_kernel<256, 256, 4, 2, false, true, false, true, true>;
-        if (hipError_t e = iso_allow_lds(reinterpret_cast<const void *>(kern), LDS_BYTES, &lds_allowed); e != hipSuccess)
-            return e;
-        hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(Cfg::NT), LDS_BYTES, s, (const bf16_t *)a, (const bf16_t *)w,
-                           (bf16_t *)qkv, M, N, K, tiles_m, tiles_n, (unsigned char *)nullptr, 0u, (unsigned *)nullptr, 1, 0,
-                           rope);
-        return hipGetLastError();
-    }
-    if (!(sk && sk->base)) return hipErrorInvalidValue;
     static iso_dev_mask lds_allowed_sk{0};
-    auto kern = gemm_bf16_dtl_kernel<256, 256, 4, 2, false, true, true, false, true>;
+    auto kern = gemm_bf16_dtl_kernel<256, 256, 4, 2, false, true, true, true>;
     if (hipError_t e = iso_allow_lds(reinterpret_cast<const void *>(kern), LDS_BYTES, &lds_allowed_sk); e != hipSuccess)
         return e;
     int TS, G, grouped;
@@ -275,11 +259,12 @@ hipError_t iso_launch_gemm_swiglu_bf16(const void *a, const void *w, void *act, 
                                        iso_sk_ws *sk, hipStream_t s) {
     int v = variant & 7;
     if (v == 0) v = sk_wanted(M, 2 * F, K, sk) ? 6 : pick_variant(M, 2 * F);
+    const iso_pp_args whole{a, w, nullptr, nullptr, act, nullptr, M, 2 * F, K, 1, {}};
     switch (v) {
-        case 1: return launch<256, 256, 4, 2, true, true, true>(a, w, act, M, 2 * F, K, s);
+        case 1: return iso_launch_gemm_pp(256, ISO_PP_SWIGLU, whole, s);
         case 2: return launch<256, 128, 4, 2, true, true>(a, w, act, M, 2 * F, K, s);
-        case 4: return launch<128, 256, 2, 4, true, true>(a, w, act, M, 2 * F, K, s);
-        case 5: return launch<192, 256, 2, 4, true, true, true>(a, w, act, M, 2 * F, K, s);
+        case 4: return iso_launch_gemm_pp(128, ISO_PP_SWIGLU, whole, s);
+        case 5: return iso_launch_gemm_pp(192, ISO_PP_SWIGLU, whole, s);
         case 6: return (sk && sk->base) ? launch_sk<true>(a, w, act, M, 2 * F, K, sk, s) : hipErrorInvalidValue;
         default: return launch<128, 128, 2, 2, true, true>(a, w, act, M, 2 * F, K, s);
     }

@@ -13,10 +13,9 @@
 //     32 consecutive rows then spread over all 64 banks (measured: 0 bank conflicts).
 //   * Workgroup tile BM x BN (up to 256 x 256), two LDS stages (a third one for W where the LDS allows,
 //     so that weight slices are requested two slices ahead); WM x WN wavefronts, each
-//     owning a (BM/WM) x (BN/WN) block of MFMA tiles (bf16: 32x32x16, or 16x16x32 in the tile-per-workgroup launch of
-//     the 256x256 tile, which does more arithmetic per watt -- this chip runs into its power limit first; FP8:
-//     32x32x64, an operand fragment is then 32 bytes per lane = two 16-byte LDS reads).  The 8-wave shapes put two
-//     waves on every SIMD, which is what keeps the matrix pipe fed: a single wave cannot issue MFMAs back to back
+//     owning a (BM/WM) x (BN/WN) block of MFMA tiles (bf16: 32x32x16; FP8: 32x32x64, an operand fragment is then 32
+//     bytes per lane = two 16-byte LDS reads).  Whole tiles of 256 columns are the business of gemm_pp_kernel.h; this
+//     body has the 128-column tiles and the stream-K launch.  The 8-wave shapes put two waves on every SIMD, which is what keeps the matrix pipe fed: a single wave cannot issue MFMAs back to back
 //     without gaps (a register-only MFMA loop reaches ~82 % of peak with one wave per SIMD, ~99 % with two).
 //   * Operand fragments are double-buffered in registers, and the slice hand-over (wait for the next
 //     slice's loads, barrier, first fragment reads of the next slice, issue of the loads two slices ahead)
@@ -42,15 +41,13 @@ typedef int i32x4_t __attribute__((ext_vector_type(4)));
 typedef int i32x8_t __attribute__((ext_vector_type(8)));
 
 // ---- element traits: what differs between the bf16 and the FP8 projection ------------------------------------------
-// EB bytes per element; KE elements per k slice; MR rows / columns of one MFMA block; CPS 16-byte chunks of a row per
-// k-step of one MFMA (so a slice is 8 / CPS k-steps); RPF 16-byte LDS reads per operand fragment (lane l holds row
-// l % MR and chunks (l / MR) * RPF .. + RPF - 1 of the k-step); HS phases a k-step is worked off in (halves of the W
-// fragments, to bound the registers of the double-buffered fragments); SCALED: one fp32 scale per A row and per W row
-// multiplies the accumulators in the epilogue.
-template <bool M16> struct Bf16Op {      // v_mfma_f32_32x32x16_bf16, or 16x16x32 (more arithmetic per watt)
+// EB bytes per element; KE elements per k slice; CPS 16-byte chunks of a row per k-step of one 32x32 MFMA (so a slice is
+// 8 / CPS k-steps); RPF 16-byte LDS reads per operand fragment (lane l holds row l % 32 and chunks (l / 32) * RPF ..
+// + RPF - 1 of the k-step); SCALED: one fp32 scale per A row and per W row multiplies the accumulators in the epilogue.
+struct Bf16Op {                          // v_mfma_f32_32x32x16_bf16
     typedef bf16_t elem;
     typedef bf16x8_t frag_t;
-    static constexpr int EB = 2, KE = 64, MR = M16 ? 16 : 32, CPS = M16 ? 4 : 2, RPF = 1, HS = M16 ? 2 : 1;
+    static constexpr int EB = 2, KE = 64, CPS = 2, RPF = 1;
     static constexpr bool SCALED = false;
     static __device__ __forceinline__ frag_t load(const unsigned char *row, int c0, int sw) {
         return *reinterpret_cast<const frag_t *>(row + ((c0 ^ sw) << 4));
@@ -58,14 +55,11 @@ template <bool M16> struct Bf16Op {      // v_mfma_f32_32x32x16_bf16, or 16x16x3
     static __device__ __forceinline__ f32x16_t mfma32(frag_t a, frag_t b, f32x16_t c) {
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
     }
-    static __device__ __forceinline__ f32x4_t mfma16(frag_t a, frag_t b, f32x4_t c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-    }
 };
 struct Fp8Op {                           // v_mfma_f32_32x32x64_f8f6f4 on E4M3 x E4M3, no block scales
     typedef unsigned char elem;
     typedef i32x8_t frag_t;
-    static constexpr int EB = 1, KE = 128, MR = 32, CPS = 4, RPF = 2, HS = 1;
+    static constexpr int EB = 1, KE = 128, CPS = 4, RPF = 2;
     static constexpr bool SCALED = true;
     static __device__ __forceinline__ frag_t load(const unsigned char *row, int c0, int sw) {
         const i32x4_t lo = *reinterpret_cast<const i32x4_t *>(row + ((c0 ^ sw) << 4));
@@ -75,7 +69,6 @@ struct Fp8Op {                           // v_mfma_f32_32x32x64_f8f6f4 on E4M3 x
     static __device__ __forceinline__ f32x16_t mfma32(frag_t a, frag_t b, f32x16_t c) {
         return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, 0, 0, 0);
     }
-    static __device__ __forceinline__ f32x4_t mfma16(frag_t, frag_t, f32x4_t c) { return c; }   // not used
 };
 
 template <int BM, int BN, int WM, int WN> struct DtlCfg {
@@ -142,7 +135,6 @@ __device__ __forceinline__ void gemm_dtl_body(const typename OP::elem *__restric
                                               unsigned *sk_err, int sk_team, int sk_grouped, const RopeArgs &rope) {
 #if defined(__HIP_DEVICE_COMPILE__)   // the buffer-resource builtins exist in the device pass only
     using Cfg = DtlCfg<BM, BN, WM, WN>;
-    constexpr bool M16 = OP::MR == 16;
     constexpr int NWAVES = Cfg::NWAVES, A_BYTES = Cfg::A_BYTES, STAGE = Cfg::STAGE;
     constexpr int A_LOADS = Cfg::A_LOADS, W_LOADS = Cfg::W_LOADS, TM = Cfg::TM, TN = Cfg::TN;
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
@@ -216,12 +208,9 @@ __device__ __forceinline__ void gemm_dtl_body(const typename OP::elem *__restric
     };
 
     // ---- LDS side: byte offsets of this lane's operand rows; the k chunk is XOR-ed in per k-step.
-    // bf16, M16: the products are issued as v_mfma_f32_16x16x32_bf16 (k-steps of 32: lane l holds row l % 16 and the
-    // 16-byte chunk l / 16 of the step) instead of 32x32x16 (k-steps of 16: row l % 32, chunk l / 32).  Same LDS tiles,
-    // same bytes read per FLOP; the smaller instruction moves a quarter of the accumulator registers per issue and
-    // measured 15 % more arithmetic per watt on random data (register-only loops: 1.91 against 1.66 PFLOP/s).
+    // bf16: k-steps of 16, lane l holds row l % 32 and the 16-byte chunk l / 32 of the step.
     // FP8: 32x32x64, a k-step is 64 bytes of the row, lane l holds row l % 32 and chunks 2 (l / 32), + 1 of the step.
-    constexpr int MR = OP::MR;                              // rows / columns of one MFMA block
+    constexpr int MR = 32;                                  // rows / columns of one MFMA block
     constexpr int NKS = 8 / OP::CPS;                        // k-steps per slice
     constexpr int FM = Cfg::WTM / MR, FN = Cfg::WTN / MR;   // operand fragments per k-step
     const int frow = lane & (MR - 1), fgrp = lane / MR;
@@ -231,56 +220,29 @@ __device__ __forceinline__ void gemm_dtl_body(const typename OP::elem *__restric
     const int f_sw = swz(frow);
     const int a_row0 = (wm * Cfg::WTM + frow) * ROW_BYTES, w_row0 = W_ORIGIN + (wn * Cfg::WTN + frow) * ROW_BYTES;
 
-    // Accumulators: one f32x16 per 32x32 block of the wave tile.  M16 keeps the four 16x16 sub-blocks (si, sj) of a
-    // block in registers 4 * (2 si + sj) .. + 3 of that vector.
-    f32x16_t acc[TM][TN];
-    // A k-step is worked off in HS phases over the W fragments (M16: two halves of four, so that the double-buffered
-    // fragments take 64 registers instead of 96; 32x32x16: one).  Phase p = (k-step p / HS, half p % HS) reads its W
-    // fragments into wf[p & 1] and, in the first half of a k-step, the A fragments into af[k-step & 1].
-    constexpr int HS = OP::HS, FNH = FN / HS, NPH = NKS * HS;
-    static_assert(!M16 || PIPE, "the 16x16x32 path exists for the interleaved main loop");
-    static_assert(NKS % 2 == 0 && FN % HS == 0, "buffers alternate cleanly across slices");
-    typename OP::frag_t af[2][FM], wf[2][FNH];
-    auto read_phase = [&](const unsigned char *abase, const unsigned char *wbase, int ph) {
-        const int ks = ph / HS, h = ph % HS;
+    f32x16_t acc[TM][TN];                                   // one per 32x32 block of the wave tile
+    static_assert(NKS % 2 == 0, "buffers alternate cleanly across slices");
+    typename OP::frag_t af[2][FM], wf[2][FN];
+    auto read_phase = [&](const unsigned char *abase, const unsigned char *wbase, int ks) {
         const int c0 = ks * OP::CPS + fgrp * OP::RPF;      // first 16-byte chunk of this lane's part of the k-step
-        if (h == 0) {
-            const unsigned char *ap = abase + a_row0;
+        const unsigned char *ap = abase + a_row0, *wp = wbase + w_row0;
 #pragma unroll
-            for (int i = 0; i < FM; ++i) af[ks & 1][i] = OP::load(ap + i * MR * ROW_BYTES, c0, f_sw);
-        }
-        const unsigned char *wp = wbase + w_row0 + h * FNH * MR * ROW_BYTES;
+        for (int i = 0; i < FM; ++i) af[ks & 1][i] = OP::load(ap + i * MR * ROW_BYTES, c0, f_sw);
 #pragma unroll
-        for (int j = 0; j < FNH; ++j) wf[ph & 1][j] = OP::load(wp + j * MR * ROW_BYTES, c0, f_sw);
+        for (int j = 0; j < FN; ++j) wf[ks & 1][j] = OP::load(wp + j * MR * ROW_BYTES, c0, f_sw);
     };
-    auto mfma_phase = [&](int ph) {
-        const int ks = ph / HS, h = ph % HS;
-        if constexpr (M16) {
+    auto mfma_phase = [&](int ks) {
 #pragma unroll
-            for (int i = 0; i < FM; ++i)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int jj = 0; jj < FNH; ++jj) {
-                    const int j = h * FNH + jj;
-                    f32x16_t &blk = acc[i / 2][j / 2];
-                    const int q = 4 * (2 * (i & 1) + (j & 1));
-                    f32x4_t sub = {blk[q], blk[q + 1], blk[q + 2], blk[q + 3]};
-                    sub = OP::mfma16(af[ks & 1][i], wf[ph & 1][jj], sub);
-                    blk[q] = sub[0]; blk[q + 1] = sub[1]; blk[q + 2] = sub[2]; blk[q + 3] = sub[3];
-                }
-        } else {
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = OP::mfma32(af[ks & 1][i], wf[ph & 1][j], acc[i][j]);
-        }
+            for (int j = 0; j < TN; ++j)
+                acc[i][j] = OP::mfma32(af[ks & 1][i], wf[ks & 1][j], acc[i][j]);
     };
     // k-step forms for the plain loop (one phase per k-step there)
     auto read_frags = [&](const unsigned char *base, int buf, int ks) { (void)buf; read_phase(base, base, ks); };
     auto mfma_step = [&](int buf) { mfma_phase(buf); };
-    // Row and column, inside its 32x32 block, of accumulator register r of this lane.
-    auto blk_row = [&](int r) { return M16 ? 16 * (r / 8) + 4 * fgrp + (r % 4) : 8 * (r / 4) + 4 * fgrp + (r % 4); };
-    auto blk_col = [&](int r) { return M16 ? 16 * ((r / 4) & 1) + frow : frow; };
+    // Row, inside its 32x32 block, of accumulator register r of this lane (column: frow).
+    auto blk_row = [&](int r) { return 8 * (r / 4) + 4 * fgrp + (r % 4); };
 
     // ---- k slices [kb, ke) of the current tile into acc
     auto run = [&](int kb, int ke) {
@@ -323,7 +285,7 @@ __device__ __forceinline__ void gemm_dtl_body(const typename OP::elem *__restric
             // hand-over step, the direct-to-LDS loads two slices ahead) are slotted between the MFMAs, one
             // memory instruction per MFMA, so a wave's memory issue runs in the shadow of its own matrix
             // instructions instead of leaving the matrix pipe idle.
-            constexpr int NMFMA = FM * FNH, NREAD = OP::RPF * (FM + FNH), NLOAD = A_LOADS + W_LOADS;   // per phase (reads: at most)
+            constexpr int NMFMA = FM * FN, NREAD = OP::RPF * (FM + FN), NLOAD = A_LOADS + W_LOADS;   // per k-step
             auto weave = [&](bool with_loads) {
                 if constexpr (NREAD <= NMFMA) {      // fewer reads than MFMAs: one behind each, the loads behind the rest
 #pragma unroll
@@ -360,7 +322,7 @@ __device__ __forceinline__ void gemm_dtl_body(const typename OP::elem *__restric
                 const int wnx = wst + 1 == WS ? 0 : wst + 1;
                 const unsigned char *abase = lds + (kt & 1) * A_STRIDE, *wbase = lds + wst * W_STRIDE;
 #pragma unroll
-                for (int ph = 0; ph < NPH - 1; ++ph) {
+                for (int ph = 0; ph < NKS - 1; ++ph) {
                     read_phase(abase, wbase, ph + 1);
                     mfma_phase(ph);
                     weave(false);
@@ -380,7 +342,7 @@ __device__ __forceinline__ void gemm_dtl_body(const typename OP::elem *__restric
                         else issue_w(kt & 1, kb + kt + 2);
                     }
                 }
-                mfma_phase(NPH - 1);
+                mfma_phase(NKS - 1);
                 if (handover) weave(more);
                 __builtin_amdgcn_sched_barrier(0);
                 wst = wnx;
@@ -392,14 +354,13 @@ __device__ __forceinline__ void gemm_dtl_body(const typename OP::elem *__restric
     };
 
     // ---- epilogue.  Accumulator register r of lane l is row 8*(r/4) + 4*(l/32) + r%4, column l%32 of its
-    //      32x32 tile (16x16x32 path: row 16*(r/8) + 4*(l/16) + r%4, column 16*((r/4)%2) + l%16).  Each wave parks its tile as bf16 in its own LDS region, then streams it out in
+    //      32x32 tile.  Each wave parks its tile as bf16 in its own LDS region, then streams it out in
     //      16-byte pieces so that every store instruction covers whole 256-byte row segments.
     auto store_tile = [&]() {
         __syncthreads();                         // every wave is done reading operand tiles
         // SCALED: the accumulators are sums of products of quantised values; row scale x column scale restores them
         float sa_r[OP::SCALED ? TM : 1][16];
         if constexpr (OP::SCALED) {
-            static_assert(!OP::SCALED || OP::MR == 32, "a lane's accumulators share one column per 32x32 block");
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -434,7 +395,7 @@ __device__ __forceinline__ void gemm_dtl_body(const typename OP::elem *__restric
                     for (int r = 0; r < 16; ++r) {
                         float v = acc[i][j][r];
                         if constexpr (OP::SCALED) v *= sa_r[i][r] * swj;
-                        ct[(i * 32 + blk_row(r)) * Cfg::CP + j * 32 + blk_col(r)] = (bf16_t)v;
+                        ct[(i * 32 + blk_row(r)) * Cfg::CP + j * 32 + frow] = (bf16_t)v;
                     }
             }
             // only this wave reads what it wrote: LDS accesses of one wave are ordered, no barrier needed
@@ -509,7 +470,7 @@ __device__ __forceinline__ void gemm_dtl_body(const typename OP::elem *__restric
                             u *= sa_r[i][r] * swu;
                         }
                         const float a = g / (1.0f + __expf(-g)) * u;
-                        ct[(i * 32 + blk_row(r)) * HP + jp * 32 + blk_col(r)] = (bf16_t)a;
+                        ct[(i * 32 + blk_row(r)) * HP + jp * 32 + frow] = (bf16_t)a;
                     }
             }
             constexpr int CPR = HW / 8;
@@ -550,7 +511,7 @@ __device__ __forceinline__ void gemm_dtl_body(const typename OP::elem *__restric
                 for (int j = 0; j < TN; ++j)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
-                        const int gm = gm0 + i * 32 + blk_row(r), gn = gn0 + j * 32 + blk_col(r);
+                        const int gm = gm0 + i * 32 + blk_row(r), gn = gn0 + j * 32 + frow;
                         if (gm < M && gn < N) P[(size_t)gm * N + gn] = acc[i][j][r];
                     }
         } else {
@@ -678,7 +639,7 @@ __device__ __forceinline__ void gemm_dtl_body(const typename OP::elem *__restric
 }
 
 // The two kernels: the body above with the element traits bound.
-template <int BM, int BN, int WM, int WN, bool SWIGLU, bool PIPE, bool SK, bool M16 = false, bool ROPE = false>
+template <int BM, int BN, int WM, int WN, bool SWIGLU, bool PIPE, bool SK, bool ROPE = false>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_dtl_kernel(const bf16_t *__restrict__ A,
                                                                      const bf16_t *__restrict__ W,
                                                                      bf16_t *__restrict__ C, int M, int N, int K,
@@ -686,7 +647,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_dtl_kernel(const bf16_
                                                                      unsigned char *sk_ws, unsigned sk_epoch,
                                                                      unsigned *sk_err, int sk_team, int sk_grouped,
                                                                      RopeArgs rope) {
-    gemm_dtl_body<Bf16Op<M16>, BM, BN, WM, WN, SWIGLU, PIPE, SK, ROPE>(A, W, nullptr, nullptr, C, M, N, K, tiles_m, tiles_n,
+    gemm_dtl_body<Bf16Op, BM, BN, WM, WN, SWIGLU, PIPE, SK, ROPE>(A, W, nullptr, nullptr, C, M, N, K, tiles_m, tiles_n,
                                                                       sk_ws, sk_epoch, sk_err, sk_team, sk_grouped, rope);
 }
 

@@ -110,24 +110,27 @@ int iso_gemm_fp8_whole(int M, int N, int K, const iso_sk_ws *sk) {
     return (long long)((M + 255) / 256) * ((N + 255) / 256) >= 128 ? 1 : 3;
 }
 
-// variant: 1 or 3 as above, 5 = 192x256, 6 = stream-K; anything else leaves the choice to the rule.
+int iso_gemm_fp8_resolve(int M, int N, int K, int variant, const iso_sk_ws *sk) {
+    const int v = variant & 7;
+    return v == 1 || (v >= 3 && v <= 6) ? v : iso_gemm_fp8_whole(M, N, K, sk);
+}
+
+// variant: 1 or 3 as above, 4 = 128x256, 5 = 192x256, 6 = stream-K; anything else leaves the choice to the rule.
 hipError_t iso_launch_gemm_fp8(const void *a8, const float *sa, const void *w8, const float *sw, void *c, int M, int N,
                                int K, int variant, iso_sk_ws *sk, hipStream_t s) {
-    int v = variant & 7;
-    if (v != 1 && v != 3 && v != 5 && v != 6) v = iso_gemm_fp8_whole(M, N, K, sk);
+    const int v = iso_gemm_fp8_resolve(M, N, K, variant, sk);
     if (v == 6) return sk && sk->base ? launch_sk<false>(a8, w8, sa, sw, c, M, N, K, sk, s) : hipErrorInvalidValue;
-    if (v == 1) return launch<256, 256, 4, 2, false>(a8, w8, sa, sw, c, M, N, K, s);
-    if (v == 5) return launch<192, 256, 2, 4, false>(a8, w8, sa, sw, c, M, N, K, s);
-    return launch<128, 128, 2, 2, false>(a8, w8, sa, sw, c, M, N, K, s);
+    if (v == 3) return launch<128, 128, 2, 2, false>(a8, w8, sa, sw, c, M, N, K, s);
+    const iso_pp_args whole{a8, w8, sa, sw, c, nullptr, M, N, K, 1, {}};
+    return iso_launch_gemm_pp(v == 1 ? 256 : v == 4 ? 128 : 192, ISO_PP_PLAIN, whole, s);
 }
 
 // act[M, F] = silu(gate) * up with w8 = [gate; up] of shape [2F, K], sw of length 2F
 hipError_t iso_launch_gemm_swiglu_fp8(const void *a8, const float *sa, const void *w8, const float *sw, void *act, int M,
                                       int F, int K, int variant, iso_sk_ws *sk, hipStream_t s) {
-    int v = variant & 7;
-    if (v != 1 && v != 3 && v != 5 && v != 6) v = iso_gemm_fp8_whole(M, 2 * F, K, sk);
+    const int v = iso_gemm_fp8_resolve(M, 2 * F, K, variant, sk);
     if (v == 6) return sk && sk->base ? launch_sk<true>(a8, w8, sa, sw, act, M, 2 * F, K, sk, s) : hipErrorInvalidValue;
-    if (v == 1) return launch<256, 256, 4, 2, true>(a8, w8, sa, sw, act, M, 2 * F, K, s);
-    if (v == 5) return launch<192, 256, 2, 4, true>(a8, w8, sa, sw, act, M, 2 * F, K, s);
-    return launch<128, 128, 2, 2, true>(a8, w8, sa, sw, act, M, 2 * F, K, s);
+    if (v == 3) return launch<128, 128, 2, 2, true>(a8, w8, sa, sw, act, M, 2 * F, K, s);
+    const iso_pp_args whole{a8, w8, sa, sw, act, nullptr, M, 2 * F, K, 1, {}};
+    return iso_launch_gemm_pp(v == 1 ? 256 : v == 4 ? 128 : 192, ISO_PP_SWIGLU, whole, s);
 }

@@ -230,8 +230,7 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::OCC) void gemm_narrow_kernel(const ty
 #endif
 }
 
-// The shares of a whole-tile kernel (gemm_dtl_kernel.h): 128 x 128 (four waves, two workgroups per unit), 256 x 256 or
-// 192 x 256.
+// The shares of the 128 x 128 tile of gemm_dtl_kernel.h (four waves, two workgroups per unit).
 template <typename OP, int BM, int BN, int WM, int WN>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_share_kernel(const typename OP::elem *__restrict__ A,
                                                                   const typename OP::elem *__restrict__ W,
@@ -371,14 +370,9 @@ template <typename OP, int EPI> hipError_t launch_cfg(int cfg, const Operands &o
     }
     if constexpr (EPI == EPI_PARTIAL) {
         if (cfg == 3) return launch_share<OP, 128, 128, 2, 2>(o, S, s);
-        if (cfg == 4) {
-            if constexpr (OP::SCALED) return launch_share<OP, 256, 256, 4, 2>(o, S, s);
-            else return launch_share<Bf16Op<true>, 256, 256, 4, 2>(o, S, s);
-        }
-        if (cfg == 5) {
-            if constexpr (OP::SCALED) return launch_share<OP, 192, 256, 2, 4>(o, S, s);
-            else return launch_share<Bf16Op<true>, 192, 256, 2, 4>(o, S, s);
-        }
+        if (cfg >= 4 && cfg <= 6)
+            return iso_launch_gemm_pp(cfg == 4 ? 256 : cfg == 5 ? 192 : 128, ISO_PP_SHARE,
+                                      iso_pp_args{o.a, o.w, o.sa, o.sw, nullptr, o.p, o.M, o.N, o.K, S, {}}, s);
     }
     return hipErrorInvalidValue;
 }
@@ -399,37 +393,41 @@ unsigned blocks_for(size_t units) { return (unsigned)((units + 255) / 256); }
 // Never below the time of the weights' bytes from HBM.  Root mean square error 3-8 %; picking the fastest by these numbers
 // gives launches 1.5 % slower than the best measured one on average, 1.38x (bf16) / 1.30x (FP8) faster than the whole-tile
 // rule alone over that grid: 2.4-4x at up to 256 rows, 1.2-1.8x at 512-1024, a few per cent above.
-// The 192 x 256 tile (whole, or its k range in shares) is for row counts that 256-row tiles fit badly or that leave units
-// idle: a round of it costs 0.81 of a 256 x 256 one for 0.75 of the arithmetic.  Whole, against the best of the others:
-// 1500 x 8192 x 3584 76.2 -> 69.3 us, 777 x 11264 x 2048 43.9 -> 38.6, 1900 x 4992 x 6656 128.9 -> 111.8, 3000 x 8192 x 2048
-// 95.9 -> 84.8; behind where 256 rows fill their rounds (2048 x 8192 x 3584 89.2 / 127.8).  In shares: 333 x 7168 x 8192
-// 56.9 -> 53.6, 1500 x 2048 x 5632 47.5 -> 43.9.  (A 256 x 128 tile in shares was the fastest in 5 of 288 shapes, by 2 %.)
+// The 256-column tiles (kinds 4 to 6, -1, -4, -5; gemm_pp_kernel.h) were fitted to 12 row counts from 64 to 8192 of the same 16
+// matrices; the fastest by these numbers is 1.0 % (bf16) and 1.0 % (FP8) slower than the best measured launch on average.  192 and
+// 128 rows are for row counts that 256 fit badly or that leave units idle: 1500 x 8192 x 3584 73.8 us with 256 rows, 65.5 with 192;
+// 8192 x 2560 x 8192 300 / 250; 1024 x 8960 x 6656 125 / 101; 777 x 7168 x 8192 123 / 105, with 128 rows 96.  Stream-K was the fastest
+// of all launches in 1 of 192 bf16 products (2048 x 8960 x 6656, 198 / 209) and in no FP8 one.  The 128-row shares carry 1.5 us that
+// the fit does not show and a layer of 200 tokens does (gate/up 138.3 / 136.5 us a pass against 256 rows in eight shares).
 struct Tile {
-    int bm, bn, per_cu, kind;    // kind: tile of this file (0 .. 5), or -v: variant v of the whole-tile kernel, one share
+    int bm, bn, per_cu, kind;    // kind: tile in shares (0 .. 6), or -v: variant v of the whole-tile kernels, one share
     double start, round, slice, crowd, pair, pair0, sum0, sum_mb;
 };
 constexpr Tile TILES_BF16[] = {
     {32, 64, 2, 0, 3.5, 0.0, 0.175, 0.042, 0.205, 0.61, 2.1, 0.54},
     {64, 64, 2, 1, 3.9, 0.0, 0.223, 0.043, 0.208, 0.95, 2.1, 0.51},
-    {128, 64, 2, 2, 3.8, 0.9, 0.299, 0.115, 0.312, 0.79, 2.1, 0.41},
+    {128, 64, 2, 2, 4.2, 0.0, 0.261, 0.111, 0.323, 0.79, 2.6, 0.48},
     {128, 128, 2, 3, 6.9, 0.0, 0.458, 0.093, 0.414, 0.64, 1.0, 0.32},
-    {256, 256, 1, 4, 4.1, 4.3, 1.048, 0.423, 0.0, 0.0, 1.3, 0.23},
-    {256, 256, 1, -1, 2.5, 6.2, 0.988, 0.453, 0.0, 0.0, 0.0, 0.0},
     {128, 128, 2, -3, 2.3, 1.6, 0.444, 0.128, 0.387, 0.67, 0.0, 0.0},
-    {128, 256, 1, -4, 0.8, 2.7, 0.668, 0.265, 0.0, 0.0, 0.0, 0.0},
-    {192, 256, 1, 5, 3.9, 4.1, 0.792, 0.440, 0.0, 0.0, 1.3, 0.20},
-    {192, 256, 1, -5, 2.0, 4.4, 0.805, 0.353, 0.0, 0.0, 0.0, 0.0},
+    {256, 256, 1, 4, 0.0, 7.4, 0.731, 0.527, 0.0, 0.0, 4.5, 0.24},
+    {192, 256, 1, 5, 0.0, 5.4, 0.617, 0.411, 0.0, 0.0, 5.9, 0.21},
+    {128, 256, 1, 6, 0.0, 1.5, 0.631, 0.167, 0.0, 0.0, 9.1, 0.27},
+    {256, 256, 1, -1, 0.0, 6.4, 0.872, 0.441, 0.0, 0.0, 0.0, 0.0},
+    {192, 256, 1, -5, 0.0, 5.3, 0.733, 0.283, 0.0, 0.0, 0.0, 0.0},
+    {128, 256, 1, -4, 0.0, 2.9, 0.658, 0.186, 0.0, 0.0, 0.0, 0.0},
 };
 constexpr Tile TILES_FP8[] = {
     {32, 64, 2, 0, 2.4, 1.8, 0.150, 0.049, 0.133, 1.0, 3.0, 0.27},
     {64, 64, 2, 1, 2.3, 2.0, 0.187, 0.051, 0.191, 1.0, 2.9, 0.32},
     {128, 64, 2, 2, 3.8, 1.1, 0.278, 0.088, 0.275, 0.94, 2.2, 0.37},
     {128, 128, 2, 3, 2.9, 2.6, 0.353, 0.284, 0.224, 0.74, 3.2, 0.26},
-    {256, 256, 1, 4, 5.3, 5.0, 0.921, 0.394, 0.0, 0.0, 0.0, 0.23},
-    {256, 256, 1, -1, 1.7, 8.2, 0.838, 0.623, 0.0, 0.0, 0.0, 0.0},
     {128, 128, 2, -3, 2.4, 1.9, 0.497, 0.131, 0.345, 0.47, 0.0, 0.0},
-    {192, 256, 1, 5, 5.3, 3.3, 0.700, 0.370, 0.0, 0.0, 0.0, 0.24},
-    {192, 256, 1, -5, 2.1, 5.5, 0.646, 0.630, 0.0, 0.0, 0.0, 0.0},
+    {256, 256, 1, 4, 0.0, 5.0, 0.756, 0.315, 0.0, 0.0, 6.9, 0.27},
+    {192, 256, 1, 5, 0.0, 3.4, 0.598, 0.293, 0.0, 0.0, 7.5, 0.27},
+    {128, 256, 1, 6, 0.0, 1.6, 0.494, 0.252, 0.0, 0.0, 9.5, 0.28},
+    {256, 256, 1, -1, 0.0, 7.4, 0.832, 0.443, 0.0, 0.0, 0.0, 0.0},
+    {192, 256, 1, -5, 0.1, 6.0, 0.663, 0.311, 0.0, 0.0, 0.0, 0.0},
+    {128, 256, 1, -4, 0.1, 4.2, 0.546, 0.270, 0.0, 0.0, 0.0, 0.0},
 };
 // Stream-K by team size 1, 2, 4, 8: start + slice * k-slices of a team + fetch * teams per tile column.
 struct StreamK {
@@ -465,28 +463,27 @@ double tile_us(const Tile &t, int M, int N, int nk, int S, int ncu, bool shared)
 }  // namespace
 
 bool iso_gemm_split_supported(bool fp8, int M, int N, int K) {
-    const int ke = fp8 ? Fp8Op::KE : Bf16Op<false>::KE;
+    const int ke = fp8 ? Fp8Op::KE : Bf16Op::KE;
     return M >= 1 && N >= 8 && (N % 8) == 0 && K >= ke && (K % ke) == 0 && (long long)M * K < (1ll << 31) &&
            (long long)N * K < (1ll << 31) && (long long)M * (N / 8) < (1ll << 31) - 256;
 }
 
-// `whole` is the whole-tile rule's own choice (variant 1, 3, 4, 5 or 6 = stream-K).  It stays unless something else is
-// estimated at least 4 % faster (8 % beside another chunk).  ws_bytes: room for partial sums (0: one share only).  `rope`: the QKV projection, where
-// only variants 1 and 6 and the tiles of this file (through their second kernel) finish with the rotary step; the others
-// need a kernel more (about 5 us).  *us_or_null: the estimate for the plan returned.
+// `whole` is the whole-tile rule's own choice (variant 1, 3, 4, 5 or 6 = stream-K).  It stays unless something else is estimated
+// faster (by 8 % beside another chunk).  ws_bytes: room for partial sums (0: one share only).  `rope`: the QKV projection; tiles
+// of 256 columns and shares (through their second kernel) finish with the rotary step, the others need a kernel more (5 us).
+// *us_or_null: the estimate for the plan returned.
 iso_split_plan iso_gemm_split_plan(bool fp8, bool rope, int whole, int M, int N, int K, size_t ws_bytes, int ncu, bool shared,
                                    double *us_or_null) {
-    const int nk = K / (fp8 ? Fp8Op::KE : Bf16Op<false>::KE);
+    const int nk = K / (fp8 ? Fp8Op::KE : Bf16Op::KE);
     const Tile *tiles = fp8 ? TILES_FP8 : TILES_BF16;
     const int n_tiles = fp8 ? (int)(sizeof(TILES_FP8) / sizeof(Tile)) : (int)(sizeof(TILES_BF16) / sizeof(Tile));
-    const double extra = rope && fp8 ? 5.0 : 0.0;
-    auto whole_extra = [&](int v) { return rope && !fp8 && v != 1 && v != 6 ? 5.0 : extra; };
+    auto whole_extra = [&](int v) { return rope && (v == 2 || v == 3 || (v == 6 && fp8)) ? 5.0 : 0.0; };
     double best = 1e30;
-    if (whole == 6) best = stream_k_us(fp8, M, N, nk, ncu) + extra;
+    if (whole == 6) best = stream_k_us(fp8, M, N, nk, ncu) + whole_extra(6);
     for (int i = 0; i < n_tiles; ++i)
         if (tiles[i].kind == -whole) best = tile_us(tiles[i], M, N, nk, 1, ncu, shared) + whole_extra(whole);
     double estimate = best;
-    best *= shared ? 0.92 : 0.96;
+    if (shared) best *= 0.92;
     iso_split_plan plan{-1, 1, whole};
     if (nk == 1) {       // a single slice is all start and epilogue, below what the fit resolves: it would pick the 128 x 256 tile
         if (us_or_null) *us_or_null = estimate;      // (K = 64: 3 x 32 3.6 / 3.1 us of the rule, 86 x 560 4.1 / 3.6, 202 x 136 3.9 / 3.6)
@@ -522,10 +519,10 @@ hipError_t iso_launch_gemm_split(const iso_split_plan &plan, const void *a, cons
     if (plan.shares > 1 && !p) return hipErrorInvalidValue;
     const Operands o{a, w, sa, sw, c, p, M, N, K};
     if (plan.shares == 1)
-        return fp8 ? launch_cfg<Fp8Op, EPI_BF16>(plan.tile, o, 1, s) : launch_cfg<Bf16Op<false>, EPI_BF16>(plan.tile, o, 1, s);
+        return fp8 ? launch_cfg<Fp8Op, EPI_BF16>(plan.tile, o, 1, s) : launch_cfg<Bf16Op, EPI_BF16>(plan.tile, o, 1, s);
     const std::lock_guard<std::mutex> hold(ws->lock);
     hipError_t e = fp8 ? launch_cfg<Fp8Op, EPI_PARTIAL>(plan.tile, o, plan.shares, s)
-                       : launch_cfg<Bf16Op<false>, EPI_PARTIAL>(plan.tile, o, plan.shares, s);
+                       : launch_cfg<Bf16Op, EPI_PARTIAL>(plan.tile, o, plan.shares, s);
     if (e != hipSuccess) return e;
     const Shares sh{p, (size_t)M * N, plan.shares, sa, sw};
     hipLaunchKernelGGL(share_sum_kernel, dim3(blocks_for((size_t)M * (N / 8))), dim3(256), 0, s, sh, (bf16_t *)c, M, N);
@@ -539,10 +536,10 @@ hipError_t iso_launch_gemm_split_swiglu(const iso_split_plan &plan, const void *
     if (plan.shares > 1 && !p) return hipErrorInvalidValue;
     const Operands o{a, w, sa, sw, act, p, M, 2 * F, K};
     if (plan.shares == 1)
-        return fp8 ? launch_cfg<Fp8Op, EPI_SWIGLU>(plan.tile, o, 1, s) : launch_cfg<Bf16Op<false>, EPI_SWIGLU>(plan.tile, o, 1, s);
+        return fp8 ? launch_cfg<Fp8Op, EPI_SWIGLU>(plan.tile, o, 1, s) : launch_cfg<Bf16Op, EPI_SWIGLU>(plan.tile, o, 1, s);
     const std::lock_guard<std::mutex> hold(ws->lock);
     hipError_t e = fp8 ? launch_cfg<Fp8Op, EPI_PARTIAL>(plan.tile, o, plan.shares, s)
-                       : launch_cfg<Bf16Op<false>, EPI_PARTIAL>(plan.tile, o, plan.shares, s);
+                       : launch_cfg<Bf16Op, EPI_PARTIAL>(plan.tile, o, plan.shares, s);
     if (e != hipSuccess) return e;
     const Shares sh{p, (size_t)M * 2 * F, plan.shares, sa, sw};
     hipLaunchKernelGGL(share_sum_swiglu_kernel, dim3(blocks_for((size_t)M * (F / 8))), dim3(256), 0, s, sh, (bf16_t *)act, M, F);
@@ -557,7 +554,7 @@ hipError_t iso_launch_gemm_split_rope(const iso_split_plan &plan, const void *a,
     const Operands o{a, w, sa, sw, nullptr, p, M, N, K};
     const std::lock_guard<std::mutex> hold(ws->lock);
     hipError_t e = sa ? launch_cfg<Fp8Op, EPI_PARTIAL>(plan.tile, o, plan.shares, s)
-                      : launch_cfg<Bf16Op<false>, EPI_PARTIAL>(plan.tile, o, plan.shares, s);
+                      : launch_cfg<Bf16Op, EPI_PARTIAL>(plan.tile, o, plan.shares, s);
     if (e != hipSuccess) return e;
     const Shares sh{p, (size_t)M * N, plan.shares, sa, sw};
     const RopeArgs rope{cos_t, sin_t, (bf16_t *)k_cache, (bf16_t *)v_cache, q_offset, nq, nkv};

@@ -167,7 +167,7 @@ iso_split_plan plan_gemm(iso_ctx *ctx, bool fp8, bool rope, int M, int N, int K,
     const iso_sk_ws *ws = split_ws_for(ctx, s, layer);
     const size_t bytes = ws ? (size_t)ws->num_wg * iso_gemm_sk_slot_bytes() : 0;
     if (forced == 7) {       // tests, measurement: bits 17..20 shares, 21..23 tile
-        iso_split_plan p{std::min(5, (ctx->flags >> 21) & 7), std::max(1, (ctx->flags >> 17) & 15), 0};
+        iso_split_plan p{std::min(6, (ctx->flags >> 21) & 7), std::max(1, (ctx->flags >> 17) & 15), 0};
         p.shares = std::min(p.shares, K / (fp8 ? 128 : 64));
         if (p.tile > 2 && p.shares < 2) return whole;          // one share of a whole tile: the whole-tile kernels
         if ((p.shares > 1 || rope) && (size_t)p.shares * M * N * 4 > bytes) return whole;
@@ -447,29 +447,35 @@ int attn_block_head(iso_ctx *ctx, const iso_weights *w, void *x, void *kc, void 
                                             c.n_kv_heads, c.head_dim, ck.s), "qkv+rope");
         return ISO_OK;
     }
-    // bf16 layers with head_dim 128: rotary embedding and KV-cache write ride in the projection's epilogue whenever
-    // the launch rule picks a kernel whose waves own whole heads (the 256-wide tile or its stream-K launch)
-    const bool dtl = c.dtype == ISO_BF16 && c.head_dim == 128 && !fp8_qkv &&
-                     !(ctx->flags & (ISO_FLAG_SIMPLE_GEMM | ISO_FLAG_GEMM_STAGED | ISO_FLAG_NO_FUSE)) &&
-                     iso_gemm_bf16_dtl_supported(ck.n, NQKV, H);
-    if (dtl) {
-        const int segs = (ctx->gemm_segments > 1 && ck.n >= 256 * ctx->gemm_segments) ? ctx->gemm_segments : 1;
-        const int per = ((ck.n + segs - 1) / segs + 255) / 256 * 256;
-        bool all_fusable = true;                    // every segment must resolve to a head-owning variant
-        for (int lo = 0; lo < ck.n; lo += per) {
-            const int n = std::min(per, ck.n - lo);
-            const iso_split_plan p = plan_gemm(ctx, false, true, n, NQKV, H, ck.s);
-            const int v = p.tile >= 0 ? 0 : iso_gemm_bf16_dtl_resolve(n, NQKV, H, p.whole, sk_for(ctx, ck.s));
-            all_fusable = all_fusable && (v == 1 || v == 6);
-        }
+    // bf16 layers: rotary embedding and KV-cache write ride in the projection's epilogue whenever the launch rule picks, for every
+    // segment, a kernel that holds whole heads (the 256-column tiles; bf16 and heads of 128 also the stream-K launch)
+    const int D = c.head_dim;
+    if (c.dtype == ISO_BF16 && (D == 64 || D == 128) && !(ctx->flags & (ISO_FLAG_SIMPLE_GEMM | ISO_FLAG_GEMM_STAGED | ISO_FLAG_NO_FUSE)) &&
+        (fp8_qkv || iso_gemm_bf16_dtl_supported(ck.n, NQKV, H))) {
+        auto variant = [&](int n) {
+            const iso_split_plan p = plan_gemm(ctx, fp8_qkv, true, n, NQKV, H, ck.s);
+            return p.tile >= 0 ? 0 : fp8_qkv ? iso_gemm_fp8_resolve(n, NQKV, H, p.whole, sk_for(ctx, ck.s))
+                                             : iso_gemm_bf16_dtl_resolve(n, NQKV, H, p.whole, sk_for(ctx, ck.s));
+        };
+        bool all_fusable = true;
+        ISO_TRY(for_segments(ctx, ck.n, [&](int, int n) {
+            const int v = variant(n);
+            all_fusable = all_fusable && (v == 1 || v == 4 || v == 5 || (v == 6 && D == 128 && !fp8_qkv));
+            return (int)ISO_OK;
+        }));
         if (all_fusable) {
+            if (fp8_qkv && !f8.prequant)
+                LAUNCH_TRY(ISO_K_QUANT, ck.s, iso_launch_quant_rows_fp8(yr, a8, sa, ck.n, H, ck.s), "fp8 row quantiser");
             Timed t_(ctx, ISO_K_GEMM_QKV, ck.s);
             return for_segments(ctx, ck.n, [&](int lo, int n) {
-                iso_sk_ws *sk = sk_for(ctx, ck.s);
-                const int v = iso_gemm_bf16_dtl_resolve(n, NQKV, H, plan_gemm(ctx, false, true, n, NQKV, H, ck.s).whole, sk);
-                hipError_t e_ = iso_launch_gemm_qkv_rope_bf16(yr + (size_t)lo * H * e, w->w_qkv, qkvr + (size_t)lo * NQKV * e, n,
-                                                              NQKV, H, v, sk, ctx->rope_cos, ctx->rope_sin, kc, vc, ck.lo + lo,
-                                                              c.n_q_heads, c.n_kv_heads, ck.s);
+                const int v = variant(n);
+                const iso_rope_args rope{ctx->rope_cos, ctx->rope_sin, kc, vc, ck.lo + lo, c.n_q_heads, c.n_kv_heads, D};
+                const void *a = fp8_qkv ? (const void *)(a8 + (size_t)lo * H) : yr + (size_t)lo * H * e;
+                void *out = qkvr + (size_t)lo * NQKV * e;
+                const iso_pp_args o{a, fp8_qkv ? f8.w8 : w->w_qkv, fp8_qkv ? sa + lo : nullptr, fp8_qkv ? f8.sw : nullptr, out, nullptr,
+                                    n, NQKV, H, 1, rope};
+                const hipError_t e_ = v == 6 ? iso_launch_gemm_qkv_rope_bf16_sk(a, w->w_qkv, out, n, NQKV, H, sk_for(ctx, ck.s), rope, ck.s)
+                                             : iso_launch_gemm_pp(v == 1 ? 256 : v == 4 ? 128 : 192, ISO_PP_ROPE, o, ck.s);
                 if (e_ != hipSuccess) return fail(ISO_ERR_HIP, "qkv+rope launch: %s", hipGetErrorString(e_));
                 return (int)ISO_OK;
             });

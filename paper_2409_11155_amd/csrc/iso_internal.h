@@ -106,10 +106,26 @@ hipError_t iso_launch_gemm_bf16_dtl(const void *a, const void *w, void *c, int M
 bool iso_gemm_bf16_dtl_supported(int M, int N, int K);
 // which variant (1..6; -1: none; +8: plain main loop) a launch with `variant` resolves to
 int iso_gemm_bf16_dtl_resolve(int M, int N, int K, int variant, const iso_sk_ws *sk_or_null);
-// QKV projection with rotary embedding + KV-cache write in the epilogue (head_dim 128; resolved variant 1 or 6)
-hipError_t iso_launch_gemm_qkv_rope_bf16(const void *a, const void *w, void *qkv, int M, int N, int K, int resolved,
-                                         iso_sk_ws *sk_or_null, const float *cos_t, const float *sin_t, void *k_cache,
-                                         void *v_cache, int q_offset, int nq, int nkv, hipStream_t s);
+// Where the rotary step and the KV-cache write of a QKV projection go (W = [q heads | k heads | v heads] x d rows).
+struct iso_rope_args {
+    const float *cos_t, *sin_t;      // [max_seq, d/2]
+    void *k_cache, *v_cache;         // [max_seq, nkv, d]
+    int q_offset, nq, nkv, d;
+};
+// Tiles of 256 columns (gemm_pp_kernel.h): bm = 256, 192 or 128 rows; bf16 operands, or FP8 ones with their row scales sa, sw.
+enum { ISO_PP_PLAIN = 0, ISO_PP_SWIGLU = 1, ISO_PP_ROPE = 2, ISO_PP_SHARE = 3 };
+struct iso_pp_args {
+    const void *a, *w;
+    const float *sa, *sw;            // null: bf16
+    void *c;                         // [M,N] (ISO_PP_SWIGLU: [M,N/2]; ISO_PP_ROPE: the q columns of [M,N])
+    float *p;                        // ISO_PP_SHARE: [shares][M][N] partial sums
+    int M, N, K, shares;
+    iso_rope_args rope;              // ISO_PP_ROPE, head_dim 64 or 128
+};
+hipError_t iso_launch_gemm_pp(int bm, int epi, const iso_pp_args &o, hipStream_t s);
+// QKV projection with rotary embedding + KV-cache write in the epilogue of the stream-K launch (bf16, head_dim 128)
+hipError_t iso_launch_gemm_qkv_rope_bf16_sk(const void *a, const void *w, void *qkv, int M, int N, int K, iso_sk_ws *sk,
+                                            const iso_rope_args &rope, hipStream_t s);
 hipError_t iso_launch_gemm_swiglu_bf16(const void *a, const void *w, void *act, int M, int F, int K, int variant,
                                        iso_sk_ws *sk_or_null, hipStream_t s);
 void iso_gemm_bf16_dtl_plan(int M, int N, int K, int num_wg, int *kind, int *team, int *grid);
@@ -134,6 +150,7 @@ struct iso_split_plan {
 iso_split_plan iso_gemm_split_plan(bool fp8, bool rope, int whole, int M, int N, int K, size_t ws_bytes, int ncu, bool shared,
                                    double *us_or_null = nullptr);
 int iso_gemm_fp8_whole(int M, int N, int K, const iso_sk_ws *sk_or_null);   // the FP8 rule's variant (1, 3 or 6)
+int iso_gemm_fp8_resolve(int M, int N, int K, int variant, const iso_sk_ws *sk_or_null);   // `variant`, or the rule's if it is none
 bool iso_gemm_split_supported(bool fp8, int M, int N, int K);
 // sa / sw null: bf16 operands, else FP8 operands and their row scales
 hipError_t iso_launch_gemm_split(const iso_split_plan &plan, const void *a, const void *w, const float *sa, const float *sw,
