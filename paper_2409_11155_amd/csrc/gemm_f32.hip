@@ -40,17 +40,29 @@ struct RopeF32 {
     int q_offset, nq, nkv, d;
 };
 
+// What stands before the product: A as it is, or A = rmsnorm(x) * g / rmsnorm(x + delta) * g, computed by every workgroup for
+// its own sixteen rows.  A wave then holds its whole part of the rows in registers (K <= 16 * KW * UNROLL), the squares meet in LDS, and the two launches before the projections of a short call are gone (128 tokens of 256: a pass is set by how fast the
+// host enqueues: 11 launches 42.3 us; 7, with this and the copies to the host below, 35.5, of which the kernels take 34).
+enum { NORM_NONE = 0, NORM_X = 1, NORM_X_DELTA = 2 };
+struct NormF32 {
+    const float *delta, *g;
+    float eps;
+};
+
 // KW waves share the k range of a tile, WM x WN tiles per workgroup; KW * WM * WN = 4.  UNROLL steps of k are requested at a
 // time: twelve where a wave has more than four of them, so that the down projection (K = 688) is one trip to memory as well
 // (128 x 256 x 688: 5.2 -> 4.1 us).
-template <int MR, int WM, int WN, int KW, int UNROLL, int EPI>
+// `sink` (small tiles, EPI_NONE): pinned host memory that receives C as well; null: none.
+template <int MR, int WM, int WN, int KW, int UNROLL, int EPI, int NORM = NORM_NONE>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ W,
-                                                       float *__restrict__ C, int M, int N, int K, RopeF32 rope) {
+                                                       float *__restrict__ C, float *__restrict__ sink, int M, int N, int K,
+                                                       RopeF32 rope, NormF32 norm) {
     using Op = F32Mfma<MR>;
     constexpr bool SWIGLU = EPI == EPI_SWIGLU, ROPE = EPI == EPI_ROPE;
     constexpr int NB = EPI == EPI_NONE ? 1 : 2;     // W row blocks per tile
     constexpr int GRP = 64 / MR, STEP = 4 * GRP;    // k per step (four matrix instructions)
     static_assert(!ROPE || KW > 1, "the rotary step works on the tile in LDS");
+    static_assert(NORM == NORM_NONE || (MR == 16 && WM == 1 && WN == 1), "one tile per workgroup");
     __shared__ float part[KW > 1 ? KW * NB * MR * (MR + 1) : 1];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int kw = wave % KW, wm = (wave / KW) % WM, wn = wave / (KW * WM);
@@ -72,8 +84,8 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
         for (int r = 0; r < Op::NACC; ++r) acc[b][r] = 0.f;
     const int steps = (K + STEP - 1) / STEP;
     const int s0 = steps * kw / KW, s1 = steps * (kw + 1) / KW;
-    for (int s = s0; s < s1; s += UNROLL) {
-        f32x4_t av[UNROLL], wv[NB][UNROLL];
+    for (int s = s0; s < (NORM == NORM_NONE ? s1 : s0 + 1); s += UNROLL) {   // NORM: one round, waves without a step included
+        f32x4_t av[UNROLL], wv[NB][UNROLL], gv[NORM == NORM_NONE ? 1 : UNROLL], dv[NORM == NORM_X_DELTA ? UNROLL : 1];
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {          // all loads of the group before its first matrix instruction
             const int k = (s + u) * STEP + 4 * grp;
@@ -82,6 +94,45 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
 #pragma unroll
             for (int b = 0; b < NB; ++b)
                 wv[b][u] = in ? *reinterpret_cast<const f32x4_t *>(wp[b] + k) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+            if constexpr (NORM != NORM_NONE)
+                gv[u] = in ? *reinterpret_cast<const f32x4_t *>(norm.g + k) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+            if constexpr (NORM == NORM_X_DELTA)
+                dv[u] = in ? *reinterpret_cast<const f32x4_t *>(norm.delta + (ap - A) + k) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+        }
+        if constexpr (NORM != NORM_NONE) {
+            // the squares are added in the norm kernel's order (16-byte pieces of a row over 64 lanes, lane bits from the highest
+            // down, then the waves), so that it makes no difference which of the two computes a row
+            constexpr int PIECES = 4 * KW * UNROLL;
+            __shared__ float sums[MR][PIECES + 1];
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u) {
+                if constexpr (NORM == NORM_X_DELTA) av[u] += dv[u];
+                float ss = 0.f;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) ss += av[u][j] * av[u][j];
+                if (s + u < s1) sums[lrow][4 * (s + u) + grp] = ss;
+            }
+            __syncthreads();
+            float total = 0.f;
+#pragma unroll
+            for (int w = 0; w < PIECES / 64; ++w) {
+                float v[16];
+#pragma unroll
+                for (int q = 0; q < 16; ++q) {
+                    const int at = 64 * w + 4 * q + grp;
+                    v[q] = at < 4 * steps ? sums[lrow][at] : 0.f;
+                }
+#pragma unroll
+                for (int o = 8; o > 0; o >>= 1)
+#pragma unroll
+                    for (int q = 0; q < o; ++q) v[q] += v[q + o];
+                v[0] += __shfl_xor(v[0], 32, 64);
+                v[0] += __shfl_xor(v[0], 16, 64);
+                total = w ? total + v[0] : v[0];
+            }
+            const float scale = 1.0f / sqrtf(total / (float)K + norm.eps);
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u) av[u] = av[u] * scale * gv[u];
         }
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u)
@@ -137,6 +188,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
                 lo[half] = b;
             } else {
                 C[(size_t)m * n_out + n] = v[0];
+                if (EPI == EPI_NONE && sink) sink[(size_t)m * n_out + n] = v[0];
             }
         }
     }
@@ -145,22 +197,29 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
 // Small tiles until there are 256 of the large ones.
 bool small_tiles(int M, int n_out) { return (long long)((M + 63) / 64) * ((n_out + 63) / 64) < 256; }
 
-template <int EPI>
-hipError_t launch_f32(const void *a, const void *w, void *c, int M, int N, int K, const RopeF32 &rope, hipStream_t s) {
+constexpr int NORM_MAX_K = 16 * 4 * 12;      // a row in the registers of four waves
+
+template <int EPI, int NORM = NORM_NONE>
+hipError_t launch_f32(const void *a, const void *w, void *c, void *sink, int M, int N, int K, const RopeF32 &rope,
+                      const NormF32 &norm, hipStream_t s) {
     const int n_out = EPI == EPI_NONE ? N : N / 2;
     const float *af = (const float *)a, *wf = (const float *)w;
     const dim3 grid16((n_out + 15) / 16, (M + 15) / 16);
-    if constexpr (EPI != EPI_ROPE) {
+    if constexpr (EPI != EPI_ROPE && NORM == NORM_NONE) {
         if (!small_tiles(M, n_out)) {
+            if (sink) return hipErrorInvalidValue;
             hipLaunchKernelGGL((gemm_f32_kernel<32, 2, 2, 1, 4, EPI>), dim3((n_out + 63) / 64, (M + 63) / 64), dim3(256), 0, s, af, wf,
-                               (float *)c, M, N, K, rope);
+                               (float *)c, (float *)nullptr, M, N, K, rope, norm);
             return hipGetLastError();
         }
     }
+    if (NORM != NORM_NONE && K > NORM_MAX_K) return hipErrorInvalidValue;
     if (K <= 4 * 4 * 16)
-        hipLaunchKernelGGL((gemm_f32_kernel<16, 1, 1, 4, 4, EPI>), grid16, dim3(256), 0, s, af, wf, (float *)c, M, N, K, rope);
+        hipLaunchKernelGGL((gemm_f32_kernel<16, 1, 1, 4, 4, EPI, NORM>), grid16, dim3(256), 0, s, af, wf, (float *)c, (float *)sink, M,
+                           N, K, rope, norm);
     else
-        hipLaunchKernelGGL((gemm_f32_kernel<16, 1, 1, 4, 12, EPI>), grid16, dim3(256), 0, s, af, wf, (float *)c, M, N, K, rope);
+        hipLaunchKernelGGL((gemm_f32_kernel<16, 1, 1, 4, 12, EPI, NORM>), grid16, dim3(256), 0, s, af, wf, (float *)c, (float *)sink,
+                           M, N, K, rope, norm);
     return hipGetLastError();
 }
 
@@ -170,12 +229,24 @@ bool iso_gemm_f32_supported(const void *a, const void *w, int M, int N, int K) {
     return (K % 4) == 0 && ((uintptr_t)a | (uintptr_t)w) % 16 == 0 && (M + 15) / 16 <= 65535;
 }
 
-hipError_t iso_launch_gemm_f32(const void *a, const void *w, void *c, int M, int N, int K, hipStream_t s) {
-    return launch_f32<EPI_NONE>(a, w, c, M, N, K, RopeF32{}, s);
+bool iso_gemm_f32_sink_supported(int M, int N) { return small_tiles(M, N); }
+
+hipError_t iso_launch_gemm_f32(const void *a, const void *w, void *c, void *sink, int M, int N, int K, hipStream_t s) {
+    return launch_f32<EPI_NONE>(a, w, c, sink, M, N, K, RopeF32{}, NormF32{}, s);
 }
 
-hipError_t iso_launch_gemm_swiglu_f32(const void *a, const void *w, void *act, int M, int F, int K, hipStream_t s) {
-    return launch_f32<EPI_SWIGLU>(a, w, act, M, 2 * F, K, RopeF32{}, s);
+// The projections behind a norm take the norm's inputs instead of its output where a row fits the registers of a workgroup and
+// the tiles are the small ones.
+bool iso_gemm_f32_norm_supported(const iso_norm_args &norm, int M, int n_out, int K) {
+    return K <= NORM_MAX_K && small_tiles(M, n_out) && ((uintptr_t)norm.x | (uintptr_t)norm.delta | (uintptr_t)norm.g) % 16 == 0;
+}
+
+hipError_t iso_launch_gemm_swiglu_f32(const void *a, const void *w, void *act, int M, int F, int K, const iso_norm_args *norm,
+                                      hipStream_t s) {
+    if (!norm) return launch_f32<EPI_SWIGLU>(a, w, act, nullptr, M, 2 * F, K, RopeF32{}, NormF32{}, s);
+    const NormF32 nf{(const float *)norm->delta, (const float *)norm->g, norm->eps};
+    return norm->delta ? launch_f32<EPI_SWIGLU, NORM_X_DELTA>(norm->x, w, act, nullptr, M, 2 * F, K, RopeF32{}, nf, s)
+                       : launch_f32<EPI_SWIGLU, NORM_X>(norm->x, w, act, nullptr, M, 2 * F, K, RopeF32{}, nf, s);
 }
 
 // QKV projection with rotary embedding and KV-cache write in its epilogue (the k and v columns of qkv are not written): one
@@ -185,8 +256,12 @@ bool iso_gemm_rope_f32_supported(const void *a, const void *w, int M, int N, int
     return iso_gemm_f32_supported(a, w, M, N, K) && small_tiles(M, N);
 }
 
-hipError_t iso_launch_gemm_rope_f32(const void *a, const void *w, void *qkv, int M, int K, const float *cos_t, const float *sin_t,
-                                    void *k_cache, void *v_cache, int q_offset, int nq, int nkv, int d, hipStream_t s) {
-    const RopeF32 rope{cos_t, sin_t, (float *)k_cache, (float *)v_cache, q_offset, nq, nkv, d};
-    return launch_f32<EPI_ROPE>(a, w, qkv, M, (nq + 2 * nkv) * d, K, rope, s);
+hipError_t iso_launch_gemm_rope_f32(const void *a, const void *w, void *qkv, int M, int K, const iso_norm_args *norm,
+                                    const iso_rope_args &rp, hipStream_t s) {
+    const RopeF32 rope{rp.cos_t, rp.sin_t, (float *)rp.k_cache, (float *)rp.v_cache, rp.q_offset, rp.nq, rp.nkv, rp.d};
+    const int N = (rp.nq + 2 * rp.nkv) * rp.d;
+    if (!norm) return launch_f32<EPI_ROPE>(a, w, qkv, nullptr, M, N, K, rope, NormF32{}, s);
+    if (norm->delta) return hipErrorInvalidValue;
+    return launch_f32<EPI_ROPE, NORM_X>(norm->x, w, qkv, nullptr, M, N, K, rope,
+                                        NormF32{nullptr, (const float *)norm->g, norm->eps}, s);
 }

@@ -280,7 +280,7 @@ int gemm(iso_ctx *ctx, int kind, const void *a, const void *w, void *c, int M, i
         else if (mfma && iso_gemm_bf16_mfma_supported(n, N, K))
             e = iso_launch_gemm_bf16_mfma(ar, w, cr, n, N, K, s);
         else if (ctx->cfg.dtype == ISO_F32 && !(ctx->flags & ISO_FLAG_SIMPLE_GEMM) && iso_gemm_f32_supported(ar, w, n, N, K))
-            e = iso_launch_gemm_f32(ar, w, cr, n, N, K, s);
+            e = iso_launch_gemm_f32(ar, w, cr, nullptr, n, N, K, s);
         else
             e = iso_launch_gemm_simple(ctx->cfg.dtype, ar, w, cr, n, N, K, s);
         if (e != hipSuccess)
@@ -349,10 +349,14 @@ int sk_status(const iso_ctx *ctx) {
 // two of them beside one product of 2048 x 7168 x 8192 on the other stream (150 us): copies of 2 MB 156 / 204 us, 4 MB 255 / 263,
 // 6 MB 301 / 328; alone, product and copy 58 / 46, 97 / 90, 136 / 129.
 // A graph capture records the kernel as well.
+bool comm_by_kernel(size_t bytes, bool overlap, hipStream_t s) {
+    return bytes <= (overlap ? 1u << 20 : 6u << 20) || capturing(s);
+}
+
 hipError_t comm_copy(void *dst, const void *src, size_t pitch, size_t rows, bool overlap, hipStream_t s) {
-    const size_t bytes = pitch * rows, by_kernel = overlap ? 1u << 20 : 6u << 20;
+    const size_t bytes = pitch * rows;
     if (((uintptr_t)dst | (uintptr_t)src) % 16) return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
-    if (bytes <= by_kernel || capturing(s)) return iso_launch_copy_out(dst, src, bytes, s);
+    if (comm_by_kernel(bytes, overlap, s)) return iso_launch_copy_out(dst, src, bytes, s);
     // The engine moves rows of 512 bytes and more at the rate of the link (4 MB: 84 us; of 256 bytes 104, of 64 227, of 16 885),
     // so narrow rows, which lie one behind the other, go several to a row.
     size_t per = 1;
@@ -398,6 +402,18 @@ struct Chunk {
     bool overlap;      // another chunk's kernels may run beside this one's
 };
 
+// A short fp32 payload that a kernel would copy is stored to the host by the projection that computes it: the place in the host
+// sink, or null.
+void *sink_of_projection(const iso_ctx *ctx, int comm, int which, const Chunk &ck, const void *a, const void *w, int K) {
+    const iso_cfg &c = ctx->cfg;
+    const size_t pitch = (size_t)c.hidden * ctx->elt;
+    if (c.dtype != ISO_F32 || comm != ISO_COMM_D2H || ctx->gemm_segments > 1 || (ctx->flags & (ISO_FLAG_SIMPLE_GEMM | ISO_FLAG_NO_FUSE)) ||
+        !comm_by_kernel(pitch * ck.n, ck.overlap, ck.s) || !iso_gemm_f32_supported(a, w, ck.n, c.hidden, K) ||
+        !iso_gemm_f32_sink_supported(ck.n, c.hidden))
+        return nullptr;
+    return (char *)ctx->host_sink + ((size_t)which * c.max_seq + ck.lo) * pitch;
+}
+
 // Attention block of one chunk.  `first_norm_delta`: when not NULL the block starts with the residual add
 // left over from the previous layer's MLP block (x += delta) fused into this norm.
 int attn_block_head(iso_ctx *ctx, const iso_weights *w, void *x, void *kc, void *vc, const Chunk &ck,
@@ -409,6 +425,11 @@ int attn_block_head(iso_ctx *ctx, const iso_weights *w, void *x, void *kc, void 
     char *yr = at(ctx->y, ck.lo, H, e);
     char *qkvr = at(ctx->qkv, ck.lo, NQKV, e);
     // 8-bit projection: the norm writes the FP8 codes and row scales of y itself, y is never stored
+    // fp32 and short: the QKV projection takes the norm's inputs
+    const iso_norm_args norm{xr, nullptr, w->g_attn, c.rms_eps};
+    const bool rope_f32 = c.dtype == ISO_F32 && !(ctx->flags & (ISO_FLAG_SIMPLE_GEMM | ISO_FLAG_NO_FUSE)) && ctx->gemm_segments <= 1 &&
+                          iso_gemm_rope_f32_supported(yr, w->w_qkv, ck.n, NQKV, H);
+    const bool norm_f32 = rope_f32 && !add_prev_partial && iso_gemm_f32_norm_supported(norm, ck.n, NQKV / 2, H);
     F8Arg f8{w->w_qkv_f8, w->s_qkv, ck.lo};
     f8.prequant = use_fp8(ctx, f8, ck.n, NQKV, H) && iso_rmsnorm_fp8_supported(H);
     unsigned char *a8 = ctx->a8 + (size_t)ck.lo * ctx->a8_pitch;
@@ -424,7 +445,7 @@ int attn_block_head(iso_ctx *ctx, const iso_weights *w, void *x, void *kc, void 
     } else if (f8.prequant) {
         LAUNCH_TRY(ISO_K_RMSNORM, ck.s, iso_launch_rmsnorm_fp8(xr, nullptr, nullptr, nullptr, w->g_attn, a8, sa, ck.n, H, c.rms_eps, ck.s),
                    "rmsnorm+fp8");
-    } else {
+    } else if (!norm_f32) {
         LAUNCH_TRY(ISO_K_RMSNORM, ck.s, iso_launch_rmsnorm(c.dtype, xr, nullptr, nullptr, nullptr, w->g_attn, yr, ck.n, H, c.rms_eps, ck.s), "rmsnorm");
     }
     // A split product's second kernel does the rotary embedding and the KV-cache write on the way.
@@ -440,11 +461,10 @@ int attn_block_head(iso_ctx *ctx, const iso_weights *w, void *x, void *kc, void 
                                               c.n_kv_heads, c.head_dim, ck.s), "split qkv+rope");
         return ISO_OK;
     }
-    if (c.dtype == ISO_F32 && !(ctx->flags & (ISO_FLAG_SIMPLE_GEMM | ISO_FLAG_NO_FUSE)) && ctx->gemm_segments <= 1 &&
-        iso_gemm_rope_f32_supported(yr, w->w_qkv, ck.n, NQKV, H)) {
+    if (rope_f32) {
+        const iso_rope_args rope{ctx->rope_cos, ctx->rope_sin, kc, vc, ck.lo, c.n_q_heads, c.n_kv_heads, c.head_dim};
         LAUNCH_TRY(ISO_K_GEMM_QKV, ck.s,
-                   iso_launch_gemm_rope_f32(yr, w->w_qkv, qkvr, ck.n, H, ctx->rope_cos, ctx->rope_sin, kc, vc, ck.lo, c.n_q_heads,
-                                            c.n_kv_heads, c.head_dim, ck.s), "qkv+rope");
+                   iso_launch_gemm_rope_f32(yr, w->w_qkv, qkvr, ck.n, H, norm_f32 ? &norm : nullptr, rope, ck.s), "qkv+rope");
         return ISO_OK;
     }
     // bf16 layers: rotary embedding and KV-cache write ride in the projection's epilogue whenever the launch rule picks, for every
@@ -496,9 +516,13 @@ int attn_block_tail(iso_ctx *ctx, const iso_weights *w, void *kc, void *vc, cons
     char *attnr = at(ctx->attn, ck.lo, NQD, e);
     char *partr = at(ctx->part, ck.lo, H, e);
     ISO_TRY(attention(ctx, qkvr, NQKV, kc, vc, attnr, ck.n, ck.lo, ck.lo + ck.n, ck.s));
-    ISO_TRY(gemm(ctx, ISO_K_GEMM_O, attnr, w->w_o, partr, ck.n, H, NQD, ck.s, F8Arg{w->w_o_f8, w->s_o, ck.lo}));
+    void *sink = sink_of_projection(ctx, comm, 0, ck, attnr, w->w_o, NQD);
+    if (sink)
+        LAUNCH_TRY(ISO_K_GEMM_O, ck.s, iso_launch_gemm_f32(attnr, w->w_o, partr, sink, ck.n, H, NQD, ck.s), "o_proj + copy to the host");
+    else
+        ISO_TRY(gemm(ctx, ISO_K_GEMM_O, attnr, w->w_o, partr, ck.n, H, NQD, ck.s, F8Arg{w->w_o_f8, w->s_o, ck.lo}));
     if (after_compute) HIP_TRY(hipEventRecord(after_compute, ck.s));
-    return comm_point(ctx, comm, 0, ck.lo, ck.n, ck.overlap, ck.s);
+    return sink ? ISO_OK : comm_point(ctx, comm, 0, ck.lo, ck.n, ck.overlap, ck.s);
 }
 
 int mlp_block(iso_ctx *ctx, const iso_weights *w, void *x, const Chunk &ck, int comm) {
@@ -518,10 +542,14 @@ int mlp_block(iso_ctx *ctx, const iso_weights *w, void *x, const Chunk &ck, int 
     f8gu.prequant = use_fp8(ctx, f8gu, ck.n, 2 * F, H) && iso_rmsnorm_fp8_supported(H);
     unsigned char *a8 = ctx->a8 + (size_t)ck.lo * ctx->a8_pitch;
     float *sa = ctx->a8s + ck.lo;
+    const iso_norm_args norm{xr, pa, w->g_mlp, c.rms_eps};
+    const bool swiglu_f32 = c.dtype == ISO_F32 && !(ctx->flags & (ISO_FLAG_SIMPLE_GEMM | ISO_FLAG_NO_FUSE)) && ctx->gemm_segments <= 1 &&
+                            iso_gemm_f32_supported(yr, w->w_gate_up, ck.n, 2 * F, H);
+    const bool norm_f32 = swiglu_f32 && iso_gemm_f32_norm_supported(norm, ck.n, F, H);
     if (f8gu.prequant)
         LAUNCH_TRY(ISO_K_RESID_NORM, ck.s, iso_launch_rmsnorm_fp8(xr, pa, nullptr, nullptr, w->g_mlp, a8, sa, ck.n, H, c.rms_eps, ck.s),
                    "residual+rmsnorm+fp8");
-    else
+    else if (!norm_f32)
         LAUNCH_TRY(ISO_K_RESID_NORM, ck.s, iso_launch_rmsnorm(c.dtype, xr, pa, nullptr, nullptr, w->g_mlp, yr, ck.n, H, c.rms_eps, ck.s),
                    "residual+rmsnorm");
     const bool fused = c.dtype == ISO_BF16 && !(ctx->flags & (ISO_FLAG_SIMPLE_GEMM | ISO_FLAG_GEMM_STAGED | ISO_FLAG_NO_FUSE)) &&
@@ -552,12 +580,16 @@ int mlp_block(iso_ctx *ctx, const iso_weights *w, void *x, const Chunk &ck, int 
             if (e_ != hipSuccess) return fail(ISO_ERR_HIP, "gate/up+swiglu launch: %s", hipGetErrorString(e_));
             return (int)ISO_OK;
         }));
-    } else if (c.dtype == ISO_F32 && !(ctx->flags & (ISO_FLAG_SIMPLE_GEMM | ISO_FLAG_NO_FUSE)) && ctx->gemm_segments <= 1 &&
-               iso_gemm_f32_supported(yr, w->w_gate_up, ck.n, 2 * F, H)) {
-        LAUNCH_TRY(ISO_K_GEMM_GATE_UP, ck.s, iso_launch_gemm_swiglu_f32(yr, w->w_gate_up, actr, ck.n, F, H, ck.s), "gate/up+swiglu");
+    } else if (swiglu_f32) {
+        LAUNCH_TRY(ISO_K_GEMM_GATE_UP, ck.s,
+                   iso_launch_gemm_swiglu_f32(yr, w->w_gate_up, actr, ck.n, F, H, norm_f32 ? &norm : nullptr, ck.s), "gate/up+swiglu");
     } else {
         ISO_TRY(gemm(ctx, ISO_K_GEMM_GATE_UP, yr, w->w_gate_up, gur, ck.n, 2 * F, H, ck.s, f8gu));
         LAUNCH_TRY(ISO_K_SWIGLU, ck.s, iso_launch_swiglu(c.dtype, gur, actr, ck.n, F, ck.s), "swiglu");
+    }
+    if (void *sink = sink_of_projection(ctx, comm, 1, ck, actr, w->w_down, F)) {
+        LAUNCH_TRY(ISO_K_GEMM_DOWN, ck.s, iso_launch_gemm_f32(actr, w->w_down, partr, sink, ck.n, H, F, ck.s), "down + copy to the host");
+        return ISO_OK;
     }
     ISO_TRY(gemm(ctx, ISO_K_GEMM_DOWN, actr, w->w_down, partr, ck.n, H, F, ck.s, F8Arg{w->w_down_f8, w->s_down, ck.lo}));
     return comm_point(ctx, comm, 1, ck.lo, ck.n, ck.overlap, ck.s);

@@ -92,11 +92,26 @@ hipError_t iso_launch_gemm_simple(int dtype, const void *a, const void *w, void 
                                   hipStream_t s);
 // fp32 matrix instructions; *_supported: K % 4 == 0, 16-byte aligned operands
 bool iso_gemm_f32_supported(const void *a, const void *w, int M, int N, int K);
-hipError_t iso_launch_gemm_f32(const void *a, const void *w, void *c, int M, int N, int K, hipStream_t s);
-hipError_t iso_launch_gemm_swiglu_f32(const void *a, const void *w, void *act, int M, int F, int K, hipStream_t s);
+bool iso_gemm_f32_sink_supported(int M, int N);
+// sink_or_null: pinned host memory that receives c as well
+hipError_t iso_launch_gemm_f32(const void *a, const void *w, void *c, void *sink_or_null, int M, int N, int K, hipStream_t s);
+// Where the rotary step and the KV-cache write of a QKV projection go (W = [q heads | k heads | v heads] x d rows).
+struct iso_rope_args {
+    const float *cos_t, *sin_t;      // [max_seq, d/2]
+    void *k_cache, *v_cache;         // [max_seq, nkv, d]
+    int q_offset, nq, nkv, d;
+};
+// A projection's operand rmsnorm(x (+ delta)) * g, computed by the projection (then its `a` is not looked at).
+struct iso_norm_args {
+    const void *x, *delta, *g;       // delta may be null
+    float eps;
+};
+bool iso_gemm_f32_norm_supported(const iso_norm_args &norm, int M, int n_out, int K);
+hipError_t iso_launch_gemm_swiglu_f32(const void *a, const void *w, void *act, int M, int F, int K, const iso_norm_args *norm_or_null,
+                                      hipStream_t s);
 bool iso_gemm_rope_f32_supported(const void *a, const void *w, int M, int N, int K);
-hipError_t iso_launch_gemm_rope_f32(const void *a, const void *w, void *qkv, int M, int K, const float *cos_t, const float *sin_t,
-                                    void *k_cache, void *v_cache, int q_offset, int nq, int nkv, int d, hipStream_t s);
+hipError_t iso_launch_gemm_rope_f32(const void *a, const void *w, void *qkv, int M, int K, const iso_norm_args *norm_or_null,
+                                    const iso_rope_args &rope, hipStream_t s);
 hipError_t iso_launch_attn_f32(const void *q, const void *k, const void *v, void *out, int Tc, int q_offset, int kv_len, int nq,
                                int nkv, int d, int q_stride, hipStream_t s);
 hipError_t iso_launch_gemm_bf16_mfma(const void *a, const void *w, void *c, int M, int N, int K, hipStream_t s);
@@ -106,12 +121,6 @@ hipError_t iso_launch_gemm_bf16_dtl(const void *a, const void *w, void *c, int M
 bool iso_gemm_bf16_dtl_supported(int M, int N, int K);
 // which variant (1..6; -1: none; +8: plain main loop) a launch with `variant` resolves to
 int iso_gemm_bf16_dtl_resolve(int M, int N, int K, int variant, const iso_sk_ws *sk_or_null);
-// Where the rotary step and the KV-cache write of a QKV projection go (W = [q heads | k heads | v heads] x d rows).
-struct iso_rope_args {
-    const float *cos_t, *sin_t;      // [max_seq, d/2]
-    void *k_cache, *v_cache;         // [max_seq, nkv, d]
-    int q_offset, nq, nkv, d;
-};
 // Tiles of 256 columns (gemm_pp_kernel.h): bm = 256, 192 or 128 rows; bf16 operands, or FP8 ones with their row scales sa, sw.
 enum { ISO_PP_PLAIN = 0, ISO_PP_SWIGLU = 1, ISO_PP_ROPE = 2, ISO_PP_SHARE = 3 };
 struct iso_pp_args {

@@ -3,6 +3,8 @@
 Bound: fp32 sums of K products of N(0, 1) and N(0, 1/K) values, relative to the rms of a result (1): K rounding errors of at
 most 2^-24 |partial sum| each, of random sign -- 2e-5 covers K = 1664 in the other projection tests as well.
 """
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -66,3 +68,31 @@ def test_rotary_step_and_cache_write_in_the_qkv_epilogue_f32(hidden, nq, nkv, d,
             got.append((f64(kc)[:T], vc.numpy()[:T]))
         np.testing.assert_allclose(got[0][0], got[1][0], rtol=0, atol=2.0 ** -22 * np.abs(got[1][0]).max())
         np.testing.assert_array_equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("hidden,T,split", [(8, 1, 0), (60, 17, 0), (256, 37, 16), (264, 150, 61), (768, 33, 0), (776, 33, 0)])
+def test_norms_and_copies_of_a_short_layer_in_its_projections_f32(hidden, T, split):
+    """Norms computed by the projections behind them and partials stored to the host by the projections in front of the copies, up
+    to the longest row that a workgroup holds and one piece past it, against the kernels one by one: only the sums of squares are
+    added in another order, 2^-24 relative per addition of `hidden` positive terms, so the rest of the layer moves by as much."""
+    hidden += hidden % 8
+    nq, nkv, d, ffn = 2, 1, 64, 72
+    w = iso_inputs.make_layer(hidden, nq, nkv, d, ffn, seed=47, dtype="f32")
+    x = iso_inputs.make_hidden(T, hidden, seed=47, dtype="f32")
+    ref = orc.layer_unsplit(h64(x, "f32"), oracle_weights(w, "f32"), shape_of(hidden, nq, nkv, d, ffn))
+    with make_ctx(hidden, nq, nkv, d, ffn, "f32", T + 3) as ctx:
+        sink = np.frombuffer((ctypes.c_char * (2 * (T + 3) * hidden * 4)).from_address(ctx.host_sink()), dtype=np.float32)
+        sink = sink.reshape(2, T + 3, hidden)
+        got = []
+        for flags in (0, iso.ISO_FLAG_NO_FUSE):
+            ctx.set_flags(flags | iso.ISO_FLAG_KEEP_CUT)
+            sink[:] = np.nan
+            out, kc, vc = run_layer(ctx, iso.upload_weights(w, "f32"), x, "f32", T, split, nkv, d, T + 3, iso.ISO_COMM_D2H,
+                                    poison=True)
+            assert orc.max_rel_err(f64(out), ref["x_out"]) <= TOL_LAYER["f32"]
+            assert np.isnan(sink[:, T:]).all()
+            got.append((f64(out), sink[:, :T].astype(np.float64)))
+        for a, b in zip(*got):
+            assert orc.max_rel_err(a, b) <= 1e-5
+        # what the host holds is what the layer added to its input
+        np.testing.assert_allclose(got[0][0], h64(x, "f32") + got[0][1][0] + got[0][1][1], rtol=0, atol=1e-5)
