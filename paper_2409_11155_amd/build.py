@@ -12,7 +12,7 @@ CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libiso.so")
 
 SOURCES = ["iso_api.hip", "elementwise.hip", "gemm_simple.hip", "gemm_bf16_mfma.hip", "gemm_bf16_dtl.hip", "gemm_fp8_dtl.hip", "gemm_pp.hip", "gemm_split.hip", "gemm_f32.hip", "attn_f32.hip", "attn_simple.hip",
-           "attn_bf16_mfma.hip", "attn_bf16_dtl.hip"]
+           "attn_bf16_mfma.hip", "attn_bf16_dtl.hip", "attn_bf16_wave.hip"]
 
 
 def hipcc() -> str:

@@ -303,9 +303,13 @@ int attention(iso_ctx *ctx, const void *q, int q_stride, const void *kc, const v
     const bool few = !((ctx->flags >> 12) & 31) && keys <= (c.dtype == ISO_F32 ? (c.head_dim == 128 ? 40 : 16) : c.head_dim == 64 ? 14 : 0);
     const bool simple = few || (ctx->flags & ISO_FLAG_SIMPLE_ATTN);
     const bool mfma = c.dtype == ISO_BF16 && !simple;
-    if (mfma && !(ctx->flags & ISO_FLAG_ATTN_STAGED) && iso_attn_bf16_dtl_supported(c.head_dim, kv_len, c.n_kv_heads))
+    const int shape = (ctx->flags >> 12) & 3, shares = (ctx->flags >> 14) & 7;      // forced by tests; shares 7: the wave kernel
+    const bool dtl = mfma && !(ctx->flags & ISO_FLAG_ATTN_STAGED) && iso_attn_bf16_dtl_supported(c.head_dim, kv_len, c.n_kv_heads);
+    if (dtl && (shares ? shares == 7 : !shape && iso_attn_bf16_wave_wanted(Tc, c.n_q_heads, c.head_dim, keys)))
+        e = iso_launch_attn_bf16_wave(q, kc, vc, out, Tc, q_offset, kv_len, c.n_q_heads, c.n_kv_heads, c.head_dim, q_stride, s);
+    else if (dtl)
         e = iso_launch_attn_bf16_dtl(q, kc, vc, out, Tc, q_offset, kv_len, c.n_q_heads, c.n_kv_heads, c.head_dim, q_stride,
-                                     (ctx->flags >> 12) & 3, (ctx->flags >> 14) & 7, attn_ws_for(ctx, s), s);
+                                     shape, shares, attn_ws_for(ctx, s), s);
     else if (mfma && iso_attn_bf16_mfma_supported(c.head_dim))
         e = iso_launch_attn_bf16_mfma(q, kc, vc, out, Tc, q_offset, kv_len, c.n_q_heads, c.n_kv_heads, c.head_dim, q_stride, s);
     else if (c.dtype == ISO_F32 && !simple)

@@ -184,6 +184,10 @@ bool iso_attn_bf16_mfma_supported(int d);
 hipError_t iso_launch_attn_bf16_dtl(const void *q, const void *k, const void *v, void *out, int Tc, int q_offset,
                                     int kv_len, int nq, int nkv, int d, int q_stride, int shape, int ksplit_req,
                                     const iso_attn_ws *ws_or_null, hipStream_t s);
+// 32-row blocks, keys dealt to the waves of a workgroup; the cache as for the kernel above.  `keys`: the last row's
+bool iso_attn_bf16_wave_wanted(int Tc, int nq, int d, long long keys);
+hipError_t iso_launch_attn_bf16_wave(const void *q, const void *k, const void *v, void *out, int Tc, int q_offset, int kv_len,
+                                     int nq, int nkv, int d, int q_stride, hipStream_t s);
 size_t iso_attn_part_bytes(void);      // bytes of one partial state in an iso_attn_ws
 bool iso_attn_bf16_dtl_supported(int d, int kv_len, int nkv);
 
