@@ -175,7 +175,7 @@ iso_split_plan plan_gemm(iso_ctx *ctx, bool fp8, bool rope, int M, int N, int K,
     }
     if (forced || (ctx->flags & ISO_FLAG_NO_STREAMK)) return whole;
     const int rule = fp8 ? iso_gemm_fp8_whole(M, N, K, sk_for(ctx, s)) : iso_gemm_bf16_dtl_resolve(M, N, K, 0, sk_for(ctx, s));
-    return iso_gemm_split_plan(fp8, rope, rule, M, N, K, bytes, iso_num_cu(), ctx->sk_hold != 0);
+    return iso_gemm_split_plan(fp8, rope, rule, M, N, K, bytes, iso_num_cu(), ctx->side_by_side != 0);
 }
 
 // Key-split attention workspace for a launch on stream s: one per stream of the context's own, none for others.  Heads of 64 do
@@ -755,9 +755,10 @@ int run_stack(iso_ctx *ctx, const iso_weights *layers, int n_layers, void *x, vo
     // ones) the tile-per-workgroup launches share the chip better (measured: 4-7 % either way).
     struct SkHold {
         iso_ctx *c;
-        ~SkHold() { c->sk_hold = 0; }
+        ~SkHold() { c->sk_hold = c->side_by_side = 0; }
     } sk_hold_{ctx};
     ctx->sk_hold = overlap && comm != ISO_COMM_D2H;
+    ctx->side_by_side = overlap && comm == ISO_COMM_NONE;
     // With transfers to hide and chunks long enough to fill the chip on their own (measured: from about 1024 rows),
     // the attention blocks are chained whole; otherwise the chunks' independent front parts run side by side.
     int min_rows = edges[1] - edges[0];

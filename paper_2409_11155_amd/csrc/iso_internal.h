@@ -65,6 +65,7 @@ struct iso_ctx {
     float *rope_sin;   // [max_seq, d/2]
     int gemm_segments; // launches per projection GEMM along M (0 or 1: one launch)
     int sk_hold;       // set while a pass enqueues work for which stream-K is not to be picked
+    int side_by_side;  // set while a pass enqueues chunks whose kernels share the chip all the time
     // GEMM workspaces (bf16 contexts only; base == null otherwise): [0], [1] for the caller's streams, used by the stream-K
     // launch and by split products; [k] for xstream[k], split products only
     iso_sk_ws sk[ISO_MAX_CHUNKS];
