@@ -407,11 +407,11 @@ struct Chunk {
 };
 
 // A short fp32 payload that a kernel would copy is stored to the host by the projection that computes it: the place in the host
-// sink, or null.
+// sink, or null.  (Not while launches are timed one by one: the copy then is a launch, as its record says.)
 void *sink_of_projection(const iso_ctx *ctx, int comm, int which, const Chunk &ck, const void *a, const void *w, int K) {
     const iso_cfg &c = ctx->cfg;
     const size_t pitch = (size_t)c.hidden * ctx->elt;
-    if (c.dtype != ISO_F32 || comm != ISO_COMM_D2H || ctx->gemm_segments > 1 || (ctx->flags & (ISO_FLAG_SIMPLE_GEMM | ISO_FLAG_NO_FUSE)) ||
+    if (c.dtype != ISO_F32 || comm != ISO_COMM_D2H || ctx->timing || ctx->gemm_segments > 1 || (ctx->flags & (ISO_FLAG_SIMPLE_GEMM | ISO_FLAG_NO_FUSE)) ||
         !comm_by_kernel(pitch * ck.n, ck.overlap, ck.s) || !iso_gemm_f32_supported(a, w, ck.n, c.hidden, K) ||
         !iso_gemm_f32_sink_supported(ck.n, c.hidden))
         return nullptr;
