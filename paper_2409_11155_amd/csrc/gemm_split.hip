@@ -35,13 +35,31 @@ template <typename OP, int BM_, int BN_, int NS_, int OCC_> struct NarrowCfg {
     static_assert((NS - 1) * LOADS < 64, "outstanding loads are counted in six bits");
 };
 
+// Eight results of a row as bf16 to c + at; or, with a residual (the layer's last step), x = (x + pa) + that, in fp32 and in the
+// order of the residual kernel.
+__device__ __forceinline__ void store_row_piece(const float (&v)[8], bf16_t *__restrict__ c, size_t at, const iso_resid_args &resid) {
+    bf16x8_t o;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = (bf16_t)v[e];
+    if (resid.x) {
+        bf16_t *x = (bf16_t *)resid.x + at;
+        const bf16x8_t xv = *reinterpret_cast<const bf16x8_t *>(x), pv = *reinterpret_cast<const bf16x8_t *>((const bf16_t *)resid.pa + at);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = (bf16_t)((float)xv[e] + (float)pv[e] + (float)o[e]);
+        *reinterpret_cast<bf16x8_t *>(x) = o;
+    } else {
+        *reinterpret_cast<bf16x8_t *>(c + at) = o;
+    }
+}
+
 template <typename Cfg, typename OP, int EPI>
 __global__ __launch_bounds__(Cfg::NT, Cfg::OCC) void gemm_narrow_kernel(const typename OP::elem *__restrict__ A,
                                                                         const typename OP::elem *__restrict__ W,
                                                                         const float *__restrict__ sa,
                                                                         const float *__restrict__ sw,
                                                                         bf16_t *__restrict__ C, float *__restrict__ P, int M,
-                                                                        int N, int K, int tiles_m, int tiles_n, int S) {
+                                                                        int N, int K, int tiles_m, int tiles_n, int S,
+                                                                        iso_resid_args resid) {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int BM = Cfg::BM, BN = Cfg::BN, NS = Cfg::NS, NW = Cfg::NW, KW = Cfg::KW, FM = Cfg::FM, FN = Cfg::FN;
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
@@ -191,13 +209,11 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::OCC) void gemm_narrow_kernel(const ty
                     o[0] = f32x4_t{v[0], v[1], v[2], v[3]};
                     o[1] = f32x4_t{v[4], v[5], v[6], v[7]};
                 } else {
-                    bf16x8_t o;
+                    if constexpr (OP::SCALED) {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        if constexpr (OP::SCALED) v[e] *= sa[gm] * sw[gn + e];
-                        o[e] = (bf16_t)v[e];
+                        for (int e = 0; e < 8; ++e) v[e] *= sa[gm] * sw[gn + e];
                     }
-                    *reinterpret_cast<bf16x8_t *>(C + (size_t)gm * N + gn) = o;
+                    store_row_piece(v, C, (size_t)gm * N + gn, resid);
                 }
             }
         } else {
@@ -265,16 +281,13 @@ __device__ __forceinline__ void sum_shares(const Shares &sh, int row, int col, i
     }
 }
 
-__global__ __launch_bounds__(256) void share_sum_kernel(Shares sh, bf16_t *__restrict__ C, int M, int N) {
+__global__ __launch_bounds__(256) void share_sum_kernel(Shares sh, bf16_t *__restrict__ C, int M, int N, iso_resid_args resid) {
     const int u = blockIdx.x * 256 + threadIdx.x, per_row = N / 8;
     const int row = u / per_row, col = (u % per_row) * 8;
     if (row >= M) return;
     float v[8];
     sum_shares(sh, row, col, N, v);
-    bf16x8_t o;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] = (bf16_t)v[e];
-    *reinterpret_cast<bf16x8_t *>(C + (size_t)row * N + col) = o;
+    store_row_piece(v, C, (size_t)row * N + col, resid);
 }
 
 __global__ __launch_bounds__(256) void share_sum_swiglu_kernel(Shares sh, bf16_t *__restrict__ act, int M, int F) {
@@ -330,6 +343,7 @@ struct Operands {
     void *c;
     float *p;
     int M, N, K;
+    iso_resid_args resid;
 };
 
 template <typename OP, typename Cfg, int EPI> hipError_t launch_narrow(const Operands &o, int S, hipStream_t s) {
@@ -340,7 +354,7 @@ template <typename OP, typename Cfg, int EPI> hipError_t launch_narrow(const Ope
     const int tiles_m = (o.M + Cfg::BM - 1) / Cfg::BM, tiles_n = (o.N + Cfg::BN - 1) / Cfg::BN;
     typedef const typename OP::elem *ptr;
     hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n * S), dim3(Cfg::NT), Cfg::LDS_BYTES, s, (ptr)o.a, (ptr)o.w, o.sa, o.sw,
-                       (bf16_t *)o.c, o.p, o.M, o.N, o.K, tiles_m, tiles_n, S);
+                       (bf16_t *)o.c, o.p, o.M, o.N, o.K, tiles_m, tiles_n, S, o.resid);
     return hipGetLastError();
 }
 
@@ -513,11 +527,11 @@ iso_split_plan iso_gemm_split_plan(bool fp8, bool rope, int whole, int M, int N,
 }
 
 hipError_t iso_launch_gemm_split(const iso_split_plan &plan, const void *a, const void *w, const float *sa, const float *sw,
-                                 void *c, int M, int N, int K, iso_sk_ws *ws, hipStream_t s) {
+                                 void *c, int M, int N, int K, iso_sk_ws *ws, const iso_resid_args &resid, hipStream_t s) {
     const bool fp8 = sa != nullptr;
     float *p = plan.shares > 1 && ws && ws->base ? (float *)((char *)ws->base + SK_HDR) : nullptr;
     if (plan.shares > 1 && !p) return hipErrorInvalidValue;
-    const Operands o{a, w, sa, sw, c, p, M, N, K};
+    const Operands o{a, w, sa, sw, c, p, M, N, K, resid};
     if (plan.shares == 1)
         return fp8 ? launch_cfg<Fp8Op, EPI_BF16>(plan.tile, o, 1, s) : launch_cfg<Bf16Op, EPI_BF16>(plan.tile, o, 1, s);
     const std::lock_guard<std::mutex> hold(ws->lock);
@@ -525,7 +539,8 @@ hipError_t iso_launch_gemm_split(const iso_split_plan &plan, const void *a, cons
                        : launch_cfg<Bf16Op, EPI_PARTIAL>(plan.tile, o, plan.shares, s);
     if (e != hipSuccess) return e;
     const Shares sh{p, (size_t)M * N, plan.shares, sa, sw};
-    hipLaunchKernelGGL(share_sum_kernel, dim3(blocks_for((size_t)M * (N / 8))), dim3(256), 0, s, sh, (bf16_t *)c, M, N);
+    hipLaunchKernelGGL(share_sum_kernel, dim3(blocks_for((size_t)M * (N / 8))), dim3(256), 0, s, sh, (bf16_t *)c, M, N,
+                       resid);
     return hipGetLastError();
 }
 
@@ -534,7 +549,7 @@ hipError_t iso_launch_gemm_split_swiglu(const iso_split_plan &plan, const void *
     const bool fp8 = sa != nullptr;
     float *p = plan.shares > 1 && ws && ws->base ? (float *)((char *)ws->base + SK_HDR) : nullptr;
     if (plan.shares > 1 && !p) return hipErrorInvalidValue;
-    const Operands o{a, w, sa, sw, act, p, M, 2 * F, K};
+    const Operands o{a, w, sa, sw, act, p, M, 2 * F, K, {}};
     if (plan.shares == 1)
         return fp8 ? launch_cfg<Fp8Op, EPI_SWIGLU>(plan.tile, o, 1, s) : launch_cfg<Bf16Op, EPI_SWIGLU>(plan.tile, o, 1, s);
     const std::lock_guard<std::mutex> hold(ws->lock);
@@ -551,7 +566,7 @@ hipError_t iso_launch_gemm_split_rope(const iso_split_plan &plan, const void *a,
                                       void *k_cache, void *v_cache, int q_offset, int nq, int nkv, int d, hipStream_t s) {
     if (!ws || !ws->base) return hipErrorInvalidValue;
     float *p = (float *)((char *)ws->base + SK_HDR);
-    const Operands o{a, w, sa, sw, nullptr, p, M, N, K};
+    const Operands o{a, w, sa, sw, nullptr, p, M, N, K, {}};
     const std::lock_guard<std::mutex> hold(ws->lock);
     hipError_t e = sa ? launch_cfg<Fp8Op, EPI_PARTIAL>(plan.tile, o, plan.shares, s)
                       : launch_cfg<Bf16Op, EPI_PARTIAL>(plan.tile, o, plan.shares, s);

@@ -154,6 +154,12 @@ hipError_t iso_launch_gemm_swiglu_fp8(const void *a8, const float *sa, const voi
                                       int F, int K, int variant, iso_sk_ws *sk_or_null, hipStream_t s);
 // What a projection is launched as.  tile >= 0: a tile shape of gemm_split.hip with the k range in `shares` parts (more than
 // one share, and the rotary form always, needs a workspace); tile < 0: variant `whole` of the whole-tile kernels.
+// Residual added by the product whose result closes the layer: x += pa + bf16(result) (x, pa: [M,N]); x null: none, the result is
+// stored.
+struct iso_resid_args {
+    void *x;
+    const void *pa;
+};
 struct iso_split_plan {
     int tile, shares, whole;
 };
@@ -164,7 +170,7 @@ int iso_gemm_fp8_resolve(int M, int N, int K, int variant, const iso_sk_ws *sk_o
 bool iso_gemm_split_supported(bool fp8, int M, int N, int K);
 // sa / sw null: bf16 operands, else FP8 operands and their row scales
 hipError_t iso_launch_gemm_split(const iso_split_plan &plan, const void *a, const void *w, const float *sa, const float *sw,
-                                 void *c, int M, int N, int K, iso_sk_ws *ws_or_null, hipStream_t s);
+                                 void *c, int M, int N, int K, iso_sk_ws *ws_or_null, const iso_resid_args &resid, hipStream_t s);
 hipError_t iso_launch_gemm_split_swiglu(const iso_split_plan &plan, const void *a, const void *w, const float *sa,
                                         const float *sw, void *act, int M, int F, int K, iso_sk_ws *ws_or_null, hipStream_t s);
 hipError_t iso_launch_gemm_split_rope(const iso_split_plan &plan, const void *a, const void *w, const float *sa, const float *sw,

@@ -91,3 +91,29 @@ def test_layer_through_split_products(tile, shares, hidden, nq, nkv, d, ffn, T, 
             assert np.isnan(f64(kc)[T:]).all() and np.isnan(f64(vc)[T:]).all()
             v_rows.append(vc.numpy()[:T])
         np.testing.assert_array_equal(v_rows[0], v_rows[1])
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("tile,shares", [(0, 1), (1, 3), (2, 1), (2, 2), (3, 2), (4, 2), (5, 3), (6, 2)])
+@pytest.mark.parametrize("T,split,n_layers", [(97, 0, 1), (300, 130, 2)])
+def test_residual_in_the_last_down_projection(tile, shares, fp8, T, split, n_layers):
+    """With nothing to send the last layer's down projection adds the residual itself: same arithmetic in the same order as the
+    kernel that adds it where the partials are sent, so the hidden states are the same bits."""
+    hidden, nq, nkv, d, ffn, dt = 512, 4, 1, 128, 768, "bf16"
+    x = iso_inputs.make_hidden(T, hidden, seed=71, dtype=dt)
+    with make_ctx(hidden, nq, nkv, d, ffn, dt, T) as ctx:
+        layers = [iso.upload_weights(iso_inputs.make_layer(hidden, nq, nkv, d, ffn, seed=71 + l, dtype=dt), dt) for l in range(n_layers)]
+        if fp8:
+            layers = [ctx.add_fp8_weights(w) for w in layers]
+        ctx.set_flags(forced(tile, shares) | iso.ISO_FLAG_KEEP_CUT | (iso.ISO_FLAG_FP8_GEMM if fp8 else 0))
+        got = []
+        for comm, launches in ((iso.ISO_COMM_NONE, 0), (iso.ISO_COMM_D2H, 2 if split else 1)):
+            xd = dev(x, dt)
+            kc, vc = (iso.DeviceArray((n_layers, T, nkv, d), dt, fill_byte=NAN_BYTE) for _ in range(2))
+            ctx.timing_enable(True)
+            ctx.stack_prefill(layers, xd, kc, vc, T, split, comm)
+            ctx.sync()
+            assert ctx.timing_read()["residual"][1] == launches
+            ctx.timing_enable(False)
+            got.append(xd.numpy())
+        np.testing.assert_array_equal(got[0], got[1])
