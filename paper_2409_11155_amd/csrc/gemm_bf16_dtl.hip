@@ -207,7 +207,7 @@ hipError_t iso_launch_gemm_bf16_dtl(const void *a, const void *w, void *c, int M
 #define ISO_DTL(BM_, BN_, WM_, WN_)                                                       \
     return plain ? launch<BM_, BN_, WM_, WN_, false, false>(a, w, c, M, N, K, s)          \
                  : launch<BM_, BN_, WM_, WN_, false, true>(a, w, c, M, N, K, s)
-    const iso_pp_args whole{a, w, nullptr, nullptr, c, nullptr, M, N, K, 1, {}};
+    const iso_pp_args whole{a, w, nullptr, nullptr, c, nullptr, M, N, K, 1, {}, {}};
     switch (v) {
         case 1:
             return plain ? launch<256, 256, 4, 2, false, false>(a, w, c, M, N, K, s) : iso_launch_gemm_pp(256, ISO_PP_PLAIN, whole, s);
@@ -259,7 +259,7 @@ hipError_t iso_launch_gemm_swiglu_bf16(const void *a, const void *w, void *act, 
                                        iso_sk_ws *sk, hipStream_t s) {
     int v = variant & 7;
     if (v == 0) v = sk_wanted(M, 2 * F, K, sk) ? 6 : pick_variant(M, 2 * F);
-    const iso_pp_args whole{a, w, nullptr, nullptr, act, nullptr, M, 2 * F, K, 1, {}};
+    const iso_pp_args whole{a, w, nullptr, nullptr, act, nullptr, M, 2 * F, K, 1, {}, {}};
     switch (v) {
         case 1: return iso_launch_gemm_pp(256, ISO_PP_SWIGLU, whole, s);
         case 2: return launch<256, 128, 4, 2, true, true>(a, w, act, M, 2 * F, K, s);

@@ -121,7 +121,7 @@ hipError_t iso_launch_gemm_fp8(const void *a8, const float *sa, const void *w8, 
     const int v = iso_gemm_fp8_resolve(M, N, K, variant, sk);
     if (v == 6) return sk && sk->base ? launch_sk<false>(a8, w8, sa, sw, c, M, N, K, sk, s) : hipErrorInvalidValue;
     if (v == 3) return launch<128, 128, 2, 2, false>(a8, w8, sa, sw, c, M, N, K, s);
-    const iso_pp_args whole{a8, w8, sa, sw, c, nullptr, M, N, K, 1, {}};
+    const iso_pp_args whole{a8, w8, sa, sw, c, nullptr, M, N, K, 1, {}, {}};
     return iso_launch_gemm_pp(v == 1 ? 256 : v == 4 ? 128 : 192, ISO_PP_PLAIN, whole, s);
 }
 
@@ -131,6 +131,6 @@ hipError_t iso_launch_gemm_swiglu_fp8(const void *a8, const float *sa, const voi
     const int v = iso_gemm_fp8_resolve(M, 2 * F, K, variant, sk);
     if (v == 6) return sk && sk->base ? launch_sk<true>(a8, w8, sa, sw, act, M, 2 * F, K, sk, s) : hipErrorInvalidValue;
     if (v == 3) return launch<128, 128, 2, 2, true>(a8, w8, sa, sw, act, M, 2 * F, K, s);
-    const iso_pp_args whole{a8, w8, sa, sw, act, nullptr, M, 2 * F, K, 1, {}};
+    const iso_pp_args whole{a8, w8, sa, sw, act, nullptr, M, 2 * F, K, 1, {}, {}};
     return iso_launch_gemm_pp(v == 1 ? 256 : v == 4 ? 128 : 192, ISO_PP_SWIGLU, whole, s);
 }

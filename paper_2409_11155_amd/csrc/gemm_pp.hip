@@ -15,7 +15,7 @@ template <bool F8, int BM, int EPI> hipError_t launch(const iso_pp_args &o, hipS
                         o.rope.nq, o.rope.nkv};
     hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n * (EPI == PP_SHARE ? o.shares : 1)), dim3(Cfg::NT), LDS_BYTES, s,
                        (const unsigned char *)o.a, (const unsigned char *)o.w, o.sa, o.sw, (bf16_t *)o.c, o.p, o.M, o.N, o.K,
-                       tiles_m, tiles_n, o.shares, rope);
+                       tiles_m, tiles_n, o.shares, rope, o.resid);
     return hipGetLastError();
 }
 
@@ -24,6 +24,7 @@ template <bool F8, int BM> hipError_t launch_epi(int epi, const iso_pp_args &o, 
         case ISO_PP_PLAIN: return launch<F8, BM, PP_PLAIN>(o, s);
         case ISO_PP_SWIGLU: return launch<F8, BM, PP_SWIGLU>(o, s);
         case ISO_PP_SHARE: return launch<F8, BM, PP_SHARE>(o, s);
+        case ISO_PP_RESID: return launch<F8, BM, PP_RESID>(o, s);
         case ISO_PP_ROPE:
             if (o.N != (o.rope.nq + 2 * o.rope.nkv) * o.rope.d) return hipErrorInvalidValue;
             if (o.rope.d == 128) return launch<F8, BM, PP_ROPE128>(o, s);

@@ -26,7 +26,7 @@
 
 namespace {
 
-enum { PP_PLAIN = 0, PP_SWIGLU, PP_ROPE128, PP_ROPE64, PP_SHARE };
+enum { PP_PLAIN = 0, PP_SWIGLU, PP_ROPE128, PP_ROPE64, PP_SHARE, PP_RESID };
 
 template <int BM_> struct PpCfg {
     static constexpr int BM = BM_, BN = 256, NT = 512;
@@ -59,7 +59,7 @@ template <bool F8, int BM, int EPI>
 __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const unsigned char *__restrict__ A, const unsigned char *__restrict__ W,
                                                          const float *__restrict__ sa, const float *__restrict__ sw,
                                                          bf16_t *__restrict__ C, float *__restrict__ P, int M, int N, int K,
-                                                         int tiles_m, int tiles_n, int S, RopeArgs rope) {
+                                                         int tiles_m, int tiles_n, int S, RopeArgs rope, iso_resid_args resid) {
 #if defined(__HIP_DEVICE_COMPILE__)
     using Cfg = PpCfg<BM>;
     constexpr int EB = F8 ? 1 : 2, KE = F8 ? 128 : 64;
@@ -299,6 +299,27 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const unsigned char *__
     }
     constexpr int OC = EPI == PP_SWIGLU ? 128 : 256;     // output columns of the tile
     constexpr int PITCH = OC * 2 + 16;
+    // PP_RESID: x (+ pa) of this thread's pieces, in two batches: the first is requested here and travels under the staging
+    constexpr int PIECES = BM * (OC / 8) / 512, BATCH = PIECES / 2;
+    bf16x8_t xv[EPI == PP_RESID ? BATCH : 1], pv[EPI == PP_RESID ? BATCH : 1];
+    auto piece_at = [&](int it, size_t &at) {
+        const int p = etid + it * 512, gm = m0 + p / (OC / 8), gn = n0 + (p % (OC / 8)) * 8;
+        at = (size_t)gm * N + gn;
+        return gm < M && gn < N;
+    };
+    auto fetch = [&](int first) {
+        if constexpr (EPI == PP_RESID) {
+#pragma unroll
+            for (int i = 0; i < BATCH; ++i) {
+                size_t at;
+                if (piece_at(first + i, at)) {
+                    xv[i] = *reinterpret_cast<const bf16x8_t *>((const bf16_t *)resid.x + at);
+                    pv[i] = *reinterpret_cast<const bf16x8_t *>((const bf16_t *)resid.pa + at);
+                }
+            }
+        }
+    };
+    fetch(0);
     f32x4_t scale_w[2][2];
     if constexpr (F8) {
 #pragma unroll
@@ -349,6 +370,24 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const unsigned char *__
             const int row = p / PPR, cc = (p % PPR) * 8, gm = m0 + row, gn = base + cc;
             if (gm < M && gn < cols)
                 *reinterpret_cast<uint4 *>(C + (size_t)gm * cols + gn) = *reinterpret_cast<const uint4 *>(lds + row * PITCH + cc * 2);
+        }
+    }
+    if constexpr (EPI == PP_RESID) {
+        // x = (x + pa) + bf16(result), in fp32 and in the order of the residual kernel
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            if (b) fetch(BATCH);
+#pragma unroll
+            for (int i = 0; i < BATCH; ++i) {
+                const int p = etid + (b * BATCH + i) * 512;
+                size_t at;
+                if (!piece_at(b * BATCH + i, at)) continue;
+                const bf16x8_t v = *reinterpret_cast<const bf16x8_t *>(lds + p / PPR * PITCH + (p % PPR) * 16);
+                bf16x8_t o;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) o[e] = (bf16_t)((float)xv[i][e] + (float)pv[i][e] + (float)v[e]);
+                *reinterpret_cast<bf16x8_t *>((bf16_t *)resid.x + at) = o;
+            }
         }
     }
     if constexpr (EPI == PP_ROPE128 || EPI == PP_ROPE64) {

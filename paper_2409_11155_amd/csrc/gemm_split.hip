@@ -386,7 +386,7 @@ template <typename OP, int EPI> hipError_t launch_cfg(int cfg, const Operands &o
         if (cfg == 3) return launch_share<OP, 128, 128, 2, 2>(o, S, s);
         if (cfg >= 4 && cfg <= 6)
             return iso_launch_gemm_pp(cfg == 4 ? 256 : cfg == 5 ? 192 : 128, ISO_PP_SHARE,
-                                      iso_pp_args{o.a, o.w, o.sa, o.sw, nullptr, o.p, o.M, o.N, o.K, S, {}}, s);
+                                      iso_pp_args{o.a, o.w, o.sa, o.sw, nullptr, o.p, o.M, o.N, o.K, S, {}, {}}, s);
     }
     return hipErrorInvalidValue;
 }

@@ -497,7 +497,7 @@ int attn_block_head(iso_ctx *ctx, const iso_weights *w, void *x, void *kc, void 
                 const void *a = fp8_qkv ? (const void *)(a8 + (size_t)lo * H) : yr + (size_t)lo * H * e;
                 void *out = qkvr + (size_t)lo * NQKV * e;
                 const iso_pp_args o{a, fp8_qkv ? f8.w8 : w->w_qkv, fp8_qkv ? sa + lo : nullptr, fp8_qkv ? f8.sw : nullptr, out, nullptr,
-                                    n, NQKV, H, 1, rope};
+                                    n, NQKV, H, 1, rope, {}};
                 const hipError_t e_ = v == 6 ? iso_launch_gemm_qkv_rope_bf16_sk(a, w->w_qkv, out, n, NQKV, H, sk_for(ctx, ck.s), rope, ck.s)
                                              : iso_launch_gemm_pp(v == 1 ? 256 : v == 4 ? 128 : 192, ISO_PP_ROPE, o, ck.s);
                 if (e_ != hipSuccess) return fail(ISO_ERR_HIP, "qkv+rope launch: %s", hipGetErrorString(e_));
@@ -596,19 +596,26 @@ int mlp_block(iso_ctx *ctx, const iso_weights *w, void *x, const Chunk &ck, int 
         LAUNCH_TRY(ISO_K_GEMM_DOWN, ck.s, iso_launch_gemm_f32(actr, w->w_down, partr, sink, ck.n, H, F, ck.s), "down + copy to the host");
         return ISO_OK;
     }
-    // Nothing to send, last layer, a product small enough for the tiles and shares of gemm_split.hip: it adds the residual too.
-    // One launch and 13 MB less at 200 tokens of 8192, 3 %.  (Whole 256-column tiles would wait for x and the attention partial
-    // with nothing beside them on their unit; they keep the separate kernel.)
+    // Nothing to send and the last layer: the small tiles and shares of gemm_split.hip and the whole 256-column tiles add the
+    // residual on their way out.  A launch less, and x and the attention partial read instead of three rows read and one written.
     F8Arg f8down{w->w_down_f8, w->s_down, ck.lo};
-    if (closed && comm == ISO_COMM_NONE && c.dtype == ISO_BF16 && ctx->gemm_segments <= 1 && !(ctx->flags & ISO_FLAG_NO_FUSE)) {
+    if (closed && comm == ISO_COMM_NONE && c.dtype == ISO_BF16 && ctx->gemm_segments <= 1 &&
+        !(ctx->flags & (ISO_FLAG_SIMPLE_GEMM | ISO_FLAG_GEMM_STAGED | ISO_FLAG_NO_FUSE))) {
         const bool fp8 = use_fp8(ctx, f8down, ck.n, H, F);
         const iso_split_plan sp = plan_gemm(ctx, fp8, false, ck.n, H, F, ck.s);
-        if (sp.tile >= 0) {
+        const int v = sp.tile >= 0 || !(fp8 || iso_gemm_bf16_dtl_supported(ck.n, H, F)) ? 0
+                      : fp8 ? iso_gemm_fp8_resolve(ck.n, H, F, sp.whole, sk_for(ctx, ck.s))
+                            : iso_gemm_bf16_dtl_resolve(ck.n, H, F, sp.whole, sk_for(ctx, ck.s));
+        if (sp.tile >= 0 || v == 1 || v == 4 || v == 5) {
             if (fp8) LAUNCH_TRY(ISO_K_QUANT, ck.s, iso_launch_quant_rows_fp8(actr, a8, sa, ck.n, F, ck.s), "fp8 row quantiser");
+            const void *in = fp8 ? (const void *)a8 : actr, *wd = fp8 ? f8down.w8 : w->w_down;
+            const float *s_in = fp8 ? sa : nullptr, *s_w = fp8 ? f8down.sw : nullptr;
+            const iso_resid_args resid{xr, pa};
             LAUNCH_TRY(ISO_K_GEMM_DOWN, ck.s,
-                       iso_launch_gemm_split(sp, fp8 ? (const void *)a8 : actr, fp8 ? f8down.w8 : w->w_down, fp8 ? sa : nullptr,
-                                             fp8 ? f8down.sw : nullptr, partr, ck.n, H, F, split_ws_for(ctx, ck.s),
-                                             iso_resid_args{xr, pa}, ck.s), "down + residual");
+                       sp.tile >= 0 ? iso_launch_gemm_split(sp, in, wd, s_in, s_w, partr, ck.n, H, F, split_ws_for(ctx, ck.s), resid, ck.s)
+                                    : iso_launch_gemm_pp(v == 1 ? 256 : v == 4 ? 128 : 192, ISO_PP_RESID,
+                                                         iso_pp_args{in, wd, s_in, s_w, nullptr, nullptr, ck.n, H, F, 1, {}, resid}, ck.s),
+                       "down + residual");
             *closed = true;
             return ISO_OK;
         }

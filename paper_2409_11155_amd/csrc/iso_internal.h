@@ -122,8 +122,14 @@ hipError_t iso_launch_gemm_bf16_dtl(const void *a, const void *w, void *c, int M
 bool iso_gemm_bf16_dtl_supported(int M, int N, int K);
 // which variant (1..6; -1: none; +8: plain main loop) a launch with `variant` resolves to
 int iso_gemm_bf16_dtl_resolve(int M, int N, int K, int variant, const iso_sk_ws *sk_or_null);
+// Residual added by the product whose result closes the layer: x += pa + bf16(result) (x, pa: [M,N]); x null: none, the result is
+// stored.
+struct iso_resid_args {
+    void *x;
+    const void *pa;
+};
 // Tiles of 256 columns (gemm_pp_kernel.h): bm = 256, 192 or 128 rows; bf16 operands, or FP8 ones with their row scales sa, sw.
-enum { ISO_PP_PLAIN = 0, ISO_PP_SWIGLU = 1, ISO_PP_ROPE = 2, ISO_PP_SHARE = 3 };
+enum { ISO_PP_PLAIN = 0, ISO_PP_SWIGLU = 1, ISO_PP_ROPE = 2, ISO_PP_SHARE = 3, ISO_PP_RESID = 4 };
 struct iso_pp_args {
     const void *a, *w;
     const float *sa, *sw;            // null: bf16
@@ -131,6 +137,7 @@ struct iso_pp_args {
     float *p;                        // ISO_PP_SHARE: [shares][M][N] partial sums
     int M, N, K, shares;
     iso_rope_args rope;              // ISO_PP_ROPE, head_dim 64 or 128
+    iso_resid_args resid;            // ISO_PP_RESID
 };
 hipError_t iso_launch_gemm_pp(int bm, int epi, const iso_pp_args &o, hipStream_t s);
 // QKV projection with rotary embedding + KV-cache write in the epilogue of the stream-K launch (bf16, head_dim 128)
@@ -154,12 +161,6 @@ hipError_t iso_launch_gemm_swiglu_fp8(const void *a8, const float *sa, const voi
                                       int F, int K, int variant, iso_sk_ws *sk_or_null, hipStream_t s);
 // What a projection is launched as.  tile >= 0: a tile shape of gemm_split.hip with the k range in `shares` parts (more than
 // one share, and the rotary form always, needs a workspace); tile < 0: variant `whole` of the whole-tile kernels.
-// Residual added by the product whose result closes the layer: x += pa + bf16(result) (x, pa: [M,N]); x null: none, the result is
-// stored.
-struct iso_resid_args {
-    void *x;
-    const void *pa;
-};
 struct iso_split_plan {
     int tile, shares, whole;
 };

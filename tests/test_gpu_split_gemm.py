@@ -94,18 +94,19 @@ def test_layer_through_split_products(tile, shares, hidden, nq, nkv, d, ffn, T, 
 
 
 @pytest.mark.parametrize("fp8", [False, True])
-@pytest.mark.parametrize("tile,shares", [(0, 1), (1, 3), (2, 1), (2, 2), (3, 2), (4, 2), (5, 3), (6, 2)])
+@pytest.mark.parametrize("flags", [forced(0, 1), forced(1, 3), forced(2, 1), forced(2, 2), forced(3, 2), forced(4, 2), forced(5, 3),
+                                   forced(6, 2), 1 << 8, 4 << 8, 5 << 8])          # the last three: whole 256-column tiles
 @pytest.mark.parametrize("T,split,n_layers", [(97, 0, 1), (300, 130, 2)])
-def test_residual_in_the_last_down_projection(tile, shares, fp8, T, split, n_layers):
+def test_residual_in_the_last_down_projection(flags, fp8, T, split, n_layers):
     """With nothing to send the last layer's down projection adds the residual itself: same arithmetic in the same order as the
     kernel that adds it where the partials are sent, so the hidden states are the same bits."""
-    hidden, nq, nkv, d, ffn, dt = 512, 4, 1, 128, 768, "bf16"
+    hidden, nq, nkv, d, ffn, dt = 640, 4, 1, 128, 768, "bf16"        # 640: two column tiles and a half
     x = iso_inputs.make_hidden(T, hidden, seed=71, dtype=dt)
     with make_ctx(hidden, nq, nkv, d, ffn, dt, T) as ctx:
         layers = [iso.upload_weights(iso_inputs.make_layer(hidden, nq, nkv, d, ffn, seed=71 + l, dtype=dt), dt) for l in range(n_layers)]
         if fp8:
             layers = [ctx.add_fp8_weights(w) for w in layers]
-        ctx.set_flags(forced(tile, shares) | iso.ISO_FLAG_KEEP_CUT | (iso.ISO_FLAG_FP8_GEMM if fp8 else 0))
+        ctx.set_flags(flags | iso.ISO_FLAG_KEEP_CUT | (iso.ISO_FLAG_FP8_GEMM if fp8 else 0))
         got = []
         for comm, launches in ((iso.ISO_COMM_NONE, 0), (iso.ISO_COMM_D2H, 2 if split else 1)):
             xd = dev(x, dt)
