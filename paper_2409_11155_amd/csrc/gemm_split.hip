@@ -395,53 +395,52 @@ unsigned blocks_for(size_t units) { return (unsigned)((units + 255) / 256); }
 
 
 // ---- which kernel ----------------------------------------------------------------------------------------------
-// Microseconds of a launch, as fitted to 22 000 launches measured on MI355X (16 matrix shapes of the 30B / 70B shards and
-// of a heads-of-64 layer, 16 to 16384 rows, every tile with 1 to 15 shares, weights from HBM):
-//     start + rounds * round + slices * slice(load) + [shares > 1] (sum0 + sum_mb * MB of partial sums)
+// Microseconds of a launch, as fitted to 24 000 launches measured on MI355X (16 matrix shapes of the 30B / 70B shards and
+// of a heads-of-64 layer, 22 row counts from 16 to 8192, every tile with 1 to 8 shares, weights from HBM):
+//     start + rounds * round + slices * slice(load) + w_mb * MB of weights + [shares > 1] (sum0 + sum_mb * MB of partial sums)
 // with rounds = times the launch fills the chip (`per_cu` workgroups on each unit), load = workgroups per unit in the last
 // round: slice(load) = slice + crowd * min(load, 1), and + pair * (pair0 + (1 - pair0) (load - 1)) when some units hold two.
 // A launch that shares the chip with the other chunk's (`shared`: two chunks computing side by side) leaves its last round's
 // idle units to that one, so there 0.7 of the price is the part of the chip it uses (measured over 60 split layers: 0 and 1
 // instead of 0.7 lose 5 and 2 %) and the switch has to promise 8 %.  (A blend, not a model of the other launch: the QKV products
 // of a 4096-token 70B TP=8 prompt cut in half, 2048 x 1280 x 8192 each, are priced at 55 us and take 94 and 127 side by side.)
-// Never below the time of the weights' bytes from HBM.  Root mean square error 3-8 %; picking the fastest by these numbers
-// gives launches 1.5 % slower than the best measured one on average, 1.38x (bf16) / 1.30x (FP8) faster than the whole-tile
-// rule alone over that grid: 2.4-4x at up to 256 rows, 1.2-1.8x at 512-1024, a few per cent above.
-// The 256-column tiles (kinds 4 to 6, -1, -4, -5; gemm_pp_kernel.h) were fitted to 12 row counts from 64 to 8192 of the same 16
-// matrices; the fastest by these numbers is 1.0 % (bf16) and 1.0 % (FP8) slower than the best measured launch on average.  192 and
-// 128 rows are for row counts that 256 fit badly or that leave units idle: 1500 x 8192 x 3584 73.8 us with 256 rows, 65.5 with 192;
-// 8192 x 2560 x 8192 300 / 250; 1024 x 8960 x 6656 125 / 101; 777 x 7168 x 8192 123 / 105, with 128 rows 96.  Stream-K was the fastest
-// of all launches in 1 of 192 bf16 products (2048 x 8960 x 6656, 198 / 209) and in no FP8 one.  The 128-row shares carry 1.5 us that
-// the fit does not show and a layer of 200 tokens does (gate/up 138.3 / 136.5 us a pass against 256 rows in eight shares).
+// Never below the time of the weights' bytes from HBM.  Root mean square error 5-8 %; the fastest by these numbers is 0.7 % (bf16
+// and FP8) slower than the best measured launch on average, 1.2-1.9 % up to 128 rows.  (Without the term for the weights' bytes
+// the small tiles' error is 8-14 % and the pick 1.1 % slower.)
+// The 256-column tiles (kinds 4 to 6, -1, -4, -5) are those of gemm_pp_kernel.h; 192 and 128 rows are for row counts that 256 fit
+// badly or that leave units idle: 1500 x 8192 x 3584 73.8 us with 256 rows, 65.5 with 192; 8192 x 2560 x 8192 300 / 250; 1024 x 8960
+// x 6656 125 / 101; 777 x 7168 x 8192 123 / 105, with 128 rows 96.  Stream-K was the fastest of all launches in 1 of 192 bf16
+// products (2048 x 8960 x 6656, 198 / 209) and in no FP8 one.  The 128-row shares carry 1.5 us that the fit does not show and a
+// layer of 200 tokens does (gate/up 138.3 / 136.5 us a pass against 256 rows in eight shares).
 struct Tile {
     int bm, bn, per_cu, kind;    // kind: tile in shares (0 .. 6), or -v: variant v of the whole-tile kernels, one share
-    double start, round, slice, crowd, pair, pair0, sum0, sum_mb;
+    double start, round, slice, crowd, pair, pair0, w_mb, sum0, sum_mb;
 };
 constexpr Tile TILES_BF16[] = {
-    {32, 64, 2, 0, 3.5, 0.0, 0.175, 0.042, 0.205, 0.61, 2.1, 0.54},
-    {64, 64, 2, 1, 3.9, 0.0, 0.223, 0.043, 0.208, 0.95, 2.1, 0.51},
-    {128, 64, 2, 2, 4.2, 0.0, 0.261, 0.111, 0.323, 0.79, 2.6, 0.48},
-    {128, 128, 2, 3, 6.9, 0.0, 0.458, 0.093, 0.414, 0.64, 1.0, 0.32},
-    {128, 128, 2, -3, 2.3, 1.6, 0.444, 0.128, 0.387, 0.67, 0.0, 0.0},
-    {256, 256, 1, 4, 0.0, 7.4, 0.731, 0.527, 0.0, 0.0, 4.5, 0.24},
-    {192, 256, 1, 5, 0.0, 5.4, 0.617, 0.411, 0.0, 0.0, 5.9, 0.21},
-    {128, 256, 1, 6, 0.0, 1.5, 0.631, 0.167, 0.0, 0.0, 9.1, 0.27},
-    {256, 256, 1, -1, 0.0, 6.4, 0.872, 0.441, 0.0, 0.0, 0.0, 0.0},
-    {192, 256, 1, -5, 0.0, 5.3, 0.733, 0.283, 0.0, 0.0, 0.0, 0.0},
-    {128, 256, 1, -4, 0.0, 2.9, 0.658, 0.186, 0.0, 0.0, 0.0, 0.0},
+    {32, 64, 2, 0, 2.0, 0.0, 0.131, 0.012, 0.142, 0.87, 0.111, 2.5, 0.55},
+    {64, 64, 2, 1, 2.5, 0.0, 0.162, 0.029, 0.188, 0.88, 0.089, 2.3, 0.59},
+    {128, 64, 2, 2, 3.5, 0.4, 0.242, 0.082, 0.285, 0.88, 0.048, 2.2, 0.51},
+    {128, 128, 2, 3, 6.2, 0.0, 0.456, 0.018, 0.317, 0.93, 0.068, 0.0, 0.35},
+    {128, 128, 2, -3, 0.1, 2.3, 0.462, 0.049, 0.395, 0.64, 0.077, 0.0, 0.00},
+    {256, 256, 1, 4, 0.0, 6.2, 0.737, 0.288, 0.000, 0.00, 0.049, 4.1, 0.29},
+    {192, 256, 1, 5, 5.4, 3.9, 0.637, 0.184, 0.000, 0.00, 0.053, 0.0, 0.29},
+    {128, 256, 1, 6, 7.6, 1.2, 0.591, 0.076, 0.000, 0.00, 0.067, 0.0, 0.32},
+    {256, 256, 1, -1, 0.0, 6.0, 0.854, 0.378, 0.000, 0.00, 0.020, 0.0, 0.00},
+    {192, 256, 1, -5, 0.0, 4.9, 0.710, 0.257, 0.000, 0.00, 0.033, 0.0, 0.00},
+    {128, 256, 1, -4, 0.0, 2.4, 0.600, 0.165, 0.000, 0.00, 0.106, 0.0, 0.00},
 };
 constexpr Tile TILES_FP8[] = {
-    {32, 64, 2, 0, 2.4, 1.8, 0.150, 0.049, 0.133, 1.0, 3.0, 0.27},
-    {64, 64, 2, 1, 2.3, 2.0, 0.187, 0.051, 0.191, 1.0, 2.9, 0.32},
-    {128, 64, 2, 2, 3.8, 1.1, 0.278, 0.088, 0.275, 0.94, 2.2, 0.37},
-    {128, 128, 2, 3, 2.9, 2.6, 0.353, 0.284, 0.224, 0.74, 3.2, 0.26},
-    {128, 128, 2, -3, 2.4, 1.9, 0.497, 0.131, 0.345, 0.47, 0.0, 0.0},
-    {256, 256, 1, 4, 0.0, 5.0, 0.756, 0.315, 0.0, 0.0, 6.9, 0.27},
-    {192, 256, 1, 5, 0.0, 3.4, 0.598, 0.293, 0.0, 0.0, 7.5, 0.27},
-    {128, 256, 1, 6, 0.0, 1.6, 0.494, 0.252, 0.0, 0.0, 9.5, 0.28},
-    {256, 256, 1, -1, 0.0, 7.4, 0.832, 0.443, 0.0, 0.0, 0.0, 0.0},
-    {192, 256, 1, -5, 0.1, 6.0, 0.663, 0.311, 0.0, 0.0, 0.0, 0.0},
-    {128, 256, 1, -4, 0.1, 4.2, 0.546, 0.270, 0.0, 0.0, 0.0, 0.0},
+    {32, 64, 2, 0, 2.1, 0.7, 0.100, 0.013, 0.153, 0.81, 0.116, 2.2, 0.53},
+    {64, 64, 2, 1, 2.6, 0.6, 0.129, 0.046, 0.200, 0.77, 0.091, 2.0, 0.55},
+    {128, 64, 2, 2, 3.0, 1.4, 0.196, 0.116, 0.280, 0.77, 0.052, 1.6, 0.48},
+    {128, 128, 2, 3, 0.0, 0.0, 0.472, 0.018, 0.126, 1.00, 0.088, 6.3, 0.40},
+    {128, 128, 2, -3, 0.0, 3.0, 0.485, 0.064, 0.280, 0.55, 0.149, 0.0, 0.00},
+    {256, 256, 1, 4, 6.1, 4.6, 0.773, 0.073, 0.000, 0.00, 0.050, 0.0, 0.30},
+    {192, 256, 1, 5, 7.0, 2.4, 0.642, 0.032, 0.000, 0.00, 0.054, 0.0, 0.33},
+    {128, 256, 1, 6, 8.4, 0.9, 0.524, 0.053, 0.000, 0.00, 0.068, 0.0, 0.34},
+    {256, 256, 1, -1, 0.0, 7.4, 0.812, 0.376, 0.000, 0.00, 0.023, 0.0, 0.00},
+    {192, 256, 1, -5, 0.0, 5.8, 0.628, 0.283, 0.000, 0.00, 0.068, 0.0, 0.00},
+    {128, 256, 1, -4, 0.0, 3.9, 0.480, 0.234, 0.000, 0.00, 0.151, 0.0, 0.00},
 };
 // Stream-K by team size 1, 2, 4, 8: start + slice * k-slices of a team + fetch * teams per tile column.
 struct StreamK {
@@ -469,7 +468,7 @@ double tile_us(const Tile &t, int M, int N, int nk, int S, int ncu, bool shared)
     };
     double us = t.start + (full + 1.0) * t.round + slices * (full * slice(t.per_cu) + slice(load));
     if (shared) us = 0.3 * us + 0.7 * (t.start + wgs / slots * (t.round + slices * slice(t.per_cu)));
-    us = std::max(us, t.start + bytes_us(M, N, nk));
+    us = std::max(us + t.w_mb * ((double)N * nk * ROW_BYTES * 1e-6), t.start + bytes_us(M, N, nk));
     if (S > 1) us += t.sum0 + t.sum_mb * ((double)S * M * N * 4e-6);
     return us;
 }
