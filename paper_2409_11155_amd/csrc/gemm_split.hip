@@ -404,7 +404,7 @@ unsigned blocks_for(size_t units) { return (unsigned)((units + 255) / 256); }
 // idle units to that one, so there 0.7 of the price is the part of the chip it uses (measured over 60 split layers: 0 and 1
 // instead of 0.7 lose 5 and 2 %) and the switch has to promise 8 %.  (A blend, not a model of the other launch: the QKV products
 // of a 4096-token 70B TP=8 prompt cut in half, 2048 x 1280 x 8192 each, are priced at 55 us and take 94 and 127 side by side.)
-// Never below the time of the weights' bytes from HBM.  Root mean square error 5-8 %; the fastest by these numbers is 0.7 % (bf16
+// Never below the time of the weights' bytes from HBM.  Root mean square error 5-8 %; the fastest by these numbers is 0.9 % (bf16
 // and FP8) slower than the best measured launch on average, 1.2-1.9 % up to 128 rows.  (Without the term for the weights' bytes
 // the small tiles' error is 8-14 % and the pick 1.1 % slower.)
 // The 256-column tiles (kinds 4 to 6, -1, -4, -5) are those of gemm_pp_kernel.h; 192 and 128 rows are for row counts that 256 fit
@@ -470,6 +470,7 @@ double tile_us(const Tile &t, int M, int N, int nk, int S, int ncu, bool shared)
     if (shared) us = 0.3 * us + 0.7 * (t.start + wgs / slots * (t.round + slices * slice(t.per_cu)));
     us = std::max(us + t.w_mb * ((double)N * nk * ROW_BYTES * 1e-6), t.start + bytes_us(M, N, nk));
     if (S > 1) us += t.sum0 + t.sum_mb * ((double)S * M * N * 4e-6);
+    if (S > 6) us *= 1.05;       // eight shares take 5 % more than this on every tile (as many streams of stores)
     return us;
 }
 
