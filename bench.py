@@ -179,7 +179,7 @@ def measure(iso, iso_inputs, args, name, L, K, W, split_arg, full, cpu_baseline)
             except Exception:
                 traffic = None
         r = {"bound": "mfma" if bf16 else "alu",
-             "kernel": ("gemm_bf16_dtl_kernel<.., SWIGLU=true> (gate/up projection + SwiGLU)" if bf16
+             "kernel": ("gemm_pp_kernel<.., SWIGLU> (gate/up projection + SwiGLU)" if bf16
                         else "gemm_f32_kernel<.., EPI_SWIGLU> (gate/up projection + SwiGLU)"),
              "achieved": ach, "peak": peak, "unit": "TFLOP/s", "frac": ach / peak, "traffic": traffic,
              "algorithmic_bytes_per_launch": algorithmic,

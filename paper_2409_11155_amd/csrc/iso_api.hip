@@ -731,6 +731,8 @@ int run_stack(iso_ctx *ctx, const iso_weights *layers, int n_layers, void *x, vo
     //     projections' estimates promise 4.5 %: 70B TP=4 8192 cut at 60 % 3190 -> 3012 us, 70B TP=8 4500 1080 -> 989; of the
     //     cuts that this takes back the mean measured 0.95 of the cut's time, the worst 1.05.  (FP8 estimates leave out the
     //     quantisers and do not tell: 0.90-1.12 at the same estimate.)
+    //     With the 256-column tiles that let two groups of waves take turns, whole / the better of two cuts, four shards: 1024
+    //     and 2048 tokens 0.72-0.98 (bf16) and 0.83-0.96 (FP8), 2900 to 12288 tokens 0.90-1.10 and 0.95-1.14.
     int edges[ISO_MAX_CHUNKS + 1];
     std::copy(edges_in, edges_in + nc + 1, edges);
     const int T = edges[nc];
