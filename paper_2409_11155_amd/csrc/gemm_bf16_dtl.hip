@@ -250,6 +250,24 @@ hipError_t iso_launch_gemm_qkv_rope_bf16_sk(const void *a, const void *w, void *
     return hipGetLastError();
 }
 
+// The same in the 128 x 128 tile, whose waves own 64 output columns (head_dim 64).  The separate kernel is a launch of 5 us that
+// reads and writes all of q, k and v again; layers of 32 + 8 + 8 heads, hidden 2048, where the rule takes this tile: 777 tokens
+// 141.9 -> 139.1 us, 1024 164.9 -> 162.9, two chunks with transfers 1500 404 -> 396.
+hipError_t iso_launch_gemm_qkv_rope_bf16_128(const void *a, const void *w, void *qkv, int M, int N, int K, const iso_rope_args &rp,
+                                             hipStream_t s) {
+    if (rp.d != 64 || N != (rp.nq + 2 * rp.nkv) * 64) return hipErrorInvalidValue;
+    using Cfg = DtlCfg<128, 128, 2, 2>;
+    constexpr int LDS_BYTES = Cfg::W3 ? Cfg::LDS_BYTES_W3 : Cfg::LDS_BYTES;
+    const RopeArgs rope{rp.cos_t, rp.sin_t, (bf16_t *)rp.k_cache, (bf16_t *)rp.v_cache, rp.q_offset, rp.nq, rp.nkv};
+    const int tiles_m = (M + 127) / 128, tiles_n = (N + 127) / 128;
+    static iso_dev_mask lds_allowed{0};
+    auto kern = gemm_bf16_dtl_kernel<128, 128, 2, 2, false, true, false, true>;
+    if (hipError_t e = iso_allow_lds(reinterpret_cast<const void *>(kern), LDS_BYTES, &lds_allowed); e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(tiles_m * tiles_n), dim3(Cfg::NT), LDS_BYTES, s, (const bf16_t *)a, (const bf16_t *)w,
+                       (bf16_t *)qkv, M, N, K, tiles_m, tiles_n, (unsigned char *)nullptr, 0u, (unsigned *)nullptr, 1, 0, rope);
+    return hipGetLastError();
+}
+
 // act[M, F] = silu(a w_gate^T) * (a w_up^T) with w = [gate; up] of shape [2F, K].
 bool iso_gemm_swiglu_bf16_supported(int M, int F, int K) {
     return iso_gemm_bf16_dtl_supported(M, 2 * F, K) && (F % 8) == 0;

@@ -112,16 +112,16 @@ template <int BM, int BN, int WM, int WN> struct DtlCfg {
 // exceeds the spin limit raises *sk_err (a pinned host word that the library reads at its next entry point and in
 // iso_sync) and carries on with a wrong tile.
 //
-// ROPE = true (the QKV projection of a layer with head_dim 128; W = [q heads | k heads | v heads] x 128 rows): the
+// ROPE = true (the QKV projection; W = [q heads | k heads | v heads] x head_dim rows): the
 // epilogue finishes the step that follows the projection (rotary embedding and KV-cache write, what the next chunk's
-// attention waits for, paper Section 3.1).  A wave's 128 output columns are exactly one head, and the rotation pairs
-// (c, c + 64) of a row are both in the wave's staging area, so q and k heads are rotated at position q_offset + row
+// attention waits for, paper Section 3.1).  A wave's output columns are exactly one head (128 of them in the stream-K
+// launch, 64 in the 128 x 128 tile), and the rotation pairs (c, c + head_dim / 2) of a row are both in the wave's staging area, so q and k heads are rotated at position q_offset + row
 // on their way from the staging area to memory (same arithmetic and roundings as the separate rotary kernel: the
 // bf16 projection output is rotated in fp32 and rounded again), q heads go to C, k and v heads straight to rows
 // q_offset + row of the caches; the k/v columns of C are not written.
 struct RopeArgs {
-    const float *cos_t, *sin_t;      // [max_seq, 64] fp32 tables
-    bf16_t *k_cache, *v_cache;       // [max_seq, nkv, 128]
+    const float *cos_t, *sin_t;      // [max_seq, head_dim / 2] fp32 tables
+    bf16_t *k_cache, *v_cache;       // [max_seq, nkv, head_dim]
     int q_offset, nq, nkv;
 };
 
@@ -367,6 +367,7 @@ __device__ __forceinline__ void gemm_dtl_body(const typename OP::elem *__restric
                 for (int r = 0; r < 16; ++r) sa_r[i][r] = sa[min(m0 + wm * Cfg::WTM + i * 32 + blk_row(r), M - 1)];
         }
         if (!SWIGLU) {
+            constexpr int HD = Cfg::WTN;                         // ROPE: head_dim
             const int gm0 = m0 + wm * Cfg::WTM, gn0 = n0 + wn * Cfg::WTN;
             // where this wave's columns go: C, or (ROPE) the head's place in a cache row
             bf16_t *dst = C + gn0;
@@ -374,13 +375,13 @@ __device__ __forceinline__ void gemm_dtl_body(const typename OP::elem *__restric
             int dst_row0 = gm0;
             bool rotate = false;                                 // wave-uniform
             if constexpr (ROPE) {
-                static_assert(Cfg::WTN == 128 && TN == 4, "a wave's columns are one head of 128");
-                const int head = gn0 / 128;                      // wave-uniform
+                static_assert(Cfg::WTN == 128 || Cfg::WTN == 64, "a wave's columns are one head");
+                const int head = gn0 / HD;                       // wave-uniform
                 rotate = head < rope.nq + rope.nkv;              // q and k heads
                 if (head >= rope.nq) {                           // k or v head: rows q_offset + m of its cache
                     const bool is_k = head < rope.nq + rope.nkv;
-                    dst = (is_k ? rope.k_cache : rope.v_cache) + (size_t)(head - rope.nq - (is_k ? 0 : rope.nkv)) * 128;
-                    dst_stride = (size_t)rope.nkv * 128;
+                    dst = (is_k ? rope.k_cache : rope.v_cache) + (size_t)(head - rope.nq - (is_k ? 0 : rope.nkv)) * HD;
+                    dst_stride = (size_t)rope.nkv * HD;
                     dst_row0 = rope.q_offset + gm0;
                 }
             }
@@ -403,8 +404,8 @@ __device__ __forceinline__ void gemm_dtl_body(const typename OP::elem *__restric
             constexpr int PIECES = Cfg::WTM * CPR;
             static_assert(PIECES % 64 == 0, "whole wave-stores");
             if (ROPE && rotate) {
-                // rotary embedding on the way out: a lane takes the 16-byte piece at columns cc .. cc + 7 (cc < 64) of
-                // a row together with its partner at cc + 64, the row's cos / sin for those eight pairs as four
+                // rotary embedding on the way out: a lane takes the 16-byte piece at columns cc .. cc + 7 of the
+                // head's first half in a row together with its partner in the second half, the row's cos / sin for those eight pairs as four
                 // 16-byte loads, and writes both rotated pieces (the accumulators are no longer live here, so the
                 // table loads of several pieces can be in flight at once)
                 constexpr int HPR = CPR / 2;         // piece pairs per row
@@ -414,7 +415,7 @@ __device__ __forceinline__ void gemm_dtl_body(const typename OP::elem *__restric
                     const int row = p / HPR, cc = (p % HPR) * 8;
                     const int gm = gm0 + row;
                     if (gm < M && gn0 < N) {         // a head is entirely inside or outside the matrix
-                        const size_t t = (size_t)(rope.q_offset + gm) * 64 + cc;
+                        const size_t t = (size_t)(rope.q_offset + gm) * (HD / 2) + cc;
                         const float4 c0 = *reinterpret_cast<const float4 *>(rope.cos_t + t);
                         const float4 c1 = *reinterpret_cast<const float4 *>(rope.cos_t + t + 4);
                         const float4 s0 = *reinterpret_cast<const float4 *>(rope.sin_t + t);
@@ -422,17 +423,17 @@ __device__ __forceinline__ void gemm_dtl_body(const typename OP::elem *__restric
                         const float cs[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
                         const float sn[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
                         const bf16x8_t lo = *reinterpret_cast<const bf16x8_t *>(ct + row * Cfg::CP + cc);
-                        const bf16x8_t hi = *reinterpret_cast<const bf16x8_t *>(ct + row * Cfg::CP + cc + 64);
+                        const bf16x8_t hi = *reinterpret_cast<const bf16x8_t *>(ct + row * Cfg::CP + cc + HD / 2);
                         bf16x8_t olo, ohi;
 #pragma unroll
                         for (int e = 0; e < 8; ++e) {
                             const float l = (float)lo[e], h = (float)hi[e];
-                            olo[e] = (bf16_t)(l * cs[e] - h * sn[e]);
-                            ohi[e] = (bf16_t)(h * cs[e] + l * sn[e]);
+                            olo[e] = (bf16_t)fmaf(l, cs[e], -(h * sn[e]));   // fused on the same side as in rope_kv_kernel
+                            ohi[e] = (bf16_t)fmaf(h, cs[e], l * sn[e]);
                         }
                         bf16_t *o = dst + (size_t)(dst_row0 + row) * dst_stride + cc;
                         *reinterpret_cast<bf16x8_t *>(o) = olo;
-                        *reinterpret_cast<bf16x8_t *>(o + 64) = ohi;
+                        *reinterpret_cast<bf16x8_t *>(o + HD / 2) = ohi;
                     }
                 }
             } else {

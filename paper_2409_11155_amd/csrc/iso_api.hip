@@ -472,7 +472,7 @@ int attn_block_head(iso_ctx *ctx, const iso_weights *w, void *x, void *kc, void 
         return ISO_OK;
     }
     // bf16 layers: rotary embedding and KV-cache write ride in the projection's epilogue whenever the launch rule picks, for every
-    // segment, a kernel that holds whole heads (the 256-column tiles; bf16 and heads of 128 also the stream-K launch)
+    // segment, a kernel that holds whole heads (the 256-column tiles; bf16 also, for heads of 128, the stream-K launch and, for heads of 64, the 128 x 128 tile)
     const int D = c.head_dim;
     if (c.dtype == ISO_BF16 && (D == 64 || D == 128) && !(ctx->flags & (ISO_FLAG_SIMPLE_GEMM | ISO_FLAG_GEMM_STAGED | ISO_FLAG_NO_FUSE)) &&
         (fp8_qkv || iso_gemm_bf16_dtl_supported(ck.n, NQKV, H))) {
@@ -484,7 +484,7 @@ int attn_block_head(iso_ctx *ctx, const iso_weights *w, void *x, void *kc, void 
         bool all_fusable = true;
         ISO_TRY(for_segments(ctx, ck.n, [&](int, int n) {
             const int v = variant(n);
-            all_fusable = all_fusable && (v == 1 || v == 4 || v == 5 || (v == 6 && D == 128 && !fp8_qkv));
+            all_fusable = all_fusable && (v == 1 || v == 4 || v == 5 || (!fp8_qkv && v == (D == 128 ? 6 : 3)));
             return (int)ISO_OK;
         }));
         if (all_fusable) {
@@ -499,6 +499,7 @@ int attn_block_head(iso_ctx *ctx, const iso_weights *w, void *x, void *kc, void 
                 const iso_pp_args o{a, fp8_qkv ? f8.w8 : w->w_qkv, fp8_qkv ? sa + lo : nullptr, fp8_qkv ? f8.sw : nullptr, out, nullptr,
                                     n, NQKV, H, 1, rope, {}};
                 const hipError_t e_ = v == 6 ? iso_launch_gemm_qkv_rope_bf16_sk(a, w->w_qkv, out, n, NQKV, H, sk_for(ctx, ck.s), rope, ck.s)
+                                : v == 3 ? iso_launch_gemm_qkv_rope_bf16_128(a, w->w_qkv, out, n, NQKV, H, rope, ck.s)
                                              : iso_launch_gemm_pp(v == 1 ? 256 : v == 4 ? 128 : 192, ISO_PP_ROPE, o, ck.s);
                 if (e_ != hipSuccess) return fail(ISO_ERR_HIP, "qkv+rope launch: %s", hipGetErrorString(e_));
                 return (int)ISO_OK;
