@@ -485,6 +485,7 @@ bool iso_gemm_split_supported(bool fp8, int M, int N, int K) {
 // `whole` is the whole-tile rule's own choice (variant 1, 3, 4, 5 or 6 = stream-K).  It stays unless something else is estimated
 // faster (by 8 % beside another chunk).  ws_bytes: room for partial sums (0: one share only).  `rope`: the QKV projection; tiles
 // of 256 columns and shares (through their second kernel) finish with the rotary step, the others need a kernel more (5 us).
+// (bf16 128 x 128 tiles with heads of 64 rotate as well and keep that price: at the measured 2.2 us 14 layers chose the same.)
 // *us_or_null: the estimate for the plan returned.
 iso_split_plan iso_gemm_split_plan(bool fp8, bool rope, int whole, int M, int N, int K, size_t ws_bytes, int ncu, bool shared,
                                    double *us_or_null) {
