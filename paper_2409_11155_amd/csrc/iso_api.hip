@@ -294,6 +294,9 @@ int attention(iso_ctx *ctx, const void *q, int q_stride, const void *kc, const v
     const iso_cfg &c = ctx->cfg;
     Timed t_(ctx, ISO_K_ATTN, s);
     hipError_t e;
+    // From kv_len on every row sees the whole cache.  The kernels add row numbers to the offset in 32 bits: near 2^31 the sum would
+    // overflow, and with it the end of what they may read.
+    q_offset = std::min(q_offset, kv_len);
     // Over a handful of keys the one-wave-per-row kernel is done before the others have filled their first tile.  Kernel times
     // in us, it / the matrix-core kernel of the type, as many rows as keys: fp32 heads of 64 over 1 key 2.9 / 4.0, over 16 4.7 /
     // 5.2, 32 6.3 / 5.3; fp32 heads of 128 1 key 3.8 / 7.8, 37 8.6 / 9.7, 64 12.1 / 9.6; bf16 heads of 64 1 key 3.1 / 5.0, 13 5.0 /

@@ -17,7 +17,7 @@ static std::mutex g_lock;
 static std::string g_log;                       // one line per call: what, stream, detail
 static std::map<const void *, std::string> &names() { static std::map<const void *, std::string> m; return m; }
 static size_t g_refuse;                         // hipMalloc of this many bytes fails
-static int g_last, g_launch_us, g_capturing;
+static int g_last, g_launch_us, g_capturing, g_arg = -1;
 static std::set<const void *> g_pinned;
 static long g_handles = 0x100;
 struct Call { dim3 grid, block; size_t lds; stream_t s; };
@@ -32,6 +32,7 @@ extern "C" {
 void fake_refuse(size_t bytes) { g_refuse = bytes; }
 void fake_launch_us(int us) { g_launch_us = us; }
 void fake_capturing(int on) { g_capturing = on; }
+void fake_int_argument(int i) { g_arg = i; }     // note the i-th argument of every launch, an int (-1: none)
 const char *fake_log() { return g_log.c_str(); }
 void fake_clear() { g_log.clear(); }
 
@@ -41,8 +42,9 @@ void __hipRegisterFunction(void **, const void *host, char *, const char *name, 
 void __hipRegisterVar(void **, void *, char *, char *, int, size_t, int, int) {}
 int __hipPushCallConfiguration(dim3 g, dim3 b, size_t lds, stream_t s) { t_call = Call{g, b, lds, s}; return 0; }
 int __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *lds, stream_t *s) { *g = t_call.grid; *b = t_call.block; *lds = t_call.lds; *s = t_call.s; return 0; }
-int hipLaunchKernel(const void *f, dim3 g, dim3, void **, size_t, stream_t s) {
-    note("kernel", s, names()[f] + " " + std::to_string(g.x) + "x" + std::to_string(g.y) + "x" + std::to_string(g.z));
+int hipLaunchKernel(const void *f, dim3 g, dim3, void **args, size_t, stream_t s) {
+    note("kernel", s, names()[f] + " " + std::to_string(g.x) + "x" + std::to_string(g.y) + "x" + std::to_string(g.z) +
+                          (g_arg < 0 ? "" : " " + std::to_string(*(int *)args[g_arg])));
     if (g_launch_us) usleep(g_launch_us);
     return 0;
 }

@@ -61,6 +61,18 @@ def test_a_later_tokens_non_finite_value(d, Tc, q_offset, bad):
     invisible.test_a_later_tokens_non_finite_value_stays_out_of_the_earlier_rows("bf16", d, WAVE, Tc, q_offset, bad)
 
 
+@pytest.mark.parametrize("dt,d,flags", [("bf16", 64, WAVE), ("bf16", 128, WAVE), ("bf16", 128, 1 << 14), ("bf16", 128, 3 << 12),
+                                        ("f32", 64, 0), ("f32", 128, 0)])
+def test_a_chunk_that_begins_far_behind_the_cache(dt, d, flags):
+    """Every row sees the whole cache: the same bits as from the offset where that begins."""
+    Tc, kv, nq = 70, 90, 4
+    q, k, v = iso_inputs.make_qkv_cache(Tc, kv, nq, 2, d, seed=5, dtype=dt)
+    with make_ctx(256, nq, 2, d, 64, dt, kv) as ctx:
+        ctx.set_flags(flags)
+        near, far = (invisible.attend(ctx, q, k, v, dt, nq, d, Tc, off, kv) for off in (kv - 1, 2 ** 31 - 1))
+    assert (near == far).all()
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_scores_far_below_zero(d):
     invisible.test_scores_far_below_zero("bf16", d, WAVE)

@@ -209,3 +209,23 @@ with iso.Context(iso.make_cfg(hidden, nq, nkv, d, ffn, "bf16", T)) as ctx:
         assert e.code == iso.ISO_ERR_HIP
     call()
 """)
+
+
+def test_an_offset_far_behind_the_cache_reaches_the_kernels_as_the_end_of_the_cache(fake):
+    """A chunk may begin behind the last key: every row sees the whole cache then, whatever the offset.  The kernels add row numbers
+    to it in 32 bits; a sum that overflows would put the last visible key below zero and the end of the buffer anywhere."""
+    run(fake, """
+fake.fake_int_argument(5)                    # q_offset of every attention kernel
+for dt in ("f32", "bf16"):
+    for d in (64, 128):
+        with iso.Context(iso.make_cfg(256, 4, 2, d, 64, dt, 700)) as ctx:
+            q = array(700, 512, dt=dt)
+            for flags in (0, 7 << 14, 1 << 12, 2 << 14, iso.ISO_FLAG_ATTN_STAGED, iso.ISO_FLAG_SIMPLE_ATTN):
+                ctx.set_flags(flags)
+                for Tc, kv in ((1, 1), (300, 8), (64, 700), (700, 300)):
+                    for off in (0, kv - 1, kv, kv + 1, 2 ** 31 - Tc - 1, 2 ** 31 - 1):
+                        log()
+                        ctx.attn_chunk(q, q, q, q, Tc, off, kv, ctx.stream0)
+                        (launch,) = log()
+                        assert int(launch[2].split()[-1]) == min(off, kv), (dt, d, flags, Tc, kv, off, launch)
+""")
