@@ -15,6 +15,11 @@ SOURCES = ["iso_api.hip", "elementwise.hip", "gemm_simple.hip", "gemm_bf16_mfma.
            "attn_bf16_mfma.hip", "attn_bf16_dtl.hip", "attn_bf16_wave.hip"]
 
 
+# what decides the device code
+DEVICE_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+                "-I", os.path.join(ROOT, "include"), "-I", CSRC]
+
+
 def hipcc() -> str:
     for cand in (shutil.which("hipcc"), "/opt/rocm/bin/hipcc"):
         if cand and os.path.exists(cand):
@@ -24,11 +29,7 @@ def hipcc() -> str:
 
 def build(verbose: bool = True) -> str:
     """Compiles every HIP source for gfx950 and links libiso.so next to this file."""
-    cmd = [hipcc(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
-           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-           "-Wno-unused-command-line-argument",
-           "-I", os.path.join(ROOT, "include"), "-I", CSRC,
-           "-o", LIB_PATH] + [os.path.join(CSRC, s) for s in SOURCES]
+    cmd = [hipcc(), *DEVICE_FLAGS, "-fPIC", "-shared", "-Wno-unused-command-line-argument", "-o", LIB_PATH] + [os.path.join(CSRC, s) for s in SOURCES]
     if verbose:
         print(" ".join(cmd), flush=True)
     proc = subprocess.run(cmd, capture_output=True, text=True)

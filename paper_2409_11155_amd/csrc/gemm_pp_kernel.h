@@ -48,7 +48,8 @@ template <int BM_> struct PpCfg {
 
 // c += a b^T, 16 x 16 x 128 E4M3.  In place: left to the builtin the compiler gives the result other registers than the sum it
 // adds to, and the accumulators travel through the register file until some are spilled inside the loop.  The compiler does not
-// see that this is a matrix instruction: nothing but another of the same may touch `c` within 18 cycles behind it.
+// see that this is a matrix instruction: nothing but another of the same may touch `c` within 18 wait states behind it, which the
+// kernel sees to behind its loop and tests/test_isa_cpu.py in what is built.
 __device__ __forceinline__ void pp_mac8(f32x4_t &c, const i32x8_t &a, const i32x8_t &b) {
 #if defined(__HIP_DEVICE_COMPILE__)
     asm volatile("v_mfma_f32_16x16x128_f8f6f4 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
@@ -261,7 +262,17 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const unsigned char *__
     }
     if (t < nk) slice(t, I0{}, I0{}, I1{});
     if (!wm) swap();
-    if constexpr (F8) asm volatile("s_nop 15\n\ts_nop 15");   // the last products, see pp_mac8
+    if constexpr (F8) {                  // the last products, see pp_mac8: no use of a sum moves above the wait
+        asm volatile("s_nop 15\n\ts_nop 15");
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) asm volatile("" : "+v"(acc[h][g][i][j]));
+    }
     PP_WAIT(0);
     swap();                              // nothing is on its way to LDS any more, nobody reads operands
 #undef PP_WAIT
@@ -299,8 +310,9 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const unsigned char *__
     }
     constexpr int OC = EPI == PP_SWIGLU ? 128 : 256;     // output columns of the tile
     constexpr int PITCH = OC * 2 + 16;
-    // PP_RESID: x (+ pa) of this thread's pieces, in two batches: the first is requested here and travels under the staging
-    constexpr int PIECES = BM * (OC / 8) / 512, BATCH = PIECES / 2;
+    // PP_RESID: x (+ pa) of this thread's pieces, in two batches (FP8, 256 rows: four, or three registers are spilled): the first is
+    // requested here and travels under the staging
+    constexpr int PIECES = BM * (OC / 8) / 512, BATCHES = F8 && BM == 256 ? 4 : 2, BATCH = PIECES / BATCHES;
     bf16x8_t xv[EPI == PP_RESID ? BATCH : 1], pv[EPI == PP_RESID ? BATCH : 1];
     auto piece_at = [&](int it, size_t &at) {
         const int p = etid + it * 512, gm = m0 + p / (OC / 8), gn = n0 + (p % (OC / 8)) * 8;
@@ -375,8 +387,8 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const unsigned char *__
     if constexpr (EPI == PP_RESID) {
         // x = (x + pa) + bf16(result), in fp32 and in the order of the residual kernel
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            if (b) fetch(BATCH);
+        for (int b = 0; b < BATCHES; ++b) {
+            if (b) fetch(b * BATCH);
 #pragma unroll
             for (int i = 0; i < BATCH; ++i) {
                 const int p = etid + (b * BATCH + i) * 512;
