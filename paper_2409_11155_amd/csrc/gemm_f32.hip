@@ -41,8 +41,10 @@ struct RopeF32 {
 };
 
 // What stands before the product: A as it is, or A = rmsnorm(x) * g / rmsnorm(x + delta) * g, computed by every workgroup for
-// its own sixteen rows.  A wave then holds its whole part of the rows in registers (K <= 16 * KW * UNROLL), the squares meet in LDS, and the two launches before the projections of a short call are gone (128 tokens of 256: a pass is set by how fast the
-// host enqueues: 11 launches 42.3 us; 7, with this and the copies to the host below, 35.5, of which the kernels take 34).
+// its own sixteen rows.  A wave then holds its whole part of the rows in registers (K <= 16 * KW * UNROLL), the squares meet in LDS,
+// and the two launches before the projections of a short call are gone (128 tokens of 256: a pass is set by how fast the host
+// enqueues: 11 launches 42.3 us; 7, with this and the copies to the host below, 35.5, of which the kernels take 34).  Where that
+// pays: iso_gemm_f32_norm_supported.
 enum { NORM_NONE = 0, NORM_X = 1, NORM_X_DELTA = 2 };
 struct NormF32 {
     const float *delta, *g;
@@ -197,7 +199,8 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
 // Small tiles until there are 256 of the large ones.
 bool small_tiles(int M, int n_out) { return (long long)((M + 63) / 64) * ((n_out + 63) / 64) < 256; }
 
-constexpr int NORM_MAX_K = 16 * 4 * 12;      // a row in the registers of four waves
+// A row in the registers of four waves, with the rounds of loads that a norm is built for (see iso_gemm_f32_norm_supported).
+constexpr int norm_max_k(int norm) { return 16 * 4 * (norm == NORM_X_DELTA ? 4 : 12); }
 
 template <int EPI, int NORM = NORM_NONE>
 hipError_t launch_f32(const void *a, const void *w, void *c, void *sink, int M, int N, int K, const RopeF32 &rope,
@@ -213,13 +216,16 @@ hipError_t launch_f32(const void *a, const void *w, void *c, void *sink, int M, 
             return hipGetLastError();
         }
     }
-    if (NORM != NORM_NONE && K > NORM_MAX_K) return hipErrorInvalidValue;
-    if (K <= 4 * 4 * 16)
-        hipLaunchKernelGGL((gemm_f32_kernel<16, 1, 1, 4, 4, EPI, NORM>), grid16, dim3(256), 0, s, af, wf, (float *)c, (float *)sink, M,
-                           N, K, rope, norm);
-    else
-        hipLaunchKernelGGL((gemm_f32_kernel<16, 1, 1, 4, 12, EPI, NORM>), grid16, dim3(256), 0, s, af, wf, (float *)c, (float *)sink,
-                           M, N, K, rope, norm);
+    if (NORM != NORM_NONE && K > norm_max_k(NORM)) return hipErrorInvalidValue;
+    if constexpr (NORM != NORM_X_DELTA) {
+        if (K > 4 * 4 * 16) {
+            hipLaunchKernelGGL((gemm_f32_kernel<16, 1, 1, 4, 12, EPI, NORM>), grid16, dim3(256), 0, s, af, wf, (float *)c,
+                               (float *)sink, M, N, K, rope, norm);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((gemm_f32_kernel<16, 1, 1, 4, 4, EPI, NORM>), grid16, dim3(256), 0, s, af, wf, (float *)c, (float *)sink, M, N,
+                       K, rope, norm);
     return hipGetLastError();
 }
 
@@ -235,10 +241,20 @@ hipError_t iso_launch_gemm_f32(const void *a, const void *w, void *c, void *sink
     return launch_f32<EPI_NONE>(a, w, c, sink, M, N, K, RopeF32{}, NormF32{}, s);
 }
 
-// The projections behind a norm take the norm's inputs instead of its output where a row fits the registers of a workgroup and
-// the tiles are the small ones.
+// The projections behind a norm take the norm's inputs instead of its output where that is not behind the norm kernel: every column
+// tile computes the norm again, against one launch and one trip to memory saved.  Layers of seven shapes, 1 to 2048 tokens, us a
+// layer with the norm kernel / in the projection:
+//   * Gate/up, whose norm adds two rows and whose tiles hold two blocks of W: K <= 256 and two tiles for every unit.  K = 256: 128
+//     tokens (344 tiles) 29.2 / 28.8, 160 (430) 31.0 / 30.4, 192 (516) 34.0 / 34.4, 777 (2107) 66.6 / 69.8; K = 128: 333 tokens
+//     (462) 31.6 / 30.6.  Beyond K = 256 a wave holds twelve rounds of everything and never gains: K = 512, 32 tokens 38.0 / 38.9, 64
+//     42.6 / 47.1, 512 122 / 166; K = 768, 400 tokens 191 / 253.
+//   * QKV: K <= 256 always, beyond it four tiles for every unit.  K = 256: 128 tokens 30.6 / 29.2, 777 69.1 / 66.6; K = 512: 333
+//     tokens (1008 tiles) 94.8 / 93.1; K = 264: 640 tokens (640) 78.2 / 78.4, 1472 (1472) 135.0 / 137.8.
 bool iso_gemm_f32_norm_supported(const iso_norm_args &norm, int M, int n_out, int K) {
-    return K <= NORM_MAX_K && small_tiles(M, n_out) && ((uintptr_t)norm.x | (uintptr_t)norm.delta | (uintptr_t)norm.g) % 16 == 0;
+    const long long tiles = (long long)((M + 15) / 16) * ((n_out + 15) / 16), units = iso_num_cu();
+    if (norm.delta ? K > norm_max_k(NORM_X_DELTA) || tiles > 2 * units : K > 256 && (K > norm_max_k(NORM_X) || tiles > 4 * units))
+        return false;
+    return small_tiles(M, n_out) && ((uintptr_t)norm.x | (uintptr_t)norm.delta | (uintptr_t)norm.g) % 16 == 0;
 }
 
 hipError_t iso_launch_gemm_swiglu_f32(const void *a, const void *w, void *act, int M, int F, int K, const iso_norm_args *norm,

@@ -229,3 +229,22 @@ for dt in ("f32", "bf16"):
                         (launch,) = log()
                         assert int(launch[2].split()[-1]) == min(off, kv), (dt, d, flags, Tc, kv, off, launch)
 """)
+
+
+def test_norms_stay_kernels_where_the_fp32_projections_would_repeat_them_too_often(fake):
+    """Gate/up computes its norm up to 256 columns of hidden state and two tiles (16 x 16) a unit, QKV up to 768 columns and, beyond
+    256 of them, four tiles a unit; both sides of each line."""
+    run(fake, """
+for hidden, heads, ffn, T, in_qkv, in_gate_up in (
+        (256, 4, 688, 128, 1, 1), (256, 4, 688, 176, 1, 1), (256, 4, 688, 192, 1, 0), (256, 4, 688, 1024, 1, 0), (128, 2, 344, 368, 1, 1),
+        (128, 2, 344, 400, 1, 0), (264, 4, 688, 16, 1, 0), (512, 8, 1376, 333, 1, 0), (512, 8, 1376, 352, 0, 0), (768, 6, 1024, 400, 1, 0),
+        (776, 6, 1024, 16, 0, 0)):
+    w = layer(hidden, heads, heads, 64, ffn, "f32")
+    with iso.Context(iso.make_cfg(hidden, heads, heads, 64, ffn, "f32", T)) as ctx:
+        x, k, v = array(T, hidden, dt="f32"), array(T, heads, 64, dt="f32"), array(T, heads, 64, dt="f32")
+        log()
+        ctx.layer_prefill(w, x, k, v, T, 0, iso.ISO_COMM_NONE)
+        names = [l[2] for l in log() if l[0] == "kernel"]
+        norms = [sum("rmsnorm_kernelIfLi%dELb0ELb1E" % deltas in n for n in names) for deltas in (0, 1)]
+        assert norms == [1 - in_qkv, 1 - in_gate_up], (hidden, T, norms)
+""")
