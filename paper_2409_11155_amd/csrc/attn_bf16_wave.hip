@@ -280,15 +280,27 @@ hipError_t launch(const void *q, const void *k, const void *v, void *out, int Tc
 }  // namespace
 
 // Where this kernel is ahead of the 128-row blocks.  It takes 5 us and 4 us for every 1000 keys of a round of the chip, the other
-// one 7 to 12 us, less for every further key and row.  Measured, us, that one / this one, 396 sizes: 13 heads of 128, 333 rows over
-// 333 keys 12.1 / 7.8, over 1333 19.3 / 12.6, over 2333 22.7 / 18.1, over 4333 29.1 / 29.2; 16 rows over 2016 17.4 / 13.5, over 4016
-// 20.7 / 25.5; 8 heads, 200 rows alone 10.2 / 6.8, 1024 rows alone 19.5 / 11.3.  Two workgroups for every place on the chip: 13
-// heads, 777 rows over 1277 keys 21.7 / 20.8, over 1777 25.4 / 25.8; 16 heads, 1024 rows alone 20.5 / 17.1, three 26.6 / 29.2.  Heads
-// of 64 (two workgroups fit a unit): 32 heads, 333 rows over 1333 keys 18.1 / 15.5, 777 over 1777 30.2 / 26.8, 1024 alone 20.2 / 19.0,
-// 2048 alone 38.7 / 46.3.
+// one 7 to 12 us, less for every further key and row.  Measured, us, that one / this one (3700 sizes, 8 to 64 heads):
+//   * One round: 13 heads of 128, 333 rows over 333 keys 12.1 / 7.8, over 1333 19.3 / 12.6, over 2333 22.7 / 18.1, over 4333 29.1 /
+//     29.2; 16 rows over 2016 17.4 / 13.5, over 4016 20.7 / 25.5; 8 heads, 200 rows alone 10.2 / 6.8, 1024 rows alone 19.5 / 11.3.
+//     Heads of 64 put two workgroups on a unit; where they do and the other kernel deals the keys to three workgroups, its line
+//     is earlier: 12 heads, 859 rows alone 12.0 / 10.6, over 1609 keys 15.5 / 15.8, over 2459 18.6 / 20.8.
+//   * Two rounds: no longer twice as good a start, so rows enough (more than 480) that the second round's blocks are short ones: 64
+//     heads of 128, 197 rows alone 10.4 / 12.0; 28 heads, 384 rows over 1384 keys 20.4 / 22.3; 64 heads of 64, 453 rows 11.3 / 13.8.
+//     Heads of 128: 13 heads, 777 rows over 1277 keys 22.3 / 21.8, over 1777 25.4 / 25.8; 16 heads, 1024 rows alone 22.5 / 18.6; where the
+//     other kernel deals the keys to three workgroups, only while the block that runs second on a place ends before the longest
+//     one: 8 heads, 1189 rows over 1439 18.2 / 16.6, but 20 heads, 507 rows over 1507 20.2 / 22.5.  Heads of 64 up to 1.6 rounds: 32
+//     heads, 600 rows alone 13.5 / 12.0, 777 15.8 / 15.6, over 1777 30.6 / 27.8, but 965 over 1965 (1.94 rounds) 29.8 / 31.7, 40
+//     heads, 667 alone (1.64) 13.5 / 14.6, 20 heads, 1600 alone (1.95) 23.5 / 24.2.
+// At 2070 sizes that the lines were not drawn with (8 to 52 heads, a third of a round to two): 0.83 of the other kernel's time; 37 of
+// them are more than 2 % behind it, 18 more than 4 %, the worst 12 % (36 heads of 64, 704 rows alone 13.3 / 14.9).
 bool iso_attn_bf16_wave_wanted(int Tc, int nq, int d, long long keys) {
-    const long long wgs = (long long)((Tc + RB - 1) / RB) * nq, places = (long long)iso_num_cu() * (d == 64 ? 2 : 1);
-    return wgs <= places ? keys <= 2816 : wgs <= 2 * places && keys <= (d == 64 ? 2048 : 1536);
+    const long long ncu = iso_num_cu(), wgs = (long long)((Tc + RB - 1) / RB) * nq, places = ncu * (d == 64 ? 2 : 1);
+    const bool in_three = 3ll * ((Tc + 127) / 128) * nq <= ncu;      // the other kernel's 128-row blocks, keys in three shares
+    if (wgs <= places) return keys <= (wgs > ncu && in_three ? 1536 : 2816);
+    if (Tc <= 480) return false;
+    if (d == 64) return 5 * wgs <= 8 * places && keys <= 2048;
+    return wgs <= 2 * places && keys <= 1536 && !(in_three && keys * wgs > 2ll * Tc * places);
 }
 
 hipError_t iso_launch_attn_bf16_wave(const void *q, const void *k, const void *v, void *out, int Tc, int q_offset, int kv_len,

@@ -248,3 +248,23 @@ for hidden, heads, ffn, T, in_qkv, in_gate_up in (
         norms = [sum("rmsnorm_kernelIfLi%dELb0ELb1E" % deltas in n for n in names) for deltas in (0, 1)]
         assert norms == [1 - in_qkv, 1 - in_gate_up], (hidden, T, norms)
 """)
+
+
+def test_attention_of_few_rows_takes_the_wave_kernel_where_it_is_ahead(fake):
+    """Both sides of every line of the rule, on 256 units: keys and rounds, the rows that a second round needs, and the places
+    where the other kernel splits the keys over three workgroups."""
+    run(fake, """
+for d, heads, Tc, keys, wave in (
+        (128, 13, 333, 2816, 1), (128, 13, 333, 2817, 0), (128, 8, 1024, 2816, 1), (64, 32, 512, 2816, 1), (64, 8, 32, 2817, 0),
+        (64, 12, 704, 1536, 1), (64, 12, 704, 1537, 0), (64, 12, 672, 2816, 1), (64, 12, 897, 2816, 1),
+        (128, 16, 513, 960, 1), (128, 20, 480, 480, 0), (128, 20, 481, 481, 1), (64, 40, 480, 480, 0), (64, 40, 481, 481, 1),
+        (128, 16, 1024, 1536, 1), (128, 16, 1024, 1537, 0), (128, 16, 1025, 1025, 0),
+        (128, 16, 600, 1010, 1), (128, 16, 600, 1011, 0), (128, 16, 700, 1536, 1),
+        (64, 32, 800, 2048, 1), (64, 32, 800, 2049, 0), (64, 32, 801, 801, 0)):
+    with iso.Context(iso.make_cfg(256, heads, heads, d, 64, "bf16", keys)) as ctx:
+        q = array(8, 8)
+        log()
+        ctx.attn_chunk(q, q, q, q, Tc, keys - Tc if keys >= Tc else 0, keys, ctx.stream0)
+        (launch,) = log()
+        assert ("attn_bf16_wave" in launch[2]) == bool(wave), (d, heads, Tc, keys, launch)
+""")
