@@ -395,8 +395,10 @@ unsigned blocks_for(size_t units) { return (unsigned)((units + 255) / 256); }
 
 
 // ---- which kernel ----------------------------------------------------------------------------------------------
-// Microseconds of a launch, as fitted to 24 000 launches measured on MI355X (16 matrix shapes of the 30B / 70B shards and
-// of a heads-of-64 layer, 22 row counts from 16 to 8192, every tile with 1 to 8 shares, weights from HBM):
+// Microseconds of a launch, as fitted to 70 000 launches of 1751 products measured on MI355X (16 matrix shapes of the 30B / 70B shards
+// and of a heads-of-64 layer with 39 row counts from 1 to 6000, 260 others with 8 to 12000 columns and k from 128 to 14336; every tile
+// whole up to four rounds of the chip and with 2 to 15 shares; every launch's weights from HBM, which takes a gigabyte of them in
+// turn: 24 copies of a small matrix stay in the 256 MB cache):
 //     start + rounds * round + slices * slice(load) + w_mb * MB of weights + [shares > 1] (sum0 + sum_mb * MB of partial sums)
 // with rounds = times the launch fills the chip (`per_cu` workgroups on each unit), load = workgroups per unit in the last
 // round: slice(load) = slice + crowd * min(load, 1), and + pair * (pair0 + (1 - pair0) (load - 1)) when some units hold two.
@@ -404,43 +406,44 @@ unsigned blocks_for(size_t units) { return (unsigned)((units + 255) / 256); }
 // idle units to that one, so there 0.7 of the price is the part of the chip it uses (measured over 60 split layers: 0 and 1
 // instead of 0.7 lose 5 and 2 %) and the switch has to promise 8 %.  (A blend, not a model of the other launch: the QKV products
 // of a 4096-token 70B TP=8 prompt cut in half, 2048 x 1280 x 8192 each, are priced at 55 us and take 94 and 127 side by side.)
-// Never below the time of the weights' bytes from HBM.  Root mean square error 5-8 %; the fastest by these numbers is 0.9 % (bf16
-// and FP8) slower than the best measured launch on average, 1.2-1.9 % up to 128 rows.  (Without the term for the weights' bytes
-// the small tiles' error is 8-14 % and the pick 1.1 % slower.)
+// Never below the time of the weights' bytes from HBM.  Root mean square error 4-7 % where a launch is within 1.3 of the best; the
+// fastest by these numbers is 1.0 % (bf16) and 1.7 % (FP8) slower than the best measured launch on average.  (Fitted to launches of
+// at most 600 workgroups and eight shares over weights half of which were in the cache it was 2.2 and 2.8 %, and narrow tiles were
+// taken for twenty rounds of the chip: 5442 x 7992 x 192 83 us, now 33.)  338 layers of seven shards, 1 to 9000 tokens, against that
+// fit: 0.995 of the time, 71 more than 1.5 % faster and 17 slower.
 // The 256-column tiles (kinds 4 to 6, -1, -4, -5) are those of gemm_pp_kernel.h; 192 and 128 rows are for row counts that 256 fit
 // badly or that leave units idle: 1500 x 8192 x 3584 73.8 us with 256 rows, 65.5 with 192; 8192 x 2560 x 8192 300 / 250; 1024 x 8960
-// x 6656 125 / 101; 777 x 7168 x 8192 123 / 105, with 128 rows 96.  Stream-K was the fastest of all launches in 1 of 192 bf16
-// products (2048 x 8960 x 6656, 198 / 209) and in no FP8 one.  The 128-row shares carry 1.5 us that the fit does not show and a
-// layer of 200 tokens does (gate/up 138.3 / 136.5 us a pass against 256 rows in eight shares).
+// x 6656 125 / 101; 777 x 7168 x 8192 123 / 105, with 128 rows 96.  Stream-K was the fastest of all launches in 3 of 884 bf16
+// products and in no FP8 one, and is picked for none of them.
 struct Tile {
     int bm, bn, per_cu, kind;    // kind: tile in shares (0 .. 6), or -v: variant v of the whole-tile kernels, one share
     double start, round, slice, crowd, pair, pair0, w_mb, sum0, sum_mb;
 };
 constexpr Tile TILES_BF16[] = {
-    {32, 64, 2, 0, 2.0, 0.0, 0.131, 0.012, 0.142, 0.87, 0.111, 2.5, 0.55},
-    {64, 64, 2, 1, 2.5, 0.0, 0.162, 0.029, 0.188, 0.88, 0.089, 2.3, 0.59},
-    {128, 64, 2, 2, 3.5, 0.4, 0.242, 0.082, 0.285, 0.88, 0.048, 2.2, 0.51},
-    {128, 128, 2, 3, 6.2, 0.0, 0.456, 0.018, 0.317, 0.93, 0.068, 0.0, 0.35},
-    {128, 128, 2, -3, 0.1, 2.3, 0.462, 0.049, 0.395, 0.64, 0.077, 0.0, 0.00},
-    {256, 256, 1, 4, 0.0, 6.2, 0.737, 0.288, 0.000, 0.00, 0.049, 4.1, 0.29},
-    {192, 256, 1, 5, 5.4, 3.9, 0.637, 0.184, 0.000, 0.00, 0.053, 0.0, 0.29},
-    {128, 256, 1, 6, 7.6, 1.2, 0.591, 0.076, 0.000, 0.00, 0.067, 0.0, 0.32},
-    {256, 256, 1, -1, 0.0, 6.0, 0.854, 0.378, 0.000, 0.00, 0.020, 0.0, 0.00},
-    {192, 256, 1, -5, 0.0, 4.9, 0.710, 0.257, 0.000, 0.00, 0.033, 0.0, 0.00},
-    {128, 256, 1, -4, 0.0, 2.4, 0.600, 0.165, 0.000, 0.00, 0.106, 0.0, 0.00},
+    {32, 64, 2, 0, 2.19, 1.32, 0.131, 0.019, 0.145, 1.00, 0.081, 2.28, 0.481},
+    {64, 64, 2, 1, 2.60, 1.34, 0.172, 0.032, 0.201, 1.00, 0.056, 2.20, 0.500},
+    {128, 64, 2, 2, 4.08, 1.45, 0.261, 0.065, 0.308, 0.84, 0.025, 1.93, 0.438},
+    {128, 128, 2, 3, 5.11, 1.31, 0.475, 0.000, 0.325, 0.91, 0.061, 0.52, 0.324},
+    {128, 128, 2, -3, 0.66, 3.18, 0.483, 0.042, 0.380, 0.68, 0.052, 0.00, 0.000},
+    {256, 256, 1, 4, 1.03, 6.65, 0.813, 0.222, 0.000, 0.00, 0.039, 2.38, 0.288},
+    {192, 256, 1, 5, 4.52, 3.77, 0.713, 0.089, 0.000, 0.00, 0.044, 0.70, 0.316},
+    {128, 256, 1, 6, 4.27, 3.09, 0.634, 0.041, 0.000, 0.00, 0.054, 0.13, 0.308},
+    {256, 256, 1, -1, 0.00, 6.83, 0.838, 0.417, 0.000, 0.00, 0.014, 0.00, 0.000},
+    {192, 256, 1, -5, 0.00, 6.03, 0.708, 0.279, 0.000, 0.00, 0.019, 0.00, 0.000},
+    {128, 256, 1, -4, 1.13, 3.73, 0.607, 0.165, 0.000, 0.00, 0.067, 0.00, 0.000},
 };
 constexpr Tile TILES_FP8[] = {
-    {32, 64, 2, 0, 2.1, 0.7, 0.100, 0.013, 0.153, 0.81, 0.116, 2.2, 0.53},
-    {64, 64, 2, 1, 2.6, 0.6, 0.129, 0.046, 0.200, 0.77, 0.091, 2.0, 0.55},
-    {128, 64, 2, 2, 3.0, 1.4, 0.196, 0.116, 0.280, 0.77, 0.052, 1.6, 0.48},
-    {128, 128, 2, 3, 0.0, 0.0, 0.472, 0.018, 0.126, 1.00, 0.088, 6.3, 0.40},
-    {128, 128, 2, -3, 0.0, 3.0, 0.485, 0.064, 0.280, 0.55, 0.149, 0.0, 0.00},
-    {256, 256, 1, 4, 6.1, 4.6, 0.773, 0.073, 0.000, 0.00, 0.050, 0.0, 0.30},
-    {192, 256, 1, 5, 7.0, 2.4, 0.642, 0.032, 0.000, 0.00, 0.054, 0.0, 0.33},
-    {128, 256, 1, 6, 8.4, 0.9, 0.524, 0.053, 0.000, 0.00, 0.068, 0.0, 0.34},
-    {256, 256, 1, -1, 0.0, 7.4, 0.812, 0.376, 0.000, 0.00, 0.023, 0.0, 0.00},
-    {192, 256, 1, -5, 0.0, 5.8, 0.628, 0.283, 0.000, 0.00, 0.068, 0.0, 0.00},
-    {128, 256, 1, -4, 0.0, 3.9, 0.480, 0.234, 0.000, 0.00, 0.151, 0.0, 0.00},
+    {32, 64, 2, 0, 2.24, 1.20, 0.131, 0.024, 0.154, 1.00, 0.078, 2.27, 0.501},
+    {64, 64, 2, 1, 2.59, 1.27, 0.166, 0.048, 0.213, 1.00, 0.051, 2.15, 0.479},
+    {128, 64, 2, 2, 3.63, 1.38, 0.250, 0.104, 0.311, 0.86, 0.014, 1.94, 0.415},
+    {128, 128, 2, 3, 1.81, 1.26, 0.613, 0.003, 0.122, 1.00, 0.065, 3.62, 0.337},
+    {128, 128, 2, -3, 1.14, 3.47, 0.598, 0.029, 0.226, 0.68, 0.082, 0.00, 0.000},
+    {256, 256, 1, 4, 2.61, 6.41, 0.833, 0.055, 0.000, 0.00, 0.043, 1.19, 0.311},
+    {192, 256, 1, 5, 5.00, 4.08, 0.694, 0.035, 0.000, 0.00, 0.050, 0.01, 0.325},
+    {128, 256, 1, 6, 5.18, 2.51, 0.634, 0.000, 0.000, 0.00, 0.056, 0.02, 0.331},
+    {256, 256, 1, -1, 0.00, 8.44, 0.795, 0.398, 0.000, 0.00, 0.012, 0.00, 0.000},
+    {192, 256, 1, -5, 0.00, 7.03, 0.674, 0.267, 0.000, 0.00, 0.034, 0.00, 0.000},
+    {128, 256, 1, -4, 1.87, 3.82, 0.582, 0.180, 0.000, 0.00, 0.069, 0.00, 0.000},
 };
 // Stream-K by team size 1, 2, 4, 8: start + slice * k-slices of a team + fetch * teams per tile column.
 struct StreamK {
@@ -470,7 +473,7 @@ double tile_us(const Tile &t, int M, int N, int nk, int S, int ncu, bool shared)
     if (shared) us = 0.3 * us + 0.7 * (t.start + wgs / slots * (t.round + slices * slice(t.per_cu)));
     us = std::max(us + t.w_mb * ((double)N * nk * ROW_BYTES * 1e-6), t.start + bytes_us(M, N, nk));
     if (S > 1) us += t.sum0 + t.sum_mb * ((double)S * M * N * 4e-6);
-    if (S > 6) us *= 1.05;       // eight shares take 5 % more than this on every tile (as many streams of stores)
+    if (S > 6) us *= S > 8 ? 1.10 : 1.02;      // eight shares take 1-2 % more than this, twelve 6 % (at 1.06 ties go to twelve, 2-4 % behind eight)
     return us;
 }
 
@@ -483,16 +486,19 @@ bool iso_gemm_split_supported(bool fp8, int M, int N, int K) {
 }
 
 // `whole` is the whole-tile rule's own choice (variant 1, 3, 4, 5 or 6 = stream-K).  It stays unless something else is estimated
-// faster (by 8 % beside another chunk).  ws_bytes: room for partial sums (0: one share only).  `rope`: the QKV projection; tiles
-// of 256 columns and shares (through their second kernel) finish with the rotary step, the others need a kernel more (5 us).
-// (bf16 128 x 128 tiles with heads of 64 rotate as well and keep that price: at the measured 2.2 us 14 layers chose the same.)
+// faster (by 8 % beside another chunk).  ws_bytes: room for partial sums (0: one share only).  `rope`: the QKV projection's head_dim
+// (0: another product); tiles of 256 columns and shares (through their second kernel) finish with the rotary step, the others need
+// a kernel more (5 us), bf16 128 x 128 tiles with heads of 64 rotate as well (2.2 us).
 // *us_or_null: the estimate for the plan returned.
-iso_split_plan iso_gemm_split_plan(bool fp8, bool rope, int whole, int M, int N, int K, size_t ws_bytes, int ncu, bool shared,
+iso_split_plan iso_gemm_split_plan(bool fp8, int rope, int whole, int M, int N, int K, size_t ws_bytes, int ncu, bool shared,
                                    double *us_or_null) {
     const int nk = K / (fp8 ? Fp8Op::KE : Bf16Op::KE);
     const Tile *tiles = fp8 ? TILES_FP8 : TILES_BF16;
     const int n_tiles = fp8 ? (int)(sizeof(TILES_FP8) / sizeof(Tile)) : (int)(sizeof(TILES_BF16) / sizeof(Tile));
-    auto whole_extra = [&](int v) { return rope && (v == 2 || v == 3 || (v == 6 && fp8)) ? 5.0 : 0.0; };
+    auto whole_extra = [&](int v) {
+        if (!rope || !(v == 2 || v == 3 || (v == 6 && fp8))) return 0.0;
+        return v == 3 && rope == 64 && !fp8 ? 2.2 : 5.0;
+    };
     double best = 1e30;
     if (whole == 6) best = stream_k_us(fp8, M, N, nk, ncu) + whole_extra(6);
     for (int i = 0; i < n_tiles; ++i)
@@ -504,7 +510,7 @@ iso_split_plan iso_gemm_split_plan(bool fp8, bool rope, int whole, int M, int N,
         if (us_or_null) *us_or_null = estimate;      // (K = 64: 3 x 32 3.6 / 3.1 us of the rule, 86 x 560 4.1 / 3.6, 202 x 136 3.9 / 3.6)
         return plan;
     }
-    constexpr int SHARES[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 15};
+    constexpr int SHARES[] = {1, 2, 3, 4, 5, 6, 8, 12};      // (small tiles with ten shares are 8 % over the estimate, with fifteen 16 %)
     const double floor_us = bytes_us(M, N, nk), mb = (double)M * N * 4e-6;
     for (int i = 0; i < n_tiles; ++i) {
         const Tile &t = tiles[i];

@@ -175,7 +175,7 @@ iso_split_plan plan_gemm(iso_ctx *ctx, bool fp8, bool rope, int M, int N, int K,
     }
     if (forced || (ctx->flags & ISO_FLAG_NO_STREAMK)) return whole;
     const int rule = fp8 ? iso_gemm_fp8_whole(M, N, K, sk_for(ctx, s)) : iso_gemm_bf16_dtl_resolve(M, N, K, 0, sk_for(ctx, s));
-    return iso_gemm_split_plan(fp8, rope, rule, M, N, K, bytes, iso_num_cu(), ctx->side_by_side != 0);
+    return iso_gemm_split_plan(fp8, rope ? ctx->cfg.head_dim : 0, rule, M, N, K, bytes, iso_num_cu(), ctx->side_by_side != 0);
 }
 
 // Key-split attention workspace for a launch on stream s: one per stream of the context's own, none for others.  Heads of 64 do
@@ -693,7 +693,7 @@ double projections_us(const iso_ctx *ctx, int rows, bool shared) {
         const int N = nk[i][0], K = nk[i][1];
         if (!ws->base || !iso_gemm_split_supported(false, rows, N, K)) return -1.0;
         double us = 0.0;
-        (void)iso_gemm_split_plan(false, i == 0, iso_gemm_bf16_dtl_resolve(rows, N, K, 0, shared ? nullptr : ws), rows, N, K,
+        (void)iso_gemm_split_plan(false, i == 0 ? c.head_dim : 0, iso_gemm_bf16_dtl_resolve(rows, N, K, 0, shared ? nullptr : ws), rows, N, K,
                                   (size_t)ws->num_wg * iso_gemm_sk_slot_bytes(), iso_num_cu(), shared, &us);
         sum += us;
     }

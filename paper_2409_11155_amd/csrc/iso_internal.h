@@ -166,7 +166,7 @@ hipError_t iso_launch_gemm_swiglu_fp8(const void *a8, const float *sa, const voi
 struct iso_split_plan {
     int tile, shares, whole;
 };
-iso_split_plan iso_gemm_split_plan(bool fp8, bool rope, int whole, int M, int N, int K, size_t ws_bytes, int ncu, bool shared,
+iso_split_plan iso_gemm_split_plan(bool fp8, int rope, int whole, int M, int N, int K, size_t ws_bytes, int ncu, bool shared,
                                    double *us_or_null = nullptr);
 int iso_gemm_fp8_whole(int M, int N, int K, const iso_sk_ws *sk_or_null);   // the FP8 rule's variant (1, 3 or 6)
 int iso_gemm_fp8_resolve(int M, int N, int K, int variant, const iso_sk_ws *sk_or_null);   // `variant`, or the rule's if it is none

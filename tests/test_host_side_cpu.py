@@ -268,3 +268,23 @@ for d, heads, Tc, keys, wave in (
         (launch,) = log()
         assert ("attn_bf16_wave" in launch[2]) == bool(wave), (d, heads, Tc, keys, launch)
 """)
+
+
+def test_launches_that_the_estimates_have_to_get_right_by_far(fake):
+    """Narrow tiles are not taken for many rounds of the chip (two to three times the time of the large tiles), and a few rows are
+    not dealt to more shares than the second kernel adds in the time that they save."""
+    run(fake, """
+with iso.Context(iso.make_cfg(256, 4, 4, 64, 64, "bf16", 256)) as ctx:
+    a = array(64, 64)
+    for M, N, K in ((1734, 7976, 128), (5442, 7992, 192), (1744, 9704, 256), (5442, 7992, 128)):
+        log()
+        ctx.gemm_rowpar(a, a, a, M, N, K, ctx.stream0)
+        assert "gemm_narrow_kernel" not in log()[0][2], (M, N, K)
+    for M, most in ((1, 8), (16, 8), (31, 8), (48, 8)):
+        log()
+        ctx.gemm_rowpar(a, a, a, M, 1280, 8192, ctx.stream0)
+        name, grid = log()[0][2].rsplit(" ", 1)
+        rows = int(name.split("NarrowCfgIN")[1].split("ELi")[1].split("E")[0]) if "NarrowCfgIN" in name else 32
+        tiles = -(-M // rows) * 20
+        assert int(grid.split("x")[0]) <= most * tiles, (M, name, grid)
+""")
