@@ -197,7 +197,7 @@ void iso_gemm_bf16_dtl_plan(int M, int N, int K, int num_wg, int *kind, int *tea
 }
 
 // variant: 0 = pick by shape; 1 = 256x256, 4 = 128x256, 5 = 192x256 (gemm_pp_kernel.h), 2 = 256x128 8 waves, 3 = 128x128
-//          4 waves, 6 = 256x256 stream-K; +8 selects the plain (non-interleaved) main loop of 1, 2 and 3.
+//          4 waves, 6 = 256x256 stream-K; +8 selects the plain (non-interleaved) main loop of 1 to 4.
 // sk may be null: then the stream-K kernel is not considered (variant 6 is an error).
 hipError_t iso_launch_gemm_bf16_dtl(const void *a, const void *w, void *c, int M, int N, int K, int variant,
                                     iso_sk_ws *sk, hipStream_t s) {
@@ -212,7 +212,8 @@ hipError_t iso_launch_gemm_bf16_dtl(const void *a, const void *w, void *c, int M
         case 1:
             return plain ? launch<256, 256, 4, 2, false, false>(a, w, c, M, N, K, s) : iso_launch_gemm_pp(256, ISO_PP_PLAIN, whole, s);
         case 2: ISO_DTL(256, 128, 4, 2);
-        case 4: return iso_launch_gemm_pp(128, ISO_PP_PLAIN, whole, s);
+        case 4:
+            return plain ? launch<128, 256, 2, 4, false, false>(a, w, c, M, N, K, s) : iso_launch_gemm_pp(128, ISO_PP_PLAIN, whole, s);
         case 5: return iso_launch_gemm_pp(192, ISO_PP_PLAIN, whole, s);
         case 6: return (sk && sk->base) ? launch_sk<false>(a, w, c, M, N, K, sk, s) : hipErrorInvalidValue;
         default: ISO_DTL(128, 128, 2, 2);

@@ -39,6 +39,18 @@ def test_gemm(bm, M, N, K, S):
         assert orc.max_rel_err(f64(c), orc.linear(h64(a, "bf16"), h64(w, "bf16"))) <= TOL_STEP["bf16"]
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 8, 64), (129, 264, 128), (300, 520, 704)])
+def test_plain_main_loop_of_the_128_x_256_tile(M, N, K):
+    a = iso_inputs.randn((M, K), seed=M + N, dtype="bf16")
+    w = iso_inputs.randn((N, K), seed=M + K, dtype="bf16", scale=K ** -0.5)
+    with make_ctx(256, 4, 4, 64, 64, "bf16", 512) as ctx:
+        ctx.set_flags(12 << 8)
+        c = iso.DeviceArray((M, N), "bf16", fill_byte=NAN_BYTE)
+        ctx.gemm_rowpar(dev(a, "bf16"), dev(w, "bf16"), c, M, N, K, ctx.stream0)
+        ctx.sync()
+        assert orc.max_rel_err(f64(c), orc.linear(h64(a, "bf16"), h64(w, "bf16"))) <= TOL_STEP["bf16"]
+
+
 @pytest.mark.parametrize("bm", [256, 192, 128])
 @pytest.mark.parametrize("M,N,K,S", [(1, 8, 128, 1), (97, 264, 256, 1), (129, 504, 384, 1), (257, 520, 640, 1), (300, 264, 1408, 3)])
 def test_gemm_fp8(bm, M, N, K, S):

@@ -288,3 +288,16 @@ with iso.Context(iso.make_cfg(256, 4, 4, 64, 64, "bf16", 256)) as ctx:
         tiles = -(-M // rows) * 20
         assert int(grid.split("x")[0]) <= most * tiles, (M, name, grid)
 """)
+
+
+def test_the_plain_main_loop_can_be_forced_for_every_tile_that_has_one(fake):
+    run(fake, """
+with iso.Context(iso.make_cfg(256, 4, 4, 64, 64, "bf16", 256)) as ctx:
+    a = array(64, 64)
+    for variant, rows, columns in ((1, 256, 256), (2, 256, 128), (3, 128, 128), (4, 128, 256)):
+        ctx.set_flags((variant + 8) << 8)
+        log()
+        ctx.gemm_rowpar(a, a, a, 300, 520, 256, ctx.stream0)
+        (launch,) = log()
+        assert "gemm_bf16_dtl_kernelILi%dELi%dE" % (rows, columns) in launch[2] and "ELb0ELb0ELb0E" in launch[2], (variant, launch)
+""")
