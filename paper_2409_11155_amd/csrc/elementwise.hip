@@ -202,8 +202,8 @@ __global__ __launch_bounds__(256) void rope_kv_kernel(T *qkv, T *__restrict__ k_
 #pragma unroll
             for (int i = 0; i < VEC; ++i) {
                 const float c = cp[i], s = sp[i];
-                olo[i] = lo[i] * c - hi[i] * s;
-                ohi[i] = hi[i] * c + lo[i] * s;
+                olo[i] = fmaf(lo[i], c, -(hi[i] * s));     // which product is fused is written out, here and wherever a
+                ohi[i] = fmaf(hi[i], c, lo[i] * s);        // projection rotates on its way out: same bits
             }
             T *dst = (head < nq) ? lo_p : k_cache + ((size_t)pos * nkv + (head - nq)) * d + i0;
             store16<T>(dst, olo);

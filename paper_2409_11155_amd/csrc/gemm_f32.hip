@@ -183,8 +183,8 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
                 float a = v[0], b = v[1];
                 if (head < rope.nq + rope.nkv) {
                     const float c = rope.cos_t[(size_t)pos * half + i], sn = rope.sin_t[(size_t)pos * half + i];
-                    a = v[0] * c - v[1] * sn;
-                    b = v[1] * c + v[0] * sn;
+                    a = fmaf(v[0], c, -(v[1] * sn));
+                    b = fmaf(v[1], c, v[0] * sn);
                 }
                 lo[0] = a;
                 lo[half] = b;

@@ -421,8 +421,8 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const unsigned char *__
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     const float l = (float)lo[e], h = (float)hi[e], c = cs[e / 4][e % 4], s = sn[e / 4][e % 4];
-                    lo[e] = (bf16_t)(l * c - h * s);
-                    hi[e] = (bf16_t)(h * c + l * s);
+                    lo[e] = (bf16_t)fmaf(l, c, -(h * s));
+                    hi[e] = (bf16_t)fmaf(h, c, l * s);
                 }
             }
             bf16_t *dst;

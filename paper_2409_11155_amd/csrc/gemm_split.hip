@@ -328,8 +328,8 @@ __global__ __launch_bounds__(256) void share_sum_rope_kernel(Shares sh, bf16_t *
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const float l = (float)(bf16_t)lo[e], h = (float)(bf16_t)hi[e];
-            olo[e] = (bf16_t)(l * cp[e] - h * sp[e]);
-            ohi[e] = (bf16_t)(h * cp[e] + l * sp[e]);
+            olo[e] = (bf16_t)fmaf(l, cp[e], -(h * sp[e]));
+            ohi[e] = (bf16_t)fmaf(h, cp[e], l * sp[e]);
         }
     }
     *reinterpret_cast<bf16x8_t *>(dst) = olo;
