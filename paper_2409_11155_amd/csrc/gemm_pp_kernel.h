@@ -310,23 +310,23 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const unsigned char *__
     }
     constexpr int OC = EPI == PP_SWIGLU ? 128 : 256;     // output columns of the tile
     constexpr int PITCH = OC * 2 + 16;
-    // PP_RESID: x (+ pa) of this thread's pieces, in two batches (FP8, 256 rows: four, or three registers are spilled): the first is
-    // requested here and travels under the staging
-    constexpr int PIECES = BM * (OC / 8) / 512, BATCHES = F8 && BM == 256 ? 4 : 2, BATCH = PIECES / BATCHES;
-    bf16x8_t xv[EPI == PP_RESID ? BATCH : 1], pv[EPI == PP_RESID ? BATCH : 1];
+    // PP_RESID: x (+ pa) of this thread's pieces, in two batches: the first is requested here and travels under the staging.  (FP8,
+    // 256 rows: in four, each requested one ahead of its use; two spill three registers.)
+    constexpr int PIECES = BM * (OC / 8) / 512, BATCHES = F8 && BM == 256 ? 4 : 2, BATCH = PIECES / BATCHES, SETS = BATCHES / 2;
+    bf16x8_t xv[SETS][EPI == PP_RESID ? BATCH : 1], pv[SETS][EPI == PP_RESID ? BATCH : 1];
     auto piece_at = [&](int it, size_t &at) {
         const int p = etid + it * 512, gm = m0 + p / (OC / 8), gn = n0 + (p % (OC / 8)) * 8;
         at = (size_t)gm * N + gn;
         return gm < M && gn < N;
     };
-    auto fetch = [&](int first) {
+    auto fetch = [&](int b) {
         if constexpr (EPI == PP_RESID) {
 #pragma unroll
             for (int i = 0; i < BATCH; ++i) {
                 size_t at;
-                if (piece_at(first + i, at)) {
-                    xv[i] = *reinterpret_cast<const bf16x8_t *>((const bf16_t *)resid.x + at);
-                    pv[i] = *reinterpret_cast<const bf16x8_t *>((const bf16_t *)resid.pa + at);
+                if (piece_at(b * BATCH + i, at)) {
+                    xv[b % SETS][i] = *reinterpret_cast<const bf16x8_t *>((const bf16_t *)resid.x + at);
+                    pv[b % SETS][i] = *reinterpret_cast<const bf16x8_t *>((const bf16_t *)resid.pa + at);
                 }
             }
         }
@@ -388,7 +388,7 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const unsigned char *__
         // x = (x + pa) + bf16(result), in fp32 and in the order of the residual kernel
 #pragma unroll
         for (int b = 0; b < BATCHES; ++b) {
-            if (b) fetch(b * BATCH);
+            if (SETS == 1 ? b > 0 : b + 1 < BATCHES) fetch(SETS == 1 ? b : b + 1);
 #pragma unroll
             for (int i = 0; i < BATCH; ++i) {
                 const int p = etid + (b * BATCH + i) * 512;
@@ -397,7 +397,7 @@ __global__ __launch_bounds__(512, 2) void gemm_pp_kernel(const unsigned char *__
                 const bf16x8_t v = *reinterpret_cast<const bf16x8_t *>(lds + p / PPR * PITCH + (p % PPR) * 16);
                 bf16x8_t o;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) o[e] = (bf16_t)((float)xv[i][e] + (float)pv[i][e] + (float)v[e]);
+                for (int e = 0; e < 8; ++e) o[e] = (bf16_t)((float)xv[b % SETS][i][e] + (float)pv[b % SETS][i][e] + (float)v[e]);
                 *reinterpret_cast<bf16x8_t *>((bf16_t *)resid.x + at) = o;
             }
         }
