@@ -395,10 +395,10 @@ unsigned blocks_for(size_t units) { return (unsigned)((units + 255) / 256); }
 
 
 // ---- which kernel ----------------------------------------------------------------------------------------------
-// Microseconds of a launch, as fitted to 70 000 launches of 1751 products measured on MI355X (16 matrix shapes of the 30B / 70B shards
-// and of a heads-of-64 layer with 39 row counts from 1 to 6000, 260 others with 8 to 12000 columns and k from 128 to 14336; every tile
-// whole up to four rounds of the chip and with 2 to 15 shares; every launch's weights from HBM, which takes a gigabyte of them in
-// turn: 24 copies of a small matrix stay in the 256 MB cache):
+// Microseconds of a launch, as fitted to 75 000 launches of 2434 products measured on MI355X (16 matrix shapes of the 30B / 70B shards
+// and of a heads-of-64 layer with 58 row counts from 1 to 16384, 300 others with 8 to 16000 columns and k from 128 to 14336; narrow
+// tiles whole up to four rounds of the chip, all tiles with 2 to 15 shares; every launch's weights from HBM, which takes a gigabyte of
+// them in turn: 24 copies of a small matrix stay in the 256 MB cache):
 //     start + rounds * round + slices * slice(load) + w_mb * MB of weights + [shares > 1] (sum0 + sum_mb * MB of partial sums)
 // with rounds = times the launch fills the chip (`per_cu` workgroups on each unit), load = workgroups per unit in the last
 // round: slice(load) = slice + crowd * min(load, 1), and + pair * (pair0 + (1 - pair0) (load - 1)) when some units hold two.
@@ -406,44 +406,44 @@ unsigned blocks_for(size_t units) { return (unsigned)((units + 255) / 256); }
 // idle units to that one, so there 0.7 of the price is the part of the chip it uses (measured over 60 split layers: 0 and 1
 // instead of 0.7 lose 5 and 2 %) and the switch has to promise 8 %.  (A blend, not a model of the other launch: the QKV products
 // of a 4096-token 70B TP=8 prompt cut in half, 2048 x 1280 x 8192 each, are priced at 55 us and take 94 and 127 side by side.)
-// Never below the time of the weights' bytes from HBM.  Root mean square error 4-7 % where a launch is within 1.3 of the best; the
-// fastest by these numbers is 1.0 % (bf16) and 1.7 % (FP8) slower than the best measured launch on average.  (Fitted to launches of
-// at most 600 workgroups and eight shares over weights half of which were in the cache it was 2.2 and 2.8 %, and narrow tiles were
-// taken for twenty rounds of the chip: 5442 x 7992 x 192 83 us, now 33.)  338 layers of seven shards, 1 to 9000 tokens, against that
-// fit: 0.995 of the time, 71 more than 1.5 % faster and 17 slower.
+// Never below the time of the weights' bytes from HBM.  Root mean square error 3-7 % where a launch is within 1.3 of the best; the
+// fastest by these numbers is 0.8 % (bf16) and 1.4 % (FP8) slower than the best measured launch on average.  (Fitted to launches of
+// at most 600 workgroups and eight shares over weights half of which were in the cache it was 1.4 and 2.1 %, and narrow tiles were
+// taken for twenty rounds of the chip: 5442 x 7992 x 192 83 us, now 33.)  251 layers of six shards, 1 to 16000 tokens, against that
+// fit: 0.992 of the time.
 // The 256-column tiles (kinds 4 to 6, -1, -4, -5) are those of gemm_pp_kernel.h; 192 and 128 rows are for row counts that 256 fit
 // badly or that leave units idle: 1500 x 8192 x 3584 73.8 us with 256 rows, 65.5 with 192; 8192 x 2560 x 8192 300 / 250; 1024 x 8960
-// x 6656 125 / 101; 777 x 7168 x 8192 123 / 105, with 128 rows 96.  Stream-K was the fastest of all launches in 3 of 884 bf16
-// products and in no FP8 one, and is picked for none of them.
+// x 6656 125 / 101; 777 x 7168 x 8192 123 / 105, with 128 rows 96.  Stream-K was the fastest of all launches in 5 of 1228
+// bf16 products and in no FP8 one.
 struct Tile {
     int bm, bn, per_cu, kind;    // kind: tile in shares (0 .. 6), or -v: variant v of the whole-tile kernels, one share
     double start, round, slice, crowd, pair, pair0, w_mb, sum0, sum_mb;
 };
 constexpr Tile TILES_BF16[] = {
     {32, 64, 2, 0, 2.19, 1.32, 0.131, 0.019, 0.145, 1.00, 0.081, 2.28, 0.481},
-    {64, 64, 2, 1, 2.60, 1.34, 0.172, 0.032, 0.201, 1.00, 0.056, 2.20, 0.500},
-    {128, 64, 2, 2, 4.08, 1.45, 0.261, 0.065, 0.308, 0.84, 0.025, 1.93, 0.438},
-    {128, 128, 2, 3, 5.11, 1.31, 0.475, 0.000, 0.325, 0.91, 0.061, 0.52, 0.324},
-    {128, 128, 2, -3, 0.66, 3.18, 0.483, 0.042, 0.380, 0.68, 0.052, 0.00, 0.000},
-    {256, 256, 1, 4, 1.03, 6.65, 0.813, 0.222, 0.000, 0.00, 0.039, 2.38, 0.288},
-    {192, 256, 1, 5, 4.52, 3.77, 0.713, 0.089, 0.000, 0.00, 0.044, 0.70, 0.316},
-    {128, 256, 1, 6, 4.27, 3.09, 0.634, 0.041, 0.000, 0.00, 0.054, 0.13, 0.308},
-    {256, 256, 1, -1, 0.00, 6.83, 0.838, 0.417, 0.000, 0.00, 0.014, 0.00, 0.000},
-    {192, 256, 1, -5, 0.00, 6.03, 0.708, 0.279, 0.000, 0.00, 0.019, 0.00, 0.000},
-    {128, 256, 1, -4, 1.13, 3.73, 0.607, 0.165, 0.000, 0.00, 0.067, 0.00, 0.000},
+    {64, 64, 2, 1, 2.59, 1.37, 0.172, 0.033, 0.202, 1.00, 0.055, 2.19, 0.497},
+    {128, 64, 2, 2, 4.08, 1.49, 0.260, 0.070, 0.314, 0.83, 0.023, 1.90, 0.433},
+    {128, 128, 2, 3, 2.92, 1.29, 0.475, 0.000, 0.326, 0.91, 0.061, 2.73, 0.323},
+    {128, 128, 2, -3, 1.12, 2.87, 0.470, 0.048, 0.385, 0.68, 0.055, 0.00, 0.000},
+    {256, 256, 1, 4, 1.69, 6.60, 0.812, 0.247, 0.000, 0.00, 0.036, 1.78, 0.285},
+    {192, 256, 1, 5, 3.46, 3.74, 0.712, 0.101, 0.000, 0.00, 0.043, 1.79, 0.313},
+    {128, 256, 1, 6, 4.28, 3.07, 0.632, 0.038, 0.000, 0.00, 0.055, 0.14, 0.309},
+    {256, 256, 1, -1, 0.00, 7.14, 0.811, 0.461, 0.000, 0.00, 0.011, 0.00, 0.000},
+    {192, 256, 1, -5, 0.73, 5.52, 0.680, 0.322, 0.000, 0.00, 0.020, 0.00, 0.000},
+    {128, 256, 1, -4, 1.60, 3.56, 0.574, 0.187, 0.000, 0.00, 0.080, 0.00, 0.000},
 };
 constexpr Tile TILES_FP8[] = {
     {32, 64, 2, 0, 2.24, 1.20, 0.131, 0.024, 0.154, 1.00, 0.078, 2.27, 0.501},
-    {64, 64, 2, 1, 2.59, 1.27, 0.166, 0.048, 0.213, 1.00, 0.051, 2.15, 0.479},
-    {128, 64, 2, 2, 3.63, 1.38, 0.250, 0.104, 0.311, 0.86, 0.014, 1.94, 0.415},
-    {128, 128, 2, 3, 1.81, 1.26, 0.613, 0.003, 0.122, 1.00, 0.065, 3.62, 0.337},
-    {128, 128, 2, -3, 1.14, 3.47, 0.598, 0.029, 0.226, 0.68, 0.082, 0.00, 0.000},
-    {256, 256, 1, 4, 2.61, 6.41, 0.833, 0.055, 0.000, 0.00, 0.043, 1.19, 0.311},
-    {192, 256, 1, 5, 5.00, 4.08, 0.694, 0.035, 0.000, 0.00, 0.050, 0.01, 0.325},
-    {128, 256, 1, 6, 5.18, 2.51, 0.634, 0.000, 0.000, 0.00, 0.056, 0.02, 0.331},
-    {256, 256, 1, -1, 0.00, 8.44, 0.795, 0.398, 0.000, 0.00, 0.012, 0.00, 0.000},
-    {192, 256, 1, -5, 0.00, 7.03, 0.674, 0.267, 0.000, 0.00, 0.034, 0.00, 0.000},
-    {128, 256, 1, -4, 1.87, 3.82, 0.582, 0.180, 0.000, 0.00, 0.069, 0.00, 0.000},
+    {64, 64, 2, 1, 2.59, 1.27, 0.166, 0.049, 0.213, 1.00, 0.051, 2.14, 0.478},
+    {128, 64, 2, 2, 3.61, 1.41, 0.250, 0.109, 0.316, 0.84, 0.012, 1.94, 0.412},
+    {128, 128, 2, 3, 3.30, 1.21, 0.611, 0.000, 0.119, 1.00, 0.067, 2.18, 0.338},
+    {128, 128, 2, -3, 1.32, 3.51, 0.572, 0.032, 0.228, 0.73, 0.095, 0.00, 0.000},
+    {256, 256, 1, 4, 2.01, 6.36, 0.832, 0.077, 0.000, 0.00, 0.041, 1.85, 0.308},
+    {192, 256, 1, 5, 4.50, 4.01, 0.692, 0.039, 0.000, 0.00, 0.050, 0.59, 0.324},
+    {128, 256, 1, 6, 5.10, 2.48, 0.629, 0.000, 0.000, 0.00, 0.057, 0.15, 0.331},
+    {256, 256, 1, -1, 0.31, 8.33, 0.772, 0.433, 0.000, 0.00, 0.012, 0.00, 0.000},
+    {192, 256, 1, -5, 1.05, 6.26, 0.638, 0.294, 0.000, 0.00, 0.048, 0.00, 0.000},
+    {128, 256, 1, -4, 2.05, 4.06, 0.540, 0.177, 0.000, 0.00, 0.095, 0.00, 0.000},
 };
 // Stream-K by team size 1, 2, 4, 8: start + slice * k-slices of a team + fetch * teams per tile column.
 struct StreamK {
