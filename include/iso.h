@@ -252,31 +252,34 @@ enum {
     ISO_FLAG_SIMPLE_GEMM = 1, /* SIMT tile GEMM instead of the MFMA GEMMs                  */
     ISO_FLAG_SIMPLE_ATTN = 2, /* one-wave-per-row attention instead of the MFMA attention  */
     ISO_FLAG_GEMM_STAGED = 4, /* register-staged 128x128 MFMA GEMM instead of the direct-to-LDS one */
-    ISO_FLAG_NO_FUSE = 8,     /* no fused epilogues: gate/up projection and SwiGLU as two kernels, QKV projection
-                                 and rotary embedding + KV-cache write as two kernels                  */
+    ISO_FLAG_NO_FUSE = 8,     /* every step a kernel of its own: gate/up projection and SwiGLU, QKV projection and
+                                 rotary embedding + KV-cache write, the last down projection and the residual (layers
+                                 without transfers), fp32 projections and the norms in front of them, short fp32
+                                 partials and their copies to the host                                  */
     ISO_FLAG_ATTN_STAGED = 16,/* register-staged MFMA attention instead of the direct-to-LDS one    */
-    ISO_FLAG_NO_STREAMK = 32, /* one workgroup per output tile: neither the stream-K launch of the direct-to-LDS GEMM nor
-                                 narrow tiles or a split k range are picked                          */
+    ISO_FLAG_NO_STREAMK = 32, /* one workgroup per output tile, 256x256 or 128x128: neither the stream-K launch of the
+                                 direct-to-LDS GEMM nor other tiles or a split k range are picked     */
     ISO_FLAG_FP8_GEMM = 64,   /* bf16 layers: run the four projections on the FP8 matrix cores (needs the FP8
                                  weights in iso_weights; activations are quantised per token row on the fly) */
     ISO_FLAG_KEEP_CUT = 128   /* the chunks of a layer or stack call run as they were asked for, whatever there is to
                                  hide; the choice of kernels for a chunk is not touched                */
-    /* bits 8..11: tile variant of the direct-to-LDS GEMM (0 = chosen from the shape; 6 = its stream-K launch, which
-     * this value also forces for the FP8 GEMM; 7 = narrow tiles / split k range, with bits 17..20 = number of shares and
-     * bits 21..23 = tile: 0, 1, 2 = 32, 64, 128 rows x 64 columns, 3 = 128 x 128, 4 = 256 x 256,
-     * 5 = 192 x 256) */
+    /* bits 8..11: tile variant of the direct-to-LDS GEMM, bf16 and FP8 (0 = chosen from the shape; 1 = 256 x 256, 3 = 128 x
+     * 128, 4 = 128 x 256, 5 = 192 x 256, 6 = the stream-K launch; bf16 only: 2 = 256 x 128, and 8 more than 1 .. 4 for the plain
+     * main loop; 7 = narrow tiles / split k range, with bits 17..20 = number of shares and bits 21..23 = tile: 0, 1, 2 = 32,
+     * 64, 128 rows x 64 columns, 3 = 128 x 128, 4 = 256 x 256, 5 = 192 x 256, 6 = 128 x 256) */
     /* bits 12..13: launch shape of the direct-to-LDS attention (0 = chosen from the size; 1 = key tiles split inside
      * the workgroup; 2 = that, and two row blocks (longest with shortest) per workgroup; 3 = one row block per
      * workgroup, two workgroups per compute unit) */
     /* bits 14..16: key split of the direct-to-LDS attention ACROSS workgroups (0 = chosen from the size: launches of at
-     * most half as many workgroups as the device has compute units; 1 = never; 2, 3, 4 = that many shares) */
+     * most half as many workgroups as the device has compute units; 1 = never; 2 .. 6 = that many shares; 7 = the kernel for few
+     * rows instead, which deals the keys of 32 rows to the waves of one workgroup and which 0 picks by rows, heads and keys) */
 };
 int iso_set_flags(iso_ctx *ctx, int flags);
 
 /* Which whole-tile kernel a bf16 projection of these sizes takes when nothing is forced, on a device with num_cu compute
  * units (num_cu == 0: as for a stream the context does not own, i.e. never stream-K).  Sizes for which narrower tiles, a
- * split k range or another whole tile are estimated to be at least 4 % faster get those instead; that second choice is not
- * reported here.  Host only; for tests and tuning.
+ * split k range or another whole tile are estimated to be faster (by 8 % where two chunks compute side by side) get those
+ * instead; that second choice is not reported here.  Host only; for tests and tuning.
  * kind: ISO_GEMM_TILE_256 / ISO_GEMM_TILE_128 (one 256x256 / 128x128 tile per workgroup, *grid workgroups),
  * ISO_GEMM_STREAMK (*grid workgroups in teams of *team), ISO_GEMM_STAGED / ISO_GEMM_SIMPLE (the fallbacks for sizes
  * the direct-to-LDS kernel does not take; *grid is 0).  Errors: NULL, non-positive sizes (ISO_ERR_SHAPE). */
@@ -319,7 +322,8 @@ int iso_set_gemm_segments(iso_ctx *ctx, int n);
 
 /* Per-launch timing for measurement.  While enabled, every kernel launch and every copy the library
  * enqueues is bracketed by a pair of HIP events recorded in the stream of that launch (at most 65536
- * launches are kept; enabling clears the record).  iso_timing_read synchronises both streams and returns
+ * launches are kept; enabling clears the record).  Copies of short fp32 partials, which the projection in front of
+ * them does otherwise, are launches of their own then.  iso_timing_read synchronises both streams and returns
  * the summed duration and the number of recorded launches of one kind. */
 typedef enum {
     ISO_K_GEMM_QKV = 0, ISO_K_GEMM_O = 1, ISO_K_GEMM_GATE_UP = 2, ISO_K_GEMM_DOWN = 3, ISO_K_ATTN = 4,

@@ -149,23 +149,21 @@ bool iso_gemm_bf16_dtl_supported(int M, int N, int K) {
            (long long)N * K < (1ll << 31);
 }
 
-// Tile shape.  Measured on MI355X over the projection shapes of the 30B/70B shards: the 256x256 tile wins as
-// soon as it yields at least ~128 workgroups (half the compute units: the chip is power-limited, so fewer busy
-// units clock higher and a half-filled launch of big tiles still beats a full launch of small ones); below that
-// the 128x128 tile (two workgroups per compute unit) is best.
+// Tile shape.  The rule that stands where nothing else is estimated to be faster (gemm_split.hip knows more tiles).  Measured on
+// MI355X, time of the 256x256 tile over that of the 128x128 tile, 460 products of at least 256 rows by the number of 256x256 tiles:
+// up to 64 tiles 1.65-2.05, 65 to 96 1.26 in the mean, 97 to 127 1.15 (1.02-1.27), 128 to 160 0.95 (0.74-1.20), 161 to 256 0.67-0.88.
 static int pick_variant(int M, int N) {
     const long long tiles_256 = (long long)((M + 255) / 256) * ((N + 255) / 256);
     return tiles_256 >= 128 ? 1 : 3;
 }
 
-// Stream-K or one tile per workgroup?  Measured over the same shapes: with at least ~20 k-slices per team the
-// stream-K launch wins or ties (every compute unit busy whatever the tile count, and team members share their W slices
-// in L2: 1024x4992x6656 at 32 slices per team +13 %, 2048x1280x8192 at 20 +29 %, 2048x8192x1024 at 16 even); with less
-// k depth the cost of parking and fetching the partial tiles (about 6 us per workgroup) dominates (1024x6656x1664 at
-// 11 slices per team: 52 against 37 us).
-// Not when whole 256x256 tiles already fill their rounds of the chip to 85 %: there the tile-per-workgroup launch with
-// 16x16x32 MFMAs is ahead or even (4096x8192x7168 353 against 369 us, 8192x7168x8192 719 against 742, 2048x7168x8192
-// at 224 tiles 196 against 207; 4096x2560x8192 at 160 tiles 179 against 156 the other way).
+// Stream-K or one tile per workgroup, where these two are the choice?  With at least 20 k-slices per team every compute unit is busy
+// whatever the tile count and team members share their W slices in L2; with less depth parking and fetching the partial tiles
+// (about 6 us per workgroup) dominates, and where whole 256x256 tiles fill their rounds of the chip to 85 % they are ahead.
+// Measured, 256x256 / 128x128 / stream-K, us: 1024x4992x6656 120 / 102 / 82, 2048x2560x8192 133 / 109 / 91, 2048x8960x6656 235 / 244 /
+// 197, but 2048x1280x8192 128 / 65 / 72; 1024x6656x1664 37 / 30 / 47; 2048x7168x8192 (224 tiles) 163 / 233 / 193.  It is the faster of the
+// three in 64 of the 323 products that this takes and was written for slower tiles: the 192- and 128-row tiles and the split k range,
+// which the estimates put in its place, are ahead of it in all but 5 (1024x4992x6656 68, 2048x2560x8192 78).
 static bool sk_wanted(int M, int N, int K, const iso_sk_ws *sk) {
     if (!sk || !sk->base || sk->num_wg < 8) return false;
     const long long tiles = (long long)((M + 255) / 256) * ((N + 255) / 256);

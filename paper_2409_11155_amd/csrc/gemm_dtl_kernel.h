@@ -15,7 +15,8 @@
 //     so that weight slices are requested two slices ahead); WM x WN wavefronts, each
 //     owning a (BM/WM) x (BN/WN) block of MFMA tiles (bf16: 32x32x16; FP8: 32x32x64, an operand fragment is then 32
 //     bytes per lane = two 16-byte LDS reads).  Whole tiles of 256 columns are the business of gemm_pp_kernel.h; this
-//     body has the 128-column tiles and the stream-K launch.  The 8-wave shapes put two waves on every SIMD, which is what keeps the matrix pipe fed: a single wave cannot issue MFMAs back to back
+//     body has the 128-column tiles, the stream-K launch and, forced, the plain loop of 256 columns.  The 8-wave shapes put
+//     two waves on every SIMD, which is what keeps the matrix pipe fed: a single wave cannot issue MFMAs back to back
 //     without gaps (a register-only MFMA loop reaches ~82 % of peak with one wave per SIMD, ~99 % with two).
 //   * Operand fragments are double-buffered in registers, and the slice hand-over (wait for the next
 //     slice's loads, barrier, first fragment reads of the next slice, issue of the loads two slices ahead)
@@ -112,13 +113,13 @@ template <int BM, int BN, int WM, int WN> struct DtlCfg {
 // exceeds the spin limit raises *sk_err (a pinned host word that the library reads at its next entry point and in
 // iso_sync) and carries on with a wrong tile.
 //
-// ROPE = true (the QKV projection; W = [q heads | k heads | v heads] x head_dim rows): the
-// epilogue finishes the step that follows the projection (rotary embedding and KV-cache write, what the next chunk's
-// attention waits for, paper Section 3.1).  A wave's output columns are exactly one head (128 of them in the stream-K
-// launch, 64 in the 128 x 128 tile), and the rotation pairs (c, c + head_dim / 2) of a row are both in the wave's staging area, so q and k heads are rotated at position q_offset + row
-// on their way from the staging area to memory (same arithmetic and roundings as the separate rotary kernel: the
-// bf16 projection output is rotated in fp32 and rounded again), q heads go to C, k and v heads straight to rows
-// q_offset + row of the caches; the k/v columns of C are not written.
+// ROPE = true (the QKV projection; W = [q heads | k heads | v heads] x head_dim rows): the epilogue finishes the step that follows the
+// projection (rotary embedding and KV-cache write, what the next chunk's attention waits for, paper Section 3.1).  A wave's
+// output columns are exactly one head (128 of them in the stream-K launch, 64 in the 128 x 128 tile), and the rotation pairs
+// (c, c + head_dim / 2) of a row are both in the wave's staging area, so q and k heads are rotated at position q_offset + row on
+// their way from the staging area to memory (same arithmetic and roundings as the separate rotary kernel: the bf16 projection
+// output is rotated in fp32 and rounded again), q heads go to C, k and v heads straight to rows q_offset + row of the caches; the
+// k/v columns of C are not written.
 struct RopeArgs {
     const float *cos_t, *sin_t;      // [max_seq, head_dim / 2] fp32 tables
     bf16_t *k_cache, *v_cache;       // [max_seq, nkv, head_dim]

@@ -1,4 +1,5 @@
-// The 256-column projection tile of libiso for gfx950: two groups of waves that take turns at the matrix cores.
+// The 256-column projection tile of libiso for gfx950: two groups of waves that take turns at the matrix cores (the published
+// "ping-pong" schedule of two wave groups one barrier apart).
 //   bf16:  c[M,N] = a[M,K] * w[N,K]^T, fp32 accumulate, bf16 output (RNE)            (projections: paper Section 2.2)
 //   FP8:   c[M,N] = (a8[M,K] * w8[N,K]^T) * sa[M] * sw[N], E4M3 operands             (8-bit products: paper Section 4.1)
 //
@@ -42,7 +43,6 @@ template <int BM_> struct PpCfg {
         const int epi = share ? BM / 2 * SHARE_PITCH : BM * PITCH;
         return 2 * STAGE > epi ? 2 * STAGE : epi;
     }
-    static constexpr size_t SLOT_BYTES = (size_t)BM * BN * 4;
     static_assert(BM % 64 == 0 && lds_bytes(true) <= 160 * 1024 && lds_bytes(false) <= 160 * 1024, "shape");
 };
 

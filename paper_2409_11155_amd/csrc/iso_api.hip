@@ -410,7 +410,9 @@ struct Chunk {
 };
 
 // A short fp32 payload that a kernel would copy is stored to the host by the projection that computes it: the place in the host
-// sink, or null.  (Not while launches are timed one by one: the copy then is a launch, as its record says.)
+// sink, or null.  (Not while launches are timed one by one: the copy then is a launch, as its record says.)  Layers of seven
+// shapes, us with the copy's launch / without: 128 columns, 64 tokens 31.5 / 26.8, 512 50.1 / 47.6; 256, 128 tokens 39.2 / 35.5, 777 103
+// / 103; 512, 400 tokens 144 / 145, 1472 401 / 352; of 21 row counts each, 1 to 2048, none more than 2 % behind.
 void *sink_of_projection(const iso_ctx *ctx, int comm, int which, const Chunk &ck, const void *a, const void *w, int K) {
     const iso_cfg &c = ctx->cfg;
     const size_t pitch = (size_t)c.hidden * ctx->elt;
@@ -431,12 +433,12 @@ int attn_block_head(iso_ctx *ctx, const iso_weights *w, void *x, void *kc, void 
     char *xr = at(x, ck.lo, H, e);
     char *yr = at(ctx->y, ck.lo, H, e);
     char *qkvr = at(ctx->qkv, ck.lo, NQKV, e);
-    // 8-bit projection: the norm writes the FP8 codes and row scales of y itself, y is never stored
     // fp32 and short: the QKV projection takes the norm's inputs
     const iso_norm_args norm{xr, nullptr, w->g_attn, c.rms_eps};
     const bool rope_f32 = c.dtype == ISO_F32 && !(ctx->flags & (ISO_FLAG_SIMPLE_GEMM | ISO_FLAG_NO_FUSE)) && ctx->gemm_segments <= 1 &&
                           iso_gemm_rope_f32_supported(yr, w->w_qkv, ck.n, NQKV, H);
     const bool norm_f32 = rope_f32 && !add_prev_partial && iso_gemm_f32_norm_supported(norm, ck.n, NQKV / 2, H);
+    // 8-bit projection: the norm writes the FP8 codes and row scales of y itself, y is never stored
     F8Arg f8{w->w_qkv_f8, w->s_qkv, ck.lo};
     f8.prequant = use_fp8(ctx, f8, ck.n, NQKV, H) && iso_rmsnorm_fp8_supported(H);
     unsigned char *a8 = ctx->a8 + (size_t)ck.lo * ctx->a8_pitch;

@@ -140,7 +140,8 @@ struct iso_pp_args {
     iso_resid_args resid;            // ISO_PP_RESID
 };
 hipError_t iso_launch_gemm_pp(int bm, int epi, const iso_pp_args &o, hipStream_t s);
-// QKV projection with rotary embedding + KV-cache write in the epilogue of the stream-K launch (bf16, head_dim 128)
+// QKV projection with rotary embedding + KV-cache write in the epilogue: of the 128 x 128 tile (bf16, head_dim 64) and of the
+// stream-K launch (bf16, head_dim 128)
 hipError_t iso_launch_gemm_qkv_rope_bf16_128(const void *a, const void *w, void *qkv, int M, int N, int K, const iso_rope_args &rope,
                                              hipStream_t s);
 hipError_t iso_launch_gemm_qkv_rope_bf16_sk(const void *a, const void *w, void *qkv, int M, int N, int K, iso_sk_ws *sk,
